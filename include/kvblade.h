@@ -362,7 +362,9 @@ size_t kv_decode_attn_workspace(const kv_plan_t *plan, int n_splits, int max_len
  * query-head group); tokens (host [B], nullable) = token rows per split of each sequence.  Host arithmetic only.
  * A uniform batch, or a given n_splits, takes one split length for all sequences; a ragged batch of up to 64
  * sequences with n_splits = 0 gets per-sequence split lengths (whole 16-token tiles, 32 tokens for head_dim 64) such
- * that every workgroup reads about the same number of tokens (about one workgroup per compute unit in all).
+ * that every workgroup reads about the same number of tokens (about one workgroup per compute unit in all), counting
+ * one workgroup per 4 (2, 1) query heads of a KV head.  This plan is what the workspace has to hold; with n_splits = 0
+ * the launch may cut the tokens differently within the workspace it is given.
  */
 int kv_decode_attn_splits(const kv_plan_t *plan, const int32_t *seq_lens_host, int n_splits, int *n_splits_out,
                           int *first, int *tokens);

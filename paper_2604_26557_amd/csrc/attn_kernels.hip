@@ -1,28 +1,34 @@
 // Split-K decode attention over resident KV (Sec. II-A: the query's similarity with the keys weights
 // the values):  out[b,hq,:] = softmax_j(q[b,hq,:].K[b,h,j,:] / sqrt(D)) V[b,h,j,:],  h = hq / G.
 //
-// Partial kernel: one workgroup of 8 wavefronts per (sequence, query-head group, token split), about one
+// Partial kernel: one workgroup of 8 wavefronts (6 when D = 256) per (sequence, query-head group, token split), about one
 // workgroup per compute unit.  A step is a tile of 16 tokens (two tiles when D = 64); the steps of a split
 // are handed out to the wavefronts on demand through a counter in LDS, so a wavefront whose loads come back
-// late takes fewer steps and all eight reach the merge together (with a fixed round-robin the slowest
+// late takes fewer steps and all of them reach the merge together (with a fixed round-robin the slowest
 // wavefront, and the second workgroup of a compute unit, finished 2-4 us after the median).
 //  * q K^T on the matrix cores: one v_mfma_f32_16x16x32 per 32-wide slice of D with the K tile as the
-//    16 x 32 A operand (lane = token row, 16 contiguous bytes of it) and the query heads of the group,
-//    repeated across the 16 columns, as the B operand.  A 16-byte global load is exactly one operand
-//    register set, so K never passes through LDS, and no cross-lane reduction over D is needed.
-//  * The 16 x 16 fp32 result leaves lane (column n, row group tg) with the scores of tokens 4tg..4tg+3
-//    for query head n mod GT.  Each lane runs the running softmax (m, l) of its own (head, row group)
-//    in fp32; probabilities and rescale factors reach the other heads' lanes by quad broadcasts (DPP).
-//  * P V stays on the vector ALU: the 16 lanes of a row group hold the V rows of their own 4 tokens
-//    (16 bytes per lane), so acc[g][d] += p[g][token] * V[token][d] needs no transpose of V.
+//    16 x 32 A operand (lane = token row, 16 contiguous bytes of it) and the query heads of the group
+//    as the columns of B.  A 16-byte global load is exactly one operand register set, so K never passes
+//    through LDS, and no cross-lane reduction over D is needed.
+//  * The 16 x 16 fp32 result leaves lane (column n, row group tg) with the scores of tokens 4tg..4tg+3 for query
+//    head n, which is the layout of the B operand of V^T P: probabilities never leave their lane.
+//  * V^T P on the matrix cores as well: the 16 lanes of a row group load the V rows of their own 4 tokens, 16 bytes
+//    per lane; byte permutes gather the 4 tokens of each of the lane's 8 columns, and that is the A operand.
+//    The probabilities stay 32-bit: each is the sum of three bf16 (exactly) or two fp16 terms (to 2^-24), one product each.
+//    On the vector ALU this product cost 32 fused multiply-adds per query head and tile, so a workgroup took at most
+//    4 heads, and only 1 or 2 of a group that 4 does not divide: 7 heads per KV head read K and V seven times
+//    (8 KV heads x 32K tokens x 128, bf16: 220 us, now 25.7; 3 heads 100, now 25.6; 4 heads 25.7, now 25.6).
 //  * K and V are read once and never again: the loads are nontemporal.
-// The 32 (wavefront, row group) softmax states of a head are merged through LDS and one fp32 partial per
-// (b, hq, split) is written; the combine kernel merges the splits.  HBM-bound (G flop per byte).
+// The wavefronts' softmax states of a head are merged through LDS and one fp32 partial per (b, hq, split) is
+// written; the combine kernel merges the splits.  When every sequence is a single split the partial kernel writes the
+// results itself (batch 32 x 32 heads of 512-544 tokens: 50.4 us with the second launch, 47.3 without).
+// HBM-bound (G flop per byte).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "plan.hpp"
 
@@ -35,12 +41,21 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kWaves = 8;
-constexpr int kThreads = 64 * kWaves;
+// Wavefronts of a workgroup.  A step is 8 KiB of K and V, at head_dim 256 16 KiB: eight wavefronts then have more loads in
+// flight than HBM likes (8 KV heads x 4 x 8K tokens x 256, one query head each: 46.0 us with eight, 45.2 with six; at
+// head_dim 128 eight and six are equal on long sequences and eight better on many short ones, 47.3 against 54.2 us).
+constexpr int waves(int D) { return D >= 256 ? 6 : 8; }
 constexpr int kTile = 16;             // tokens per MFMA tile
 constexpr int tiles_per_step(int D) { return D >= 128 ? 1 : 2; }  // 8 KiB of K and V in flight per wavefront
 constexpr float kEmptyMax = -1.0e30f; // running maximum of a row group that has seen no token
+// How K and V are addressed: a strided view; a block pool whose blocks hold whole tiles (split starts are multiples of
+// the tile); any other block pool.
+constexpr int kStrided = 0, kPagedTiles = 1, kPagedRows = 2;
+constexpr int kMaxHeads = 16;         // query heads one workgroup takes: the columns of an MFMA
 constexpr int kMaxTableSeqs = 64;     // ragged batches up to this size get per-sequence split counts
 
 // Ragged batch: sequence b owns work items [first[b], first[b+1]) of the grid's x dimension, each of
@@ -62,29 +77,14 @@ struct AttnParams {
     const int *table;      // paged layout
     int max_blocks, bt, bt_shift, n_pool;
     int H, Hq, G, B;
+    int gt, subs;          // query heads per workgroup (at most kMaxHeads); workgroups that share a KV head
+    int direct_mode;       // >= 0: every sequence has one split, results go to `out` in this mode (store_out); -1: partials
+    void *out;             // [B, Hq, D]
     int use_table;         // 1: blockIdx.x is a work item of the split table; 0: grid (split, head group, sequence)
     int n_splits, split_tokens;
     int max_len;           // host-checked bound on every sequence length
-    int one_id;            // paged: every 16-token tile lies inside one block (one table lookup per tile)
     float scale_log2e;     // log2(e) / sqrt(D)
 };
-
-template <bool BF16>
-__device__ __forceinline__ void unpack8(u32x4 v, float f[8])
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const unsigned w = v[i];
-        if (BF16) {
-            f[2 * i] = __uint_as_float(w << 16);
-            f[2 * i + 1] = __uint_as_float(w & 0xffff0000u);
-        } else {
-            const f16x2 h = __builtin_bit_cast(f16x2, w);
-            f[2 * i] = (float)h[0];
-            f[2 * i + 1] = (float)h[1];
-        }
-    }
-}
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float x)
@@ -114,36 +114,6 @@ __device__ __forceinline__ float wave_sum(float x)
     return (rdlane(x, 0) + rdlane(x, 16)) + (rdlane(x, 32) + rdlane(x, 48));
 }
 
-// Value of quad lane Q (0..3) in every lane of the quad.
-template <int Q>
-__device__ __forceinline__ float quad_bcast(float x)
-{
-    return dpp_mov<Q * 0x55>(x);
-}
-template <int GT>
-__device__ __forceinline__ float head_bcast(float x, int g)
-{
-    if (GT == 1) return x;
-    switch (g) {
-    case 0: return quad_bcast<0>(x);
-    case 1: return quad_bcast<1>(x);
-    case 2: return quad_bcast<2>(x);
-    default: return quad_bcast<3>(x);
-    }
-}
-
-// Merge the running softmax state of another lane into this one.
-template <int N>
-__device__ __forceinline__ void merge(float &m, float &l, float acc[N], float m2, float l2, const float acc2[N])
-{
-    const float M = fmaxf(m, m2);
-    const float a = exp2f(m - M), b = exp2f(m2 - M);
-    l = l * a + l2 * b;
-#pragma unroll
-    for (int i = 0; i < N; ++i) acc[i] = acc[i] * a + acc2[i] * b;
-    m = M;
-}
-
 template <bool BF16>
 __device__ __forceinline__ f32x4 mfma_16x16x32(u32x4 a, u32x4 b, f32x4 c)
 {
@@ -163,20 +133,111 @@ __device__ __forceinline__ int table_owner(const SplitTable &t, int B, int item)
     return lo;
 }
 
-template <int D, int GT, bool BF16, bool PAGED>
-__global__ void __launch_bounds__(kThreads) kv_attn_partial_kernel(AttnParams p, SplitTable tab)
+__device__ __forceinline__ unsigned short f32_to_bf16_rne(float f)
 {
-    constexpr int NJ = D / 32;               // MFMA slices along D
+    unsigned u = __float_as_uint(f);
+    if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40);  // quiet NaN
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return (unsigned short)(u >> 16);
+}
+
+// mode: 0 fp32, 1 fp16, 2 bf16, both rounded to nearest even.
+__device__ __forceinline__ void store_out(void *out, long long i, int mode, float r)
+{
+    if (mode == 0) ((float *)out)[i] = r;
+    else if (mode == 1) ((_Float16 *)out)[i] = (_Float16)r;
+    else ((unsigned short *)out)[i] = f32_to_bf16_rne(r);
+}
+// Four in a row (i is a multiple of 4); the buffer itself need only be aligned to its elements.
+__device__ __forceinline__ void store_out4(void *out, long long i, int mode, f32x4 r)
+{
+    if (mode == 0 && !((uintptr_t)out & 15)) {
+        *(f32x4 *)((float *)out + i) = r;
+    } else if (mode != 0 && !((uintptr_t)out & 7)) {
+        unsigned short v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = mode == 1 ? __builtin_bit_cast(unsigned short, (_Float16)r[k]) : f32_to_bf16_rne(r[k]);
+        *(u32x2 *)((unsigned short *)out + i) = u32x2{(unsigned)v[0] | (unsigned)v[1] << 16, (unsigned)v[2] | (unsigned)v[3] << 16};
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) store_out(out, i + k, mode, r[k]);
+    }
+}
+
+// C += A B with 4 (one tile of 16 tokens) or 8 (two tiles) tokens per lane as the contracted index.
+template <bool BF16, int TI>
+__device__ __forceinline__ f32x4 mfma_pv(const unsigned *a, const unsigned *b, f32x4 c)
+{
+    if constexpr (TI == 2) {
+        return mfma_16x16x32<BF16>(u32x4{a[0], a[1], a[2], a[3]}, u32x4{b[0], b[1], b[2], b[3]}, c);
+    } else {
+        const u32x2 av{a[0], a[1]}, bv{b[0], b[1]};
+        if (BF16)
+            return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, av), __builtin_bit_cast(s16x4, bv), c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, av), __builtin_bit_cast(f16x4, bv), c, 0, 0, 0);
+    }
+}
+
+// Maximum / sum over the four row groups (lanes n, n + 16, n + 32, n + 48), in every one of them.
+__device__ __forceinline__ float rows_max(float x)
+{
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
+}
+__device__ __forceinline__ float rows_sum(float x)
+{
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
+
+// A probability in fp32 is the exact sum of three bf16 numbers (the upper half of its bits, twice of what is left), or
+// of two fp16 numbers up to 2^-24 of itself; P V is one product per term.
+template <bool BF16> constexpr int kTerms = BF16 ? 3 : 2;
+
+template <bool BF16>
+__device__ __forceinline__ void split2(float x, float y, unsigned out[kTerms<BF16>])   // two tokens per register
+{
+    if constexpr (BF16) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const unsigned a = __float_as_uint(x), b = __float_as_uint(y);
+            out[t] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+            x -= __uint_as_float(a & 0xffff0000u);
+            y -= __uint_as_float(b & 0xffff0000u);
+        }
+    } else {
+        const f16x2 h = __builtin_convertvector(f32x2{x, y}, f16x2);
+        const f16x2 l = __builtin_convertvector(f32x2{x - (float)h[0], y - (float)h[1]}, f16x2);
+        out[0] = __builtin_bit_cast(unsigned, h);
+        out[1] = __builtin_bit_cast(unsigned, l);
+    }
+}
+
+// Probabilities are exp2(score - reference): the reference follows the running maximum only when a score passes it by
+// kRise, so most tiles neither reduce a maximum over the row groups nor rescale the accumulators.
+constexpr float kRise = 4.f;
+// fp16 terms are taken of 2^11 times the probability (up to 2^15), which puts what they drop below 2^-36 of the largest.
+template <bool BF16> constexpr float kLift = BF16 ? 1.f : 2048.f;
+
+template <int D, int NH, bool BF16, int LAYOUT>
+__global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_partial_kernel(AttnParams p, SplitTable tab)
+{
+    constexpr int kWaves = waves(D), kThreads = 64 * kWaves;
+    constexpr int NJ = D / 32;               // MFMA slices along D of q K^T
     constexpr int DV = D / 8;                // 16-byte vectors per row
-    constexpr int LPRV = DV < 16 ? DV : 16;  // lanes holding one V row inside a 16-lane row group
-    constexpr int TPL = 16 / LPRV;           // V rows one row group covers per load (1, or 2 when D = 64)
-    constexpr int NV = DV / LPRV;            // vectors per lane per V row (1, or 2 when D = 256)
-    constexpr int NU = 4 / TPL;              // V loads (per vector) for the 4 tokens of a row group
-    constexpr int AE = 8 * NV;               // accumulator elements per head per lane
+    constexpr int E = D >= 128 ? 8 : 4;      // V elements per lane and load: 16 lanes hold a row of 16 * E
+    constexpr int NV = D / (16 * E);         // loads per V row (1, or 2 when D = 256)
     constexpr int TI = tiles_per_step(D);    // tiles of one step
     constexpr int kStepTok = kTile * TI;
+    constexpr int NT = kTerms<BF16>;
+    constexpr bool PAGED = LAYOUT != kStrided, TILE_ID = LAYOUT == kPagedTiles;
+    typedef unsigned vload_t __attribute__((ext_vector_type(E / 2)));
 
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int split = blockIdx.x, b = blockIdx.z, split_tokens = p.split_tokens;
     if (p.use_table) {
         // Ragged batch: the grid's x dimension counts only splits that hold tokens, sequence after sequence,
@@ -186,61 +247,57 @@ __global__ void __launch_bounds__(kThreads) kv_attn_partial_kernel(AttnParams p,
         split = (int)blockIdx.x - tab.first[b];
         split_tokens = tab.tokens[b];
     }
-    const int hq0 = blockIdx.y * GT;
-    const int h = hq0 / p.G;
-    const int n = lane & 15;    // MFMA column; also the K row this lane loads
+    const int h = p.subs == 1 ? blockIdx.y : blockIdx.y / p.subs, g0 = (blockIdx.y - h * p.subs) * p.gt;
+    const int hq0 = h * p.G + g0;
+    const int ng = min(p.gt, p.G - g0);   // query heads of this workgroup
+    const int n = lane & 15;    // MFMA column (query head n; columns past the last head repeat it); also the K row this lane loads
     const int tg = lane >> 4;   // row group: owns tokens 4tg..4tg+3 of a tile; also the D sub-slice of the operands
-    const int g_own = n % GT;
-    const int lr = n % LPRV, half = n / LPRV;
 
     const int len = p.len_uniform >= 0 ? p.len_uniform : min(p.seq_lens[b], p.max_len);
     const int t_begin = min(len, split * split_tokens);
     const int t_end = min(len, t_begin + split_tokens);
 
-    // B operand: column n carries query head n mod GT; this lane holds elements 32j + 8tg .. +7 of it.
+    // B operand: column n carries query head n; this lane holds elements 32j + 8tg .. +7 of it.
     u32x4 qv[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) qv[j] = p.q[((long long)b * p.Hq + hq0 + g_own) * DV + 4 * j + tg];
+    for (int j = 0; j < NJ; ++j) qv[j] = p.q[((long long)b * p.Hq + hq0 + min(n, ng - 1)) * DV + 4 * j + tg];
 
-    float m_own = kEmptyMax, l_own = 0.f;
-    float acc[GT][AE];
+    float m = kEmptyMax, l = 0.f;     // reference (the same in the four row groups) and this row group's sum
+    f32x4 acc[NV][E];                 // element (w, e)[i]: column d = w * 16E + (4tg + i) * E + e of query head n
 #pragma unroll
-    for (int g = 0; g < GT; ++g)
+    for (int w = 0; w < NV; ++w)
 #pragma unroll
-        for (int e = 0; e < AE; ++e) acc[g][e] = 0.f;
+        for (int e = 0; e < E; ++e) acc[w][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const long long head_off = PAGED ? 0 : (p.seq_off ? p.seq_off[b] / 8 : (long long)b * p.sb) + (long long)h * p.sh;
     const int *tbl = PAGED ? p.table + (long long)b * p.max_blocks : nullptr;
     auto block_of = [&](int row) -> int { return p.bt_shift >= 0 ? (row >> p.bt_shift) : (row / p.bt); };
-    // vector index of the first element of token row `row` (paged: in pool block blk; ok = false for a block
-    // id outside the pool, which then reads block 0 and is masked)
-    auto row_base = [&](int row, int blk, bool &ok) -> long long {
+    // vector index of the first element of token row `row` (paged: in pool block blk; a block id outside the pool
+    // reads block 0 and is masked)
+    auto row_base = [&](int row, int blk) -> long long {
         if (PAGED) {
             const int slot = row - block_of(row) * p.bt;
-            if ((unsigned)blk >= (unsigned)p.n_pool) { blk = 0; ok = false; }
+            if ((unsigned)blk >= (unsigned)p.n_pool) blk = 0;
             return (((long long)blk * p.H + h) * p.bt + slot) * DV;
         }
         return head_off + (long long)row * p.ss;
     };
-    // Paged layout: the block ids of one step's rows -- this lane's K row and the 4 tokens of its row group,
-    // per tile -- are fetched one step ahead, so that the table lookup is off the load chain.  When the block
-    // size is a multiple of the tile a tile lies inside one block, and one lookup per tile serves all five
-    // (30.4 instead of 31.2 us at a ragged batch of 8 sequences of 2-8K tokens, 16-token blocks).
-    struct Ids { int k[TI]; int t[TI][4]; };
+    // Paged layout: the block ids of one step's rows are fetched ahead, so that the table lookup is off the load chain.
+    // When the block size is a multiple of the tile a tile lies inside one block (kPagedTiles): one lookup per tile, the
+    // same for the whole wavefront and so a scalar load.  Otherwise a lane looks up its K row and the 4 tokens of
+    // its row group.
+    struct Ids { int k[TI], t[TI][TILE_ID ? 1 : 4]; };
     auto fetch_ids = [&](int Tw, Ids &ids) {
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) {
             const int T0 = Tw + kTile * ti;
             const int fb = T0 < t_end ? T0 : Tw;   // a valid row of this tile's block (of the step's first tile when the tile is empty)
-            if (p.one_id) {
-                const int id = tbl[block_of(fb)];
-                ids.k[ti] = id;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) ids.t[ti][i] = id;
+            if (TILE_ID) {
+                ids.k[ti] = ids.t[ti][0] = tbl[block_of(fb)];
             } else {
                 ids.k[ti] = tbl[block_of((T0 + n < t_end) ? T0 + n : fb)];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < (TILE_ID ? 1 : 4); ++i) {
                     const int tok = T0 + 4 * tg + i;
                     ids.t[ti][i] = tbl[block_of(tok < t_end ? tok : fb)];
                 }
@@ -248,174 +305,236 @@ __global__ void __launch_bounds__(kThreads) kv_attn_partial_kernel(AttnParams p,
         }
     };
 
+    // One step in registers: the K tiles in A-operand order, the V rows of this row group's tokens, and which of them count.
+    struct Step {
+        u32x4 k[TI][NJ];
+        vload_t v[TI][4][NV];
+        bool ok[TI][4];
+    };
+    auto load_step = [&](int st, const Ids &ids, Step &x) {
+        const int Tw = t_begin + st * kStepTok;
+#pragma unroll
+        for (int ti = 0; ti < TI; ++ti) {
+            const int T0 = Tw + kTile * ti;
+            const int R0 = T0 < t_end ? T0 : Tw;      // the tile's first row (an empty tile: the step's)
+            const int rem = t_end - T0;               // rows past the end re-read row R0; masked below
+            if constexpr (LAYOUT != kPagedRows) {
+                // one base per tile, the same for the wavefront; the lane's part is a row number times the row length
+                const long long tb = row_base(R0, PAGED ? ids.k[ti] : 0);
+                const unsigned long long row_vecs = PAGED ? DV : p.ss;
+                const bool in_pool = !PAGED || (unsigned)ids.k[ti] < (unsigned)p.n_pool;
+                const u32x4 *kp = p.K + tb + (unsigned)(n < rem ? n : 0) * row_vecs;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) x.k[ti][j] = __builtin_nontemporal_load(kp + 4 * j + tg);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = 4 * tg + i;
+                    x.ok[ti][i] = in_pool && r < rem;
+                    const vload_t *vp = (const vload_t *)(p.V + tb + (unsigned)(r < rem ? r : 0) * row_vecs) + n;
+#pragma unroll
+                    for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load(vp + w * 16);
+                }
+            } else {
+                const u32x4 *kp = p.K + row_base(n < rem ? T0 + n : R0, ids.k[ti]);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) x.k[ti][j] = __builtin_nontemporal_load(kp + 4 * j + tg);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = 4 * tg + i, blk = ids.t[ti][TILE_ID ? 0 : i];
+                    x.ok[ti][i] = r < rem && (unsigned)blk < (unsigned)p.n_pool;
+                    const vload_t *vp = (const vload_t *)(p.V + row_base(r < rem ? T0 + r : R0, blk)) + n;
+#pragma unroll
+                    for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load(vp + w * 16);
+                }
+            }
+        }
+    };
+    auto attend = [&](const Step &x) {
+        // ---- scores of 16 tokens x 16 columns per tile on the matrix cores
+        f32x4 sc[TI];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int ti = 0; ti < TI; ++ti) {
+            f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) c = mfma_16x16x32<BF16>(x.k[ti][j], qv[j], c);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sc[ti][i] = x.ok[ti][i] ? c[i] : -INFINITY;
+                mx = fmaxf(mx, sc[ti][i]);
+            }
+        }
+        // ---- the reference follows the maximum when some score has left it too far behind
+        mx *= p.scale_log2e;
+        if (__any(mx > m + kRise)) {
+            const float mn = fmaxf(m, rows_max(mx));
+            const float alpha = exp2f(m - mn);
+            l *= alpha;
+            m = mn;
+#pragma unroll
+            for (int w = 0; w < NV; ++w)
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[w][e] *= alpha;
+        }
+        // ---- probabilities, as sums of 16-bit terms: the B operand (row = token, column = query head)
+        unsigned pt[NT][2 * TI];
+#pragma unroll
+        for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+            for (int i2 = 0; i2 < 2; ++i2) {
+                const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[ti][2 * i2], p.scale_log2e, -m));
+                const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[ti][2 * i2 + 1], p.scale_log2e, -m));
+                l += p0 + p1;
+                unsigned t[NT];
+                split2<BF16>(p0 * kLift<BF16>, p1 * kLift<BF16>, t);
+#pragma unroll
+                for (int k = 0; k < NT; ++k) pt[k][2 * ti + i2] = t[k];
+            }
+        // ---- acc += V^T P: A operand row n holds column d = w * 16E + n * E + e of V for this row group's tokens,
+        // which this lane has loaded; four tokens of one column are gathered from four registers by byte permutes.
+        // Each tile's sum goes into the accumulator by one addition, so that what a tile adds is rounded once at the
+        // accumulator's magnitude.  The largest term first: within one operation the matrix core drops what lies far
+        // below the largest summand.  For the same reason only the two smallest terms share a product (of twice the
+        // depth, V twice as the A operand, with one tile per step: it takes no longer).
+        // Four columns at a time: eight would take the kernel past 128 registers and with that cost the second workgroup of
+        // a compute unit (bf16, batch 32 x 32 heads of 512-544 tokens: 50.0 instead of 45.3 us).
+        constexpr int kCols = 4, kAlone = TI == 1 ? NT - 2 : NT;
+#pragma unroll
+        for (int w = 0; w < NV; ++w)
+#pragma unroll
+            for (int e0 = 0; e0 < E; e0 += kCols) {
+                unsigned av[kCols][2 * TI];
+                f32x4 t[kCols];
+#pragma unroll
+                for (int e = 0; e < kCols; ++e) {
+                    t[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ti = 0; ti < TI; ++ti)
+#pragma unroll
+                        for (int i2 = 0; i2 < 2; ++i2)
+                            av[e][2 * ti + i2] = __builtin_amdgcn_perm(x.v[ti][2 * i2 + 1][w][(e0 + e) / 2], x.v[ti][2 * i2][w][(e0 + e) / 2],
+                                                                       (e & 1) ? 0x07060302u : 0x05040100u);
+                }
+#pragma unroll
+                for (int k = 0; k < kAlone; ++k)
+#pragma unroll
+                    for (int e = 0; e < kCols; ++e) t[e] = mfma_pv<BF16, TI>(av[e], pt[k], t[e]);
+                if constexpr (kAlone < NT) {
+                    constexpr int K = kAlone;
+#pragma unroll
+                    for (int e = 0; e < kCols; ++e)
+                        t[e] = mfma_16x16x32<BF16>(u32x4{av[e][0], av[e][1], av[e][0], av[e][1]},
+                                                   u32x4{pt[K][0], pt[K][1], pt[K + 1][0], pt[K + 1][1]}, t[e]);
+                }
+#pragma unroll
+                for (int e = 0; e < kCols; ++e) acc[w][e0 + e] += t[e];
+            }
+    };
+
     // Steps are handed out in order, on demand.  A wavefront always knows its current and its next step; the
     // one after that is claimed (one LDS atomic by lane 0) right after the current step's loads are issued,
     // so neither the atomic nor, for the paged layout, the block-table lookup sits on the load chain.
-    __shared__ int sh_next;
+    __shared__ int sh_next, sh_bad;
     const int n_steps = (t_end - t_begin + kStepTok - 1) / kStepTok;
-    if (threadIdx.x == 0) sh_next = 2 * kWaves;   // steps 0 .. 2*kWaves-1 are preassigned: w and w + kWaves to wavefront w
+    if (threadIdx.x == 0) {
+        sh_next = 2 * kWaves;   // steps 0 .. 2*kWaves-1 are preassigned: w and w + kWaves to wavefront w
+        sh_bad = 0;
+    }
     __syncthreads();
     int s_cur = wave, s_nxt = wave + kWaves;
     Ids ids{};
     if (PAGED && s_cur < n_steps) fetch_ids(t_begin + s_cur * kStepTok, ids);
-
     while (s_cur < n_steps) {
-        const int Tw = t_begin + s_cur * kStepTok;
-        // ---- loads of the step's tiles: K tile in A-operand order, V rows of this row group's tokens
-        u32x4 kvec[TI][NJ];
-        u32x4 vvec[TI][NU][NV];
-        bool tok_ok[TI][4];
-#pragma unroll
-        for (int ti = 0; ti < TI; ++ti) {
-            const int T0 = Tw + kTile * ti;
-            bool k_ok = true;
-            const int fb = T0 < t_end ? T0 : Tw;
-            const int krow = (T0 + n < t_end) ? T0 + n : fb;  // rows past the end re-read a valid row; masked below
-            const long long kb = row_base(krow, PAGED ? ids.k[ti] : 0, k_ok);
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) kvec[ti][j] = __builtin_nontemporal_load(p.K + kb + 4 * j + tg);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                // a token whose block id is outside the pool is not attended; every lane of the row group
-                // sees the same four ids, so they agree on the flag
-                tok_ok[ti][i] = (T0 + 4 * tg + i) < t_end;
-                if (PAGED) tok_ok[ti][i] = tok_ok[ti][i] && (unsigned)ids.t[ti][i] < (unsigned)p.n_pool;
-            }
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                const int i = u * TPL + half;
-                const int tok = T0 + 4 * tg + i;
-                bool ok = true;
-                const int blk = !PAGED ? 0 : (TPL == 1 ? ids.t[ti][u] : (half ? ids.t[ti][(2 * u + 1) & 3] : ids.t[ti][(2 * u) & 3]));
-                const long long vb = row_base(tok < t_end ? tok : fb, blk, ok);
-#pragma unroll
-                for (int w = 0; w < NV; ++w) vvec[ti][u][w] = __builtin_nontemporal_load(p.V + vb + lr + w * LPRV);
-            }
-        }
+        Step x;
+        load_step(s_cur, ids, x);
         int s_new = 0;
         if (lane == 0) s_new = atomicAdd(&sh_next, 1);
         s_new = __builtin_amdgcn_readfirstlane(s_new);
         if (PAGED && s_nxt < n_steps) fetch_ids(t_begin + s_nxt * kStepTok, ids);
-
-#pragma unroll
-        for (int ti = 0; ti < TI; ++ti) {
-            // ---- scores of 16 tokens x 16 columns on the matrix core
-            f32x4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) c = mfma_16x16x32<BF16>(kvec[ti][j], qv[j], c);
-
-            // ---- running softmax of (head n mod GT, row group tg)
-            float s[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] = tok_ok[ti][i] ? c[i] * p.scale_log2e : -INFINITY;
-            const float mn = fmaxf(fmaxf(m_own, fmaxf(s[0], s[1])), fmaxf(s[2], s[3]));
-            const float alpha = exp2f(m_own - mn);
-            float pr[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) pr[i] = exp2f(s[i] - mn);
-            l_own = l_own * alpha + ((pr[0] + pr[1]) + (pr[2] + pr[3]));
-            m_own = mn;
-
-            // ---- acc[g] = acc[g] * alpha_g + sum_i p[g][i] * V[i]
-#pragma unroll
-            for (int g = 0; g < GT; ++g) {
-                const float ag = head_bcast<GT>(alpha, g);
-#pragma unroll
-                for (int e = 0; e < AE; ++e) acc[g][e] *= ag;
-            }
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                const float pi = TPL == 1 ? pr[u] : (half ? pr[(2 * u + 1) & 3] : pr[(2 * u) & 3]);
-                float vf[NV][8];
-#pragma unroll
-                for (int w = 0; w < NV; ++w) unpack8<BF16>(vvec[ti][u][w], vf[w]);
-#pragma unroll
-                for (int g = 0; g < GT; ++g) {
-                    const float pg = head_bcast<GT>(pi, g);
-#pragma unroll
-                    for (int w = 0; w < NV; ++w)
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) acc[g][w * 8 + e] = fmaf(pg, vf[w][e], acc[g][w * 8 + e]);
-                }
-            }
-        }
+        attend(x);
         s_cur = s_nxt;
         s_nxt = s_new;
     }
 
-    // ---- merge: every (wavefront, row group) is one softmax state (m, l, acc[D]) per head.  The states go to
-    // LDS as they are (when four heads of 256 columns would not fit, row-group pairs are first merged by one
-    // shuffle round).  After one barrier a wavefront that forms 64 outputs of head g computes the weights
-    // exp2(m - M) of that head's states itself (lane = state, two DPP reductions) and takes them from the lanes
-    // by readlane while it sums the weighted states.
-    constexpr int SR = GT * D > 512 ? 1 : 0;   // shuffle rounds before LDS
-    constexpr int NS = kWaves * (4 >> SR);     // states per head in LDS
-    static_assert(NS <= 64, "one lane per state");
-    float mg = m_own, lg = l_own;
-    if (TPL == 2) {  // the two halves of a row group share (m, l) and hold different tokens of the same d
+    // ---- merge: a wavefront is one softmax state (m, l, acc[D]) per head; the states meet in LDS
+    constexpr int DP = D + 4;   // 4 floats of padding: the 16-byte stores of 8 neighbouring heads fall into different banks
+    __shared__ __attribute__((aligned(16))) float sh_acc[kWaves][NH][DP];
+    __shared__ f32x2 sh_ml[kWaves][NH];
+    l = rows_sum(l);
+    float nf = 0.f;   // NaN if some accumulated value is not finite
+    if (n < ng) {
 #pragma unroll
-        for (int g = 0; g < GT; ++g)
+        for (int w = 0; w < NV; ++w)
 #pragma unroll
-            for (int e = 0; e < AE; ++e) acc[g][e] += __shfl_xor(acc[g][e], 8);
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e4 = 0; e4 < E; e4 += 4) {
+                    const f32x4 v{acc[w][e4][i], acc[w][e4 + 1][i], acc[w][e4 + 2][i], acc[w][e4 + 3][i]};
+                    nf += ((v[0] + v[1]) + (v[2] + v[3])) * 0.f;
+                    *(f32x4 *)&sh_acc[wave][n][w * 16 * E + (4 * tg + i) * E + e4] = v;
+                }
+        if (tg == 0) sh_ml[wave][n] = f32x2{m, l};
     }
-    if (SR == 1) {   // lane (n, tg) and lane (n, tg ^ 1) hold states of the same head n mod GT
-        float mh[GT], lh[GT];
-#pragma unroll
-        for (int g = 0; g < GT; ++g) {
-            mh[g] = head_bcast<GT>(m_own, g);
-            lh[g] = head_bcast<GT>(l_own, g);
-            const float m2 = __shfl_xor(mh[g], 16), l2 = __shfl_xor(lh[g], 16);
-            float a2[AE];
-#pragma unroll
-            for (int e = 0; e < AE; ++e) a2[e] = __shfl_xor(acc[g][e], 16);
-            merge<AE>(mh[g], lh[g], acc[g], m2, l2, a2);
-        }
-        // back to "lane n holds the state of head n mod GT"
-        mg = mh[0]; lg = lh[0];
-#pragma unroll
-        for (int g = 1; g < GT; ++g)
-            if (g_own == g) { mg = mh[g]; lg = lh[g]; }
-    }
-
-    __shared__ __attribute__((aligned(16))) float sh_acc[NS][GT][D];
-    __shared__ f32x2 sh_ml[GT][NS];
-    const int state = wave * (4 >> SR) + (tg >> SR);
-    if ((tg & ((1 << SR) - 1)) == 0 && half == 0) {
-#pragma unroll
-        for (int g = 0; g < GT; ++g) {
-#pragma unroll
-            for (int w = 0; w < NV; ++w) {
-                // a wavefront's 16-byte stores are contiguous: position ((2w + e4) * LPRV + lr) * 4 + k of a state
-                // row holds column d = (lr + w * LPRV) * 8 + 4 * e4 + k
-                *(f32x4 *)&sh_acc[state][g][((2 * w) * LPRV + lr) * 4] = f32x4{acc[g][w * 8 + 0], acc[g][w * 8 + 1], acc[g][w * 8 + 2], acc[g][w * 8 + 3]};
-                *(f32x4 *)&sh_acc[state][g][((2 * w + 1) * LPRV + lr) * 4] = f32x4{acc[g][w * 8 + 4], acc[g][w * 8 + 5], acc[g][w * 8 + 6], acc[g][w * 8 + 7]};
-            }
-        }
-        if (n < GT) sh_ml[n][state] = f32x2{mg, lg};   // lane n < GT holds the state of head n
-    }
+    if (nf != 0.f) sh_bad = 1;
     __syncthreads();
-    for (int base = wave * 64; base < GT * D; base += kThreads) {   // 64 consecutive positions of one head per wavefront
-        const int g = base / D, pos = base - g * D + lane;
-        const int d = (((pos >> 2) % LPRV) + ((pos >> 2) / LPRV / 2) * LPRV) * 8 + (((pos >> 2) / LPRV) & 1) * 4 + (pos & 3);
-        const f32x2 ml = lane < NS ? sh_ml[g][lane] : f32x2{kEmptyMax, 0.f};
-        const float M = wave_max(ml[0]);
-        const float wgt = exp2f(ml[0] - M);
-        const float L = wave_sum(ml[1] * wgt);
-        float A = 0.f;
-#pragma unroll
-        for (int st = 0; st < NS; ++st) A = fmaf(sh_acc[st][g][pos], rdlane(wgt, st), A);
-        const long long o = ((long long)b * p.Hq + hq0 + g) * p.n_splits + split;
-        p.part_acc[o * D + d] = A;
-        if (pos == 0) *(f32x2 *)&p.part_ml[o * 2] = f32x2{M, L};
-    }
-}
 
-__device__ __forceinline__ unsigned short f32_to_bf16_rne(float f)
-{
-    unsigned u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40);  // quiet NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
+    auto head_out = [&](int g) { return ((long long)b * p.Hq + hq0 + g) * D; };
+    auto head_part = [&](int g) { return ((long long)b * p.Hq + hq0 + g) * p.n_splits + split; };
+    if (sh_bad) {
+        // V (or K, or q) holds infinities or NaNs.  The terms of a probability meet an infinite V one by one, and one
+        // that is zero or negative turns it into a NaN, so the split is done again with the probability as one factor:
+        // a wavefront per head, a token at a time.
+        for (int g = wave; g < ng; g += kWaves) {
+            constexpr int C = D / 64;
+            typedef typename std::conditional<BF16, __bf16, _Float16>::type elem_t;
+            const elem_t *qp = (const elem_t *)(p.q + ((long long)b * p.Hq + hq0 + g) * DV);
+            float qs[C], a[C], ms = kEmptyMax, ls = 0.f;
+#pragma unroll
+            for (int c = 0; c < C; ++c) { qs[c] = (float)qp[c * 64 + lane]; a[c] = 0.f; }
+            for (int t = t_begin; t < t_end; ++t) {
+                const int blk = PAGED ? tbl[block_of(t)] : 0;
+                if (PAGED && (unsigned)blk >= (unsigned)p.n_pool) continue;
+                const long long rb = row_base(t, blk);
+                const elem_t *kp = (const elem_t *)(p.K + rb), *vp = (const elem_t *)(p.V + rb);
+                float sc = 0.f;
+#pragma unroll
+                for (int c = 0; c < C; ++c) sc = fmaf(qs[c], (float)kp[c * 64 + lane], sc);
+                sc = wave_sum(sc) * p.scale_log2e;
+                const float mn = fmaxf(ms, sc), al = exp2f(ms - mn), pr = exp2f(sc - mn);
+                ls = ls * al + pr;
+#pragma unroll
+                for (int c = 0; c < C; ++c) a[c] = fmaf(pr, (float)vp[c * 64 + lane], a[c] * al);
+                ms = mn;
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (p.direct_mode >= 0) store_out(p.out, head_out(g) + c * 64 + lane, p.direct_mode, ls > 0.f ? a[c] / ls : 0.f);
+                else p.part_acc[head_part(g) * D + c * 64 + lane] = a[c];
+            }
+            if (p.direct_mode < 0 && lane == 0) *(f32x2 *)&p.part_ml[head_part(g) * 2] = f32x2{ms, ls};
+        }
+        return;
+    }
+    for (int idx = threadIdx.x; idx < ng * (D / 4); idx += kThreads) {   // four consecutive columns of one head
+        const int g = idx / (D / 4), d = (idx - g * (D / 4)) * 4;
+        f32x2 ml[kWaves];
+        float M = kEmptyMax, L = 0.f;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) { ml[k] = sh_ml[k][g]; M = fmaxf(M, ml[k][0]); }
+        f32x4 A = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) {
+            const float wgt = exp2f(ml[k][0] - M);
+            L = fmaf(ml[k][1], wgt, L);
+            A += *(const f32x4 *)&sh_acc[k][g][d] * (wgt * (1.f / kLift<BF16>));
+        }
+        if (p.direct_mode >= 0) {   // the only split of its sequence: the result itself
+            store_out4(p.out, head_out(g) + d, p.direct_mode, L > 0.f ? A / L : f32x4{0.f, 0.f, 0.f, 0.f});
+        } else {
+            *(f32x4 *)&p.part_acc[head_part(g) * D + d] = A;
+            if (d == 0) *(f32x2 *)&p.part_ml[head_part(g) * 2] = f32x2{M, L};
+        }
+    }
 }
 
 // out_mode: 0 fp32, 1 fp16, 2 bf16.  One workgroup of 256 threads per (hq, b): threads are (column, split group);
@@ -498,16 +617,17 @@ kv_attn_combine_kernel(const float *__restrict__ part_acc, const float *__restri
     if (grp == 0) {
         const float r = L > 0.f ? A / L : 0.f;
         const long long oi = ((long long)b * Hq + hq) * D + d;
-        if (out_mode == 0) ((float *)out)[oi] = r;
-        else if (out_mode == 1) ((_Float16 *)out)[oi] = (_Float16)r;  // round to nearest even
-        else ((unsigned short *)out)[oi] = f32_to_bf16_rne(r);
+        store_out(out, oi, out_mode, r);
     }
 }
 
-int pick_gt(int G) { return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1); }
+// Workgroups that share a KV head: as few as the columns of an MFMA allow, so that K and V are read once.
+int group_parts(int G) { return (G + kMaxHeads - 1) / kMaxHeads; }
+// What kv_decode_attn_splits plans with, and so what the workspace has to hold: parts of 4, 2 or 1 query heads.
+int planned_parts(int G) { return G % 4 == 0 ? G / 4 : (G % 2 == 0 ? G / 2 : G); }
 
-// Tokens per split are a multiple of this: half a round of the workgroup's wavefronts.
-int split_quantum(int D) { return kWaves / 2 * kTile * tiles_per_step(D); }
+// Tokens per split are a multiple of this: four steps.
+int split_quantum(int D) { return 4 * kTile * tiles_per_step(D); }
 
 // Most splits the automatic choice can make for sequences of up to max_len tokens (sizes the workspace).
 int max_auto_splits(const kv_plan *p, int max_len)
@@ -533,11 +653,11 @@ int target_workgroups()
 
 // Uniform batch: split length from the total token count, so that about one workgroup per compute unit has
 // tokens to read; never shorter than the quantum.
-int choose_splits(const kv_plan *p, long long total_tokens, int max_len)
+int choose_splits(const kv_plan *p, int parts, long long total_tokens, int max_len)
 {
     if (max_len <= 0) return 1;
     const int q = split_quantum(p->D);
-    const long long groups_per_seq = p->Hq / pick_gt(p->Hq / p->H);
+    const long long groups_per_seq = (long long)p->H * parts;
     const long long wgs = target_workgroups();
     long long st = (total_tokens * groups_per_seq + wgs - 1) / wgs;
     st = std::max<long long>(q, (st + q - 1) / q * q);
@@ -559,10 +679,10 @@ int split_tokens_for(const kv_plan *p, int n_splits, int max_len)
 // A sequence's split length is then rounded up to whole steps only, not to the quantum: steps are handed out
 // on demand, so nothing is gained by a whole number of rounds, and the longest split gets shorter.
 // Returns the largest split count.
-int apportion_splits(const kv_plan *p, const int32_t *lens, int cap, SplitTable *t)
+int apportion_splits(const kv_plan *p, int parts, const int32_t *lens, int cap, SplitTable *t)
 {
     const int q = split_quantum(p->D);
-    const long long groups_per_seq = p->Hq / pick_gt(p->Hq / p->H);
+    const long long groups_per_seq = (long long)p->H * parts;
     int nb[kMaxTableSeqs];
     long long used = 0;
     for (int b = 0; b < p->B; ++b) { nb[b] = lens[b] > 0 ? 1 : 0; used += nb[b]; }
@@ -596,24 +716,27 @@ int apportion_splits(const kv_plan *p, const int32_t *lens, int cap, SplitTable 
     return most;
 }
 
-template <int D, int GT>
-void launch_partial(bool bf16, bool paged, dim3 grid, hipStream_t st, const AttnParams &a, const SplitTable &t)
+template <int D, int NH, bool BF16>
+void launch_partial(dim3 grid, hipStream_t st, const AttnParams &a, const SplitTable &t)
 {
-    if (bf16) {
-        if (paged) hipLaunchKernelGGL((kv_attn_partial_kernel<D, GT, true, true>), grid, dim3(kThreads), 0, st, a, t);
-        else hipLaunchKernelGGL((kv_attn_partial_kernel<D, GT, true, false>), grid, dim3(kThreads), 0, st, a, t);
-    } else {
-        if (paged) hipLaunchKernelGGL((kv_attn_partial_kernel<D, GT, false, true>), grid, dim3(kThreads), 0, st, a, t);
-        else hipLaunchKernelGGL((kv_attn_partial_kernel<D, GT, false, false>), grid, dim3(kThreads), 0, st, a, t);
-    }
+    if (!a.table) hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kStrided>), grid, dim3(64 * waves(D)), 0, st, a, t);
+    else if (a.bt % kTile == 0) hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedTiles>), grid, dim3(64 * waves(D)), 0, st, a, t);
+    else hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedRows>), grid, dim3(64 * waves(D)), 0, st, a, t);
+}
+
+template <int D, int NH>
+void launch_partial_type(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const SplitTable &t)
+{
+    if (bf16) launch_partial<D, NH, true>(grid, st, a, t);
+    else launch_partial<D, NH, false>(grid, st, a, t);
 }
 
 template <int D>
-void launch_partial_gt(int gt, bool bf16, bool paged, dim3 grid, hipStream_t st, const AttnParams &a, const SplitTable &t)
+void launch_partial_nh(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const SplitTable &t)
 {
-    if (gt == 4) launch_partial<D, 4>(bf16, paged, grid, st, a, t);
-    else if (gt == 2) launch_partial<D, 2>(bf16, paged, grid, st, a, t);
-    else launch_partial<D, 1>(bf16, paged, grid, st, a, t);
+    if (a.gt <= 4) launch_partial_type<D, 4>(bf16, grid, st, a, t);   // NH only sizes the merge's LDS
+    else if (a.gt <= 8) launch_partial_type<D, 8>(bf16, grid, st, a, t);
+    else launch_partial_type<D, kMaxHeads>(bf16, grid, st, a, t);
 }
 
 }  // namespace
@@ -628,8 +751,9 @@ extern "C" size_t kv_decode_attn_workspace(const kv_plan_t *p, int n_splits, int
 namespace {
 
 // Split choice for the given lengths: fills the table (ragged batches of up to kMaxTableSeqs sequences) or the
-// common split length; returns the split count the partials are laid out for.
-int plan_splits(const kv_plan *p, const int32_t *lens, int n_splits, bool *use_table, SplitTable *tab, int *split_tokens)
+// common split length; returns the split count the partials are laid out for, at most `cap` unless the caller gave it.
+int plan_splits(const kv_plan *p, int parts, const int32_t *lens, int n_splits, int cap, bool *use_table, SplitTable *tab,
+                int *split_tokens)
 {
     int max_len = 0;
     long long total_len = 0;
@@ -642,9 +766,9 @@ int plan_splits(const kv_plan *p, const int32_t *lens, int n_splits, bool *use_t
     *use_table = !uniform && p->B <= kMaxTableSeqs;
     if (*use_table && n_splits == 0) {
         *split_tokens = split_quantum(p->D);  // not used by the kernels in table mode
-        return apportion_splits(p, lens, max_auto_splits(p, max_len), tab);
+        return apportion_splits(p, parts, lens, std::min(cap, max_auto_splits(p, max_len)), tab);
     }
-    const int ns = n_splits > 0 ? n_splits : choose_splits(p, total_len, max_len);
+    const int ns = n_splits > 0 ? n_splits : std::min(cap, choose_splits(p, parts, total_len, max_len));
     *split_tokens = split_tokens_for(p, ns, max_len);
     if (*use_table) {
         int first = 0;
@@ -707,7 +831,6 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
         a.bt = kv->block_tokens;
         a.bt_shift = (a.bt & (a.bt - 1)) == 0 ? __builtin_ctz((unsigned)a.bt) : -1;
         a.n_pool = kv->n_pool_blocks;
-        a.one_id = a.bt % kTile == 0;   // split starts are multiples of the quantum, itself a multiple of the tile
     } else {
         return KV_EINVAL;
     }
@@ -723,12 +846,20 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     // workgroup reads about the same number of tokens.
     SplitTable tab{};
     bool use_table = false;
-    const int ns = plan_splits(p, kv->seq_lens_host, n_splits, &use_table, &tab, &a.split_tokens);
+    const int G = p->Hq / p->H;
+    int ns = plan_splits(p, planned_parts(G), kv->seq_lens_host, n_splits, kMaxSplits, &use_table, &tab, &a.split_tokens);
+    const size_t per_split = (size_t)p->B * p->Hq * (p->D + 2) * sizeof(float);
+    if (ws_bytes < per_split * ns) return KV_ENOSPC;
+    // The plan counts a workgroup per 4, 2 or 1 query heads; where one workgroup takes more, the same number of
+    // workgroups makes more splits, as far as the workspace holds them.
+    if (n_splits == 0 && planned_parts(G) != group_parts(G)) {
+        const int cap = (int)std::min<size_t>(kMaxSplits, ws_bytes / per_split);
+        ns = plan_splits(p, group_parts(G), kv->seq_lens_host, 0, cap, &use_table, &tab, &a.split_tokens);
+    }
     a.use_table = use_table;
-    const size_t need = (size_t)p->B * p->Hq * ns * (p->D + 2) * sizeof(float);
-    if (ws_bytes < need) return KV_ENOSPC;
 
-    const int G = p->Hq / p->H, gt = pick_gt(G);
+    a.subs = group_parts(G);
+    a.gt = (G + a.subs - 1) / a.subs;
     a.K = (const u32x4 *)K; a.V = (const u32x4 *)V; a.q = (const u32x4 *)q;
     a.seq_lens = kv->seq_lens_dev;
     a.part_acc = (float *)workspace;
@@ -740,18 +871,26 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
 
     hipStream_t st = (hipStream_t)hip_stream;
     const bool bf16 = p->dtype == KV_BF16;
+    const int out_mode = out_dtype == KV_OUT_F32 ? 0 : (bf16 ? 2 : 1);
+    // One split per sequence: there is nothing to combine, and the partial kernel writes the results.  (In the table's
+    // grid a sequence without tokens has no workgroup that could write its zeros.)
+    bool direct = ns == 1 && max_len > 0;
+    for (int b = 0; use_table && b < p->B; ++b) direct = direct && kv->seq_lens_host[b] > 0;
+    a.direct_mode = direct ? out_mode : -1;
+    a.out = out;
     const long long n_items = a.use_table ? tab.first[p->B] : (max_len > 0 ? (long long)ns * p->B : 0);
-    dim3 grid((unsigned)ns, (unsigned)(p->Hq / gt), (unsigned)p->B);
-    if (a.use_table) grid = dim3((unsigned)n_items, (unsigned)(p->Hq / gt), 1u);
+    const unsigned groups = (unsigned)(p->H * a.subs);
+    dim3 grid((unsigned)ns, groups, (unsigned)p->B);
+    if (a.use_table) grid = dim3((unsigned)n_items, groups, 1u);
     if (n_items > 0) {
-        if (p->D == 64) launch_partial_gt<64>(gt, bf16, paged, grid, st, a, tab);
-        else if (p->D == 128) launch_partial_gt<128>(gt, bf16, paged, grid, st, a, tab);
-        else launch_partial_gt<256>(gt, bf16, paged, grid, st, a, tab);
+        if (p->D == 64) launch_partial_nh<64>(bf16, grid, st, a, tab);
+        else if (p->D == 128) launch_partial_nh<128>(bf16, grid, st, a, tab);
+        else launch_partial_nh<256>(bf16, grid, st, a, tab);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { kvb::set_hip_error((int)e); return KV_EHIP; }
     }
 
-    const int out_mode = out_dtype == KV_OUT_F32 ? 0 : (bf16 ? 2 : 1);
+    if (direct) return KV_OK;
     const dim3 cgrid((unsigned)p->Hq, (unsigned)p->B, 1u);
 #define KV_COMBINE(DD)                                                                                                   \
     hipLaunchKernelGGL((kv_attn_combine_kernel<DD>), cgrid, dim3(kCombineThreads), 0, st, a.part_acc, a.part_ml, out,   \
@@ -786,7 +925,7 @@ extern "C" int kv_decode_attn_splits(const kv_plan_t *p, const int32_t *seq_lens
     SplitTable tab{};
     bool use_table = false;
     int st = 0;
-    *n_splits_out = plan_splits(p, seq_lens_host, n_splits, &use_table, &tab, &st);
+    *n_splits_out = plan_splits(p, planned_parts(p->Hq / p->H), seq_lens_host, n_splits, kMaxSplits, &use_table, &tab, &st);
     int acc = 0;
     for (int b = 0; b < p->B; ++b) {
         if (first) first[b] = acc;

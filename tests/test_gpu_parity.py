@@ -373,6 +373,54 @@ def test_decode_attention_long_splits_every_head_shape(D, G, paged):
             _attn_check(out, want)
 
 
+@pytest.mark.parametrize("D", [64, 128, 256])
+@pytest.mark.parametrize("G,bt", [(3, 16), (5, 12), (7, 0), (16, 32), (17, 0)])
+def test_decode_attention_head_groups(D, G, bt):
+    """Query-head groups that fill the MFMA columns partly, wholly and in two unequal parts, with sequence lengths at
+    the edges of a tile, of a step and of a split, split and whole (results written by the partial kernel, to an output
+    that is aligned to its elements only).  Bar: products of 16-bit numbers are exact in fp32, sums of up to n of them err by at
+    most n 2^-24 of the sum of magnitudes; the usual bar of this file is far above that at these lengths."""
+    H, lens = 2, [1, 15, 16, 17, 33, 64, 65, 129]
+    cfg = W.KVConfig(f"groups_D{D}_G{G}", 1300 + D + G, 1, H, H * G, D, len(lens), W.BF16 if G % 3 else W.F16, 512, 8, 2, W.PER_SEQ,
+                     W.PAGED if bt else W.BHSD, 0, len_range=(1, 2), block_tokens=max(bt, 1))
+    case = Case(cfg, "cuda", lens=lens)
+    q = W.query(cfg, 0, "cpu")
+    want = case.expected_attention(0, q)
+    for n_splits in (0, 1, 2):
+        flat = torch.full((len(lens) * H * G * D + 1,), float("nan"), dtype=torch.float32, device="cuda")
+        out = flat[1:].view(len(lens), H * G, D)
+        ws = torch.empty(kv.kv_decode_attn_workspace(case.plan, n_splits, max(lens)), dtype=torch.uint8, device="cuda")
+        kv.kv_decode_attn(case.plan, case.view, 0, q.cuda(), out, kv.KV_OUT_F32, n_splits, ws)
+        torch.cuda.synchronize()
+        _attn_check(out, want)
+
+
+@pytest.mark.parametrize("dtype", [W.F16, W.BF16])
+@pytest.mark.parametrize("n_splits", [1, 3])
+def test_decode_attention_infinite_values(dtype, n_splits):
+    """An infinite element of V makes its column infinite for the heads of its KV head and leaves every other result as it
+    is (a probability is multiplied in parts, some of which are zero); a NaN in V gives NaN in that column."""
+    H, G, D, lens = 2, 4, 128, [100, 700]
+    cfg = W.KVConfig("inf", 1400, 1, H, H * G, D, len(lens), dtype, 512, 8, 2, W.PER_SEQ, W.BHSD, 0, len_range=(1, 2))
+    case = Case(cfg, "cuda", lens=lens)
+    q = W.query(cfg, 0, "cpu")
+    want = case.expected_attention(0, q)
+    v = case.v[0].clone()
+    v[0, 0, 7, 5] = float("inf")
+    v[1, 1, 650, 70] = -float("inf")
+    v[1, 0, 3, 127] = float("nan")
+    view = case.make_view(case.k, [v])
+    out = torch.zeros((len(lens), H * G, D), dtype=torch.float32, device="cuda")
+    ws = torch.empty(kv.kv_decode_attn_workspace(case.plan, n_splits, max(lens)), dtype=torch.uint8, device="cuda")
+    kv.kv_decode_attn(case.plan, view, 0, q.cuda(), out, kv.KV_OUT_F32, n_splits, ws)
+    torch.cuda.synchronize()
+    got = out.double().cpu().numpy()
+    assert (got[0, :G, 5] == np.inf).all() and (got[1, G:, 70] == -np.inf).all() and np.isnan(got[1, :G, 127]).all()
+    rest = np.ones(got.shape, dtype=bool)
+    rest[0, :G, 5] = rest[1, G:, 70] = rest[1, :G, 127] = False
+    assert np.isfinite(got[rest]).all() and np.abs(got - want)[rest].max() <= ATTN_ATOL
+
+
 @pytest.mark.parametrize("bt", [1, 8, 12, 32, 48])
 def test_paged_source_other_block_sizes(bt):
     """Paged pools whose blocks hold other than 16 token rows (a power of two below and above the 16-row tile, sizes
