@@ -144,6 +144,42 @@ kv_layout_kernel(SrcDesc s, u32x4 *__restrict__ img, SegTable segs, int rowv, in
     }
 }
 
+// The newest token rows of many tensors and sequences, one workgroup column per row: a decode step's write-back is a few
+// KiB per tensor, so what it costs is launches and copies, not bytes.  The tables go by value: 32 layers and 128
+// sequences per launch (one launch for 512 rows of 2 KiB, where segments of 32 rows took 16 launches).  The rows are
+// written where the host reads them: into pinned memory, 16 bytes per lane and whole rows per workgroup, without a
+// staging copy (the runtime's 1 MiB device-to-host copy alone takes 20 us behind the last launch).
+constexpr int kRowLayers = 32, kRowSeqs = 128;
+struct RowTable {
+    const u32x4 *base[2 * kRowLayers];  // K, V of each layer
+    int tok[kRowSeqs];                  // the row of each sequence
+};
+
+template <bool PAGED>
+__global__ void __launch_bounds__(kThreads)
+kv_rows_kernel(SrcDesc s, u32x4 *__restrict__ dst, RowTable t, int rowv, int nseq, int b_first)
+{
+    const int tok = t.tok[blockIdx.x];
+    const u32x4 *const base = t.base[blockIdx.y];
+    const int hd = s.H * s.dvec;
+    u32x4 *const row = dst + ((long long)blockIdx.y * nseq + blockIdx.x) * rowv;
+    for (int r = blockIdx.z * blockDim.x + threadIdx.x; r < rowv; r += gridDim.z * blockDim.x) {
+        const int b = b_first >= 0 ? b_first + (int)blockIdx.x : r / hd;   // token-major: a row holds all sequences
+        const int rem = b_first >= 0 ? r : r - b * hd;
+        const int h = rem / s.dvec, dv = rem - h * s.dvec;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (PAGED) {
+            const int j = s.bt_shift >= 0 ? (tok >> s.bt_shift) : (tok / s.bt);
+            const int blk = s.table[(long long)b * s.max_blocks + j];
+            if ((unsigned)blk < (unsigned)s.n_pool)   // ids outside the pool are skipped: their bytes read as zero
+                v = ld(base + (((long long)blk * s.H + h) * s.bt + (tok - j * s.bt)) * s.dvec + dv);
+        } else {
+            v = ld(base + (long long)b * s.sb + (long long)h * s.sh + (long long)tok * s.ss + dv);
+        }
+        st(row + r, v);
+    }
+}
+
 int check_view(const kv_plan *p, const kv_view_t *v, int layer)
 {
     if (!v || !v->k_layers || !v->v_layers || !v->seq_lens_host) return KV_EINVAL;
@@ -412,34 +448,49 @@ namespace kvb {
 // [layer_begin, layer_end) and every sequence, in extent order, packed back to back at dst in the order
 // (layer, K then V, sequence) -- one row of all sequences per tensor in token-major mode.  No sector
 // alignment rule and no padding: the decode append merges the rows into their sectors on the host.
-// All tensors share launches (one run per row, up to 32 runs per launch).
+// dst: device memory or pinned host memory, which the kernel writes through the link.
 int pack_last_rows(const kv_plan *p, const kv_view_t *v, int layer_begin, int layer_end, void *dst, size_t dst_bytes,
                    hipStream_t stream)
 {
     if (!p || !dst || ((uintptr_t)dst & 15)) return KV_EINVAL;
     if (layer_begin < 0 || layer_end > p->L || layer_begin >= layer_end) return KV_ERANGE;
+    if (p->row_bytes / 16 > (uint64_t)INT_MAX) return KV_EINVAL;
     const int nseq = p->mode == KV_TOKEN_MAJOR ? 1 : p->B;
     const uint64_t n_rows = (uint64_t)(layer_end - layer_begin) * 2 * (uint64_t)nseq;
     if (dst_bytes < n_rows * p->row_bytes) return KV_ENOSPC;
-    std::vector<Seg> segs;
-    segs.reserve((size_t)n_rows);
     for (int l = layer_begin; l < layer_end; ++l) {
-        int rc = check_view(p, v, l);
+        const int rc = check_view(p, v, l);
         if (rc != KV_OK) return rc;
-        for (int kind = 0; kind < 2; ++kind)
-            for (int i = 0; i < nseq; ++i) {
-                const int b = p->mode == KV_TOKEN_MAJOR ? -1 : i;
-                const int len = v->seq_lens_host[i];
-                if (len < 1 || len > p->cap[i]) return KV_ERANGE;
-                rc = check_rows(p, v, b, len - 1, 1);
-                if (rc != KV_OK) return rc;
-                Seg s{};
-                s.img_off = (uint64_t)segs.size() * (p->row_bytes / 16);
-                s.b = b; s.tok0 = len - 1; s.ntok = 1; s.base = tensor_base(v, l, kind);
-                segs.push_back(s);
-            }
     }
-    return launch<true>(p, v, segs.data(), (int)segs.size(), dst, stream);
+    for (int i = 0; i < nseq; ++i) {   // the same for every layer
+        const int len = v->seq_lens_host[i];
+        if (len < 1 || len > p->cap[i]) return KV_ERANGE;
+        const int rc = check_rows(p, v, p->mode == KV_TOKEN_MAJOR ? -1 : i, len - 1, 1);
+        if (rc != KV_OK) return rc;
+    }
+    const SrcDesc s = make_src(p, v);
+    const int rowv = (int)(p->row_bytes / 16);
+    const int threads = std::min(kThreads, (rowv + 63) / 64 * 64);
+    const unsigned gz = (unsigned)std::min((rowv + threads - 1) / threads, 65535);
+    for (int l0 = layer_begin; l0 < layer_end; l0 += kRowLayers) {
+        const int nl = std::min(kRowLayers, layer_end - l0);
+        for (int b0 = 0; b0 < nseq; b0 += kRowSeqs) {
+            const int nb = std::min(kRowSeqs, nseq - b0);
+            RowTable t{};
+            for (int i = 0; i < 2 * nl; ++i) t.base[i] = tensor_base(v, l0 + i / 2, i % 2);
+            for (int i = 0; i < nb; ++i) t.tok[i] = v->seq_lens_host[b0 + i] - 1;
+            u32x4 *out = (u32x4 *)dst + ((size_t)(l0 - layer_begin) * 2 * nseq + b0) * rowv;
+            const dim3 grid((unsigned)nb, (unsigned)(2 * nl), gz);
+            const int b_first = p->mode == KV_TOKEN_MAJOR ? -1 : b0;
+            if (v->layout == KV_LAYOUT_PAGED)
+                hipLaunchKernelGGL((kv_rows_kernel<true>), grid, dim3(threads), 0, stream, s, out, t, rowv, nseq, b_first);
+            else
+                hipLaunchKernelGGL((kv_rows_kernel<false>), grid, dim3(threads), 0, stream, s, out, t, rowv, nseq, b_first);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) { kvb::set_hip_error((int)e); return KV_EHIP; }
+        }
+    }
+    return KV_OK;
 }
 }
 

@@ -1029,7 +1029,7 @@ extern "C" int kv_append_tokens(kv_plan_t *p, int layer_begin, int layer_end, co
 
     const size_t n_rows = (size_t)(layer_end - layer_begin) * 2 * (size_t)nseq;
     const size_t total = n_rows * rb;
-    int rc = ensure_pipeline(p, 1, kvb::round_up(total, 4096), 1, 0, false, 0, 0, 0);
+    int rc = create_pipe(p);
     if (rc != KV_OK) return rc;
     kv_pipeline *q = p->pipe;
     if (q->append_host_bytes < total) {
@@ -1050,16 +1050,14 @@ extern "C" int kv_append_tokens(kv_plan_t *p, int layer_begin, int layer_end, co
     rc = order_after_caller(q, caller_stream);
     if (rc != KV_OK) return rc;
 
-    // GPU side: the new row of every tensor (and sequence) in extent order, then one transfer
-    rc = kvb::pack_last_rows(p, view, layer_begin, layer_end, q->staging, q->staging_bytes, q->s_compute);
+    // GPU side: the new row of every tensor (and sequence) in extent order, straight into pinned memory
+    rc = kvb::pack_last_rows(p, view, layer_begin, layer_end, q->append_host, q->append_host_bytes, q->s_compute);
     if (rc != KV_OK) { (void)hipStreamSynchronize(q->s_compute); return rc; }
-    KV_HIP(hipMemcpyAsync(q->append_host, q->staging, total, hipMemcpyDeviceToHost, q->s_compute));
     KV_HIP(hipStreamSynchronize(q->s_compute));
 
     // Host side: Alg. 2 with i0 = len-1 gives the row's byte range; the write command carries whole
     // sectors, so a row that starts inside a sector is merged with that sector's earlier bytes
     // (read-modify-write; the sector image is kept for the next append) and the rest is zeros.
-    std::vector<char> tmp;
     size_t idx = 0;
     for (int l = layer_begin; l < layer_end; ++l)
         for (int kind = 0; kind < 2; ++kind)
@@ -1071,21 +1069,25 @@ extern "C" int kv_append_tokens(kv_plan_t *p, int layer_begin, int layer_end, co
                 const uint64_t off = kvb::extent_host_off(p, n) + p->seq_base[b] * sec + sec0 * sec;
                 if (off + nsec * sec > (direct ? region_bytes : pageable_bytes)) return KV_ENOSPC;
                 char *host = (char *)(direct ? lba_region : pageable) + off;
+                const char *row = (const char *)q->append_host + idx * rb;
                 const size_t entry = ((size_t)n * nseq) + (size_t)b;
-                tmp.assign(nsec * sec, 0);
-                const uint64_t head = a - sec0 * sec;
-                if (head > 0) {
-                    if (q->tail_sector[entry] == (int64_t)sec0) {
-                        std::memcpy(tmp.data(), q->tail_img.data() + entry * sec, head);
+                char *img = q->tail_img.data() + entry * sec;
+                const uint64_t head = a - sec0 * sec, end = e - sec0 * sec, pad = nsec * sec - end;
+                const bool kept = q->tail_sector[entry] == (int64_t)sec0;
+                if (head > 0 && !kept && stats) stats->n_rmw_reads++;
+                // write command (nlb = nsec - 1): the head from the kept image, or as the read has found it; the row; zeros
+                if (head > 0 && kept) std::memcpy(host, img, head);
+                std::memcpy(host + head, row, rb);
+                if (pad > 0) std::memset(host + end, 0, pad);
+                if (pad > 0) {  // the row ends inside a sector: keep that sector's image for the next append
+                    const uint64_t tail = sec - pad;   // valid bytes of the last sector
+                    if (nsec == 1) {
+                        if (head > 0 && !kept) std::memcpy(img, host, head);
+                        std::memcpy(img + head, row, rb);
                     } else {
-                        std::memcpy(tmp.data(), host, head);  // the read of the read-modify-write
-                        if (stats) stats->n_rmw_reads++;
+                        std::memcpy(img, row + (rb - tail), tail);
                     }
-                }
-                std::memcpy(tmp.data() + head, (char *)q->append_host + idx * rb, rb);
-                std::memcpy(host, tmp.data(), nsec * sec);    // write command: nlb = nsec - 1
-                if (e % sec != 0) {
-                    std::memcpy(q->tail_img.data() + entry * sec, tmp.data() + (nsec - 1) * sec, sec);
+                    std::memset(img + tail, 0, pad);
                     q->tail_sector[entry] = (int64_t)(sec1 - 1);
                 } else {
                     q->tail_sector[entry] = -1;

@@ -823,6 +823,24 @@ def test_decode_append(cfg):
     assert e.value.code == kv.KV_ERANGE
 
 
+@pytest.mark.parametrize("layout,mode,B", [(W.PAGED, W.PER_SEQ, 130), (W.BHSD, W.PER_SEQ, 128), (W.BHSD, W.TOKEN_MAJOR, 40)])
+def test_append_more_rows_than_one_launch_holds(layout, mode, B):
+    """The rows of 33 layers and up to 130 sequences (a launch holds 32 layers and 128 sequences), and rows of all
+    sequences together that are wider than a workgroup: offload without the newest row, append it, compare the extents."""
+    cfg = W.KVConfig("append_many", 1500 + B, 33, 1, 1, 64, B, W.BF16, 512, 8, 2, mode, layout, 9,
+                     len_range=(1, 9) if mode == W.PER_SEQ else None)
+    case = Case(cfg, "cuda", raw=True)
+    r = case.ref
+    region = pinned_bytes(r.region_bytes, 0x5A)
+    arena = np.full(max(r.pageable_bytes, 1), 0x5A, dtype=np.uint8)
+    before = case.make_view(case.k, case.v, [n - 1 for n in case.lens])
+    kv.kv_pipeline_run(case.plan, kv.KV_DIR_OFFLOAD, 0, cfg.n_layers, before, region, arena, depth=2)
+    st = kv.kv_append_tokens(case.plan, 0, cfg.n_layers, case.view, region, arena)
+    assert st.n_cmds == cfg.n_layers * 2 * (B if mode == W.PER_SEQ else 1)
+    want_region, _ = case.expected_host(fill=0x5A)
+    assert np.array_equal(region.numpy()[:r.region_bytes], want_region[:r.region_bytes])
+
+
 def test_append_after_trim_and_after_a_change_of_region():
     """The kept tail-sector image must not outlive the bytes it mirrors: after kv_plan_trim the sector reads zeros,
     and another region buffer holds whatever it holds.  offload, append, trim, append / append into a copy."""
