@@ -41,9 +41,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 // Wavefronts of a workgroup.  A step is 8 KiB of K and V, at head_dim 256 16 KiB: eight wavefronts then have more loads in
 // flight than HBM likes (8 KV heads x 4 x 8K tokens x 256, one query head each: 46.0 us with eight, 45.2 with six; at
@@ -164,18 +164,13 @@ __device__ __forceinline__ void store_out4(void *out, long long i, int mode, f32
     }
 }
 
-// C += A B with 4 (one tile of 16 tokens) or 8 (two tiles) tokens per lane as the contracted index.
-template <bool BF16, int TI>
-__device__ __forceinline__ f32x4 mfma_pv(const unsigned *a, const unsigned *b, f32x4 c)
+// C += A B with the four tokens of a row group in a tile as the lane's share of the contracted index.
+template <bool BF16>
+__device__ __forceinline__ f32x4 mfma_16x16x16(u32x2 a, u32x2 b, f32x4 c)
 {
-    if constexpr (TI == 2) {
-        return mfma_16x16x32<BF16>(u32x4{a[0], a[1], a[2], a[3]}, u32x4{b[0], b[1], b[2], b[3]}, c);
-    } else {
-        const u32x2 av{a[0], a[1]}, bv{b[0], b[1]};
-        if (BF16)
-            return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, av), __builtin_bit_cast(s16x4, bv), c, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, av), __builtin_bit_cast(f16x4, bv), c, 0, 0, 0);
-    }
+    if (BF16)
+        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, a), __builtin_bit_cast(f16x4, b), c, 0, 0, 0);
 }
 
 // Maximum / sum over the four row groups (lanes n, n + 16, n + 32, n + 48), in every one of them.
@@ -394,11 +389,13 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
         // which this lane has loaded; four tokens of one column are gathered from four registers by byte permutes.
         // Each tile's sum goes into the accumulator by one addition, so that what a tile adds is rounded once at the
         // accumulator's magnitude.  The largest term first: within one operation the matrix core drops what lies far
-        // below the largest summand.  For the same reason only the two smallest terms share a product (of twice the
-        // depth, V twice as the A operand, with one tile per step: it takes no longer).
+        // below the largest summand.  For the same reason bf16 terms do not share a product; the two fp16 terms of one tile do
+        // (V twice as the A operand).  Products that follow each other in one accumulator are of one shape on purpose: a
+        // 16x16x32 product a few instructions after a 16x16x16 product whose result it adds to has read the last two rows
+        // of that result too early here.
         // Four columns at a time: eight would take the kernel past 128 registers and with that cost the second workgroup of
         // a compute unit (bf16, batch 32 x 32 heads of 512-544 tokens: 50.0 instead of 45.3 us).
-        constexpr int kCols = 4, kAlone = TI == 1 ? NT - 2 : NT;
+        constexpr int kCols = 4;
 #pragma unroll
         for (int w = 0; w < NV; ++w)
 #pragma unroll
@@ -415,16 +412,22 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
                             av[e][2 * ti + i2] = __builtin_amdgcn_perm(x.v[ti][2 * i2 + 1][w][(e0 + e) / 2], x.v[ti][2 * i2][w][(e0 + e) / 2],
                                                                        (e & 1) ? 0x07060302u : 0x05040100u);
                 }
-#pragma unroll
-                for (int k = 0; k < kAlone; ++k)
-#pragma unroll
-                    for (int e = 0; e < kCols; ++e) t[e] = mfma_pv<BF16, TI>(av[e], pt[k], t[e]);
-                if constexpr (kAlone < NT) {
-                    constexpr int K = kAlone;
+                if constexpr (TI == 1 && NT == 2) {
 #pragma unroll
                     for (int e = 0; e < kCols; ++e)
                         t[e] = mfma_16x16x32<BF16>(u32x4{av[e][0], av[e][1], av[e][0], av[e][1]},
-                                                   u32x4{pt[K][0], pt[K][1], pt[K + 1][0], pt[K + 1][1]}, t[e]);
+                                                   u32x4{pt[0][0], pt[0][1], pt[1][0], pt[1][1]}, t[e]);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < NT; ++k)
+#pragma unroll
+                        for (int e = 0; e < kCols; ++e) {
+                            if constexpr (TI == 2)
+                                t[e] = mfma_16x16x32<BF16>(u32x4{av[e][0], av[e][1], av[e][2], av[e][3]},
+                                                           u32x4{pt[k][0], pt[k][1], pt[k][2], pt[k][3]}, t[e]);
+                            else
+                                t[e] = mfma_16x16x16<BF16>(u32x2{av[e][0], av[e][1]}, u32x2{pt[k][0], pt[k][1]}, t[e]);
+                        }
                 }
 #pragma unroll
                 for (int e = 0; e < kCols; ++e) acc[w][e0 + e] += t[e];
@@ -847,12 +850,17 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     SplitTable tab{};
     bool use_table = false;
     const int G = p->Hq / p->H;
-    int ns = plan_splits(p, planned_parts(G), kv->seq_lens_host, n_splits, kMaxSplits, &use_table, &tab, &a.split_tokens);
     const size_t per_split = (size_t)p->B * p->Hq * (p->D + 2) * sizeof(float);
-    if (ws_bytes < per_split * ns) return KV_ENOSPC;
     // The plan counts a workgroup per 4, 2 or 1 query heads; where one workgroup takes more, the same number of
-    // workgroups makes more splits, as far as the workspace holds them.
-    if (n_splits == 0 && planned_parts(G) != group_parts(G)) {
+    // workgroups makes more splits, as far as the workspace holds them.  (A workspace for the most splits any plan makes
+    // holds the plan, and it need not be made: it costs about 1 us for 4 sequences.)
+    const bool replan = n_splits == 0 && planned_parts(G) != group_parts(G);
+    int ns = 0;
+    if (!replan || ws_bytes < per_split * max_auto_splits(p, max_len)) {
+        ns = plan_splits(p, planned_parts(G), kv->seq_lens_host, n_splits, kMaxSplits, &use_table, &tab, &a.split_tokens);
+        if (ws_bytes < per_split * ns) return KV_ENOSPC;
+    }
+    if (replan) {
         const int cap = (int)std::min<size_t>(kMaxSplits, ws_bytes / per_split);
         ns = plan_splits(p, group_parts(G), kv->seq_lens_host, 0, cap, &use_table, &tab, &a.split_tokens);
     }
