@@ -676,6 +676,13 @@ int split_tokens_for(const kv_plan *p, int n_splits, int max_len)
     return (int)std::max<long long>(st, q);
 }
 
+// Sequences whose K and V are this short per KV head are not split: the second launch and the partials cost more than one
+// workgroup needs for two rounds of its wavefronts (8 KV heads, us per layer from a graph, one split against the automatic
+// choice: 128 x 64 tokens 4.1 / 4.1, x 128 5.3 / 6.7, x 256 7.0 / 6.9, x 384 8.8 / 7.0; head_dim 64, 256 tokens 4.5 / 6.3, 512 6.8 / 6.3;
+// head_dim 256, 128 tokens 7.4 / 8.1, 256 10.7 / 8.3).  Launched call by call the line lies at the longest of these: a launch
+// that is left out saves 3.4 us of host time.
+constexpr long long kWholeBytes = 128 * 1024;
+
 // Ragged batch of up to kMaxTableSeqs sequences: every sequence with tokens gets one split; the remaining
 // workgroups of the budget (one per compute unit, shared by the query-head groups) go, one at a time, to the
 // sequence whose splits are longest; no sequence gets more than cap splits or splits shorter than the quantum.
@@ -854,13 +861,18 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     // The plan counts a workgroup per 4, 2 or 1 query heads; where one workgroup takes more, the same number of
     // workgroups makes more splits, as far as the workspace holds them.  (A workspace for the most splits any plan makes
     // holds the plan, and it need not be made: it costs about 1 us for 4 sequences.)
-    const bool replan = n_splits == 0 && planned_parts(G) != group_parts(G);
+    const bool whole = n_splits == 0 && (long long)max_len * p->D * 4 <= kWholeBytes;
+    const bool replan = n_splits == 0 && !whole && planned_parts(G) != group_parts(G);
     int ns = 0;
-    if (!replan || ws_bytes < per_split * max_auto_splits(p, max_len)) {
+    if (!(whole || replan) || ws_bytes < per_split * max_auto_splits(p, max_len)) {
         ns = plan_splits(p, planned_parts(G), kv->seq_lens_host, n_splits, kMaxSplits, &use_table, &tab, &a.split_tokens);
         if (ws_bytes < per_split * ns) return KV_ENOSPC;
     }
-    if (replan) {
+    if (whole) {
+        use_table = false;
+        ns = 1;
+        a.split_tokens = split_tokens_for(p, 1, max_len);
+    } else if (replan) {
         const int cap = (int)std::min<size_t>(kMaxSplits, ws_bytes / per_split);
         ns = plan_splits(p, group_parts(G), kv->seq_lens_host, 0, cap, &use_table, &tab, &a.split_tokens);
     }
