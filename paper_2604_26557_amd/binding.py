@@ -337,12 +337,24 @@ def _stream_ptr(stream) -> Optional[int]:
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+_raw_stream = None   # (current device, its current stream as a pointer), once PyTorch has initialised the GPU
+
+
 def _caller_stream(stream) -> Optional[int]:
-    """The stream handed to the blocking calls: the given one, else PyTorch's current stream."""
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return _stream_ptr(stream)
+    """The stream handed to the native calls: the given one, else PyTorch's current stream.  The pointer is asked for
+    directly: the Stream object that torch.cuda.current_stream() makes costs 2.4 us of a call that is issued in 6."""
+    global _raw_stream
+    if stream is not None:
+        return _stream_ptr(stream)
+    if _raw_stream is not None:
+        return _raw_stream[1](_raw_stream[0]())
+    import torch
+    ptr = torch.cuda.current_stream().cuda_stream
+    get_device = getattr(torch._C, "_cuda_getDevice", None)
+    get_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if get_device is not None and get_stream is not None and get_stream(get_device()) == ptr:
+        _raw_stream = (get_device, get_stream)
+    return ptr
 
 
 # ------------------------------------------------------------------------------------------ kernels
