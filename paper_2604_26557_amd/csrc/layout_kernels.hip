@@ -4,10 +4,11 @@
 // The innermost D row (D*2 bytes, a multiple of 16) is preserved by the permutation, so the kernels
 // move whole 16-byte vectors: one lane = one global_load_dwordx4 + one global_store_dwordx4.
 // Threads are laid out as (rx, ty): rx walks the vectors of one extent row (consecutive lanes ->
-// consecutive extent bytes, so a wavefront touches >= 1 KiB of contiguous extent and whole head rows
-// of the source), ty walks token rows.  The (b, h, d) decomposition of a row position is done once
-// per thread per row position and reused for every token, so the inner loop is adds, U independent
-// 16-byte loads, then U stores.  HBM-bound: 2 bytes of traffic per payload byte, no reuse, no LDS.
+// consecutive extent bytes and whole head rows of the source), ty walks token rows.  The (b, h, d)
+// decomposition of a row position is done once per thread per row position and reused for every token, so
+// the inner loop is adds, U independent 16-byte loads, then U stores.  HBM-bound: 2 bytes of traffic per
+// payload byte, no reuse, no LDS; 5.8-6.3 TB/s, where a plain copy reaches 6.3 (32 layers of 8 heads x 4K
+// tokens x 128 out of one launch pair: 169 us for 1 GiB of traffic, 187 with the tiles before pick_shape's).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -245,26 +246,33 @@ SrcDesc make_src(const kv_plan *p, const kv_view_t *v)
     return s;
 }
 
-// Launch shape.  rx_cap: most lanes (log2) along an extent row; unroll: token rows in flight per thread (2, 4
-// or 8); tile_bytes: extent bytes one workgroup moves; run_bytes: consecutive source bytes per head row a tile
-// should reach when the row is cut into chunks.
+// Launch shape.  rx_cap: most lanes (log2) along an extent row; unroll: token rows in flight per thread (1 or 2);
+// tile_bytes: extent bytes one workgroup moves; run_bytes: consecutive source bytes per head row a tile should reach when
+// the row is cut into chunks.
 struct Shape {
     int rx_cap, unroll, tile_bytes, run_bytes;
 };
 
-// Measured best on MI355X (sweeps over rx_cap 4-8, unroll 2/4/8, tiles 16-512 KiB, runs 0.5-64 KiB at the 2 KiB-row
-// and 32 KiB-row shapes, strided and paged, 8 MiB to 256 MiB tensors).  What the table encodes: a tile should touch
-// few attention-side head streams, each for a long run of consecutive tokens; on the extent side 256-512 byte
-// pieces are fine, since they fall inside one compact window of the image.  So a narrow row gets 16-32 lanes along
-// the row and 64-128 tokens per tile, a very wide row is cut into chunks so that a tile does not touch every head's
-// stream for a few hundred bytes, and launches too small to give every compute unit several tiles take the finer
-// shape.  The pack / unpack difference in lane count and unroll is empirical.
-Shape pick_shape(bool pack, bool paged, int rowv, unsigned long long launch_bytes)
+// Many small workgroups that each move 4-8 KiB in one burst, one or two vectors per lane, beat fewer and larger ones at every
+// shape measured: the launch order then walks both sides nearly in order, so what is in flight at one time is a compact
+// window of memory, where 16-64 KiB tiles with 4-8 vectors per lane kept hundreds of scattered streams open.  What
+// differs is which way a workgroup lies in the permutation (us, 32-64 KiB tiles as before -> now; pack / unpack; 128-wide heads):
+//  * strided, rows of up to 4 KiB: one head row by the workgroup's tokens (4 KiB of one head's stream).  8 heads x 4K tokens,
+//    32 layers in one launch pair 188 / 188 -> 171 / 171; x 32K, 8 layers 381 / 372 -> 367 / 355; 30001 tokens 374 / 347 -> 331 / 330; ragged
+//    batch of 8 472 / 458 -> 422 / 420.  Whole rows (16 KiB) are as good at 4K but alias at power-of-two strides (32K: 411).
+//  * strided, wider rows: 4 KiB of one token's row.  16 heads x 256 x batch 4, 8K tokens 368 / 387 -> 370 / 375; 8 heads, batch 8
+//    214 / 214 -> 201 / 199; 32 heads, batch 32, 520 tokens 445 / 446 -> 397 / 381; 4 heads x 64, batch 28 191 / 186 -> 175 / 171.
+//  * paged, rows of up to 4 KiB: whole rows, since a pool block holds all heads of its tokens.  Ragged batch of 8 438 / 480 -> 413 / 449;
+//    8 heads x 256, batch 6 404 / 515 -> 376 / 391; one sequence of 8000 243 / 250 -> 219 / 226.
+//  * paged, wider rows (several sequences, whose blocks have nothing to do with each other): two head rows by one block's
+//    tokens.  Batch 32 of 600 tokens 439 / 461 -> 250 / 256.
+Shape pick_shape(bool paged, int rowv, int dvec)
 {
-    if (rowv > 256) return Shape{8, 4, 64 * 1024, 16 * 1024};
-    if (paged) return pack ? Shape{8, 8, 32 * 1024, 16 * 1024} : Shape{4, 4, 32 * 1024, 16 * 1024};
-    if (!pack || launch_bytes < (64ull << 20)) return Shape{4, 4, 32 * 1024, 16 * 1024};
-    return Shape{5, 8, 64 * 1024, 32 * 1024};
+    if (paged) return rowv > 256 ? Shape{5, 2, 8 * 1024, 4 * 1024} : Shape{8, 2, 8 * 1024, 4 * 1024};
+    if (rowv > 256) return Shape{8, 1, 4 * 1024, 1024};
+    int lanes = 4;   // one head row, at least 16 lanes
+    while ((1 << lanes) < dvec && lanes < 8) ++lanes;
+    return Shape{lanes, 1, 4 * 1024, 2 * 1024};
 }
 
 template <bool PACK, bool PAGED, int U>
@@ -279,9 +287,8 @@ template <bool PACK, bool PAGED>
 void launch_u(int U, dim3 grid, hipStream_t stream, const SrcDesc &s, void *img, const SegTable &tab, int rowv,
               int rx_log2, int tpb, int rchunk)
 {
-    if (U == 8) launch_k<PACK, PAGED, 8>(grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
-    else if (U == 2) launch_k<PACK, PAGED, 2>(grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
-    else launch_k<PACK, PAGED, 4>(grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
+    if (U == 1) launch_k<PACK, PAGED, 1>(grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
+    else launch_k<PACK, PAGED, 2>(grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
 }
 
 template <bool PACK>
@@ -289,9 +296,7 @@ int launch(const kv_plan *p, const kv_view_t *v, const Seg *segs, int nseg, void
 {
     const int rowv = (int)(p->row_bytes / 16);
     const bool paged = v->layout == KV_LAYOUT_PAGED;
-    unsigned long long launch_bytes = 0;
-    for (int i = 0; i < nseg; ++i) launch_bytes += (unsigned long long)segs[i].ntok * p->row_bytes;
-    const Shape sh = pick_shape(PACK, paged, rowv, launch_bytes);
+    const Shape sh = pick_shape(paged, rowv, p->D / 8);
     int rx_log2 = 0;
     while ((1 << rx_log2) < rowv && rx_log2 < sh.rx_cap) ++rx_log2;
     const int TY = kThreads >> rx_log2;
@@ -307,6 +312,7 @@ int launch(const kv_plan *p, const kv_view_t *v, const Seg *segs, int nseg, void
     tpb = (tpb + TY * U - 1) / (TY * U) * (TY * U);
     const int RXv = 1 << rx_log2;
     long long chunk = std::max<long long>(RXv, tile_bytes / 16 / tpb);
+    chunk = std::max<long long>(chunk, (rowv + 65534) / 65535);   // at most 65535 chunks in the grid
     chunk = (chunk + RXv - 1) / RXv * RXv;
     const int rchunk = (int)std::min<long long>(chunk, (rowv + RXv - 1) / RXv * RXv);
     const unsigned n_rchunks = (unsigned)((rowv + rchunk - 1) / rchunk);

@@ -777,6 +777,29 @@ APPEND_CONFIGS = [
 ]
 
 
+@pytest.mark.parametrize("D,H,B", [(64, 1, 1), (64, 3, 2), (128, 16, 1), (128, 17, 1), (256, 8, 1), (256, 9, 2), (128, 5, 7)])
+@pytest.mark.parametrize("layout", [W.BHSD, W.PAGED])
+@pytest.mark.parametrize("mode", [W.TOKEN_MAJOR, W.PER_SEQ])
+def test_pack_unpack_at_the_edges_of_tiles(D, H, B, layout, mode):
+    """Extent rows of up to 256 vectors and just above (the line between two launch shapes), rows that no power of two
+    divides, lengths around a workgroup's tokens: whole extents of two layers out and back, byte for byte."""
+    cfg = W.KVConfig("edges", 1600 + D + H + B, 2, H, H, D, B, W.F16, 512, 8, 2, mode, layout, 33,
+                     len_range=(1, 35) if mode == W.PER_SEQ else None)
+    case = Case(cfg, "cuda", raw=True, lens=[1, 15, 16, 17, 31, 32, 33][:B] if mode == W.PER_SEQ else [33] * B)
+    nbytes = case.ref.n_blocks_tensor * case.ref.lba_size
+    buf, dst = _guarded(2 * 2 * nbytes)
+    kv.kv_offload_pack_layers(case.plan, 0, 2, case.view, dst)
+    torch.cuda.synchronize()
+    got = dst.cpu().numpy().reshape(4, nbytes)
+    for n in range(4):
+        assert np.array_equal(got[n], case.expected_extent(n // 2, n % 2))
+    assert _guards_intact(buf, 4 * nbytes)
+    k_new, v_new = case.blank_like_source()
+    kv.kv_reload_unpack_layers(case.plan, 0, 2, dst, case.make_view(k_new, v_new))
+    torch.cuda.synchronize()
+    _check_restored(case, k_new, v_new, range(2))
+
+
 @pytest.mark.parametrize("cfg", APPEND_CONFIGS, ids=lambda c: c.name)
 def test_decode_append(cfg):
     """Offload len tokens, then append three tokens one by one; after each the host bytes must equal the
