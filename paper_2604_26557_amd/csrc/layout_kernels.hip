@@ -265,10 +265,12 @@ struct Shape {
 //  * paged, rows of up to 4 KiB: whole rows, since a pool block holds all heads of its tokens.  Ragged batch of 8 438 / 480 -> 413 / 449;
 //    8 heads x 256, batch 6 404 / 515 -> 376 / 391; one sequence of 8000 243 / 250 -> 219 / 226.
 //  * paged, wider rows (several sequences, whose blocks have nothing to do with each other): two head rows by one block's
-//    tokens.  Batch 32 of 600 tokens 439 / 461 -> 250 / 256.
+//    tokens.  Batch 32 of 600 tokens 439 / 461 -> 250 / 256; 64-wide heads, batch 16 of 500 1046 / 1344 -> 153 / 155.  256-wide heads
+//    take 4 KiB of one token's row instead: 32 heads, batch 3 277 / 273 -> 249 / 240 (two head rows by a block's tokens: 300 / 282).
 Shape pick_shape(bool paged, int rowv, int dvec)
 {
-    if (paged) return rowv > 256 ? Shape{5, 2, 8 * 1024, 4 * 1024} : Shape{8, 2, 8 * 1024, 4 * 1024};
+    if (paged && rowv > 256) return dvec >= 32 ? Shape{8, 1, 4 * 1024, 2 * 1024} : Shape{5, 2, 8 * 1024, 4 * 1024};
+    if (paged) return Shape{8, 2, 8 * 1024, 4 * 1024};
     if (rowv > 256) return Shape{8, 1, 4 * 1024, 1024};
     int lanes = 4;   // one head row, at least 16 lanes
     while ((1 << lanes) < dvec && lanes < 8) ++lanes;
