@@ -511,7 +511,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
             }
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                if (p.direct_mode >= 0) store_out(p.out, head_out(g) + c * 64 + lane, p.direct_mode, ls > 0.f ? a[c] / ls : 0.f);
+                if (p.direct_mode >= 0) store_out(p.out, head_out(g) + c * 64 + lane, p.direct_mode, ls == 0.f ? 0.f : a[c] / ls);
                 else p.part_acc[head_part(g) * D + c * 64 + lane] = a[c];
             }
             if (p.direct_mode < 0 && lane == 0) *(f32x2 *)&p.part_ml[head_part(g) * 2] = f32x2{ms, ls};
@@ -532,7 +532,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
             A += *(const f32x4 *)&sh_acc[k][g][d] * (wgt * (1.f / kLift<BF16>));
         }
         if (p.direct_mode >= 0) {   // the only split of its sequence: the result itself
-            store_out4(p.out, head_out(g) + d, p.direct_mode, L > 0.f ? A / L : f32x4{0.f, 0.f, 0.f, 0.f});
+            store_out4(p.out, head_out(g) + d, p.direct_mode, L == 0.f ? f32x4{0.f, 0.f, 0.f, 0.f} : A / L);
         } else {
             *(f32x4 *)&p.part_acc[head_part(g) * D + d] = A;
             if (d == 0) *(f32x2 *)&p.part_ml[head_part(g) * 2] = f32x2{M, L};
@@ -618,7 +618,7 @@ kv_attn_combine_kernel(const float *__restrict__ part_acc, const float *__restri
         }
     }
     if (grp == 0) {
-        const float r = L > 0.f ? A / L : 0.f;
+        const float r = L == 0.f ? 0.f : A / L;   // nothing attended: zeros; a NaN score: NaN
         const long long oi = ((long long)b * Hq + hq) * D + d;
         store_out(out, oi, out_mode, r);
     }

@@ -421,6 +421,30 @@ def test_decode_attention_infinite_values(dtype, n_splits):
     assert np.isfinite(got[rest]).all() and np.abs(got - want)[rest].max() <= ATTN_ATOL
 
 
+@pytest.mark.parametrize("dtype", [W.F16, W.BF16])
+@pytest.mark.parametrize("n_splits", [0, 1, 3])
+def test_decode_attention_nan_scores(dtype, n_splits):
+    """A NaN in K makes every result of its KV head's query heads NaN, a NaN in q those of its own head; the other heads and
+    sequences keep their values.  An empty sequence still reads zeros."""
+    H, G, D, lens = 2, 4, 128, [100, 700, 0, 300]
+    cfg = W.KVConfig("nan", 1410, 1, H, H * G, D, len(lens), dtype, 512, 8, 2, W.PER_SEQ, W.BHSD, 0, len_range=(1, 2))
+    case = Case(cfg, "cuda", lens=lens)
+    q = W.query(cfg, 0, "cpu")
+    want = case.expected_attention(0, q)
+    k, q = case.k[0].clone(), q.clone()
+    k[1, 0, 333, 17] = float("nan")
+    q[3, 6, 100] = float("nan")
+    out = torch.zeros((len(lens), H * G, D), dtype=torch.float32, device="cuda")
+    ws = torch.empty(kv.kv_decode_attn_workspace(case.plan, n_splits, max(lens)), dtype=torch.uint8, device="cuda")
+    kv.kv_decode_attn(case.plan, case.make_view([k], case.v), 0, q.cuda(), out, kv.KV_OUT_F32, n_splits, ws)
+    torch.cuda.synchronize()
+    got = out.double().cpu().numpy()
+    hit = np.zeros(got.shape[:2], dtype=bool)
+    hit[1, :G] = hit[3, 6] = True
+    assert np.isnan(got[hit]).all()
+    assert np.isfinite(got[~hit]).all() and np.abs(got - want)[~hit].max() <= ATTN_ATOL and (got[2] == 0).all()
+
+
 @pytest.mark.parametrize("bt", [1, 8, 12, 32, 48])
 def test_paged_source_other_block_sizes(bt):
     """Paged pools whose blocks hold other than 16 token rows (a power of two below and above the 16-row tile, sizes
