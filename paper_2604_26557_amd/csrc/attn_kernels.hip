@@ -215,6 +215,11 @@ __device__ __forceinline__ void split2(float x, float y, unsigned out[kTerms<BF1
 // Probabilities are exp2(score - reference): the reference follows the running maximum only when a score passes it by
 // kRise, so most tiles neither reduce a maximum over the row groups nor rescale the accumulators.
 constexpr float kRise = 4.f;
+// The exponent of a probability is one fused multiply-add (score x scale - reference), which rounds once; the reference is itself
+// a rounded product.  Up to this magnitude that rounding shifts every exponent by at most 1/32, which cancels in the
+// normalisation; far above it the shift would leave the range of the probabilities, and the split is done again.  (Rounding
+// the products in the loop where the reference is large costs 2-3 % at head_dim 64 and 2 % on many short sequences.)
+constexpr float kFusedRef = 1048576.f;
 // fp16 terms are taken of 2^11 times the probability (up to 2^15), which puts what they drop below 2^-36 of the largest.
 template <bool BF16> constexpr float kLift = BF16 ? 1.f : 2048.f;
 
@@ -464,7 +469,8 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
     __shared__ __attribute__((aligned(16))) float sh_acc[kWaves][NH][DP];
     __shared__ f32x2 sh_ml[kWaves][NH];
     l = rows_sum(l);
-    float nf = 0.f;   // NaN if some accumulated value is not finite
+    // not 0: some accumulated value is not finite (NaN), or the reference is beyond kFusedRef
+    float nf = fabsf(m) > kFusedRef && m != kEmptyMax ? 1.f : 0.f;
     if (n < ng) {
 #pragma unroll
         for (int w = 0; w < NV; ++w)
@@ -484,9 +490,9 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
     auto head_out = [&](int g) { return ((long long)b * p.Hq + hq0 + g) * D; };
     auto head_part = [&](int g) { return ((long long)b * p.Hq + hq0 + g) * p.n_splits + split; };
     if (sh_bad) {
-        // V (or K, or q) holds infinities or NaNs.  The terms of a probability meet an infinite V one by one, and one
-        // that is zero or negative turns it into a NaN, so the split is done again with the probability as one factor:
-        // a wavefront per head, a token at a time.
+        // V (or K, or q) holds infinities or NaNs, or scores are beyond kFusedRef.  The terms of a probability meet an infinite
+        // V one by one, and one that is zero or negative turns it into a NaN, so the split is done again with the
+        // probability as one factor, and with exponents from score differences: a wavefront per head, a token at a time.
         for (int g = wave; g < ng; g += kWaves) {
             constexpr int C = D / 64;
             typedef typename std::conditional<BF16, __bf16, _Float16>::type elem_t;
@@ -502,8 +508,8 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
                 float sc = 0.f;
 #pragma unroll
                 for (int c = 0; c < C; ++c) sc = fmaf(qs[c], (float)kp[c * 64 + lane], sc);
-                sc = wave_sum(sc) * p.scale_log2e;
-                const float mn = fmaxf(ms, sc), al = exp2f(ms - mn), pr = exp2f(sc - mn);
+                sc = wave_sum(sc);
+                const float mn = fmaxf(ms, sc), al = exp2f((ms - mn) * p.scale_log2e), pr = exp2f((sc - mn) * p.scale_log2e);
                 ls = ls * al + pr;
 #pragma unroll
                 for (int c = 0; c < C; ++c) a[c] = fmaf(pr, (float)vp[c * 64 + lane], a[c] * al);
@@ -514,7 +520,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
                 if (p.direct_mode >= 0) store_out(p.out, head_out(g) + c * 64 + lane, p.direct_mode, ls == 0.f ? 0.f : a[c] / ls);
                 else p.part_acc[head_part(g) * D + c * 64 + lane] = a[c];
             }
-            if (p.direct_mode < 0 && lane == 0) *(f32x2 *)&p.part_ml[head_part(g) * 2] = f32x2{ms, ls};
+            if (p.direct_mode < 0 && lane == 0) *(f32x2 *)&p.part_ml[head_part(g) * 2] = f32x2{ms * p.scale_log2e, ls};
         }
         return;
     }

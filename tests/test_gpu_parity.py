@@ -445,6 +445,35 @@ def test_decode_attention_nan_scores(dtype, n_splits):
     assert np.isfinite(got[~hit]).all() and np.abs(got - want)[~hit].max() <= ATTN_ATOL and (got[2] == 0).all()
 
 
+@pytest.mark.parametrize("D", [64, 128, 256])
+@pytest.mark.parametrize("dtype", [W.F16, W.BF16])
+def test_decode_attention_scores_beyond_the_exact_range(D, dtype):
+    """Scores of 2^30 and more, whose last place is far above 1: the largest score of a sequence takes all the weight, and the result is
+    its row of V.  Every score is a whole multiple of a large power of two, exact in fp32, so no other token comes near."""
+    H, G, lens = 1, 2, [40 + 13 * i for i in range(12)]
+    cfg = W.KVConfig("steep", 1420 + D, 1, H, H * G, D, len(lens), dtype, 512, 8, 2, W.PER_SEQ, W.BHSD, 0, len_range=(1, 2))
+    case = Case(cfg, "cuda", lens=lens)
+    top = 2.0 ** (13 if dtype == W.F16 else 18)      # K = top (1 + j / 128): exact in both types
+    k, q = case.k[0].clone(), W.query(cfg, 0, "cpu").clone()
+    q[:] = torch.tensor([top, -top]).view(1, G, 1)   # the second head prefers the smallest key
+    best = torch.empty((len(lens), G), dtype=torch.int64)
+    for b, n in enumerate(lens):
+        j = torch.randperm(n, generator=torch.Generator().manual_seed(b)) * 100 // n
+        j[j == j.max()], j[j == j.min()] = 0, 1
+        hi, lo = b % n, (7 * b + 5) % n
+        j[hi], j[lo] = 101 + b, -1
+        k[b, 0, :n] = (top * (1 + j.double() / 128)).to(k.dtype).cuda().view(n, 1)
+        best[b] = torch.tensor([hi, lo])
+    out = torch.zeros((len(lens), H * G, D), dtype=torch.float32, device="cuda")
+    for n_splits in (0, 1, 3):
+        ws = torch.empty(kv.kv_decode_attn_workspace(case.plan, n_splits, max(lens)), dtype=torch.uint8, device="cuda")
+        kv.kv_decode_attn(case.plan, case.make_view([k], case.v), 0, q.cuda(), out, kv.KV_OUT_F32, n_splits, ws)
+        torch.cuda.synchronize()
+        for b in range(len(lens)):
+            for g in range(G):
+                assert torch.equal(out[b, g].cpu(), case.v[0][b, 0, best[b, g]].float().cpu()), (n_splits, b, g)
+
+
 @pytest.mark.parametrize("bt", [1, 8, 12, 32, 48])
 def test_paged_source_other_block_sizes(bt):
     """Paged pools whose blocks hold other than 16 token rows (a power of two below and above the 16-row tile, sizes
