@@ -492,37 +492,70 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
     if (sh_bad) {
         // V (or K, or q) holds infinities or NaNs, or scores are beyond kFusedRef.  The terms of a probability meet an infinite
         // V one by one, and one that is zero or negative turns it into a NaN, so the split is done again with the
-        // probability as one factor, and with exponents from score differences: a wavefront per head, a token at a time.
-        for (int g = wave; g < ng; g += kWaves) {
-            constexpr int C = D / 64;
-            typedef typename std::conditional<BF16, __bf16, _Float16>::type elem_t;
-            const elem_t *qp = (const elem_t *)(p.q + ((long long)b * p.Hq + hq0 + g) * DV);
-            float qs[C], a[C], ms = kEmptyMax, ls = 0.f;
+        // probability as one factor, and with exponents from score differences: a wavefront takes every kWaves-th run of 8
+        // tokens, whose loads are in flight together, for 4 heads at a time, and leaves its states in their places in LDS.
+        // (fp16, 8 KV heads x 32K x 128 with one infinity per KV head: 101 us at 4 heads, 62 at one; 539 and 511 with a
+        // wavefront per head and a token at a time.)
+        constexpr int C = D / 64, kRun = 8, kHeads = 4;
+        typedef typename std::conditional<BF16, __bf16, _Float16>::type elem_t;
+        for (int h0 = 0; h0 < ng; h0 += kHeads) {
+            float qs[kHeads][C], a[kHeads][C], ms[kHeads], ls[kHeads];
 #pragma unroll
-            for (int c = 0; c < C; ++c) { qs[c] = (float)qp[c * 64 + lane]; a[c] = 0.f; }
-            for (int t = t_begin; t < t_end; ++t) {
-                const int blk = PAGED ? tbl[block_of(t)] : 0;
-                if (PAGED && (unsigned)blk >= (unsigned)p.n_pool) continue;
-                const long long rb = row_base(t, blk);
-                const elem_t *kp = (const elem_t *)(p.K + rb), *vp = (const elem_t *)(p.V + rb);
-                float sc = 0.f;
+            for (int g = 0; g < kHeads; ++g) {
+                const elem_t *qp = (const elem_t *)(p.q + ((long long)b * p.Hq + hq0 + min(h0 + g, ng - 1)) * DV);
+                ms[g] = kEmptyMax;
+                ls[g] = 0.f;
 #pragma unroll
-                for (int c = 0; c < C; ++c) sc = fmaf(qs[c], (float)kp[c * 64 + lane], sc);
-                sc = wave_sum(sc);
-                const float mn = fmaxf(ms, sc), al = exp2f((ms - mn) * p.scale_log2e), pr = exp2f((sc - mn) * p.scale_log2e);
-                ls = ls * al + pr;
+                for (int c = 0; c < C; ++c) { qs[g][c] = (float)qp[c * 64 + lane]; a[g][c] = 0.f; }
+            }
+            for (int t0 = t_begin + kRun * wave; t0 < t_end; t0 += kRun * kWaves) {
+                elem_t kv[kRun][C], vv[kRun][C];
+                bool ok[kRun];
 #pragma unroll
-                for (int c = 0; c < C; ++c) a[c] = fmaf(pr, (float)vp[c * 64 + lane], a[c] * al);
-                ms = mn;
+                for (int i = 0; i < kRun; ++i) {   // rows past the end re-read the split's last row; masked below
+                    const int t = min(t0 + i, t_end - 1), blk = PAGED ? tbl[block_of(t)] : 0;
+                    ok[i] = t0 + i < t_end && (!PAGED || (unsigned)blk < (unsigned)p.n_pool);
+                    const long long rb = row_base(t, blk);
+                    const elem_t *kp = (const elem_t *)(p.K + rb), *vp = (const elem_t *)(p.V + rb);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) { kv[i][c] = kp[c * 64 + lane]; vv[i][c] = vp[c * 64 + lane]; }
+                }
+#pragma unroll
+                for (int g = 0; g < kHeads; ++g) {
+                    if (h0 + g >= ng) continue;
+                    float s[kRun], mn = ms[g];
+#pragma unroll
+                    for (int i = 0; i < kRun; ++i) {
+                        float dot = 0.f;
+#pragma unroll
+                        for (int c = 0; c < C; ++c) dot = fmaf(qs[g][c], (float)kv[i][c], dot);
+                        s[i] = wave_sum(dot);
+                        if (ok[i]) mn = fmaxf(mn, s[i]);
+                    }
+                    const float al = exp2f((ms[g] - mn) * p.scale_log2e);
+                    ms[g] = mn;
+                    ls[g] *= al;
+#pragma unroll
+                    for (int c = 0; c < C; ++c) a[g][c] *= al;
+#pragma unroll
+                    for (int i = 0; i < kRun; ++i) {
+                        if (!ok[i]) continue;   // its row may be another sequence's, or infinite: not even times zero
+                        const float pr = exp2f((s[i] - mn) * p.scale_log2e);
+                        ls[g] += pr;
+#pragma unroll
+                        for (int c = 0; c < C; ++c) a[g][c] = fmaf(pr, (float)vv[i][c], a[g][c]);
+                    }
+                }
             }
 #pragma unroll
-            for (int c = 0; c < C; ++c) {
-                if (p.direct_mode >= 0) store_out(p.out, head_out(g) + c * 64 + lane, p.direct_mode, ls == 0.f ? 0.f : a[c] / ls);
-                else p.part_acc[head_part(g) * D + c * 64 + lane] = a[c];
+            for (int g = 0; g < kHeads; ++g) {
+                if (h0 + g >= ng) continue;
+#pragma unroll
+                for (int c = 0; c < C; ++c) sh_acc[wave][h0 + g][c * 64 + lane] = a[g][c] * kLift<BF16>;
+                if (lane == 0) sh_ml[wave][h0 + g] = f32x2{ms[g] * p.scale_log2e, ls[g]};
             }
-            if (p.direct_mode < 0 && lane == 0) *(f32x2 *)&p.part_ml[head_part(g) * 2] = f32x2{ms * p.scale_log2e, ls};
         }
-        return;
+        __syncthreads();
     }
     for (int idx = threadIdx.x; idx < ng * (D / 4); idx += kThreads) {   // four consecutive columns of one head
         const int g = idx / (D / 4), d = (idx - g * (D / 4)) * 4;

@@ -445,6 +445,71 @@ def test_decode_attention_nan_scores(dtype, n_splits):
     assert np.isfinite(got[~hit]).all() and np.abs(got - want)[~hit].max() <= ATTN_ATOL and (got[2] == 0).all()
 
 
+def _reference_attention(case, k, v, q, skip=()):
+    """Attention in float64 from the device tensors as they are (infinities and NaNs included); `skip` holds (sequence, block)
+    pairs of a paged source whose tokens are not attended."""
+    cfg, out = case.cfg, []
+    for b, n in enumerate(case.lens):
+        if case.paged:
+            ids = case.table_dev[b, :-(-n // cfg.block_tokens)].long().clamp(0, case.n_pool - 1)
+            K, V = (t[ids].transpose(0, 1).reshape(cfg.n_kv_heads, -1, cfg.head_dim)[:, :n].double().cpu() for t in (k, v))
+        else:
+            K, V = (t[b, :, :n].double().cpu() for t in (k, v))
+        use = torch.tensor([(b, t // cfg.block_tokens) not in skip if case.paged else True for t in range(n)], dtype=torch.bool)
+        K, V = K[:, use], V[:, use]
+        qs = q[b].double().view(cfg.n_kv_heads, -1, cfg.head_dim)
+        p = torch.softmax(torch.matmul(qs, K.transpose(1, 2).contiguous()) / cfg.head_dim ** 0.5, dim=-1)
+        out.append(torch.matmul(p, V).reshape(cfg.n_q_heads, cfg.head_dim))
+    return torch.stack(out)
+
+
+@pytest.mark.parametrize("D,G,dtype", [(64, 1, W.F16), (64, 5, W.BF16), (128, 1, W.BF16), (128, 4, W.F16), (128, 16, W.BF16), (256, 2, W.F16),
+                                       (256, 9, W.BF16)])
+@pytest.mark.parametrize("bt", [0, 16, 12])
+def test_decode_attention_values_that_are_not_finite(D, G, dtype, bt):
+    """Infinities and NaNs in V, K and q, at the edges of tiles, of splits and of sequences; a block id outside the pool whose
+    stand-in (block 0) is infinite is still not attended.  Elements that are NaN or infinite in float64 are so here, and all others hold
+    the file's bar (fp32) or one rounding to the output's type beside it."""
+    H, lens = 2, [1, 100, 700, 65, 257]
+    cfg = W.KVConfig("not_finite", 1430 + D + G + bt, 1, H, H * G, D, len(lens), dtype, 512, 8, 2, W.PER_SEQ, W.PAGED if bt else W.BHSD, 0,
+                     len_range=(1, 2), block_tokens=max(bt, 1))
+    case = Case(cfg, "cuda", lens=lens)
+    k, v, q = case.k[0].clone(), case.v[0].clone(), W.query(cfg, 0, "cpu").clone()
+
+    def put(t, b, h, tok, d, x):
+        if bt:
+            t[case.table_dev[b, tok // bt], h, tok % bt, d] = x
+        else:
+            t[b, h, tok, d] = x
+    skip = set()
+    if bt:
+        bad = next(b for b in (2, 4) if 0 not in case.table_dev[b, 3:4].tolist())
+        case.table_dev[bad, 3] = case.n_pool + 5
+        skip = {(bad, 3)}
+        if 0 not in case.table_dev[2:].flatten().tolist():
+            v[0] = float("inf")                       # what an id outside the pool would read
+    put(v, 0, 0, 0, 3, -float("inf"))
+    put(v, 1, 1, 99, D - 1, float("inf"))
+    put(v, 2, 0, 15, 0, float("nan"))
+    put(v, 2, 1, 640, 40, float("inf"))
+    put(k, 3, 0, 64, 7, float("nan"))
+    q[4, 1, 5] = float("inf")                          # scores of either sign: NaN for this head alone
+    want = _reference_attention(case, k, v, q, skip)
+    view = case.make_view([k], [v])
+    for out_mode, dt, rel in ((kv.KV_OUT_F32, torch.float32, 0.0), (kv.KV_OUT_SAME, k.dtype, 2.0 ** -8 if dtype == W.BF16 else 2.0 ** -11)):
+        for n_splits in (0, 1, 3):
+            out = torch.zeros((len(lens), H * G, D), dtype=dt, device="cuda")
+            ws = torch.empty(kv.kv_decode_attn_workspace(case.plan, n_splits, max(lens)), dtype=torch.uint8, device="cuda")
+            kv.kv_decode_attn(case.plan, view, 0, q.cuda(), out, out_mode, n_splits, ws)
+            torch.cuda.synchronize()
+            got = out.double().cpu()
+            assert torch.equal(torch.isnan(got), torch.isnan(want)), n_splits
+            assert torch.equal(got[torch.isinf(want)], want[torch.isinf(want)])
+            fin = torch.isfinite(want)
+            assert torch.isfinite(got[fin]).all()
+            assert ((got - want).abs()[fin] <= ATTN_ATOL + rel * want.abs()[fin]).all()
+
+
 @pytest.mark.parametrize("D", [64, 128, 256])
 @pytest.mark.parametrize("dtype", [W.F16, W.BF16])
 def test_decode_attention_scores_beyond_the_exact_range(D, dtype):
