@@ -445,9 +445,9 @@ def test_decode_attention_nan_scores(dtype, n_splits):
     assert np.isfinite(got[~hit]).all() and np.abs(got - want)[~hit].max() <= ATTN_ATOL and (got[2] == 0).all()
 
 
-def _reference_attention(case, k, v, q, skip=()):
+def _reference_attention(case, k, v, q, skip=(), p_bits=None):
     """Attention in float64 from the device tensors as they are (infinities and NaNs included); `skip` holds (sequence, block)
-    pairs of a paged source whose tokens are not attended."""
+    pairs of a paged source whose tokens are not attended; p_bits keeps that many leading bits of a probability."""
     cfg, out = case.cfg, []
     for b, n in enumerate(case.lens):
         if case.paged:
@@ -459,8 +459,40 @@ def _reference_attention(case, k, v, q, skip=()):
         K, V = K[:, use], V[:, use]
         qs = q[b].double().view(cfg.n_kv_heads, -1, cfg.head_dim)
         p = torch.softmax(torch.matmul(qs, K.transpose(1, 2).contiguous()) / cfg.head_dim ** 0.5, dim=-1)
+        if p_bits is not None:
+            mant, e = torch.frexp(p)
+            p = torch.ldexp((mant * 2 ** p_bits).floor() / 2 ** p_bits, e)
         out.append(torch.matmul(p, V).reshape(cfg.n_q_heads, cfg.head_dim))
     return torch.stack(out)
+
+
+@pytest.mark.parametrize("D", [64, 128, 256])
+@pytest.mark.parametrize("dtype", [W.F16, W.BF16])
+@pytest.mark.parametrize("bt", [0, 16, 12])
+def test_decode_attention_keeps_32_bit_probabilities(D, dtype, bt):
+    """The error against float64, head by head, is that of 32-bit arithmetic: every head width, type, layout, group size class
+    (1 to 4, 5 to 8, 9 to 16 heads, two unequal parts), one split and several.  Bar, relative to a head's 2-norm: a score of up to 8 (in log2)
+    is rounded to 2^-24 of itself in its sum and in the exponent, 11 units of 2^-24 in the probability, and the probability,
+    its products and their sums add a few more; 20 units = 1.2e-6 (0.6e-6 measured), a single element 6 times that.  A probability that
+    has lost its last part (kept to 16 bits in bf16, 11 in fp16) misses the bar: checked against the float64 reference."""
+    H, lens, bar = 1, [1500, 333, 17], 20 * 2.0 ** -24
+    for G in (1, 2, 3, 4, 5, 7, 16, 25):
+        cfg = W.KVConfig("precise", 1500 + D + G + bt, 1, H, H * G, D, len(lens), dtype, 512, 8, 2, W.PER_SEQ, W.PAGED if bt else W.BHSD, 0,
+                         len_range=(1, 2), block_tokens=max(bt, 1))
+        case = Case(cfg, "cuda", lens=lens)
+        q = W.query(cfg, 0, "cpu")
+        want = _reference_attention(case, case.k[0], case.v[0], q)
+        norm = want.norm(dim=-1)
+        coarse = _reference_attention(case, case.k[0], case.v[0], q, p_bits=16 if dtype == W.BF16 else 11)
+        assert ((coarse - want).norm(dim=-1) / norm).max() > 2 * bar
+        for n_splits in (0, 1, 3):
+            out = torch.zeros((len(lens), H * G, D), dtype=torch.float32, device="cuda")
+            ws = torch.empty(kv.kv_decode_attn_workspace(case.plan, n_splits, max(lens)), dtype=torch.uint8, device="cuda")
+            kv.kv_decode_attn(case.plan, case.view, 0, q.cuda(), out, kv.KV_OUT_F32, n_splits, ws)
+            torch.cuda.synchronize()
+            err = out.double().cpu() - want
+            assert (err.norm(dim=-1) / norm).max() <= bar, (G, n_splits)
+            assert (err.abs().amax(dim=-1) * D ** 0.5 / norm).max() <= 6 * bar, (G, n_splits)
 
 
 @pytest.mark.parametrize("D,G,dtype", [(64, 1, W.F16), (64, 5, W.BF16), (128, 1, W.BF16), (128, 4, W.F16), (128, 16, W.BF16), (256, 2, W.F16),
