@@ -18,6 +18,7 @@
 //    On the vector ALU this product cost 32 fused multiply-adds per query head and tile, so a workgroup took at most
 //    4 heads, and only 1 or 2 of a group that 4 does not divide: 7 heads per KV head read K and V seven times
 //    (8 KV heads x 32K tokens x 128, bf16: 220 us, now 25.7; 3 heads 100, now 25.6; 4 heads 25.7, now 25.6).
+//    A single head stays on the vector ALU (see the kernel).
 //  * K and V are read once and never again: the loads are nontemporal.
 // The wavefronts' softmax states of a head are merged through LDS and one fp32 partial per (b, hq, split) is
 // written; the combine kernel merges the splits.  When every sequence is a single split the partial kernel writes the
@@ -85,6 +86,23 @@ struct AttnParams {
     int max_len;           // host-checked bound on every sequence length
     float scale_log2e;     // log2(e) / sqrt(D)
 };
+
+template <bool BF16>
+__device__ __forceinline__ void unpack8(u32x4 v, float f[8])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned w = v[i];
+        if (BF16) {
+            f[2 * i] = __uint_as_float(w << 16);
+            f[2 * i + 1] = __uint_as_float(w & 0xffff0000u);
+        } else {
+            const f16x2 h = __builtin_bit_cast(f16x2, w);
+            f[2 * i] = (float)h[0];
+            f[2 * i + 1] = (float)h[1];
+        }
+    }
+}
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float x)
@@ -223,6 +241,11 @@ constexpr float kFusedRef = 1048576.f;
 // fp16 terms are taken of 2^11 times the probability (up to 2^15), which puts what they drop below 2^-36 of the largest.
 template <bool BF16> constexpr float kLift = BF16 ? 1.f : 2048.f;
 
+// One head (NH = 1, head_dim 128 and 256): V^T P on the vector ALU.  On the matrix cores 15 of 16 columns would repeat the head,
+// and its sums would lie in 4 lanes of 64, from where they cost eight 16-byte LDS stores per wavefront where these take two: 512 against 290 cycles in front of the merge
+// of a split of 128 tokens.  us per layer from a graph, one query head each, matrix cores -> vector ALU: 8 KV heads of 128, 1K tokens
+// 7.9 -> 7.6, 4K 9.1 -> 8.8, 32K 26.1 -> 25.8, batch 32 of 520 15.0 -> 14.3; of 256, 4K 15.9 -> 15.4, 16K 31.5 -> 30.7.  Two heads
+// gain nothing (4K 9.0 / 9.0, of 256 16.1 / 16.4), and head_dim 64 had no faster vector kernel (4K 7.5 against 19).
 template <int D, int NH, bool BF16, int LAYOUT>
 __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_partial_kernel(AttnParams p, SplitTable tab)
 {
@@ -234,6 +257,8 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
     constexpr int TI = tiles_per_step(D);    // tiles of one step
     constexpr int kStepTok = kTile * TI;
     constexpr int NT = kTerms<BF16>;
+    constexpr bool VALU = NH == 1;
+    constexpr int RG = VALU ? 4 : 1;         // states of a wavefront that meet in LDS: one per row group, or one
     constexpr bool PAGED = LAYOUT != kStrided, TILE_ID = LAYOUT == kPagedTiles;
     typedef unsigned vload_t __attribute__((ext_vector_type(E / 2)));
 
@@ -260,14 +285,18 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
     // B operand: column n carries query head n; this lane holds elements 32j + 8tg .. +7 of it.
     u32x4 qv[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) qv[j] = p.q[((long long)b * p.Hq + hq0 + min(n, ng - 1)) * DV + 4 * j + tg];
+    for (int j = 0; j < NJ; ++j) qv[j] = p.q[((long long)b * p.Hq + hq0 + (VALU ? 0 : min(n, ng - 1))) * DV + 4 * j + tg];
 
     float m = kEmptyMax, l = 0.f;     // reference (the same in the four row groups) and this row group's sum
     f32x4 acc[NV][E];                 // element (w, e)[i]: column d = w * 16E + (4tg + i) * E + e of query head n
+    float vacc[NV][E];                // VALU: column d = (w * 16 + n) * E + e, this row group's share
 #pragma unroll
     for (int w = 0; w < NV; ++w)
 #pragma unroll
-        for (int e = 0; e < E; ++e) acc[w][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < E; ++e) {
+            acc[w][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+            vacc[w][e] = 0.f;
+        }
 
     const long long head_off = PAGED ? 0 : (p.seq_off ? p.seq_off[b] / 8 : (long long)b * p.sb) + (long long)h * p.sh;
     const int *tbl = PAGED ? p.table + (long long)b * p.max_blocks : nullptr;
@@ -374,7 +403,27 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
 #pragma unroll
             for (int w = 0; w < NV; ++w)
 #pragma unroll
-                for (int e = 0; e < E; ++e) acc[w][e] *= alpha;
+                for (int e = 0; e < E; ++e) {
+                    if constexpr (VALU) vacc[w][e] *= alpha;
+                    else acc[w][e] *= alpha;
+                }
+        }
+        if constexpr (VALU) {
+            // a tile's sum is formed first and enters the accumulator by one addition, as on the matrix cores
+            float pr[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) pr[i] = __builtin_amdgcn_exp2f(fmaf(sc[0][i], p.scale_log2e, -m));
+            l += (pr[0] + pr[1]) + (pr[2] + pr[3]);
+#pragma unroll
+            for (int w = 0; w < NV; ++w) {
+                float vf[4][8];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) unpack8<BF16>(x.v[0][i][w], vf[i]);
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    vacc[w][e] += fmaf(pr[3], vf[3][e], fmaf(pr[2], vf[2][e], fmaf(pr[1], vf[1][e], pr[0] * vf[0][e])));
+            }
+            return;
         }
         // ---- probabilities, as sums of 16-bit terms: the B operand (row = token, column = query head)
         unsigned pt[NT][2 * TI];
@@ -466,39 +515,63 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
 
     // ---- merge: a wavefront is one softmax state (m, l, acc[D]) per head; the states meet in LDS
     constexpr int DP = D + 4;   // 4 floats of padding: the 16-byte stores of 8 neighbouring heads fall into different banks
-    __shared__ __attribute__((aligned(16))) float sh_acc[kWaves][NH][DP];
-    __shared__ f32x2 sh_ml[kWaves][NH];
-    l = rows_sum(l);
-    // not 0: some accumulated value is not finite (NaN), or the reference is beyond kFusedRef
-    float nf = fabsf(m) > kFusedRef && m != kEmptyMax ? 1.f : 0.f;
-    if (n < ng) {
+    __shared__ __attribute__((aligned(16))) float sh_acc[kWaves][RG][NH][DP];
+    __shared__ f32x2 sh_ml[kWaves][RG * NH];
+    auto far = [](float ref) { return fabsf(ref) > kFusedRef && ref != kEmptyMax; };
+    bool again;   // some accumulated value is not finite, or some reference beyond kFusedRef: the split is done again
+    f32x2 state = {kEmptyMax, 0.f};   // VALU: lane = state
+    if constexpr (VALU) {
+        // position ((2w + e4) * 16 + n) * 4 + k of a state holds column (w * 16 + n) * 8 + 4 * e4 + k: contiguous 16-byte stores
+        float sum = 0.f;
 #pragma unroll
         for (int w = 0; w < NV; ++w)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int e4 = 0; e4 < 2; ++e4) {
+                const float *a = &vacc[w][4 * e4];
+                sum += (a[0] + a[1]) + (a[2] + a[3]);
+                *(f32x4 *)&sh_acc[wave][tg][0][((2 * w + e4) * 16 + n) * 4] = f32x4{a[0], a[1], a[2], a[3]};
+            }
+        // an infinite reference in LDS stands for values that are not finite: the references are read anyway, a flag would
+        // be one more trip to LDS
+        const bool bad = __any(!(fabsf(sum) < INFINITY));
+        if (n == 0) sh_ml[wave][tg] = f32x2{bad ? INFINITY : m, l};
+        __syncthreads();
+        if (lane < RG * kWaves) state = (&sh_ml[0][0])[lane];
+        again = __any(far(state[0]));
+    } else {
+        l = rows_sum(l);
+        float nf = far(m) ? 1.f : 0.f;   // not 0 (or NaN): again
+        if (n < ng) {
 #pragma unroll
-                for (int e4 = 0; e4 < E; e4 += 4) {
-                    const f32x4 v{acc[w][e4][i], acc[w][e4 + 1][i], acc[w][e4 + 2][i], acc[w][e4 + 3][i]};
-                    nf += ((v[0] + v[1]) + (v[2] + v[3])) * 0.f;
-                    *(f32x4 *)&sh_acc[wave][n][w * 16 * E + (4 * tg + i) * E + e4] = v;
-                }
-        if (tg == 0) sh_ml[wave][n] = f32x2{m, l};
+            for (int w = 0; w < NV; ++w)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e4 = 0; e4 < E; e4 += 4) {
+                        const f32x4 v{acc[w][e4][i], acc[w][e4 + 1][i], acc[w][e4 + 2][i], acc[w][e4 + 3][i]};
+                        nf += ((v[0] + v[1]) + (v[2] + v[3])) * 0.f;
+                        *(f32x4 *)&sh_acc[wave][0][n][w * 16 * E + (4 * tg + i) * E + e4] = v;
+                    }
+            if (tg == 0) sh_ml[wave][n] = f32x2{m, l};
+            if (nf != 0.f) sh_bad = 1;
+        }
+        __syncthreads();
+        again = sh_bad != 0;
     }
-    if (nf != 0.f) sh_bad = 1;
-    __syncthreads();
 
     auto head_out = [&](int g) { return ((long long)b * p.Hq + hq0 + g) * D; };
     auto head_part = [&](int g) { return ((long long)b * p.Hq + hq0 + g) * p.n_splits + split; };
-    if (sh_bad) {
+    if (again) {
         // V (or K, or q) holds infinities or NaNs, or scores are beyond kFusedRef.  The terms of a probability meet an infinite
         // V one by one, and one that is zero or negative turns it into a NaN, so the split is done again with the
         // probability as one factor, and with exponents from score differences: a wavefront takes every kWaves-th run of 8
         // tokens, whose loads are in flight together, for 4 heads at a time, and leaves its states in their places in LDS.
         // (fp16, 8 KV heads x 32K x 128 with one infinity per KV head: 101 us at 4 heads, 62 at one; 539 and 511 with a
         // wavefront per head and a token at a time.)
-        constexpr int C = D / 64, kRun = 8, kHeads = 4;
+        constexpr int C = D / 64, kRun = 8, kHeads = NH < 4 ? NH : 4;
         typedef typename std::conditional<BF16, __bf16, _Float16>::type elem_t;
         for (int h0 = 0; h0 < ng; h0 += kHeads) {
+            if (VALU) __syncthreads();   // the states' references have been read
             float qs[kHeads][C], a[kHeads][C], ms[kHeads], ls[kHeads];
 #pragma unroll
             for (int g = 0; g < kHeads; ++g) {
@@ -551,11 +624,46 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
             for (int g = 0; g < kHeads; ++g) {
                 if (h0 + g >= ng) continue;
 #pragma unroll
-                for (int c = 0; c < C; ++c) sh_acc[wave][h0 + g][c * 64 + lane] = a[g][c] * kLift<BF16>;
-                if (lane == 0) sh_ml[wave][h0 + g] = f32x2{ms[g] * p.scale_log2e, ls[g]};
+                for (int c = 0; c < C; ++c) {
+                    const int d = c * 64 + lane;
+                    if constexpr (VALU) {
+                        const int pos = ((2 * (d / 128) + ((d >> 2) & 1)) * 16 + ((d >> 3) & 15)) * 4 + (d & 3);
+                        sh_acc[wave][0][h0 + g][pos] = a[g][c];
+#pragma unroll
+                        for (int r = 1; r < RG; ++r) sh_acc[wave][r][h0 + g][pos] = 0.f;
+                    } else {
+                        sh_acc[wave][0][h0 + g][d] = a[g][c] * kLift<BF16>;
+                    }
+                }
+                if (VALU) {
+                    if (lane < RG) sh_ml[wave][lane] = f32x2{ms[g] * p.scale_log2e, lane == 0 ? ls[g] : 0.f};
+                } else if (lane == 0) {
+                    sh_ml[wave][h0 + g] = f32x2{ms[g] * p.scale_log2e, ls[g]};
+                }
             }
         }
         __syncthreads();
+        if (VALU && lane < RG * kWaves) state = (&sh_ml[0][0])[lane];
+    }
+    if constexpr (VALU) {
+        // 64 positions per wavefront, which forms the states' weights itself (lane = state) and takes them from the lanes by readlane
+        for (int base = wave * 64; base < D; base += kThreads) {
+            const int pos = base + lane, d = ((pos / 128) * 16 + ((pos >> 2) & 15)) * 8 + ((pos >> 6) & 1) * 4 + (pos & 3);
+            const float M = wave_max(state[0]);
+            const float wgt = exp2f(state[0] - M);
+            const float L = wave_sum(state[1] * wgt);
+            float A = 0.f;
+#pragma unroll
+            for (int k = 0; k < kWaves; ++k)
+                A = fmaf((sh_acc[k][0][0][pos] + sh_acc[k][1][0][pos]) + (sh_acc[k][2][0][pos] + sh_acc[k][3][0][pos]), rdlane(wgt, RG * k), A);
+            if (p.direct_mode >= 0) {
+                store_out(p.out, head_out(0) + d, p.direct_mode, L == 0.f ? 0.f : A / L);
+            } else {
+                p.part_acc[head_part(0) * D + d] = A;
+                if (pos == 0) *(f32x2 *)&p.part_ml[head_part(0) * 2] = f32x2{M, L};
+            }
+        }
+        return;
     }
     for (int idx = threadIdx.x; idx < ng * (D / 4); idx += kThreads) {   // four consecutive columns of one head
         const int g = idx / (D / 4), d = (idx - g * (D / 4)) * 4;
@@ -568,7 +676,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
         for (int k = 0; k < kWaves; ++k) {
             const float wgt = exp2f(ml[k][0] - M);
             L = fmaf(ml[k][1], wgt, L);
-            A += *(const f32x4 *)&sh_acc[k][g][d] * (wgt * (1.f / kLift<BF16>));
+            A += *(const f32x4 *)&sh_acc[k][0][g][d] * (wgt * (1.f / kLift<BF16>));
         }
         if (p.direct_mode >= 0) {   // the only split of its sequence: the result itself
             store_out4(p.out, head_out(g) + d, p.direct_mode, L == 0.f ? f32x4{0.f, 0.f, 0.f, 0.f} : A / L);
@@ -783,7 +891,10 @@ void launch_partial_type(bool bf16, dim3 grid, hipStream_t st, const AttnParams 
 template <int D>
 void launch_partial_nh(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const SplitTable &t)
 {
-    if (a.gt <= 4) launch_partial_type<D, 4>(bf16, grid, st, a, t);   // NH only sizes the merge's LDS
+    if constexpr (D >= 128) {
+        if (a.gt == 1) return launch_partial_type<D, 1>(bf16, grid, st, a, t);
+    }
+    if (a.gt <= 4) launch_partial_type<D, 4>(bf16, grid, st, a, t);   // from here on NH only sizes the merge's LDS
     else if (a.gt <= 8) launch_partial_type<D, 8>(bf16, grid, st, a, t);
     else launch_partial_type<D, kMaxHeads>(bf16, grid, st, a, t);
 }
