@@ -42,8 +42,17 @@ struct Seg {
     u32x4 *base;                 // the attention-side buffer this run belongs to (K or V of some layer)
 };
 
+// Grid (tiles of the longest run, run): workgroups past a shorter run's end return at once.
 struct SegTable {
+    static constexpr bool kDense = false;
     Seg seg[kMaxSegs];
+};
+// The runs lie one after the other in the grid's x dimension, run i in [first[i], first[i + 1]), and a workgroup looks up its run.
+struct DenseSegTable {
+    static constexpr bool kDense = true;
+    Seg seg[kMaxSegs];
+    int first[kMaxSegs + 1];
+    int n;
 };
 
 // Every byte is touched once: nontemporal loads and stores keep the streams out of each other's way in L2.
@@ -51,21 +60,32 @@ __device__ __forceinline__ u32x4 ld(const u32x4 *p) { return __builtin_nontempor
 __device__ __forceinline__ void st(u32x4 *p, u32x4 v) { __builtin_nontemporal_store(v, p); }
 
 // PACK: source -> image.  !PACK: image -> source.  U = token rows in flight per thread.
-template <bool PACK, bool PAGED, int U>
+template <bool PACK, bool PAGED, int U, typename TAB>
 __global__ void __launch_bounds__(kThreads)
-kv_layout_kernel(SrcDesc s, u32x4 *__restrict__ img, SegTable segs, int rowv, int rx_log2, int tpb, int rchunk)
+kv_layout_kernel(SrcDesc s, u32x4 *__restrict__ img, TAB segs, int rowv, int rx_log2, int tpb, int rchunk)
 {
-    const Seg sg = segs.seg[blockIdx.y];
+    int run = blockIdx.y, tile = blockIdx.x, n_tiles = gridDim.x;
+    if constexpr (TAB::kDense) {
+        int lo = 0, hi = segs.n;   // the last run that starts at or before this workgroup
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (segs.first[mid] <= tile) lo = mid; else hi = mid;
+        }
+        run = lo;
+        n_tiles = segs.first[run + 1] - segs.first[run];
+        tile -= segs.first[run];
+    }
+    const Seg sg = segs.seg[run];
     const int tid = threadIdx.x;
     u32x4 *const base = sg.base;
 
     if (PACK && sg.pad_vecs && blockIdx.z == 0) {
         const u32x4 z = {0u, 0u, 0u, 0u};
-        for (unsigned int i = blockIdx.x * kThreads + tid; i < sg.pad_vecs; i += gridDim.x * kThreads)
+        for (unsigned int i = tile * kThreads + tid; i < sg.pad_vecs; i += n_tiles * kThreads)
             img[sg.pad_off + i] = z;
     }
 
-    const int t_begin = blockIdx.x * tpb;
+    const int t_begin = tile * tpb;
     if (t_begin >= sg.ntok) return;
     const int t_end = min(sg.ntok, t_begin + tpb);
 
@@ -277,20 +297,19 @@ Shape pick_shape(bool paged, int rowv, int dvec)
     return Shape{lanes, 1, 4 * 1024, 2 * 1024};
 }
 
-template <bool PACK, bool PAGED, int U>
-void launch_k(dim3 grid, hipStream_t stream, const SrcDesc &s, void *img, const SegTable &tab, int rowv, int rx_log2,
-               int tpb, int rchunk)
-{
-    hipLaunchKernelGGL((kv_layout_kernel<PACK, PAGED, U>), grid, dim3(kThreads), 0, stream, s, (u32x4 *)img, tab, rowv,
-                       rx_log2, tpb, rchunk);
-}
+// A ragged batch whose tiles fill little of the grid (tiles of the longest run, run) takes the dense one.  The lookup costs a workgroup
+// some percent, one that returns at once costs about a tenth of one that moves a tile.  us per layer, first grid / dense, by how much
+// is filled: 4 % (32 sequences, one of 16K tokens and the others of about 200; 8 heads x 128) strided 131 / 38, paged 80 / 39; strided 18 %
+// (32 sequences, the others at 15 % of the longest; 2 heads x 128, 8 x 64) 15.6 / 13.2 and 22.4 / 22.1, 27 % 18.8 / 17.8 and 29.6 / 31.4;
+// paged 18 % 16.6 / 14.5 and 22.0 / 23.2.
+bool dense_grid(bool paged, long long total, int most, int n) { return total * (paged ? 8 : 5) < (long long)most * n; }
 
-template <bool PACK, bool PAGED>
-void launch_u(int U, dim3 grid, hipStream_t stream, const SrcDesc &s, void *img, const SegTable &tab, int rowv,
-              int rx_log2, int tpb, int rchunk)
+template <bool PACK, bool PAGED, typename TAB>
+void launch_u(int U, dim3 grid, hipStream_t stream, const SrcDesc &s, void *img, const TAB &tab, int rowv, int rx_log2,
+              int tpb, int rchunk)
 {
-    if (U == 1) launch_k<PACK, PAGED, 1>(grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
-    else launch_k<PACK, PAGED, 2>(grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
+    if (U == 1) hipLaunchKernelGGL((kv_layout_kernel<PACK, PAGED, 1, TAB>), grid, dim3(kThreads), 0, stream, s, (u32x4 *)img, tab, rowv, rx_log2, tpb, rchunk);
+    else hipLaunchKernelGGL((kv_layout_kernel<PACK, PAGED, 2, TAB>), grid, dim3(kThreads), 0, stream, s, (u32x4 *)img, tab, rowv, rx_log2, tpb, rchunk);
 }
 
 template <bool PACK>
@@ -319,18 +338,34 @@ int launch(const kv_plan *p, const kv_view_t *v, const Seg *segs, int nseg, void
     const int rchunk = (int)std::min<long long>(chunk, (rowv + RXv - 1) / RXv * RXv);
     const unsigned n_rchunks = (unsigned)((rowv + rchunk - 1) / rchunk);
     const SrcDesc s = make_src(p, v);
+    auto tiles_of = [&](const Seg &sg) { return std::max(1, (int)(((long long)sg.ntok + tpb - 1) / tpb)); };   // a run without rows may have a pad
 
     for (int g0 = 0; g0 < nseg; g0 += kMaxSegs) {
         const int n = std::min(kMaxSegs, nseg - g0);
-        SegTable tab{};
-        int max_tok = 0;
+        int most = 1;
+        long long total = 0;
         for (int i = 0; i < n; ++i) {
-            tab.seg[i] = segs[g0 + i];
-            max_tok = std::max(max_tok, segs[g0 + i].ntok);
+            const int tiles = tiles_of(segs[g0 + i]);
+            total += tiles;
+            most = std::max(most, tiles);
         }
-        dim3 grid((unsigned)std::max(1, (max_tok + tpb - 1) / tpb), (unsigned)n, n_rchunks);
-        if (paged) launch_u<PACK, true>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
-        else launch_u<PACK, false>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
+        if (dense_grid(paged, total, most, n)) {
+            DenseSegTable tab{};
+            for (int i = 0; i < n; ++i) {
+                tab.seg[i] = segs[g0 + i];
+                tab.first[i + 1] = tab.first[i] + tiles_of(segs[g0 + i]);
+            }
+            tab.n = n;
+            const dim3 grid((unsigned)total, 1u, n_rchunks);
+            if (paged) launch_u<PACK, true>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
+            else launch_u<PACK, false>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
+        } else {
+            SegTable tab{};
+            for (int i = 0; i < n; ++i) tab.seg[i] = segs[g0 + i];
+            const dim3 grid((unsigned)most, (unsigned)n, n_rchunks);
+            if (paged) launch_u<PACK, true>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
+            else launch_u<PACK, false>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { kvb::set_hip_error((int)e); return KV_EHIP; }
     }

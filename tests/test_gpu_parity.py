@@ -950,6 +950,29 @@ def test_pack_unpack_at_the_edges_of_tiles(D, H, B, layout, mode):
     _check_restored(case, k_new, v_new, range(2))
 
 
+@pytest.mark.parametrize("D,H", [(64, 1), (128, 8), (128, 20), (256, 2), (256, 9)])
+@pytest.mark.parametrize("layout", [W.BHSD, W.PAGED])
+@pytest.mark.parametrize("n_long", [1, 6, 20])
+def test_pack_unpack_of_a_batch_with_few_long_sequences(D, H, layout, n_long):
+    """Sequences of very different lengths, more than one launch's runs: tiles looked up in one dense grid (1 and 6 long ones) or in
+    the grid of the longest run (20).  Whole extents of two layers out and back, pads included, byte for byte."""
+    lens = [(900 - 20 * i if i % 2 == 0 and i // 2 < n_long else 1 + i % 9) for i in range(40)]
+    cfg = W.KVConfig("skewed", 1800 + D + H, 2, H, H, D, 40, W.F16, 512, 8, 2, W.PER_SEQ, layout, 900, len_range=(1, 2))
+    case = Case(cfg, "cuda", raw=True, lens=lens, cap_extra=3)
+    nbytes = case.ref.n_blocks_tensor * case.ref.lba_size
+    buf, dst = _guarded(2 * 2 * nbytes)
+    kv.kv_offload_pack_layers(case.plan, 0, 2, case.view, dst)
+    torch.cuda.synchronize()
+    got = dst.cpu().numpy().reshape(4, nbytes)
+    for n in range(4):
+        assert np.array_equal(got[n], case.expected_extent(n // 2, n % 2))
+    assert _guards_intact(buf, 4 * nbytes)
+    k_new, v_new = case.blank_like_source()
+    kv.kv_reload_unpack_layers(case.plan, 0, 2, dst, case.make_view(k_new, v_new))
+    torch.cuda.synchronize()
+    _check_restored(case, k_new, v_new, range(2))
+
+
 @pytest.mark.parametrize("cfg", APPEND_CONFIGS, ids=lambda c: c.name)
 def test_decode_append(cfg):
     """Offload len tokens, then append three tokens one by one; after each the host bytes must equal the
