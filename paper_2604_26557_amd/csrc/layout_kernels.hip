@@ -7,8 +7,9 @@
 // consecutive extent bytes and whole head rows of the source), ty walks token rows.  The (b, h, d)
 // decomposition of a row position is done once per thread per row position and reused for every token, so
 // the inner loop is adds, U independent 16-byte loads, then U stores.  HBM-bound: 2 bytes of traffic per
-// payload byte, no reuse, no LDS; 5.8-6.3 TB/s, where a plain copy reaches 6.3 (32 layers of 8 heads x 4K
-// tokens x 128 out of one launch pair: 169 us for 1 GiB of traffic, 187 with the tiles before pick_shape's).
+// payload byte, no reuse, no LDS.  Where a plain copy reaches 6.3 TB/s, launches of 128 MiB and more run at
+// 5.5-6.3 (strided, rows to 4 KiB), 5.0-5.9 (strided, wider rows of 128- and 256-wide heads; 64-wide 4.6-4.9)
+// and 4.5-5.4 (paged).  32 layers of 8 heads x 4K tokens x 128 out of one launch pair: 169 us for 1 GiB of traffic.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -268,30 +269,34 @@ SrcDesc make_src(const kv_plan *p, const kv_view_t *v)
 
 // Launch shape.  rx_cap: most lanes (log2) along an extent row; unroll: token rows in flight per thread (1 or 2);
 // tile_bytes: extent bytes one workgroup moves; run_bytes: consecutive source bytes per head row a tile should reach when
-// the row is cut into chunks.
+// the row is cut into chunks (0: one sweep of the lanes), which takes precedence over tile_bytes.
 struct Shape {
     int rx_cap, unroll, tile_bytes, run_bytes;
 };
 
-// Many small workgroups that each move 4-8 KiB in one burst, one or two vectors per lane, beat fewer and larger ones at every
-// shape measured: the launch order then walks both sides nearly in order, so what is in flight at one time is a compact
-// window of memory, where 16-64 KiB tiles with 4-8 vectors per lane kept hundreds of scattered streams open.  What
-// differs is which way a workgroup lies in the permutation (us, 32-64 KiB tiles as before -> now; pack / unpack; 128-wide heads):
+// Many small workgroups, one or two vectors per lane in flight, beat fewer and larger ones at every shape measured: the launch
+// order then walks both sides nearly in order, so what is in flight at one time is a compact window of memory, where 16-64 KiB
+// tiles with 4-8 vectors per lane kept hundreds of scattered streams open.  What differs is which way a workgroup lies in the
+// permutation (us, 32-64 KiB tiles as they were -> now; pack / unpack; heads of 128 unless stated):
 //  * strided, rows of up to 4 KiB: one head row by the workgroup's tokens (4 KiB of one head's stream).  8 heads x 4K tokens,
 //    32 layers in one launch pair 188 / 188 -> 171 / 171; x 32K, 8 layers 381 / 372 -> 367 / 355; 30001 tokens 374 / 347 -> 331 / 330; ragged
 //    batch of 8 472 / 458 -> 422 / 420.  Whole rows (16 KiB) are as good at 4K but alias at power-of-two strides (32K: 411).
-//  * strided, wider rows: 4 KiB of one token's row.  16 heads x 256 x batch 4, 8K tokens 368 / 387 -> 370 / 375; 8 heads, batch 8
-//    214 / 214 -> 201 / 199; 32 heads, batch 32, 520 tokens 445 / 446 -> 397 / 381; 4 heads x 64, batch 28 191 / 186 -> 175 / 171.
+//  * strided, wider rows: 4 KiB of the row by one token (heads of 128), by two (256: 8 KiB) or by eight (64: 32 KiB), one after the
+//    other.  us per layer: 16 heads, batch 4 of 4096 47.3 / 48.8 -> 48.4 / 46.7 (by four tokens 50.2 / 49.4), of 3500 43.4 / 44.0 -> 41.0 / 40.5
+//    (43.1 / 42.8); 20 heads, batch 3 39.2 / 38.6 -> 34.6 / 33.6 (37.5 / 35.9); 16 heads x 256, batch 2 38.7 / 39.2 -> 34.2 / 34.6 (by one
+//    token 34.9 / 33.8); 4 heads x 64, batch 28 38.6 / 37.9 -> 25.4 / 25.2; 8 x 64, batch 8 of 4096 37.9 / 37.8 -> 27.6 / 27.9 (by one 29.4 / 27.9).
 //  * paged, rows of up to 4 KiB: whole rows, since a pool block holds all heads of its tokens.  Ragged batch of 8 438 / 480 -> 413 / 449;
-//    8 heads x 256, batch 6 404 / 515 -> 376 / 391; one sequence of 8000 243 / 250 -> 219 / 226.
+//    8 heads x 256, batch 6 404 / 515 -> 376 / 391; one sequence of 8000 243 / 250 -> 219 / 226; 5 heads, where the lanes do not divide the
+//    row, 38.6 / 41.4 -> 36.4 / 38.2 per layer.
 //  * paged, wider rows (several sequences, whose blocks have nothing to do with each other): two head rows by one block's
-//    tokens.  Batch 32 of 600 tokens 439 / 461 -> 250 / 256; 64-wide heads, batch 16 of 500 1046 / 1344 -> 153 / 155.  256-wide heads
-//    take 4 KiB of one token's row instead: 32 heads, batch 3 277 / 273 -> 249 / 240 (two head rows by a block's tokens: 300 / 282).
+//    tokens (8 KiB).  Batch 32 of 600 tokens 439 / 461 -> 250 / 256; 64-wide heads, batch 16 of 500 1046 / 1344 -> 153 / 155.  256-wide heads
+//    take 4 KiB of one token's row instead: per layer 16 heads, batch 2 34.7 / 35.6 (by four tokens 37.4 / 37.5; two head rows by
+//    a block's tokens 40.9 / 40.3).
 Shape pick_shape(bool paged, int rowv, int dvec)
 {
-    if (paged && rowv > 256) return dvec >= 32 ? Shape{8, 1, 4 * 1024, 2 * 1024} : Shape{5, 2, 8 * 1024, 4 * 1024};
+    if (paged && rowv > 256) return dvec >= 32 ? Shape{8, 1, 4 * 1024, 0} : Shape{5, 2, 8 * 1024, 4 * 1024};
     if (paged) return Shape{8, 2, 8 * 1024, 4 * 1024};
-    if (rowv > 256) return Shape{8, 1, 4 * 1024, 1024};
+    if (rowv > 256) return Shape{8, 1, 4 * 1024, dvec == 16 ? 0 : 1024};
     int lanes = 4;   // one head row, at least 16 lanes
     while ((1 << lanes) < dvec && lanes < 8) ++lanes;
     return Shape{lanes, 1, 4 * 1024, 2 * 1024};
