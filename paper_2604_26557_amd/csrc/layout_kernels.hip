@@ -335,6 +335,10 @@ int launch(const kv_plan *p, const kv_view_t *v, const Seg *segs, int nseg, void
     long long want_tok = tile_bytes / (long long)p->row_bytes;
     if (rowv > (1 << rx_log2)) want_tok = std::max<long long>(want_tok, sh.run_bytes / head_row_bytes);
     int tpb = (int)std::max<long long>(1, want_tok);
+    // a grid has fewer than 2^32 threads in a dimension: at most 2^18 tiles of a run, times kMaxSegs runs, times kThreads
+    int max_tok = 0;
+    for (int i = 0; i < nseg; ++i) max_tok = std::max(max_tok, segs[i].ntok);
+    tpb = std::max(tpb, (int)(((long long)max_tok + (1 << 18) - 1) >> 18));
     tpb = (tpb + TY * U - 1) / (TY * U) * (TY * U);
     const int RXv = 1 << rx_log2;
     long long chunk = std::max<long long>(RXv, tile_bytes / 16 / tpb);

@@ -149,3 +149,23 @@ def test_tensor_larger_than_4_gib():
     assert err <= ATTN_ATOL and np.abs(out[-1].double().cpu().numpy() - ref_out[-1]).max() <= ATTN_REL_OF_MAX * scale
     # a single-token sequence attends to its only token: the output is that V row
     assert torch.equal(out[0, 0], V[0, 0, 0].float())
+
+
+def test_pack_of_more_tokens_than_one_grid_dimension_has_tiles():
+    """A run of 2^28 + 5 token rows of 256 bytes: with tiles of 16 rows its grid would hold 2^32 threads in one dimension, which a
+    launch refuses.  One sequence with one head is packed as it lies."""
+    n = (1 << 28) + 5
+    if torch.cuda.mem_get_info()[0] < 150 * (1 << 30):
+        pytest.skip("needs 150 GiB of device memory")
+    words = torch.empty((n, 32), dtype=torch.int64, device="cuda").random_()
+    k = words.view(torch.float16).view(1, 1, n, 128)
+    lens = torch.tensor([n], dtype=torch.int32, device="cuda")
+    plan = kv.kv_layout_plan(1, 1, 1, 128, [n], kv.KV_F16, 512, 8)
+    dst = torch.zeros(int(plan.info.tensor_blocks) * 512, dtype=torch.uint8, device="cuda")
+    kv.kv_offload_pack(plan, 0, kv.KV_K, kv.bhsd_view([k], [k], [n], lens), kv.KV_SEQ_ALL, 0, 0, dst)
+    torch.cuda.synchronize()
+    got = dst[:n * 256].view(torch.int64).view(n, 32)
+    step = 1 << 23
+    assert all(torch.equal(got[i:i + step], words[i:i + step]) for i in range(0, n, step))
+    del words, k, dst, got
+    torch.cuda.empty_cache()
