@@ -689,10 +689,10 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
 
 // out_mode: 0 fp32, 1 fp16, 2 bf16.  One workgroup of 256 threads per (hq, b): threads are (column, split group);
 // a wavefront covers 64 columns of one split group, so the split index is uniform over the wavefront.  Every
-// wavefront forms the split weights exp2(m_s - M) itself (lane = split, two DPP reductions; splits beyond 64 in
-// further rounds) and takes them from the lanes by readlane.  The loads of the (m, l) pairs and of a thread's
-// first 16 partial rows do not depend on each other and are issued together, so the kernel is one memory
-// latency long; the split groups are added through LDS.
+// wavefront forms the split weights exp2(m_s - M) itself (lane = split, 64 at a time, the maximum carried along)
+// and takes them from the lanes by readlane.  The loads of the (m, l) pairs and of a thread's first 16 partial rows do
+// not depend on each other and are issued together, and every further 16 rows while the ones before are added: up to
+// 64 / 32 / 16 splits (head_dim 64 / 128 / 256) the kernel is one memory latency long.  The split groups are added through LDS.
 constexpr int kCombineThreads = 256;
 constexpr int kMaxSplits = 1024;
 
@@ -719,39 +719,35 @@ kv_attn_combine_kernel(const float *__restrict__ part_acc, const float *__restri
         n_splits = min(n_splits_alloc, (len + split_tokens - 1) / split_tokens);
     }
 
-    f32x2 ml0 = f32x2{kEmptyMax, 0.f};
-    if (lane < n_splits) ml0 = *(const f32x2 *)&part_ml[(o + lane) * 2];
-    float pre[kRows];
+    auto load_ml = [&](int s0) { return s0 + lane < n_splits ? *(const f32x2 *)&part_ml[(o + s0 + lane) * 2] : f32x2{kEmptyMax, 0.f}; };
+    auto load_rows = [&](int s0, float rows[kRows]) {
 #pragma unroll
-    for (int i = 0; i < kRows; ++i) {                // first round's rows: independent of the weights
-        const int s = grp + i * NG;
-        pre[i] = s < n_splits ? part_acc[(o + s) * D + d] : 0.f;
-    }
-    // global maximum over all splits (the pairs just loaded; a tail loop when there are more than 64)
-    float M = ml0[0];
-    for (int s = 64 + lane; s < n_splits; s += 64) M = fmaxf(M, part_ml[(o + s) * 2]);
-    M = wave_max(M);
-
-    float A = 0.f, L = 0.f;
-    for (int s0 = 0; s0 < n_splits; s0 += 64) {      // rounds of 64 splits: lane = split
-        f32x2 ml = ml0;
-        if (s0 > 0) {
-            ml = f32x2{kEmptyMax, 0.f};
-            if (s0 + lane < n_splits) ml = *(const f32x2 *)&part_ml[(o + s0 + lane) * 2];
+        for (int i = 0; i < kRows; ++i) {
+            const int s = s0 + grp + i * NG;             // uniform over the wavefront
+            rows[i] = s < n_splits ? part_acc[(o + s) * D + d] : 0.f;
         }
-        const float wgt = exp2f(ml[0] - M);
-        L = fmaf(ml[1], wgt, L);
-        for (int r0 = 0; r0 < 64 && s0 + r0 < n_splits; r0 += kRows * NG) {
+    };
+    f32x2 ml = load_ml(0);
+    float rows[kRows];
+    load_rows(0, rows);                                  // independent of the weights
+    float M = kEmptyMax, A = 0.f, L = 0.f;
+    for (int s0 = 0; s0 < n_splits; s0 += 64) {          // 64 splits at a time: lane = split
+        const f32x2 ml_next = load_ml(s0 + 64);
+        const float Mn = fmaxf(M, wave_max(ml[0])), rescale = exp2f(M - Mn), wgt = exp2f(ml[0] - Mn);
+        M = Mn;
+        A *= rescale;
+        L = fmaf(ml[1], wgt, L * rescale);
 #pragma unroll
-            for (int i = 0; i < kRows; ++i) {
-                const int sl = r0 + grp + i * NG;     // uniform over the wavefront
-                const int s = s0 + sl;
-                if (sl < 64 && s < n_splits) {
-                    const float v = (s0 == 0 && r0 == 0) ? pre[i] : part_acc[(o + s) * D + d];
-                    A = fmaf(v, rdlane(wgt, sl), A);
-                }
-            }
+        for (int r0 = 0; r0 < 64; r0 += kRows * NG) {    // the next rows are on their way while these are added
+            if (s0 + r0 >= n_splits) break;
+            float next[kRows];
+            load_rows(s0 + r0 + kRows * NG, next);
+#pragma unroll
+            for (int i = 0; i < kRows; ++i) A = fmaf(rows[i], rdlane(wgt, r0 + grp + i * NG), A);
+#pragma unroll
+            for (int i = 0; i < kRows; ++i) rows[i] = next[i];
         }
+        ml = ml_next;
     }
     L = wave_sum(L);
 
