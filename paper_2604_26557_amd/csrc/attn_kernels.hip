@@ -31,9 +31,12 @@
 #include <mutex>
 #include <type_traits>
 
+#include "attn_splits.hpp"
 #include "plan.hpp"
 
 namespace {
+
+using namespace kvb;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -50,22 +53,10 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 // flight than HBM likes (8 KV heads x 4 x 8K tokens x 256, one query head each: 46.0 us with eight, 45.2 with six; at
 // head_dim 128 eight and six are equal on long sequences and eight better on many short ones, 47.3 against 54.2 us).
 constexpr int waves(int D) { return D >= 256 ? 6 : 8; }
-constexpr int kTile = 16;             // tokens per MFMA tile
-constexpr int tiles_per_step(int D) { return D >= 128 ? 1 : 2; }  // 8 KiB of K and V in flight per wavefront
 constexpr float kEmptyMax = -1.0e30f; // running maximum of a row group that has seen no token
 // How K and V are addressed: a strided view; a block pool whose blocks hold whole tiles (split starts are multiples of
 // the tile); any other block pool.
 constexpr int kStrided = 0, kPagedTiles = 1, kPagedRows = 2;
-constexpr int kMaxHeads = 16;         // query heads one workgroup takes: the columns of an MFMA
-constexpr int kMaxTableSeqs = 64;     // ragged batches up to this size get per-sequence split counts
-
-// Ragged batch: sequence b owns work items [first[b], first[b+1]) of the grid's x dimension, each of
-// tokens[b] token rows (the last one shorter).
-struct SplitTable {
-    int first[kMaxTableSeqs + 1];
-    int tokens[kMaxTableSeqs];
-};
-
 struct AttnParams {
     const u32x4 *K, *V;    // attention-side buffers of the layer
     const u32x4 *q;        // [B, Hq, D]
@@ -694,7 +685,6 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
 // not depend on each other and are issued together, and every further 16 rows while the ones before are added: up to
 // 64 / 32 / 16 splits (head_dim 64 / 128 / 256) the kernel is one memory latency long.  The split groups are added through LDS.
 constexpr int kCombineThreads = 256;
-constexpr int kMaxSplits = 1024;
 
 template <int D>
 __global__ void __launch_bounds__(kCombineThreads)
@@ -767,24 +757,7 @@ kv_attn_combine_kernel(const float *__restrict__ part_acc, const float *__restri
     }
 }
 
-// Workgroups that share a KV head: as few as the columns of an MFMA allow, so that K and V are read once.
-int group_parts(int G) { return (G + kMaxHeads - 1) / kMaxHeads; }
-// What kv_decode_attn_splits plans with, and so what the workspace has to hold: parts of 4, 2 or 1 query heads.
-int planned_parts(int G) { return G % 4 == 0 ? G / 4 : (G % 2 == 0 ? G / 2 : G); }
-
-// Tokens per split are a multiple of this: four steps.
-int split_quantum(int D) { return 4 * kTile * tiles_per_step(D); }
-
-// Most splits the automatic choice can make for sequences of up to max_len tokens (sizes the workspace).
-int max_auto_splits(const kv_plan *p, int max_len)
-{
-    const int q = split_quantum(p->D);
-    return (int)std::min<long long>(kMaxSplits, std::max<long long>(1, ((long long)max_len + q - 1) / q));
-}
-
-// Workgroups the automatic split choice aims at: one per compute unit (a workgroup is eight wavefronts; with
-// one per compute unit every one of them starts at once and none waits for a second round).
-int target_workgroups()
+AttnShape attn_shape(const kv_plan *p)
 {
     static int cus = 0;
     if (cus == 0) {
@@ -794,79 +767,7 @@ int target_workgroups()
         else
             cus = 256;
     }
-    return cus;
-}
-
-// Uniform batch: split length from the total token count, so that about one workgroup per compute unit has
-// tokens to read; never shorter than the quantum.
-int choose_splits(const kv_plan *p, int parts, long long total_tokens, int max_len)
-{
-    if (max_len <= 0) return 1;
-    const int q = split_quantum(p->D);
-    const long long groups_per_seq = (long long)p->H * parts;
-    const long long wgs = target_workgroups();
-    long long st = (total_tokens * groups_per_seq + wgs - 1) / wgs;
-    st = std::max<long long>(q, (st + q - 1) / q * q);
-    const long long ns = ((long long)max_len + st - 1) / st;
-    return (int)std::min<long long>(std::max<long long>(1, ns), max_auto_splits(p, max_len));
-}
-
-int split_tokens_for(const kv_plan *p, int n_splits, int max_len)
-{
-    const int q = split_quantum(p->D);
-    long long st = ((long long)max_len + n_splits - 1) / n_splits;
-    st = (st + q - 1) / q * q;
-    return (int)std::max<long long>(st, q);
-}
-
-// Sequences whose K and V are this short per KV head are not split: the second launch and the partials cost more than one
-// workgroup needs for two rounds of its wavefronts (8 KV heads, us per layer from a graph, one split against the automatic
-// choice: 128 x 64 tokens 4.1 / 4.1, x 128 5.3 / 6.7, x 256 7.0 / 6.9, x 384 8.8 / 7.0; head_dim 64, 256 tokens 4.5 / 6.3, 512 6.8 / 6.3;
-// head_dim 256, 128 tokens 7.4 / 8.1, 256 10.7 / 8.3).  Launched call by call the line lies at the longest of these: a launch
-// that is left out saves 3.4 us of host time.
-constexpr long long kWholeBytes = 128 * 1024;
-
-// Ragged batch of up to kMaxTableSeqs sequences: every sequence with tokens gets one split; the remaining
-// workgroups of the budget (one per compute unit, shared by the query-head groups) go, one at a time, to the
-// sequence whose splits are longest; no sequence gets more than cap splits or splits shorter than the quantum.
-// A sequence's split length is then rounded up to whole steps only, not to the quantum: steps are handed out
-// on demand, so nothing is gained by a whole number of rounds, and the longest split gets shorter.
-// Returns the largest split count.
-int apportion_splits(const kv_plan *p, int parts, const int32_t *lens, int cap, SplitTable *t)
-{
-    const int q = split_quantum(p->D);
-    const long long groups_per_seq = (long long)p->H * parts;
-    int nb[kMaxTableSeqs];
-    long long used = 0;
-    for (int b = 0; b < p->B; ++b) { nb[b] = lens[b] > 0 ? 1 : 0; used += nb[b]; }
-    const long long budget = std::max<long long>(used, target_workgroups() / groups_per_seq);
-    while (used < budget) {
-        int best = -1;
-        double longest = 0.0;
-        for (int b = 0; b < p->B; ++b) {
-            if (nb[b] == 0 || nb[b] >= cap || (long long)(nb[b] + 1) * q > (long long)lens[b] + q - 1) continue;
-            const double cur = (double)lens[b] / nb[b];
-            if (cur > longest) { longest = cur; best = b; }
-        }
-        if (best < 0) break;
-        ++nb[best];
-        ++used;
-    }
-    const int step = kTile * tiles_per_step(p->D);
-    int most = 1, first = 0;
-    for (int b = 0; b < p->B; ++b) {
-        t->first[b] = first;
-        int st = q;
-        if (nb[b] > 0) {
-            st = std::max(q, (int)((((long long)lens[b] + nb[b] - 1) / nb[b] + step - 1) / step * step));
-            nb[b] = (lens[b] + st - 1) / st;   // rounding the split length up may leave fewer splits
-        }
-        t->tokens[b] = st;
-        first += nb[b];
-        most = std::max(most, nb[b]);
-    }
-    for (int b = p->B; b <= kMaxTableSeqs; ++b) t->first[b] = first;
-    return most;
+    return AttnShape{p->B, p->H, p->Hq, p->D, cus};
 }
 
 template <int D, int NH, bool BF16>
@@ -900,43 +801,11 @@ void launch_partial_nh(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a
 extern "C" size_t kv_decode_attn_workspace(const kv_plan_t *p, int n_splits, int max_len)
 {
     if (!p || n_splits < 0 || max_len < 0) return 0;
-    const int ns = n_splits > 0 ? n_splits : max_auto_splits(p, max_len);
+    const int ns = n_splits > 0 ? n_splits : max_auto_splits(attn_shape(p), max_len);
     return (size_t)p->B * p->Hq * ns * (p->D + 2) * sizeof(float);
 }
 
 namespace {
-
-// Split choice for the given lengths: fills the table (ragged batches of up to kMaxTableSeqs sequences) or the
-// common split length; returns the split count the partials are laid out for, at most `cap` unless the caller gave it.
-int plan_splits(const kv_plan *p, int parts, const int32_t *lens, int n_splits, int cap, bool *use_table, SplitTable *tab,
-                int *split_tokens)
-{
-    int max_len = 0;
-    long long total_len = 0;
-    bool uniform = true;
-    for (int b = 0; b < p->B; ++b) {
-        max_len = std::max(max_len, lens[b]);
-        total_len += lens[b];
-        if (lens[b] != lens[0]) uniform = false;
-    }
-    *use_table = !uniform && p->B <= kMaxTableSeqs;
-    if (*use_table && n_splits == 0) {
-        *split_tokens = split_quantum(p->D);  // not used by the kernels in table mode
-        return apportion_splits(p, parts, lens, std::min(cap, max_auto_splits(p, max_len)), tab);
-    }
-    const int ns = n_splits > 0 ? n_splits : std::min(cap, choose_splits(p, parts, total_len, max_len));
-    *split_tokens = split_tokens_for(p, ns, max_len);
-    if (*use_table) {
-        int first = 0;
-        for (int b = 0; b < p->B; ++b) {
-            tab->first[b] = first;
-            tab->tokens[b] = *split_tokens;
-            first += (lens[b] + *split_tokens - 1) / *split_tokens;
-        }
-        for (int b = p->B; b <= kMaxTableSeqs; ++b) tab->first[b] = first;
-    }
-    return ns;
-}
 
 // Checks, split choice and the two launches; shared by both entry points.  Allocates nothing.
 int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *q, void *out, int out_dtype,
@@ -1000,31 +869,15 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     // workgroups only for splits that hold tokens: the x dimension of its grid walks a table of per-sequence
     // split counts, and with the automatic choice each sequence's split length is sized so that every
     // workgroup reads about the same number of tokens.
-    SplitTable tab{};
-    bool use_table = false;
-    const int G = p->Hq / p->H;
-    const size_t per_split = (size_t)p->B * p->Hq * (p->D + 2) * sizeof(float);
-    // The plan counts a workgroup per 4, 2 or 1 query heads; where one workgroup takes more, the same number of
-    // workgroups makes more splits, as far as the workspace holds them.  (A workspace for the most splits any plan makes
-    // holds the plan, and it need not be made: it costs about 1 us for 4 sequences.)
-    const bool whole = n_splits == 0 && (long long)max_len * p->D * 4 <= kWholeBytes;
-    const bool replan = n_splits == 0 && !whole && planned_parts(G) != group_parts(G);
-    int ns = 0;
-    if (!(whole || replan) || ws_bytes < per_split * max_auto_splits(p, max_len)) {
-        ns = plan_splits(p, planned_parts(G), kv->seq_lens_host, n_splits, kMaxSplits, &use_table, &tab, &a.split_tokens);
-        if (ws_bytes < per_split * ns) return KV_ENOSPC;
-    }
-    if (whole) {
-        use_table = false;
-        ns = 1;
-        a.split_tokens = split_tokens_for(p, 1, max_len);
-    } else if (replan) {
-        const int cap = (int)std::min<size_t>(kMaxSplits, ws_bytes / per_split);
-        ns = plan_splits(p, group_parts(G), kv->seq_lens_host, 0, cap, &use_table, &tab, &a.split_tokens);
-    }
+    AttnCut cut{};
+    if (!cut_tokens(attn_shape(p), kv->seq_lens_host, n_splits, ws_bytes, &cut)) return KV_ENOSPC;
+    const SplitTable &tab = cut.tab;
+    const bool use_table = cut.use_table;
+    const int ns = cut.ns, G = p->Hq / p->H;
+    a.split_tokens = cut.split_tokens;
     a.use_table = use_table;
 
-    a.subs = group_parts(G);
+    a.subs = cut.subs;
     a.gt = (G + a.subs - 1) / a.subs;
     a.K = (const u32x4 *)K; a.V = (const u32x4 *)V; a.q = (const u32x4 *)q;
     a.seq_lens = kv->seq_lens_dev;
@@ -1091,7 +944,7 @@ extern "C" int kv_decode_attn_splits(const kv_plan_t *p, const int32_t *seq_lens
     SplitTable tab{};
     bool use_table = false;
     int st = 0;
-    *n_splits_out = plan_splits(p, planned_parts(p->Hq / p->H), seq_lens_host, n_splits, kMaxSplits, &use_table, &tab, &st);
+    *n_splits_out = plan_splits(attn_shape(p), planned_parts(p->Hq / p->H), seq_lens_host, n_splits, kMaxSplits, &use_table, &tab, &st);
     int acc = 0;
     for (int b = 0; b < p->B; ++b) {
         if (first) first[b] = acc;

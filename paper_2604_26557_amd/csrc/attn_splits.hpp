@@ -1,0 +1,189 @@
+// How decode attention cuts the tokens of a batch into splits and the query heads of a KV head into workgroups: host arithmetic
+// without a GPU call, so that it can be tested on its own.
+#pragma once
+
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+
+namespace kvb {
+
+constexpr int kTile = 16;             // tokens per MFMA tile
+constexpr int tiles_per_step(int D) { return D >= 128 ? 1 : 2; }  // 8 KiB of K and V in flight per wavefront
+constexpr int kMaxHeads = 16;         // query heads one workgroup takes: the columns of an MFMA
+constexpr int kMaxTableSeqs = 64;     // ragged batches up to this size get per-sequence split counts
+
+// Ragged batch: sequence b owns work items [first[b], first[b+1]) of the grid's x dimension, each of
+// tokens[b] token rows (the last one shorter).
+struct SplitTable {
+    int first[kMaxTableSeqs + 1];
+    int tokens[kMaxTableSeqs];
+};
+
+constexpr int kMaxSplits = 1024;
+
+// cus: compute units of the GPU.  The automatic choice aims at one workgroup for each (a workgroup is eight wavefronts, six at
+// head_dim 256; with one per compute unit every one of them starts at once and none waits for a second round).
+struct AttnShape {
+    int B, H, Hq, D, cus;
+};
+
+// Workgroups that share a KV head: as few as the columns of an MFMA allow, so that K and V are read once.
+inline int group_parts(int G) { return (G + kMaxHeads - 1) / kMaxHeads; }
+// What kv_decode_attn_splits plans with, and so what the workspace has to hold: parts of 4, 2 or 1 query heads.
+inline int planned_parts(int G) { return G % 4 == 0 ? G / 4 : (G % 2 == 0 ? G / 2 : G); }
+
+// Tokens per split are a multiple of this: four steps.
+inline int split_quantum(int D) { return 4 * kTile * tiles_per_step(D); }
+
+// Most splits the automatic choice can make for sequences of up to max_len tokens (sizes the workspace).
+inline int max_auto_splits(const AttnShape &s, int max_len)
+{
+    const int q = split_quantum(s.D);
+    return (int)std::min<long long>(kMaxSplits, std::max<long long>(1, ((long long)max_len + q - 1) / q));
+}
+
+// Uniform batch: split length from the total token count, so that about one workgroup per compute unit has
+// tokens to read; never shorter than the quantum.
+inline int choose_splits(const AttnShape &s, int parts, long long total_tokens, int max_len)
+{
+    if (max_len <= 0) return 1;
+    const int q = split_quantum(s.D);
+    const long long groups_per_seq = (long long)s.H * parts;
+    const long long wgs = s.cus;
+    long long st = (total_tokens * groups_per_seq + wgs - 1) / wgs;
+    st = std::max<long long>(q, (st + q - 1) / q * q);
+    const long long ns = ((long long)max_len + st - 1) / st;
+    return (int)std::min<long long>(std::max<long long>(1, ns), max_auto_splits(s, max_len));
+}
+
+inline int split_tokens_for(const AttnShape &s, int n_splits, int max_len)
+{
+    const int q = split_quantum(s.D);
+    long long st = ((long long)max_len + n_splits - 1) / n_splits;
+    st = (st + q - 1) / q * q;
+    return (int)std::max<long long>(st, q);
+}
+
+// Ragged batch of up to kMaxTableSeqs sequences: every sequence with tokens gets one split; the remaining
+// workgroups of the budget (one per compute unit, shared by the query-head groups) go, one at a time, to the
+// sequence whose splits are longest; no sequence gets more than cap splits or splits shorter than the quantum.
+// A sequence's split length is then rounded up to whole steps only, not to the quantum: steps are handed out
+// on demand, so nothing is gained by a whole number of rounds, and the longest split gets shorter.
+// Returns the largest split count.
+inline int apportion_splits(const AttnShape &s, int parts, const int32_t *lens, int cap, SplitTable *t)
+{
+    const int q = split_quantum(s.D);
+    const long long groups_per_seq = (long long)s.H * parts;
+    int nb[kMaxTableSeqs];
+    long long used = 0;
+    for (int b = 0; b < s.B; ++b) { nb[b] = lens[b] > 0 ? 1 : 0; used += nb[b]; }
+    const long long budget = std::max<long long>(used, s.cus / groups_per_seq);
+    while (used < budget) {
+        int best = -1;
+        double longest = 0.0;
+        for (int b = 0; b < s.B; ++b) {
+            if (nb[b] == 0 || nb[b] >= cap || (long long)(nb[b] + 1) * q > (long long)lens[b] + q - 1) continue;
+            const double cur = (double)lens[b] / nb[b];
+            if (cur > longest) { longest = cur; best = b; }
+        }
+        if (best < 0) break;
+        ++nb[best];
+        ++used;
+    }
+    const int step = kTile * tiles_per_step(s.D);
+    int most = 1, first = 0;
+    for (int b = 0; b < s.B; ++b) {
+        t->first[b] = first;
+        int st = q;
+        if (nb[b] > 0) {
+            st = std::max(q, (int)((((long long)lens[b] + nb[b] - 1) / nb[b] + step - 1) / step * step));
+            nb[b] = (lens[b] + st - 1) / st;   // rounding the split length up may leave fewer splits
+        }
+        t->tokens[b] = st;
+        first += nb[b];
+        most = std::max(most, nb[b]);
+    }
+    for (int b = s.B; b <= kMaxTableSeqs; ++b) t->first[b] = first;
+    return most;
+}
+
+// Split choice for the given lengths: fills the table (ragged batches of up to kMaxTableSeqs sequences) or the
+// common split length; returns the split count the partials are laid out for, at most `cap` unless the caller gave it.
+inline int plan_splits(const AttnShape &s, int parts, const int32_t *lens, int n_splits, int cap, bool *use_table, SplitTable *tab,
+                int *split_tokens)
+{
+    int max_len = 0;
+    long long total_len = 0;
+    bool uniform = true;
+    for (int b = 0; b < s.B; ++b) {
+        max_len = std::max(max_len, lens[b]);
+        total_len += lens[b];
+        if (lens[b] != lens[0]) uniform = false;
+    }
+    *use_table = !uniform && s.B <= kMaxTableSeqs;
+    if (*use_table && n_splits == 0) {
+        *split_tokens = split_quantum(s.D);  // not used by the kernels in table mode
+        return apportion_splits(s, parts, lens, std::min(cap, max_auto_splits(s, max_len)), tab);
+    }
+    const int ns = n_splits > 0 ? n_splits : std::min(cap, choose_splits(s, parts, total_len, max_len));
+    *split_tokens = split_tokens_for(s, ns, max_len);
+    if (*use_table) {
+        int first = 0;
+        for (int b = 0; b < s.B; ++b) {
+            tab->first[b] = first;
+            tab->tokens[b] = *split_tokens;
+            first += (lens[b] + *split_tokens - 1) / *split_tokens;
+        }
+        for (int b = s.B; b <= kMaxTableSeqs; ++b) tab->first[b] = first;
+    }
+    return ns;
+}
+
+// Sequences whose K and V are this short per KV head are not split: the second launch and the partials cost more than one
+// workgroup needs for two rounds of its wavefronts (8 KV heads, us per layer from a graph, one split against the automatic
+// choice: 128 x 64 tokens 4.1 / 4.1, x 128 5.3 / 6.7, x 256 7.0 / 6.9, x 384 8.8 / 7.0; head_dim 64, 256 tokens 4.5 / 6.3, 512 6.8 / 6.3;
+// head_dim 256, 128 tokens 7.4 / 8.1, 256 10.7 / 8.3).  Launched call by call the line lies at the longest of these: a launch
+// that is left out saves 3.4 us of host time.
+constexpr long long kWholeBytes = 128 * 1024;
+
+// The cut of one launch.
+struct AttnCut {
+    int ns;             // splits the partials are laid out for
+    bool use_table;     // the grid walks `tab`; otherwise every sequence is cut into splits of split_tokens
+    int split_tokens;
+    int subs;           // workgroups that share a KV head
+    SplitTable tab;
+};
+
+// False: the workspace is too small for the plan.
+inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, size_t ws_bytes, AttnCut *c)
+{
+    int max_len = 0;
+    for (int b = 0; b < s.B; ++b) max_len = std::max(max_len, lens[b]);
+    const int G = s.Hq / s.H;
+    const size_t per_split = (size_t)s.B * s.Hq * (s.D + 2) * sizeof(float);
+    // The plan counts a workgroup per 4, 2 or 1 query heads; where one workgroup takes more, the same number of
+    // workgroups makes more splits, as far as the workspace holds them.  (A workspace for the most splits any plan makes
+    // holds the plan, and it need not be made: it costs about 1 us for 4 sequences.)
+    const bool whole = n_splits == 0 && (long long)max_len * s.D * 4 <= kWholeBytes;
+    const bool replan = n_splits == 0 && !whole && planned_parts(G) != group_parts(G);
+    c->subs = group_parts(G);
+    c->use_table = false;
+    c->ns = 0;
+    if (!(whole || replan) || ws_bytes < per_split * max_auto_splits(s, max_len)) {
+        c->ns = plan_splits(s, planned_parts(G), lens, n_splits, kMaxSplits, &c->use_table, &c->tab, &c->split_tokens);
+        if (ws_bytes < per_split * c->ns) return false;
+    }
+    if (whole) {
+        c->use_table = false;
+        c->ns = 1;
+        c->split_tokens = split_tokens_for(s, 1, max_len);
+    } else if (replan) {
+        const int cap = (int)std::min<size_t>(kMaxSplits, ws_bytes / per_split);
+        c->ns = plan_splits(s, group_parts(G), lens, 0, cap, &c->use_table, &c->tab, &c->split_tokens);
+    }
+    return true;
+}
+
+}  // namespace kvb

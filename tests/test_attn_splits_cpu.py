@@ -1,0 +1,73 @@
+"""How a decode attention launch cuts its tokens and shares out its query heads (host arithmetic, no GPU): the cut that is
+launched, which with an automatic split count differs from the plan that sizes the workspace."""
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CUS = 256
+
+
+@pytest.fixture(scope="module")
+def harness(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("splits") / "attn_splits_harness")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2604_26557_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "attn_splits_harness.cpp"), "-o", exe])
+    return exe
+
+
+def _cut(exe, cases):
+    """cases: (H, G, D, lens, n_splits, ws_splits) -> dicts"""
+    text = "".join(f"{len(lens)} {H} {H * G} {D} {CUS} {ns} {ws} {' '.join(map(str, lens))}\n" for H, G, D, lens, ns, ws in cases)
+    out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.splitlines()
+    assert len(out) == len(cases)
+    res = []
+    for line in out:
+        v = list(map(int, line.split()))
+        res.append({"ok": v[0], "ns": v[1], "table": v[2], "subs": v[4], "splits": v[5::2], "tokens": v[6::2]})
+    return res
+
+
+def _planned(G):
+    return G // 4 if G % 4 == 0 else G // 2 if G % 2 == 0 else G
+
+
+def test_every_cut_tiles_its_tokens_within_the_workspace(harness):
+    rnd = random.Random(11)
+    cases = []
+    for _ in range(600):
+        H, G, D = rnd.choice([1, 2, 3, 4, 8, 32]), rnd.choice([1, 2, 3, 4, 5, 7, 8, 12, 16, 17, 40]), rnd.choice([64, 128, 256])
+        n = rnd.choice([1, 63, 200, 1000, 5000, 40000])
+        B = rnd.choice([1, 2, 5, 64, 70])
+        lens = [n] * B if rnd.random() < 0.4 else [rnd.choice([0, 1, rnd.randint(1, n)]) for _ in range(B)]
+        cases.append((H, G, D, lens, rnd.choice([0, 0, 0, 1, 5, 16]), rnd.choice([-1, -1, 1, 3, 40])))
+    for (H, G, D, lens, n_splits, ws), c in zip(cases, _cut(harness, cases)):
+        q, step = (128, 32) if D == 64 else (64, 16)
+        most = min(1024, max(1, -(-max(lens) // q)))
+        if not c["ok"]:
+            assert ws >= 0 or n_splits > most                     # a workspace for any plan is always enough for one
+            continue
+        assert c["ns"] <= (ws if ws >= 0 else max(most, n_splits)) and (n_splits == 0 or c["ns"] == n_splits)
+        assert -(-G // 16) <= c["subs"] <= max(-(-G // 16), _planned(G))
+        for n, nb, st in zip(lens, c["splits"], c["tokens"]):
+            assert nb <= c["ns"] and st >= q and st % (step if c["table"] else q) == 0
+            assert nb == -(-n // st)
+
+
+def test_short_sequences_are_whole_and_wide_groups_fill_the_compute_units(harness):
+    r = _cut(harness, [(8, 4, 128, [256], 0, -1), (8, 4, 128, [257], 0, -1), (8, 4, 64, [512, 3], 0, -1), (1, 4, 256, [129], 0, -1),
+                       (8, 7, 128, [32768], 0, -1), (8, 8, 128, [32768], 0, -1), (8, 4, 128, [32768], 0, -1),
+                       (4, 7, 128, [200, 4000, 3000, 1000], 0, -1)])
+    assert [c["ns"] for c in r[:4]] == [1, 5, 1, 3]
+    # one workgroup takes all query heads of a KV head, and the tokens are cut for the compute units that leaves
+    assert [c["ns"] for c in r[4:7]] == [32, 32, 32] and all(c["subs"] == 1 for c in r[4:])
+    assert r[7]["table"] == 1 and 56 <= sum(r[7]["splits"]) <= CUS // 4   # split lengths are rounded up to steps
+
+
+def test_a_workspace_for_the_plan_alone_bounds_the_cut(harness):
+    """The plan of 7 heads (7 workgroups for each KV head) makes 5 splits of 32K tokens; a workspace for those is accepted and not
+    exceeded, one less is refused."""
+    r = _cut(harness, [(8, 7, 128, [32768], 0, 5), (8, 7, 128, [32768], 0, 4), (8, 7, 128, [32768], 0, 12)])
+    assert r[0]["ok"] and r[0]["ns"] == 5 and not r[1]["ok"] and r[2]["ns"] == 12
