@@ -147,6 +147,11 @@ inline int plan_splits(const AttnShape &s, int parts, const int32_t *lens, int n
 // that is left out saves 3.4 us of host time.
 constexpr long long kWholeBytes = 128 * 1024;
 
+// Where the launch cuts more finely than the plan, splits beyond 64 of a sequence hold at least 256 tokens: below that the partials cost
+// the combine kernel more than the shorter splits save (2 KV heads of 128, bf16, us per layer from a graph: 8K tokens 64 / 128 splits 9.8 / 10.9,
+// 32K 15.7 / 14.3; 1 KV head: 16K tokens 64 / 128 / 256 splits 11.3 / 11.3 / 14.4, 32K 128 / 256 13.2 / 15.5).
+inline int replan_cap(int max_len) { return std::min(kMaxSplits, std::max(64, max_len / 256)); }
+
 // The cut of one launch.
 struct AttnCut {
     int ns;             // splits the partials are laid out for
@@ -180,7 +185,7 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
         c->ns = 1;
         c->split_tokens = split_tokens_for(s, 1, max_len);
     } else if (replan) {
-        const int cap = (int)std::min<size_t>(kMaxSplits, ws_bytes / per_split);
+        const int cap = (int)std::min<size_t>(replan_cap(max_len), ws_bytes / per_split);
         c->ns = plan_splits(s, group_parts(G), lens, 0, cap, &c->use_table, &c->tab, &c->split_tokens);
     }
     return true;

@@ -71,3 +71,11 @@ def test_a_workspace_for_the_plan_alone_bounds_the_cut(harness):
     exceeded, one less is refused."""
     r = _cut(harness, [(8, 7, 128, [32768], 0, 5), (8, 7, 128, [32768], 0, 4), (8, 7, 128, [32768], 0, 12)])
     assert r[0]["ok"] and r[0]["ns"] == 5 and not r[1]["ok"] and r[2]["ns"] == 12
+
+
+def test_finer_cuts_than_the_plan_keep_256_tokens_beyond_64_splits(harness):
+    r = _cut(harness, [(2, 16, 128, [8192], 0, -1), (1, 7, 128, [16384], 0, -1), (1, 7, 128, [65536], 0, -1), (4, 8, 128, [8192], 0, -1),
+                       (1, 7, 128, [16384, 100], 0, -1)])
+    assert [c["ns"] for c in r[:4]] == [64, 64, 256, 64] and r[4]["splits"][0] == 64
+    # where the plan is launched as it is, it is not touched
+    assert _cut(harness, [(1, 4, 128, [16384], 0, -1)])[0]["ns"] == 256
