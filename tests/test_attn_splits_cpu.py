@@ -79,3 +79,12 @@ def test_finer_cuts_than_the_plan_keep_256_tokens_beyond_64_splits(harness):
     assert [c["ns"] for c in r[:4]] == [64, 64, 256, 64] and r[4]["splits"][0] == 64
     # where the plan is launched as it is, it is not touched
     assert _cut(harness, [(1, 4, 128, [16384], 0, -1)])[0]["ns"] == 256
+
+
+def test_a_given_split_count_shares_out_the_heads_within_one_l2(harness):
+    """Split counts made for a workgroup per 4, 2 or 1 query heads: idle compute units take a share of the heads where the workgroups of
+    a KV head lie a multiple of 8 apart, and never more than the plan has."""
+    r = _cut(harness, [(8, 16, 128, [32768], 8, -1), (8, 8, 128, [32768], 16, -1), (8, 8, 128, [32768], 32, -1), (8, 7, 128, [32768], 5, -1),
+                       (2, 7, 128, [4096], 16, -1), (8, 16, 128, [32768], 0, 8), (8, 16, 128, [32768], 0, -1), (8, 4, 128, [32768], 8, -1),
+                       (8, 16, 128, [8192] * 4, 2, -1), (2, 16, 128, [8192] * 2, 16, -1)])
+    assert [c["subs"] for c in r] == [4, 2, 1, 1, 7, 4, 1, 1, 1, 4]
