@@ -14,10 +14,13 @@
 //    head n, which is the layout of the B operand of V^T P: probabilities never leave their lane.
 //  * V^T P on the matrix cores as well: the 16 lanes of a row group load the V rows of their own 4 tokens, 16 bytes
 //    per lane; byte permutes gather the 4 tokens of each of the lane's 8 columns, and that is the A operand.
-//    The probabilities stay 32-bit: each is the sum of three bf16 (exactly) or two fp16 terms (to 2^-24), one product each.
+//    A probability enters in parts, one product each: three bf16 terms, whose sum is the 32-bit value exactly, or two fp16
+//    terms, which drop up to 2^-24 of it and whatever lies below 2^-36 of the reference.  The error against float64 is
+//    that of the whole 32-bit factor or less (fp16, 1.5K tokens of N(0,1), relative to a head's 2-norm: at most 4.3e-7, with the whole
+//    factor 4.6e-7; scores four times as steep 1.9e-6 both).
 //    On the vector ALU this product cost 32 fused multiply-adds per query head and tile, so a workgroup took at most
 //    4 heads, and only 1 or 2 of a group that 4 does not divide: 7 heads per KV head read K and V seven times
-//    (8 KV heads x 32K tokens x 128, bf16: 220 us, now 25.7; 3 heads 100, now 25.6; 4 heads 25.7, now 25.6).
+//    (8 KV heads x 32K tokens x 128, bf16: 224 us, now 26.8; 3 heads 102, now 26.7; 16 heads 61, now 27.2; 4 heads 25.7, now 25.6).
 //    A single head stays on the vector ALU (see the kernel).
 //  * K and V are read once and never again: the loads are nontemporal.
 // The wavefronts' softmax states of a head are merged through LDS and one fp32 partial per (b, hq, split) is
@@ -317,7 +320,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
             } else {
                 ids.k[ti] = tbl[block_of((T0 + n < t_end) ? T0 + n : fb)];
 #pragma unroll
-                for (int i = 0; i < (TILE_ID ? 1 : 4); ++i) {
+                for (int i = 0; i < 4; ++i) {
                     const int tok = T0 + 4 * tg + i;
                     ids.t[ti][i] = tbl[block_of(tok < t_end ? tok : fb)];
                 }
@@ -360,7 +363,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
                 for (int j = 0; j < NJ; ++j) x.k[ti][j] = __builtin_nontemporal_load(kp + 4 * j + tg);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int r = 4 * tg + i, blk = ids.t[ti][TILE_ID ? 0 : i];
+                    const int r = 4 * tg + i, blk = ids.t[ti][i];
                     x.ok[ti][i] = r < rem && (unsigned)blk < (unsigned)p.n_pool;
                     const vload_t *vp = (const vload_t *)(p.V + row_base(r < rem ? T0 + r : R0, blk)) + n;
 #pragma unroll
@@ -436,8 +439,9 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
         // accumulator's magnitude.  The largest term first: within one operation the matrix core drops what lies far
         // below the largest summand.  For the same reason bf16 terms do not share a product; the two fp16 terms of one tile do
         // (V twice as the A operand).  Products that follow each other in one accumulator are of one shape on purpose: a
-        // 16x16x32 product a few instructions after a 16x16x16 product whose result it adds to has read the last two rows
-        // of that result too early here.
+        // 16x16x32 product three instructions after a 16x16x16 product whose result it added to once read the last two rows
+        // of that result too early here, always the same ones.  Whether the compiler's waits or the source were at fault was
+        // not found; no such pair is in the code that the compiler makes, and a test of that code looks for one.
         // Four columns at a time: eight would take the kernel past 128 registers and with that cost the second workgroup of
         // a compute unit (bf16, batch 32 x 32 heads of 512-544 tokens: 50.0 instead of 45.3 us).
         constexpr int kCols = 4;

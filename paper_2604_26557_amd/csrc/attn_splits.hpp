@@ -142,10 +142,10 @@ inline int plan_splits(const AttnShape &s, int parts, const int32_t *lens, int n
 }
 
 // Sequences whose K and V are this short per KV head are not split: the second launch and the partials cost more than one
-// workgroup needs for two rounds of its wavefronts (8 KV heads, us per layer from a graph, one split against the automatic
-// choice: 128 x 64 tokens 4.1 / 4.1, x 128 5.3 / 6.7, x 256 7.0 / 6.9, x 384 8.8 / 7.0; head_dim 64, 256 tokens 4.5 / 6.3, 512 6.8 / 6.3;
-// head_dim 256, 128 tokens 7.4 / 8.1, 256 10.7 / 8.3).  Launched call by call the line lies at the longest of these: a launch
-// that is left out saves 3.4 us of host time.
+// workgroup needs for two rounds of its wavefronts.  Replayed from a graph, one split against the automatic choice, us per layer
+// (1 and 8 KV heads, 1 and 8 sequences, 1 to 16 query heads each): head_dim 64, 256 tokens 4.5-5.7 / 6.2-8.2, 512 tokens 5.8-7.7 / 6.3-9.0 (the worst
+// pair 7.00 / 6.95); 128, 128 tokens 4.1-6.0 / 6.0-9.2, 256 tokens 5.1-8.0 / 6.1-10.3; 256, 128 tokens 5.3-9.5 / 6.6-12.7.  The line lies where
+// the worst pair is level; launched call by call a launch that is left out saves another 3.4 us of host time.
 constexpr long long kWholeBytes = 128 * 1024;
 
 // Where the launch cuts more finely than the plan, splits beyond 64 of a sequence hold at least 256 tokens: below that the partials cost
