@@ -307,7 +307,7 @@ Shape pick_shape(bool paged, int rowv, int dvec)
 // is filled: 4 % (32 sequences, one of 16K tokens and the others of about 200; 8 heads x 128) strided 131 / 38, paged 80 / 39; strided 18 %
 // (32 sequences, the others at 15 % of the longest; 2 heads x 128, 8 x 64) 15.6 / 13.2 and 22.4 / 22.1, 27 % 18.8 / 17.8 and 29.6 / 31.4;
 // paged 18 % 16.6 / 14.5 and 22.0 / 23.2.
-bool dense_grid(bool paged, long long total, int most, int n) { return total * (paged ? 8 : 5) < (long long)most * n; }
+bool dense_grid(bool paged, unsigned total, unsigned most, int n) { return (unsigned long long)total * (paged ? 8 : 5) < (unsigned long long)most * n; }
 
 template <bool PACK, bool PAGED, typename TAB>
 void launch_u(int U, dim3 grid, hipStream_t stream, const SrcDesc &s, void *img, const TAB &tab, int rowv, int rx_log2,
@@ -336,8 +336,11 @@ int launch(const kv_plan *p, const kv_view_t *v, const Seg *segs, int nseg, void
     if (rowv > (1 << rx_log2)) want_tok = std::max<long long>(want_tok, sh.run_bytes / head_row_bytes);
     int tpb = (int)std::max<long long>(1, want_tok);
     // a grid has fewer than 2^32 threads in a dimension: at most 2^18 tiles of a run, times kMaxSegs runs, times kThreads
-    int max_tok = 0;
-    for (int i = 0; i < nseg; ++i) max_tok = std::max(max_tok, segs[i].ntok);
+    int max_tok = 0, min_tok = INT_MAX;
+    for (int i = 0; i < nseg; ++i) {
+        max_tok = std::max(max_tok, segs[i].ntok);
+        min_tok = std::min(min_tok, segs[i].ntok);
+    }
     tpb = std::max(tpb, (int)(((long long)max_tok + (1 << 18) - 1) >> 18));
     tpb = (tpb + TY * U - 1) / (TY * U) * (TY * U);
     const int RXv = 1 << rx_log2;
@@ -347,31 +350,33 @@ int launch(const kv_plan *p, const kv_view_t *v, const Seg *segs, int nseg, void
     const int rchunk = (int)std::min<long long>(chunk, (rowv + RXv - 1) / RXv * RXv);
     const unsigned n_rchunks = (unsigned)((rowv + rchunk - 1) / rchunk);
     const SrcDesc s = make_src(p, v);
-    auto tiles_of = [&](const Seg &sg) { return std::max(1, (int)(((long long)sg.ntok + tpb - 1) / tpb)); };   // a run without rows may have a pad
+    auto tiles_of = [&](int ntok) { return std::max(1u, ((unsigned)ntok + (unsigned)tpb - 1u) / (unsigned)tpb); };   // a run without rows may have a pad
 
     for (int g0 = 0; g0 < nseg; g0 += kMaxSegs) {
         const int n = std::min(kMaxSegs, nseg - g0);
-        int most = 1;
-        long long total = 0;
-        for (int i = 0; i < n; ++i) {
-            const int tiles = tiles_of(segs[g0 + i]);
-            total += tiles;
-            most = std::max(most, tiles);
+        unsigned most = tiles_of(max_tok), total = most * (unsigned)n;
+        if (min_tok != max_tok) {
+            most = total = 0;
+            for (int i = 0; i < n; ++i) {
+                const unsigned tiles = tiles_of(segs[g0 + i].ntok);
+                total += tiles;
+                most = std::max(most, tiles);
+            }
         }
         if (dense_grid(paged, total, most, n)) {
             DenseSegTable tab{};
             for (int i = 0; i < n; ++i) {
                 tab.seg[i] = segs[g0 + i];
-                tab.first[i + 1] = tab.first[i] + tiles_of(segs[g0 + i]);
+                tab.first[i + 1] = tab.first[i] + (int)tiles_of(segs[g0 + i].ntok);
             }
             tab.n = n;
-            const dim3 grid((unsigned)total, 1u, n_rchunks);
+            const dim3 grid(total, 1u, n_rchunks);
             if (paged) launch_u<PACK, true>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
             else launch_u<PACK, false>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
         } else {
             SegTable tab{};
             for (int i = 0; i < n; ++i) tab.seg[i] = segs[g0 + i];
-            const dim3 grid((unsigned)most, (unsigned)n, n_rchunks);
+            const dim3 grid(most, (unsigned)n, n_rchunks);
             if (paged) launch_u<PACK, true>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
             else launch_u<PACK, false>(U, grid, stream, s, img, tab, rowv, rx_log2, tpb, rchunk);
         }
