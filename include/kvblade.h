@@ -343,7 +343,7 @@ int kv_reload_unpack_layers(const kv_plan_t *plan, int layer_begin, int layer_en
  * V[b,h,j,:], j in [0, len_b), h = hq / (H_q/H); fp32 accumulation; split-K over tokens with a
  * combine pass.  len_b = kv->seq_lens_dev (device) with kv->seq_lens_host as its host mirror (both must
  * hold the same values: a batch whose sequences all have one length takes it from the host mirror at launch); a
- * sequence of length 0 yields zeros.  The wavefronts of a workgroup take their tiles on demand, so the order of the
+ * sequence of length 0 yields zeros; a NaN score (NaN in q or K) yields NaN.  The wavefronts of a workgroup take their tiles on demand, so the order of the
  * fp32 sums, and with it the last bits of the result, can differ between two runs on the same inputs.
  * q: device [B,H_q,D] 16-bit, 16-byte aligned; out: device [B,H_q,D] fp32 or 16-bit (out_dtype);
  * workspace: device, >= kv_decode_attn_workspace() bytes (else KV_ENOSPC); n_splits 0 = choose.
@@ -364,7 +364,8 @@ size_t kv_decode_attn_workspace(const kv_plan_t *plan, int n_splits, int max_len
  * sequences with n_splits = 0 gets per-sequence split lengths (whole 16-token tiles, 32 tokens for head_dim 64) such
  * that every workgroup reads about the same number of tokens (about one workgroup per compute unit in all), counting
  * one workgroup per 4 (2, 1) query heads of a KV head.  This plan is what the workspace has to hold; with n_splits = 0
- * the launch may cut the tokens differently within the workspace it is given.
+ * the launch may cut the tokens differently within the workspace it is given (the last bits of a result then depend on
+ * that workspace's size), or not at all where sequences are short.
  */
 int kv_decode_attn_splits(const kv_plan_t *plan, const int32_t *seq_lens_host, int n_splits, int *n_splits_out,
                           int *first, int *tokens);
