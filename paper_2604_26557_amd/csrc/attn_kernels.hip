@@ -30,7 +30,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
+#include <iterator>
 #include <mutex>
 #include <type_traits>
 
@@ -75,11 +77,24 @@ struct AttnParams {
     int gt, subs;          // query heads per workgroup (at most kMaxHeads); workgroups that share a KV head
     int direct_mode;       // >= 0: every sequence has one split, results go to `out` in this mode (store_out); -1: partials
     void *out;             // [B, Hq, D]
-    int use_table;         // 1: blockIdx.x is a work item of the split table; 0: grid (split, head group, sequence)
     int n_splits, split_tokens;
     int max_len;           // host-checked bound on every sequence length
     float scale_log2e;     // log2(e) / sqrt(D)
 };
+
+// Ragged batch: sequence b owns work items [first[b], first[b + 1]) of the grid's x dimension, each of tokens[b] token rows (the
+// last one shorter).  Entries past the batch are INT_MAX.
+struct ItemTable {
+    int first[kMaxTableSeqs], tokens[kMaxTableSeqs];
+};
+// How many splits of each sequence the combine kernel reads.
+struct CountTable {
+    unsigned short splits[kMaxTableSeqs];
+};
+static_assert(kMaxSplits <= 0xffff, "CountTable");
+// Every other batch: the grid is (split, head group, sequence), and the launch copies no table (an empty kernel costs the host 3.7 us
+// with 200 bytes of arguments, 4.0 with 500, 4.2 with 1000).
+struct NoTable {};
 
 template <bool BF16>
 __device__ __forceinline__ void unpack8(u32x4 v, float f[8])
@@ -132,17 +147,6 @@ __device__ __forceinline__ f32x4 mfma_16x16x32(u32x4 a, u32x4 b, f32x4 c)
     if (BF16)
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-
-// Sequence that owns work item `item` of the split table: the last b with first[b] <= item (uniform, scalar).
-__device__ __forceinline__ int table_owner(const SplitTable &t, int B, int item)
-{
-    int lo = 0, hi = B;  // first[lo] <= item < first[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (t.first[mid] <= item) lo = mid; else hi = mid;
-    }
-    return lo;
 }
 
 __device__ __forceinline__ unsigned short f32_to_bf16_rne(float f)
@@ -240,8 +244,8 @@ template <bool BF16> constexpr float kLift = BF16 ? 1.f : 2048.f;
 // of a split of 128 tokens.  us per layer from a graph, one query head each, matrix cores -> vector ALU: 8 KV heads of 128, 1K tokens
 // 7.9 -> 7.6, 4K 9.1 -> 8.8, 32K 26.1 -> 25.8, batch 32 of 520 15.0 -> 14.3; of 256, 4K 15.9 -> 15.4, 16K 31.5 -> 30.7.  Two heads
 // gain nothing (4K 9.0 / 9.0, of 256 16.1 / 16.4), and head_dim 64 had no faster vector kernel (4K 7.5 against 19).
-template <int D, int NH, bool BF16, int LAYOUT>
-__global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_partial_kernel(AttnParams p, SplitTable tab)
+template <int D, int NH, bool BF16, int LAYOUT, typename TAB>
+__global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_partial_kernel(AttnParams p, TAB tab)
 {
     constexpr int kWaves = waves(D), kThreads = 64 * kWaves;
     constexpr int NJ = D / 32;               // MFMA slices along D of q K^T
@@ -257,14 +261,20 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
     typedef unsigned vload_t __attribute__((ext_vector_type(E / 2)));
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int split = blockIdx.x, b = blockIdx.z, split_tokens = p.split_tokens;
-    if (p.use_table) {
+    int split = blockIdx.x, b = blockIdx.z, split_tokens = p.split_tokens, len = p.len_uniform;
+    if constexpr (std::is_same<TAB, ItemTable>::value) {
         // Ragged batch: the grid's x dimension counts only splits that hold tokens, sequence after sequence,
         // each sequence cut into its own number of equal splits (sized on the host so that every workgroup
-        // gets about the same number of tokens).
-        b = table_owner(tab, p.B, (int)blockIdx.x);
-        split = (int)blockIdx.x - tab.first[b];
-        split_tokens = tab.tokens[b];
+        // gets about the same number of tokens).  Lane = sequence: table and lengths come with one memory latency (a search
+        // of scalar loads, each waiting for the one before: 8 sequences of 1K-8K tokens, 16 layers 501 us, now 495; 60 of 100-600 23.3 us a layer, now 22.8).
+        static_assert(kMaxTableSeqs == 64, "a lane per sequence");
+        const int first = tab.first[lane], tokens = tab.tokens[lane], n_tok = p.seq_lens[min(lane, p.B - 1)];
+        b = __builtin_popcountll(__ballot(first <= (int)blockIdx.x)) - 1;   // the last sequence that starts at or before this item
+        split = (int)blockIdx.x - __builtin_amdgcn_readlane(first, b);
+        split_tokens = __builtin_amdgcn_readlane(tokens, b);
+        len = min(__builtin_amdgcn_readlane(n_tok, b), p.max_len);
+    } else if (len < 0) {
+        len = min(p.seq_lens[b], p.max_len);
     }
     const int h = p.subs == 1 ? blockIdx.y : blockIdx.y / p.subs, g0 = (blockIdx.y - h * p.subs) * p.gt;
     const int hq0 = h * p.G + g0;
@@ -272,7 +282,6 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
     const int n = lane & 15;    // MFMA column (query head n; columns past the last head repeat it); also the K row this lane loads
     const int tg = lane >> 4;   // row group: owns tokens 4tg..4tg+3 of a tile; also the D sub-slice of the operands
 
-    const int len = p.len_uniform >= 0 ? p.len_uniform : min(p.seq_lens[b], p.max_len);
     const int t_begin = min(len, split * split_tokens);
     const int t_end = min(len, t_begin + split_tokens);
 
@@ -690,12 +699,11 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
 // 64 / 32 / 16 splits (head_dim 64 / 128 / 256) the kernel is one memory latency long.  The split groups are added through LDS.
 constexpr int kCombineThreads = 256;
 
-template <int D>
+template <int D, typename TAB>
 __global__ void __launch_bounds__(kCombineThreads)
 kv_attn_combine_kernel(const float *__restrict__ part_acc, const float *__restrict__ part_ml,
                        void *__restrict__ out, int Hq, int n_splits_alloc, int out_mode,
-                       const int *__restrict__ seq_lens, int len_uniform, int max_len, int split_tokens,
-                       int use_table, SplitTable tab)
+                       const int *__restrict__ seq_lens, int len_uniform, int max_len, int split_tokens, TAB tab)
 {
     constexpr int CW = D / 64;                       // wavefronts that cover the columns once
     constexpr int NG = (kCombineThreads / 64) / CW;  // split groups (D = 256: 1, 128: 2, 64: 4)
@@ -706,8 +714,8 @@ kv_attn_combine_kernel(const float *__restrict__ part_acc, const float *__restri
     const long long o = ((long long)b * Hq + hq) * n_splits_alloc;
     // only the splits that hold tokens of this sequence were written (and matter)
     int n_splits;
-    if (use_table) {
-        n_splits = tab.first[b + 1] - tab.first[b];
+    if constexpr (std::is_same<TAB, CountTable>::value) {
+        n_splits = tab.splits[b];
     } else {
         const int len = len_uniform >= 0 ? len_uniform : min(seq_lens[b], max_len);
         n_splits = min(n_splits_alloc, (len + split_tokens - 1) / split_tokens);
@@ -774,23 +782,23 @@ AttnShape attn_shape(const kv_plan *p)
     return AttnShape{p->B, p->H, p->Hq, p->D, cus};
 }
 
-template <int D, int NH, bool BF16>
-void launch_partial(dim3 grid, hipStream_t st, const AttnParams &a, const SplitTable &t)
+template <int D, int NH, bool BF16, typename TAB>
+void launch_partial(dim3 grid, hipStream_t st, const AttnParams &a, const TAB &t)
 {
-    if (!a.table) hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kStrided>), grid, dim3(64 * waves(D)), 0, st, a, t);
-    else if (a.bt % kTile == 0) hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedTiles>), grid, dim3(64 * waves(D)), 0, st, a, t);
-    else hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedRows>), grid, dim3(64 * waves(D)), 0, st, a, t);
+    if (!a.table) hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kStrided, TAB>), grid, dim3(64 * waves(D)), 0, st, a, t);
+    else if (a.bt % kTile == 0) hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedTiles, TAB>), grid, dim3(64 * waves(D)), 0, st, a, t);
+    else hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedRows, TAB>), grid, dim3(64 * waves(D)), 0, st, a, t);
 }
 
-template <int D, int NH>
-void launch_partial_type(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const SplitTable &t)
+template <int D, int NH, typename TAB>
+void launch_partial_type(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const TAB &t)
 {
     if (bf16) launch_partial<D, NH, true>(grid, st, a, t);
     else launch_partial<D, NH, false>(grid, st, a, t);
 }
 
-template <int D>
-void launch_partial_nh(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const SplitTable &t)
+template <int D, typename TAB>
+void launch_partial_nh(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const TAB &t)
 {
     if constexpr (D >= 128) {
         if (a.gt == 1) return launch_partial_type<D, 1>(bf16, grid, st, a, t);
@@ -798,6 +806,26 @@ void launch_partial_nh(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a
     if (a.gt <= 4) launch_partial_type<D, 4>(bf16, grid, st, a, t);   // from here on NH only sizes the merge's LDS
     else if (a.gt <= 8) launch_partial_type<D, 8>(bf16, grid, st, a, t);
     else launch_partial_type<D, kMaxHeads>(bf16, grid, st, a, t);
+}
+
+template <typename TAB>
+void launch_partial_d(int D, bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const TAB &t)
+{
+    if (D == 64) launch_partial_nh<64>(bf16, grid, st, a, t);
+    else if (D == 128) launch_partial_nh<128>(bf16, grid, st, a, t);
+    else launch_partial_nh<256>(bf16, grid, st, a, t);
+}
+
+template <typename TAB>
+void launch_combine(int D, dim3 grid, hipStream_t st, const AttnParams &a, int out_mode, const TAB &t)
+{
+#define KV_COMBINE(DD)                                                                                                     \
+    hipLaunchKernelGGL((kv_attn_combine_kernel<DD, TAB>), grid, dim3(kCombineThreads), 0, st, a.part_acc, a.part_ml, a.out, \
+                       a.Hq, a.n_splits, out_mode, a.seq_lens, a.len_uniform, a.max_len, a.split_tokens, t)
+    if (D == 64) KV_COMBINE(64);
+    else if (D == 128) KV_COMBINE(128);
+    else KV_COMBINE(256);
+#undef KV_COMBINE
 }
 
 }  // namespace
@@ -879,8 +907,6 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     const bool use_table = cut.use_table;
     const int ns = cut.ns, G = p->Hq / p->H;
     a.split_tokens = cut.split_tokens;
-    a.use_table = use_table;
-
     a.subs = cut.subs;
     a.gt = (G + a.subs - 1) / a.subs;
     a.K = (const u32x4 *)K; a.V = (const u32x4 *)V; a.q = (const u32x4 *)q;
@@ -901,27 +927,30 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     for (int b = 0; use_table && b < p->B; ++b) direct = direct && kv->seq_lens_host[b] > 0;
     a.direct_mode = direct ? out_mode : -1;
     a.out = out;
-    const long long n_items = a.use_table ? tab.first[p->B] : (max_len > 0 ? (long long)ns * p->B : 0);
+    const long long n_items = use_table ? tab.first[p->B] : (max_len > 0 ? (long long)ns * p->B : 0);
     const unsigned groups = (unsigned)(p->H * a.subs);
-    dim3 grid((unsigned)ns, groups, (unsigned)p->B);
-    if (a.use_table) grid = dim3((unsigned)n_items, groups, 1u);
     if (n_items > 0) {
-        if (p->D == 64) launch_partial_nh<64>(bf16, grid, st, a, tab);
-        else if (p->D == 128) launch_partial_nh<128>(bf16, grid, st, a, tab);
-        else launch_partial_nh<256>(bf16, grid, st, a, tab);
+        if (use_table) {
+            ItemTable items;
+            std::fill(std::copy(tab.first, tab.first + p->B, items.first), std::end(items.first), INT_MAX);
+            std::copy(std::begin(tab.tokens), std::end(tab.tokens), items.tokens);
+            launch_partial_d(p->D, bf16, dim3((unsigned)n_items, groups, 1u), st, a, items);
+        } else {
+            launch_partial_d(p->D, bf16, dim3((unsigned)ns, groups, (unsigned)p->B), st, a, NoTable{});
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { kvb::set_hip_error((int)e); return KV_EHIP; }
     }
 
     if (direct) return KV_OK;
     const dim3 cgrid((unsigned)p->Hq, (unsigned)p->B, 1u);
-#define KV_COMBINE(DD)                                                                                                   \
-    hipLaunchKernelGGL((kv_attn_combine_kernel<DD>), cgrid, dim3(kCombineThreads), 0, st, a.part_acc, a.part_ml, out,   \
-                       p->Hq, ns, out_mode, a.seq_lens, a.len_uniform, max_len, a.split_tokens, a.use_table, tab)
-    if (p->D == 64) KV_COMBINE(64);
-    else if (p->D == 128) KV_COMBINE(128);
-    else KV_COMBINE(256);
-#undef KV_COMBINE
+    if (use_table) {
+        CountTable counts{};
+        for (int b = 0; b < p->B; ++b) counts.splits[b] = (unsigned short)(tab.first[b + 1] - tab.first[b]);
+        launch_combine(p->D, cgrid, st, a, out_mode, counts);
+    } else {
+        launch_combine(p->D, cgrid, st, a, out_mode, NoTable{});
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { kvb::set_hip_error((int)e); return KV_EHIP; }
     return KV_OK;
