@@ -2,7 +2,7 @@
 // the values):  out[b,hq,:] = softmax_j(q[b,hq,:].K[b,h,j,:] / sqrt(D)) V[b,h,j,:],  h = hq / G.
 //
 // Partial kernel: one workgroup of 8 wavefronts (6 when D = 256) per (sequence, query-head group, token split), about one
-// workgroup per compute unit.  A step is a tile of 16 tokens (two tiles when D = 64); the steps of a split
+// workgroup per compute unit, or up to four where one would leave them uneven (attn_splits.hpp).  A step is a tile of 16 tokens (two tiles when D = 64); the steps of a split
 // are handed out to the wavefronts on demand through a counter in LDS, so a wavefront whose loads come back
 // late takes fewer steps and all of them reach the merge together (with a fixed round-robin the slowest
 // wavefront, and the second workgroup of a compute unit, finished 2-4 us after the median).
@@ -32,7 +32,6 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
-#include <iterator>
 #include <mutex>
 #include <type_traits>
 
@@ -82,10 +81,12 @@ struct AttnParams {
     float scale_log2e;     // log2(e) / sqrt(D)
 };
 
-// Ragged batch: sequence b owns work items [first[b], first[b + 1]) of the grid's x dimension, each of tokens[b] token rows (the
-// last one shorter).  Entries past the batch are INT_MAX.
+// Ragged batch: the r-th sequence of the grid's order, seq[r], owns work items [first[r], first[r + 1]), each of tokens[r] token rows
+// (the last one shorter).  Entries past the batch are INT_MAX.
 struct ItemTable {
     int first[kMaxTableSeqs], tokens[kMaxTableSeqs];
+    unsigned char seq[kMaxTableSeqs];
+    int heads_first;   // 1: grid (head group, item); 0: grid (item, head group)
 };
 // How many splits of each sequence the combine kernel reads.
 struct CountTable {
@@ -260,27 +261,41 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
     constexpr bool PAGED = LAYOUT != kStrided, TILE_ID = LAYOUT == kPagedTiles;
     typedef unsigned vload_t __attribute__((ext_vector_type(E / 2)));
 
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int split = blockIdx.x, b = blockIdx.z, split_tokens = p.split_tokens, len = p.len_uniform;
+    int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int split = blockIdx.x, gy = blockIdx.y, b = blockIdx.z, split_tokens = p.split_tokens, len = p.len_uniform;
     if constexpr (std::is_same<TAB, ItemTable>::value) {
-        // Ragged batch: the grid's x dimension counts only splits that hold tokens, sequence after sequence,
-        // each sequence cut into its own number of equal splits (sized on the host so that every workgroup
-        // gets about the same number of tokens).  Lane = sequence: table and lengths come with one memory latency (a search
+        // Ragged batch: the grid counts only splits that hold tokens, sequence after sequence, each sequence cut into its own
+        // number of equal splits.  Lane = sequence: table and lengths come with one memory latency (a search
         // of scalar loads, each waiting for the one before: 8 sequences of 1K-8K tokens, 16 layers 501 us, now 495; 60 of 100-600 23.3 us a layer, now 22.8).
-        static_assert(kMaxTableSeqs == 64, "a lane per sequence");
-        const int first = tab.first[lane], tokens = tab.tokens[lane], n_tok = p.seq_lens[min(lane, p.B - 1)];
-        b = __builtin_popcountll(__ballot(first <= (int)blockIdx.x)) - 1;   // the last sequence that starts at or before this item
-        split = (int)blockIdx.x - __builtin_amdgcn_readlane(first, b);
-        split_tokens = __builtin_amdgcn_readlane(tokens, b);
-        len = min(__builtin_amdgcn_readlane(n_tok, b), p.max_len);
+        static_assert(kMaxTableSeqs == 128, "two sequences per lane");
+        const int item = tab.heads_first ? blockIdx.y : blockIdx.x;
+        gy = tab.heads_first ? blockIdx.x : blockIdx.y;
+        int first = tab.first[lane], tokens = tab.tokens[lane], seq = tab.seq[lane], n_tok = p.seq_lens[min(lane, p.B - 1)];
+        int rank = __builtin_popcountll(__ballot(first <= item)) - 1;   // the last sequence that starts at or before this item
+        int n_tok2 = 0;
+        if (p.B > 64) {
+            n_tok2 = p.seq_lens[min(64 + lane, p.B - 1)];
+            const int first2 = tab.first[64 + lane], in2 = __builtin_popcountll(__ballot(first2 <= item));
+            if (in2) {
+                rank = in2 - 1;
+                first = first2;
+                tokens = tab.tokens[64 + lane];
+                seq = tab.seq[64 + lane];
+            }
+        }
+        b = __builtin_amdgcn_readlane(seq, rank);
+        split = item - __builtin_amdgcn_readlane(first, rank);
+        split_tokens = __builtin_amdgcn_readlane(tokens, rank);
+        len = min(__builtin_amdgcn_readlane(b < 64 ? n_tok : n_tok2, b & 63), p.max_len);
     } else if (len < 0) {
         len = min(p.seq_lens[b], p.max_len);
     }
-    const int h = p.subs == 1 ? blockIdx.y : blockIdx.y / p.subs, g0 = (blockIdx.y - h * p.subs) * p.gt;
+    const int h = p.subs == 1 ? gy : gy / p.subs, g0 = (gy - h * p.subs) * p.gt;
     const int hq0 = h * p.G + g0;
     const int ng = min(p.gt, p.G - g0);   // query heads of this workgroup
-    const int n = lane & 15;    // MFMA column (query head n; columns past the last head repeat it); also the K row this lane loads
-    const int tg = lane >> 4;   // row group: owns tokens 4tg..4tg+3 of a tile; also the D sub-slice of the operands
+    int n = lane & 15;          // MFMA column (query head n; columns past the last head repeat it); also the K row this lane loads
+    int tg = lane >> 4;         // row group: owns tokens 4tg..4tg+3 of a tile; also the D sub-slice of the operands
 
     const int t_begin = min(len, split * split_tokens);
     const int t_end = min(len, t_begin + split_tokens);
@@ -516,6 +531,12 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
         s_cur = s_nxt;
         s_nxt = s_new;
     }
+
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // formed again: kept through the loop they cost three registers, which the largest instances do not have
+    lane = tid & 63;
+    n = lane & 15;
+    tg = lane >> 4;
 
     // ---- merge: a wavefront is one softmax state (m, l, acc[D]) per head; the states meet in LDS
     constexpr int DP = D + 4;   // 4 floats of padding: the 16-byte stores of 8 neighbouring heads fall into different banks
@@ -896,11 +917,9 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     for (int b = 0; b < p->B; ++b)
         if (kv->seq_lens_host[b] != max_len) a.len_uniform = -1;
 
-    // Splits.  A uniform batch (or a split count given by the caller) takes one split length for all sequences
-    // and the grid (split, query-head group, sequence).  A ragged batch of up to 64 sequences launches
-    // workgroups only for splits that hold tokens: the x dimension of its grid walks a table of per-sequence
-    // split counts, and with the automatic choice each sequence's split length is sized so that every
-    // workgroup reads about the same number of tokens.
+    // Splits.  A uniform batch takes one split length for all sequences and the grid (split, query-head group, sequence).  A ragged batch of up
+    // to kMaxTableSeqs sequences launches workgroups only for splits that hold tokens: its grid walks a table of per-sequence
+    // split counts.
     AttnCut cut{};
     if (!cut_tokens(attn_shape(p), kv->seq_lens_host, n_splits, ws_bytes, &cut)) return KV_ENOSPC;
     const SplitTable &tab = cut.tab;
@@ -932,9 +951,16 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     if (n_items > 0) {
         if (use_table) {
             ItemTable items;
-            std::fill(std::copy(tab.first, tab.first + p->B, items.first), std::end(items.first), INT_MAX);
-            std::copy(std::begin(tab.tokens), std::end(tab.tokens), items.tokens);
-            launch_partial_d(p->D, bf16, dim3((unsigned)n_items, groups, 1u), st, a, items);
+            for (int r = 0, first = 0; r < kMaxTableSeqs; ++r) {
+                const int b = r < p->B ? cut.order[r] : 0;
+                items.first[r] = r < p->B ? first : INT_MAX;
+                items.tokens[r] = tab.tokens[b];
+                items.seq[r] = (unsigned char)b;
+                first += tab.first[b + 1] - tab.first[b];
+            }
+            items.heads_first = cut.longest_first;
+            const dim3 grid = cut.longest_first ? dim3(groups, (unsigned)n_items, 1u) : dim3((unsigned)n_items, groups, 1u);
+            launch_partial_d(p->D, bf16, grid, st, a, items);
         } else {
             launch_partial_d(p->D, bf16, dim3((unsigned)ns, groups, (unsigned)p->B), st, a, NoTable{});
         }

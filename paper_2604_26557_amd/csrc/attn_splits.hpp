@@ -11,10 +11,10 @@ namespace kvb {
 constexpr int kTile = 16;             // tokens per MFMA tile
 constexpr int tiles_per_step(int D) { return D >= 128 ? 1 : 2; }  // 8 KiB of K and V in flight per wavefront
 constexpr int kMaxHeads = 16;         // query heads one workgroup takes: the columns of an MFMA
-constexpr int kMaxTableSeqs = 64;     // ragged batches up to this size get per-sequence split counts
+constexpr int kPlanTableSeqs = 64;    // the plan gives ragged batches up to this size per-sequence split counts
+constexpr int kMaxTableSeqs = 128;    // the launch does so up to this size
 
-// Ragged batch: sequence b owns work items [first[b], first[b+1]) of the grid's x dimension, each of
-// tokens[b] token rows (the last one shorter).
+// Ragged batch: sequence b is cut into first[b + 1] - first[b] splits, each of tokens[b] token rows (the last one shorter).
 struct SplitTable {
     int first[kMaxTableSeqs + 1];
     int tokens[kMaxTableSeqs];
@@ -23,7 +23,7 @@ struct SplitTable {
 constexpr int kMaxSplits = 1024;
 constexpr int kXcds = 8;              // dies with an L2 of their own
 
-// cus: compute units of the GPU.  The automatic choice aims at one workgroup for each (a workgroup is eight wavefronts, six at
+// cus: compute units of the GPU.  The plan aims at one workgroup for each (a workgroup is eight wavefronts, six at
 // head_dim 256; with one per compute unit every one of them starts at once and none waits for a second round).
 struct AttnShape {
     int B, H, Hq, D, cus;
@@ -66,7 +66,7 @@ inline int split_tokens_for(const AttnShape &s, int n_splits, int max_len)
     return (int)std::max<long long>(st, q);
 }
 
-// Ragged batch of up to kMaxTableSeqs sequences: every sequence with tokens gets one split; the remaining
+// Ragged batch of up to kPlanTableSeqs sequences: every sequence with tokens gets one split; the remaining
 // workgroups of the budget (one per compute unit, shared by the query-head groups) go, one at a time, to the
 // sequence whose splits are longest; no sequence gets more than cap splits or splits shorter than the quantum.
 // A sequence's split length is then rounded up to whole steps only, not to the quantum: steps are handed out
@@ -109,7 +109,7 @@ inline int apportion_splits(const AttnShape &s, int parts, const int32_t *lens, 
     return most;
 }
 
-// Split choice for the given lengths: fills the table (ragged batches of up to kMaxTableSeqs sequences) or the
+// Split choice for the given lengths: fills the table (ragged batches of up to kPlanTableSeqs sequences) or the
 // common split length; returns the split count the partials are laid out for, at most `cap` unless the caller gave it.
 inline int plan_splits(const AttnShape &s, int parts, const int32_t *lens, int n_splits, int cap, bool *use_table, SplitTable *tab,
                 int *split_tokens)
@@ -122,7 +122,7 @@ inline int plan_splits(const AttnShape &s, int parts, const int32_t *lens, int n
         total_len += lens[b];
         if (lens[b] != lens[0]) uniform = false;
     }
-    *use_table = !uniform && s.B <= kMaxTableSeqs;
+    *use_table = !uniform && s.B <= kPlanTableSeqs;
     if (*use_table && n_splits == 0) {
         *split_tokens = split_quantum(s.D);  // not used by the kernels in table mode
         return apportion_splits(s, parts, lens, std::min(cap, max_auto_splits(s, max_len)), tab);
@@ -160,7 +160,113 @@ struct AttnCut {
     int split_tokens;
     int subs;           // workgroups that share a KV head
     SplitTable tab;
+    // Table: the workgroups of all KV heads for one split lie side by side, and the sequences with the longest splits come first.
+    bool longest_first;
+    unsigned char order[kMaxTableSeqs];   // sequences in the order of the grid
 };
+
+// What a cut costs, as bytes that one compute unit reads in that time.  The plan has one workgroup per compute unit, which is the best cut where
+// it is an even one: every further workgroup costs its start and its merge.  But whole sequences, or few splits of each, are rarely
+// even, and where they are not, several smaller workgroups for every compute unit, dealt out as compute units become free, end together.
+//  * A compute unit reads no more than 1 / kAlone of its share of HBM when others are idle.
+//  * item_bytes for every workgroup after the first (1.2 us at 25 GB/s and compute unit; 4.4 us where a compute unit holds one workgroup at a time:
+//    5 sequences of 4000 tokens, 8 x 8 x 256, one / two / three workgroups for each 34.4 / 39.4 / 43.8), kCombineBytes for the second launch (3.4 us).
+// us per layer from a graph, one workgroup per compute unit (or sequence) / this cut: paged batch of 48 sequences of 200-4000 tokens, 4 KV heads
+// x 7 x 128 51.7 / 42.9, 8 x 4 x 128 113 / 76.6; 20 of 1K-8K, 8 x 4 x 128 74.9 / 65.1; 30 of 200-8000, 5 x 4 x 64 39.7 / 33.2.  Where the plan is
+// even it stays: 8 of 1K-8K 31.0 / 31.8, 3 of 2.5K-20K 26.3 / 29.5.
+constexpr double kAlone = 0.85, kCombineBytes = 84e3;
+inline double item_bytes(const AttnShape &s) { return s.D >= 256 && s.Hq > s.H ? 110e3 : 30e3; }
+
+// per_cu: workgroups per compute unit; longest: token rows of the compute unit that has most.
+inline double cut_cost(const AttnShape &s, double total_tokens, double per_cu, double longest, bool split)
+{
+    const double row = 4.0 * s.D;   // bytes of K and V
+    double c = std::max(total_tokens * s.H / s.cus, kAlone * longest) * row + item_bytes(s) * std::max(0.0, per_cu - 1);
+    if (split) c += kCombineBytes + per_cu * (s.Hq / s.H) * (s.D + 2) * 8;   // partials are written and read
+    return c;
+}
+
+// Uniform batch: the split count, of the plan's and of those that make just one, two, three or four workgroups for a compute unit.
+// us per layer from a graph: 48 sequences of 2000 tokens, 8 x 4 x 128: not split 74.2, in 2 67.2.
+inline int even_splits(const AttnShape &s, int parts, int len, int plan, int cap)
+{
+    const long long units = (long long)s.B * s.H * parts;
+    double best_cost = 0.0;
+    int best = 0;
+    for (int k = 0; k <= 4; ++k) {
+        int ns = k == 0 ? plan : (int)std::min<long long>(cap, k * (long long)s.cus / units);
+        if (ns < 1) continue;
+        const int st = split_tokens_for(s, ns, len);
+        if (k > 0) ns = (len + st - 1) / st;
+        const double per_cu = (double)((len + st - 1) / st) * units / s.cus, rounds = (double)(long long)(per_cu + 0.999999);
+        const double cost = cut_cost(s, (double)len * s.B * parts, per_cu, rounds * std::min(st, len), ns > 1);
+        if (best == 0 || cost < 0.99 * best_cost) { best = ns; best_cost = cost; }
+    }
+    return best;
+}
+
+// Sequences by descending split length.
+inline void order_splits(const AttnShape &s, const int32_t *lens, const SplitTable &t, unsigned char *order)
+{
+    static_assert(kMaxTableSeqs <= 256, "a sequence is a byte");
+    uint64_t key[kMaxTableSeqs];
+    for (int b = 0; b < s.B; ++b) key[b] = (uint64_t)std::min(t.tokens[b], (int)lens[b]) << 8 | (uint64_t)(255 - b);
+    std::sort(key, key + s.B, [](uint64_t x, uint64_t y) { return x > y; });
+    for (int r = 0; r < s.B; ++r) order[r] = (unsigned char)(255 - (key[r] & 255));
+}
+
+inline double table_cost(const AttnShape &s, int parts, const int32_t *lens, const SplitTable &t, const unsigned char *order, int most)
+{
+    const double m = (double)s.cus / (s.H * parts);   // compute units for each of the heads
+    const int n = t.first[s.B], at[3] = {0, (int)m, n - (int)m};
+    double size[3] = {0, 0, 0}, total = 0;
+    for (int r = 0, f = 0; r < s.B; ++r) {
+        const int b = order[r], e = f + t.first[b + 1] - t.first[b];
+        for (int i = 0; i < 3; ++i)
+            if (at[i] >= f && at[i] < e) size[i] = std::min(t.tokens[b], (int)lens[b]);
+        total += lens[b];
+        f = e;
+    }
+    // The grid deals the longest out first, then the next to the same compute units; the third round goes to whichever is free, and where it
+    // is not a whole one (whole sequences) part of a split is left at the end.
+    double longest = size[0] + (n > m ? size[1] : 0);
+    if (n > 2 * m) longest = std::max(longest, (total / m + (most > 1 ? 0 : size[2] / 4)) / kAlone);
+    return cut_cost(s, total * parts, n / m, longest, most > 1);
+}
+
+// Cuts every sequence into splits of at most as many tokens as make three workgroups for a compute unit, or one more for each than there are
+// sequences.  Returns the largest split count.  (48 sequences of 200-4000 tokens, 4 x 7 x 128: 1.9 workgroups for a compute unit 45.5 us, 2.5 47.2, 2.9
+// 44.7, 3.0 43.8, 3.5 47.2, 3.8 45.9.)
+inline int finer_splits(const AttnShape &s, int parts, const int32_t *lens, int cap, SplitTable *t)
+{
+    const int step = kTile * tiles_per_step(s.D), q = split_quantum(s.D);
+    long long total = 0;
+    int used = 0, max_len = 0;
+    for (int b = 0; b < s.B; ++b) { total += lens[b]; used += lens[b] > 0; max_len = std::max(max_len, (int)lens[b]); }
+    const double m = (double)s.cus / (s.H * parts);
+    const int target = std::max((int)(3 * m), used + (int)m);
+    long long lo = std::max<long long>(q, std::max<long long>(total / target, (max_len + cap - 1) / cap)), hi = std::max<long long>(lo, max_len);
+    for (int i = 0; i < 7 && lo < hi; ++i) {   // hi holds the target; lo may not
+        const unsigned st = (unsigned)((lo + hi) / 2);
+        int n = 0;
+        for (int b = 0; b < s.B; ++b) n += (int)(((unsigned)lens[b] + st - 1) / st);
+        if (n <= target) hi = st; else lo = st + 1;
+    }
+    int first = 0, most = 1;
+    for (int b = 0; b < s.B; ++b) {
+        int nb = (int)((lens[b] + hi - 1) / hi), st = q;
+        if (nb > 0) {
+            st = std::max(q, (int)((((long long)lens[b] + nb - 1) / nb + step - 1) / step * step));
+            nb = (int)(((long long)lens[b] + st - 1) / st);
+        }
+        t->first[b] = first;
+        t->tokens[b] = st;
+        first += nb;
+        most = std::max(most, nb);
+    }
+    for (int b = s.B; b <= kMaxTableSeqs; ++b) t->first[b] = first;
+    return most;
+}
 
 // False: the workspace is too small for the plan.
 inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, size_t ws_bytes, AttnCut *c)
@@ -177,19 +283,54 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
     bool limited = n_splits > 0;
     c->subs = group_parts(G);
     c->use_table = false;
+    c->longest_first = false;
     c->ns = 0;
     if (!(whole || replan) || ws_bytes < per_split * max_auto_splits(s, max_len)) {
         c->ns = plan_splits(s, planned_parts(G), lens, n_splits, kMaxSplits, &c->use_table, &c->tab, &c->split_tokens);
         if (ws_bytes < per_split * c->ns) return false;
     }
+    bool uniform = true, empty = false;
+    for (int b = 0; b < s.B; ++b) { uniform = uniform && lens[b] == max_len; empty = empty || lens[b] == 0; }
     if (whole) {
-        c->use_table = false;
         c->ns = 1;
         c->split_tokens = split_tokens_for(s, 1, max_len);
+        c->use_table = !uniform && !empty && s.B <= kMaxTableSeqs && (long long)s.B * s.H * c->subs > s.cus;
+        if (c->use_table)
+            for (int b = 0; b <= kMaxTableSeqs; ++b) {
+                c->tab.first[b] = std::min(b, s.B);
+                if (b < s.B) c->tab.tokens[b] = c->split_tokens;
+            }
     } else if (replan) {
         const int cap = (int)std::min<size_t>(replan_cap(max_len), ws_bytes / per_split);
         c->ns = plan_splits(s, group_parts(G), lens, 0, cap, &c->use_table, &c->tab, &c->split_tokens);
         limited = cap < replan_cap(max_len);
+    }
+    // The plan, or a finer cut where that is the cheaper one.
+    const int cap = (int)std::min<size_t>(replan_cap(max_len), ws_bytes / per_split);
+    if (n_splits == 0 && !whole && max_len > 0 && cap > 0) {
+        if (uniform) {
+            c->ns = even_splits(s, c->subs, max_len, c->ns, cap);
+            c->split_tokens = split_tokens_for(s, c->ns, max_len);
+        } else if (s.B <= kMaxTableSeqs) {
+            if (!c->use_table) {   // more sequences than the plan tables: as it is launched without a table
+                c->use_table = true;
+                for (int b = 0, first = 0; b <= kMaxTableSeqs; ++b) {
+                    c->tab.first[b] = first;
+                    if (b >= s.B) continue;
+                    c->tab.tokens[b] = c->split_tokens;
+                    first += (int)(((long long)lens[b] + c->split_tokens - 1) / c->split_tokens);
+                }
+            }
+            order_splits(s, lens, c->tab, c->order);
+            SplitTable fine;
+            unsigned char order[kMaxTableSeqs];
+            const int most = finer_splits(s, c->subs, lens, cap, &fine);
+            order_splits(s, lens, fine, order);
+            if (table_cost(s, c->subs, lens, fine, order, most) < 0.97 * table_cost(s, c->subs, lens, c->tab, c->order, c->ns)) {
+                c->tab = fine;
+                c->ns = most;
+            }
+        }
     }
     // A split count from the caller, or from a workspace for the plan alone, was made for a workgroup per 4, 2 or 1 heads and
     // leaves compute units idle where one takes all.  As long as there are idle ones the heads are shared out, provided that the workgroups of
@@ -201,6 +342,13 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
         const int items = c->use_table ? c->tab.first[s.B] : c->ns * s.B, apart = c->use_table ? items : c->ns;
         if (items > 0 && apart % kXcds == 0)
             c->subs = std::max(c->subs, std::min(planned_parts(G), (int)(s.cus / ((long long)items * s.H))));
+    }
+    if (c->use_table) {
+        // More workgroups than compute units: those with most to do start first, whichever KV head they belong to.  us per layer from a graph, in the order
+        // of the batch / longest first: 32 sequences of 200-1000 tokens, 32 KV heads x 1 x 128 66.0 / 53.9, 60 of 100-600, 8 x 4 x 128 23.2 / 20.6.
+        c->longest_first = c->subs == 1 && (long long)c->tab.first[s.B] * s.H > s.cus && c->tab.first[s.B] <= 65535;   // a grid's y dimension
+        if (c->longest_first) order_splits(s, lens, c->tab, c->order);
+        else for (int b = 0; b < s.B; ++b) c->order[b] = (unsigned char)b;
     }
     return true;
 }

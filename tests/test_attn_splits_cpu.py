@@ -88,3 +88,67 @@ def test_a_given_split_count_shares_out_the_heads_within_one_l2(harness):
                        (2, 7, 128, [4096], 16, -1), (8, 16, 128, [32768], 0, 8), (8, 16, 128, [32768], 0, -1), (8, 4, 128, [32768], 8, -1),
                        (8, 16, 128, [8192] * 4, 2, -1), (2, 16, 128, [8192] * 2, 16, -1)])
     assert [c["subs"] for c in r] == [4, 2, 1, 1, 7, 4, 1, 1, 1, 4]
+
+
+def test_batches_that_fill_the_compute_units_unevenly_are_cut_more_finely(harness):
+    """Where one workgroup for each compute unit, or a whole sequence for each, leaves some with far more tokens than the mean, there are several
+    workgroups for every compute unit instead; an even plan stays."""
+    rnd = random.Random(5)
+    ragged = [rnd.randint(200, 4000) for _ in range(48)]
+    r = _cut(harness, [(4, 7, 128, ragged, 0, -1), (8, 4, 128, ragged, 0, -1), (8, 4, 128, [2000] * 48, 0, -1), (3, 4, 128, [6000] * 8, 0, -1),
+                       (8, 4, 128, [4000] * 32, 0, -1), (32, 1, 128, [544] * 32, 0, -1), (8, 4, 128, [5000, 5100, 5200, 5300], 0, -1),
+                       (4, 7, 128, ragged, 0, 2)])
+    for c, H in ((r[0], 4), (r[1], 8)):
+        assert c["table"] and 2.6 * CUS <= H * sum(c["splits"]) <= 3 * CUS
+        size = [min(n, st) for n, st in zip(ragged, c["tokens"])]
+        assert max(size) * H * 2 <= sum(ragged) * H * H / CUS       # no split is longer than half of a compute unit's share
+    assert r[2]["splits"] == [2] * 48                               # 768 workgroups, three for each of 256; 384 would be one and a half
+    assert 8 * 3 * r[3]["splits"][0] <= CUS                         # not a few more than there are compute units
+    assert r[4]["ns"] == 1 and r[5]["ns"] == 1                      # one, or four, for each as it is
+    assert 0.9 * CUS <= 8 * sum(r[6]["splits"]) <= CUS              # ragged, but even with one for each
+    assert r[7]["ok"] and r[7]["ns"] <= 2                           # within the workspace
+
+
+def test_the_order_of_the_grid_holds_every_sequence(tmp_path):
+    """Every sequence is in the order once; where the longest come first, the splits' sizes fall along it."""
+    src = tmp_path / "order.cpp"
+    src.write_text(r"""
+#include <cstdio>
+#include <cstdlib>
+#include "attn_splits.hpp"
+int main()
+{
+    std::srand(7);
+    int sorted = 0;
+    for (int it = 0; it < 3000; ++it) {
+        const int G = 1 + std::rand() % 20, H = 1 + std::rand() % 32, D = 64 << (std::rand() % 3), B = 1 + std::rand() % 140, top = 1 + std::rand() % (it % 2 ? 6000 : 300);
+        int32_t lens[140];
+        for (int b = 0; b < B; ++b) lens[b] = std::rand() % 9 ? std::rand() % top + 1 : it % 3 ? 1 : 0;
+        const kvb::AttnShape s{B, H, H * G, D, 256};
+        int max_len = 0;
+        for (int b = 0; b < B; ++b) max_len = lens[b] > max_len ? lens[b] : max_len;
+        kvb::AttnCut c{};
+        const size_t ws = (size_t)B * H * G * (D + 2) * 4 * kvb::max_auto_splits(s, max_len);
+        if (!kvb::cut_tokens(s, lens, it % 5 ? 0 : 1 + std::rand() % 3, ws, &c)) continue;
+        if (!c.use_table) { if (c.longest_first) return 1; continue; }
+        bool seen[140] = {};
+        int last = 1 << 30, items = 0;
+        for (int r = 0; r < B; ++r) {
+            const int b = c.order[r], n = c.tab.first[b + 1] - c.tab.first[b], size = lens[b] < c.tab.tokens[b] ? lens[b] : c.tab.tokens[b];
+            if (b >= B || seen[b]) return 2;
+            seen[b] = true;
+            if (n < 0 || n > c.ns || (long long)n * c.tab.tokens[b] < lens[b]) return 3;
+            if (c.longest_first && size > last) return 4;
+            last = size;
+            items += n;
+        }
+        if (items != c.tab.first[B] || (c.longest_first && (items > 65535 || c.subs != 1))) return 5;
+        sorted += c.longest_first;
+    }
+    std::printf("%d\n", sorted);
+    return sorted > 100 ? 0 : 6;
+}
+""")
+    exe = str(tmp_path / "order")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=address,undefined", "-I", os.path.join(ROOT, "paper_2604_26557_amd", "csrc"), str(src), "-o", exe])
+    subprocess.check_call([exe])

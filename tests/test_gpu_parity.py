@@ -350,6 +350,34 @@ def test_decode_attention_many_ragged_sequences(B, n_splits):
     assert not out[3].any() and not out[B - 1].any()
 
 
+# 32 KV heads: 8 sequences are one workgroup for each compute unit of 256
+@pytest.mark.parametrize("H,G,D,B,lo,hi,empty,layout", [
+    (32, 1, 128, 9, 1, 1500, 0, W.BHSD),      # just over one workgroup per compute unit, longest first, cut more finely
+    (32, 2, 64, 128, 1, 40, 0, W.PAGED),      # whole sequences, the table's last entry, written without a second launch
+    (32, 2, 64, 129, 1, 40, 0, W.BHSD),       # one sequence more than the table holds
+    (16, 3, 128, 100, 20, 700, 3, W.PAGED),   # beyond 64 sequences, some without tokens
+    (32, 4, 256, 8, 1, 1200, 1, W.PAGED),
+    (32, 1, 64, 31, 300, 1300, 0, W.BHSD),
+    (5, 17, 128, 70, 5, 900, 2, W.BHSD),      # two parts of a KV head's query heads: the grid stays in the batch's order
+])
+@pytest.mark.parametrize("n_splits", [0, 2])
+def test_decode_attention_more_workgroups_than_compute_units(H, G, D, B, lo, hi, empty, layout, n_splits):
+    """Ragged batches whose workgroups outnumber the compute units.  Every sequence and head is checked, so that a split given to the
+    wrong sequence, or to none, shows.  Bar: the file's."""
+    cfg = W.KVConfig(f"crowd{B}", 1700 + B + D, 1, H, H * G, D, B, W.BF16 if G % 2 else W.F16, 512, 8, 2, W.PER_SEQ, layout, 0, len_range=(lo, hi))
+    lens = W.seq_lens(cfg)
+    for i in range(empty):
+        lens[i * B // 4] = 0
+    lens[B - 1] = hi
+    case = Case(cfg, "cuda", gen_device="cpu", lens=lens)
+    q = W.query(cfg, 0, "cpu")
+    out = torch.full((B, H * G, D), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(kv.kv_decode_attn_workspace(case.plan, n_splits, max(lens)), dtype=torch.uint8, device="cuda")
+    kv.kv_decode_attn(case.plan, case.view, 0, q.cuda(), out, kv.KV_OUT_F32, n_splits, ws)
+    torch.cuda.synchronize()
+    _attn_check(out, _reference_attention(case, case.k[0], case.v[0], q).float().numpy())
+
+
 # ------------------------------------------------------------------------------------------ pipeline
 # (span_chunks, depth, copy_streams, d2h_mode, h2d_mode)
 @pytest.mark.parametrize("D,G", [(64, 1), (64, 4), (128, 2), (128, 8), (256, 1), (256, 4)])
