@@ -62,31 +62,69 @@ constexpr float kEmptyMax = -1.0e30f; // running maximum of a row group that has
 // the tile); any other block pool.
 constexpr int kStrided = 0, kPagedTiles = 1, kPagedRows = 2;
 struct AttnParams {
-    const u32x4 *K, *V;    // attention-side buffers of the layer
-    const u32x4 *q;        // [B, Hq, D]
     const int *seq_lens;   // device [B]
-    int len_uniform;       // >= 0: every sequence has this length (saves the first dependent load); -1: read seq_lens
     float *part_acc;       // [B, Hq, n_splits, D]
     float *part_ml;        // [B, Hq, n_splits, 2]
-    long long sb, sh, ss;  // strided layout, in 16-byte vectors
     const long long *seq_off;  // strided layout, optional: element offset of each sequence (replaces b*sb)
+    int n_pool;            // paged layout
+    int direct_mode;       // >= 0: every sequence has one split, results go to `out` in this mode (store_out); -1: partials
+    float scale_log2e;     // log2(e) / sqrt(D)
+    void *out;             // [B, Hq, D]
+    int n_splits;
+    int max_len;           // host-checked bound on every sequence length
+};
+
+// Three strides below 2^40 vectors (16 TiB) in four words: 32 bits of each, and a word with 8 further bits of each.
+struct Strides {
+    unsigned long long ss, sh, sb;
+};
+struct PackedStrides {
+    unsigned long long ss_sh;
+    int sb, high;
+};
+constexpr PackedStrides pack_strides(Strides s)
+{
+    return {(s.ss & 0xffffffffull) | s.sh << 32, (int)(unsigned)s.sb,
+            (int)((unsigned)(s.ss >> 32 & 0xff) | (unsigned)(s.sh >> 32 & 0xff) << 8 | (unsigned)(s.sb >> 32 & 0xff) << 16)};
+}
+constexpr Strides unpack_strides(PackedStrides p)
+{
+    return {(p.ss_sh & 0xffffffffull) | (unsigned long long)(p.high & 0xff) << 32, p.ss_sh >> 32 | (unsigned long long)(p.high >> 8 & 0xff) << 32,
+            (unsigned)p.sb | (unsigned long long)(p.high >> 16 & 0xff) << 32};
+}
+constexpr bool strides_survive(Strides s)
+{
+    const Strides u = unpack_strides(pack_strides(s));
+    return u.ss == s.ss && u.sh == s.sh && u.sb == s.sb;
+}
+static_assert(strides_survive({16, 0x80000000ull, 0xffffffffffull}) && strides_survive({0xffffffffffull, 0x80ffffffffull, 0}) &&
+              strides_survive({0x100000000ull, 0, 0x8080000000ull}), "pack_strides");
+// What the partial kernel's first K and V addresses depend on.  These are arguments of their own, 14 words in all, because the
+// command processor can place that many in registers before a wavefront starts; a struct it cannot, and the wavefront then
+// waits for two scalar loads in turn before its first vector load.  us per layer from a graph, struct / arguments: 8 KV heads x 4 x 128, 1K tokens
+// 7.2 / 7.1, 2K 7.8 / 7.6, 4K 8.9 / 8.75; 8 x 8, 4 sequences of 1K-3K 11.6 / 11.3; paged, 2 x 7, 4K 8.2 / 8.0; batches that
+// take 16 us and more are within 1 %.
+struct AttnHead {
+    const u32x4 *K, *V;    // attention-side buffers of the layer
+    const u32x4 *q;        // [B, Hq, D]
+    int len_uniform;       // >= 0: every sequence has this length (saves the first dependent load); -1: read seq_lens
+    int split_tokens;
+    Strides strides;       // strided layout, in 16-byte vectors
     const int *table;      // paged layout
-    int max_blocks, bt, bt_shift, n_pool;
+    int max_blocks, bt;
     int H, Hq, G, B;
     int gt, subs;          // query heads per workgroup (at most kMaxHeads); workgroups that share a KV head
-    int direct_mode;       // >= 0: every sequence has one split, results go to `out` in this mode (store_out); -1: partials
-    void *out;             // [B, Hq, D]
-    int n_splits, split_tokens;
-    int max_len;           // host-checked bound on every sequence length
-    float scale_log2e;     // log2(e) / sqrt(D)
+    bool heads_first;      // table: grid (head group, item), not (item, head group)
 };
+// Numbers of heads fit 16 bits.  The sequences of a table fit 8; what other grids need of B is their z dimension.
+inline unsigned pack16(int lo, int hi) { return (unsigned)lo | (unsigned)hi << 16; }
+static_assert(kMaxHeads < 128 && kMaxTableSeqs < 256, "gt has 7 bits, B 8");
 
 // Ragged batch: the r-th sequence of the grid's order, seq[r], owns work items [first[r], first[r + 1]), each of tokens[r] token rows
 // (the last one shorter).  Entries past the batch are INT_MAX.
 struct ItemTable {
     int first[kMaxTableSeqs], tokens[kMaxTableSeqs];
     unsigned char seq[kMaxTableSeqs];
-    int heads_first;   // 1: grid (head group, item); 0: grid (item, head group)
 };
 // How many splits of each sequence the combine kernel reads.
 struct CountTable {
@@ -246,7 +284,12 @@ template <bool BF16> constexpr float kLift = BF16 ? 1.f : 2048.f;
 // 7.9 -> 7.6, 4K 9.1 -> 8.8, 32K 26.1 -> 25.8, batch 32 of 520 15.0 -> 14.3; of 256, 4K 15.9 -> 15.4, 16K 31.5 -> 30.7.  Two heads
 // gain nothing (4K 9.0 / 9.0, of 256 16.1 / 16.4), and head_dim 64 had no faster vector kernel (4K 7.5 against 19).
 template <int D, int NH, bool BF16, int LAYOUT, typename TAB>
-__global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_partial_kernel(AttnParams p, TAB tab)
+__global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) 
+kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
+                       typename std::conditional<std::is_same<TAB, ItemTable>::value, const int *, unsigned long long>::type lens_arg,
+                       unsigned heads, unsigned shares,
+                       typename std::conditional<LAYOUT != kStrided, const int *, unsigned long long>::type addr_arg, int addr2, int addr3,
+                       AttnParams p, TAB tab)
 {
     constexpr int kWaves = waves(D), kThreads = 64 * kWaves;
     constexpr int NJ = D / 32;               // MFMA slices along D of q K^T
@@ -263,19 +306,22 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
 
     int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int split = blockIdx.x, gy = blockIdx.y, b = blockIdx.z, split_tokens = p.split_tokens, len = p.len_uniform;
+    const int H = heads & 0xffff, G = heads >> 16, Hq = H * G, gt = shares & 0x7f, subs = shares >> 16;
+    int split = blockIdx.x, gy = blockIdx.y, b = blockIdx.z, split_tokens = 0, len = 0;
     if constexpr (std::is_same<TAB, ItemTable>::value) {
         // Ragged batch: the grid counts only splits that hold tokens, sequence after sequence, each sequence cut into its own
         // number of equal splits.  Lane = sequence: table and lengths come with one memory latency (a search
         // of scalar loads, each waiting for the one before: 8 sequences of 1K-8K tokens, 16 layers 501 us, now 495; 60 of 100-600 23.3 us a layer, now 22.8).
         static_assert(kMaxTableSeqs == 128, "two sequences per lane");
-        const int item = tab.heads_first ? blockIdx.y : blockIdx.x;
-        gy = tab.heads_first ? blockIdx.x : blockIdx.y;
-        int first = tab.first[lane], tokens = tab.tokens[lane], seq = tab.seq[lane], n_tok = p.seq_lens[min(lane, p.B - 1)];
+        const int B = shares >> 8 & 0xff;
+        const bool heads_first = shares & 0x80;
+        const int item = heads_first ? blockIdx.y : blockIdx.x;
+        gy = heads_first ? blockIdx.x : blockIdx.y;
+        int first = tab.first[lane], tokens = tab.tokens[lane], seq = tab.seq[lane], n_tok = lens_arg[min(lane, B - 1)];
         int rank = __builtin_popcountll(__ballot(first <= item)) - 1;   // the last sequence that starts at or before this item
         int n_tok2 = 0;
-        if (p.B > 64) {
-            n_tok2 = p.seq_lens[min(64 + lane, p.B - 1)];
+        if (B > 64) {
+            n_tok2 = lens_arg[min(64 + lane, B - 1)];
             const int first2 = tab.first[64 + lane], in2 = __builtin_popcountll(__ballot(first2 <= item));
             if (in2) {
                 rank = in2 - 1;
@@ -288,12 +334,14 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
         split = item - __builtin_amdgcn_readlane(first, rank);
         split_tokens = __builtin_amdgcn_readlane(tokens, rank);
         len = min(__builtin_amdgcn_readlane(b < 64 ? n_tok : n_tok2, b & 63), p.max_len);
-    } else if (len < 0) {
-        len = min(p.seq_lens[b], p.max_len);
+    } else {
+        split_tokens = (int)lens_arg;
+        len = (int)(lens_arg >> 32);
+        if (len < 0) len = min(p.seq_lens[b], p.max_len);
     }
-    const int h = p.subs == 1 ? gy : gy / p.subs, g0 = (gy - h * p.subs) * p.gt;
-    const int hq0 = h * p.G + g0;
-    const int ng = min(p.gt, p.G - g0);   // query heads of this workgroup
+    const int h = subs == 1 ? gy : gy / subs, g0 = (gy - h * subs) * gt;
+    const int hq0 = h * G + g0;
+    const int ng = min(gt, G - g0);   // query heads of this workgroup
     int n = lane & 15;          // MFMA column (query head n; columns past the last head repeat it); also the K row this lane loads
     int tg = lane >> 4;         // row group: owns tokens 4tg..4tg+3 of a tile; also the D sub-slice of the operands
 
@@ -303,7 +351,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
     // B operand: column n carries query head n; this lane holds elements 32j + 8tg .. +7 of it.
     u32x4 qv[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) qv[j] = p.q[((long long)b * p.Hq + hq0 + (VALU ? 0 : min(n, ng - 1))) * DV + 4 * j + tg];
+    for (int j = 0; j < NJ; ++j) qv[j] = q[((long long)b * Hq + hq0 + (VALU ? 0 : min(n, ng - 1))) * DV + 4 * j + tg];
 
     float m = kEmptyMax, l = 0.f;     // reference (the same in the four row groups) and this row group's sum
     f32x4 acc[NV][E];                 // element (w, e)[i]: column d = w * 16E + (4tg + i) * E + e of query head n
@@ -316,18 +364,27 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
             vacc[w][e] = 0.f;
         }
 
-    const long long head_off = PAGED ? 0 : (p.seq_off ? p.seq_off[b] / 8 : (long long)b * p.sb) + (long long)h * p.sh;
-    const int *tbl = PAGED ? p.table + (long long)b * p.max_blocks : nullptr;
-    auto block_of = [&](int row) -> int { return p.bt_shift >= 0 ? (row >> p.bt_shift) : (row / p.bt); };
+    unsigned long long ss = 0;
+    long long head_off = 0;
+    const int *tbl = nullptr;
+    if constexpr (PAGED) {
+        tbl = addr_arg + (long long)b * addr2;
+    } else {
+        const Strides st = unpack_strides({addr_arg, addr2, addr3});
+        ss = st.ss;
+        head_off = (p.seq_off ? p.seq_off[b] / 8 : (long long)(b * st.sb)) + (long long)(h * st.sh);
+    }
+    const int bt = addr3, bt_shift = (bt & (bt - 1)) == 0 ? __builtin_ctz((unsigned)bt) : -1;   // paged
+    auto block_of = [&](int row) -> int { return bt_shift >= 0 ? (row >> bt_shift) : (row / bt); };
     // vector index of the first element of token row `row` (paged: in pool block blk; a block id outside the pool
     // reads block 0 and is masked)
     auto row_base = [&](int row, int blk) -> long long {
         if (PAGED) {
-            const int slot = row - block_of(row) * p.bt;
+            const int slot = row - block_of(row) * bt;
             if ((unsigned)blk >= (unsigned)p.n_pool) blk = 0;
-            return (((long long)blk * p.H + h) * p.bt + slot) * DV;
+            return (((long long)blk * H + h) * bt + slot) * DV;
         }
-        return head_off + (long long)row * p.ss;
+        return head_off + (long long)row * ss;
     };
     // Paged layout: the block ids of one step's rows are fetched ahead, so that the table lookup is off the load chain.
     // When the block size is a multiple of the tile a tile lies inside one block (kPagedTiles): one lookup per tile, the
@@ -368,28 +425,28 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
             if constexpr (LAYOUT != kPagedRows) {
                 // one base per tile, the same for the wavefront; the lane's part is a row number times the row length
                 const long long tb = row_base(R0, PAGED ? ids.k[ti] : 0);
-                const unsigned long long row_vecs = PAGED ? DV : p.ss;
+                const unsigned long long row_vecs = PAGED ? DV : ss;
                 const bool in_pool = !PAGED || (unsigned)ids.k[ti] < (unsigned)p.n_pool;
-                const u32x4 *kp = p.K + tb + (unsigned)(n < rem ? n : 0) * row_vecs;
+                const u32x4 *kp = K + tb + (unsigned)(n < rem ? n : 0) * row_vecs;
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) x.k[ti][j] = __builtin_nontemporal_load(kp + 4 * j + tg);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = 4 * tg + i;
                     x.ok[ti][i] = in_pool && r < rem;
-                    const vload_t *vp = (const vload_t *)(p.V + tb + (unsigned)(r < rem ? r : 0) * row_vecs) + n;
+                    const vload_t *vp = (const vload_t *)(V + tb + (unsigned)(r < rem ? r : 0) * row_vecs) + n;
 #pragma unroll
                     for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load(vp + w * 16);
                 }
             } else {
-                const u32x4 *kp = p.K + row_base(n < rem ? T0 + n : R0, ids.k[ti]);
+                const u32x4 *kp = K + row_base(n < rem ? T0 + n : R0, ids.k[ti]);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) x.k[ti][j] = __builtin_nontemporal_load(kp + 4 * j + tg);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = 4 * tg + i, blk = ids.t[ti][i];
                     x.ok[ti][i] = r < rem && (unsigned)blk < (unsigned)p.n_pool;
-                    const vload_t *vp = (const vload_t *)(p.V + row_base(r < rem ? T0 + r : R0, blk)) + n;
+                    const vload_t *vp = (const vload_t *)(V + row_base(r < rem ? T0 + r : R0, blk)) + n;
 #pragma unroll
                     for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load(vp + w * 16);
                 }
@@ -584,8 +641,8 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
         again = sh_bad != 0;
     }
 
-    auto head_out = [&](int g) { return ((long long)b * p.Hq + hq0 + g) * D; };
-    auto head_part = [&](int g) { return ((long long)b * p.Hq + hq0 + g) * p.n_splits + split; };
+    auto head_out = [&](int g) { return ((long long)b * Hq + hq0 + g) * D; };
+    auto head_part = [&](int g) { return ((long long)b * Hq + hq0 + g) * p.n_splits + split; };
     if (again) {
         // V (or K, or q) holds infinities or NaNs, or scores are beyond kFusedRef.  The terms of a probability meet an infinite
         // V one by one, and one that is zero or negative turns it into a NaN, so the split is done again with the
@@ -600,7 +657,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
             float qs[kHeads][C], a[kHeads][C], ms[kHeads], ls[kHeads];
 #pragma unroll
             for (int g = 0; g < kHeads; ++g) {
-                const elem_t *qp = (const elem_t *)(p.q + ((long long)b * p.Hq + hq0 + min(h0 + g, ng - 1)) * DV);
+                const elem_t *qp = (const elem_t *)(q + ((long long)b * Hq + hq0 + min(h0 + g, ng - 1)) * DV);
                 ms[g] = kEmptyMax;
                 ls[g] = 0.f;
 #pragma unroll
@@ -614,7 +671,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2) kv_attn_parti
                     const int t = min(t0 + i, t_end - 1), blk = PAGED ? tbl[block_of(t)] : 0;
                     ok[i] = t0 + i < t_end && (!PAGED || (unsigned)blk < (unsigned)p.n_pool);
                     const long long rb = row_base(t, blk);
-                    const elem_t *kp = (const elem_t *)(p.K + rb), *vp = (const elem_t *)(p.V + rb);
+                    const elem_t *kp = (const elem_t *)(K + rb), *vp = (const elem_t *)(V + rb);
 #pragma unroll
                     for (int c = 0; c < C; ++c) { kv[i][c] = kp[c * 64 + lane]; vv[i][c] = vp[c * 64 + lane]; }
                 }
@@ -723,8 +780,8 @@ constexpr int kCombineThreads = 256;
 template <int D, typename TAB>
 __global__ void __launch_bounds__(kCombineThreads)
 kv_attn_combine_kernel(const float *__restrict__ part_acc, const float *__restrict__ part_ml,
-                       void *__restrict__ out, int Hq, int n_splits_alloc, int out_mode,
-                       const int *__restrict__ seq_lens, int len_uniform, int max_len, int split_tokens, TAB tab)
+                       void *__restrict__ out, const int *__restrict__ seq_lens, int Hq, int n_splits_alloc, int out_mode,
+                       int len_uniform, int max_len, int split_tokens, TAB tab)
 {
     constexpr int CW = D / 64;                       // wavefronts that cover the columns once
     constexpr int NG = (kCombineThreads / 64) / CW;  // split groups (D = 256: 1, 128: 2, 64: 4)
@@ -804,45 +861,58 @@ AttnShape attn_shape(const kv_plan *p)
 }
 
 template <int D, int NH, bool BF16, typename TAB>
-void launch_partial(dim3 grid, hipStream_t st, const AttnParams &a, const TAB &t)
+void launch_partial(dim3 grid, hipStream_t st, const AttnHead &c, const AttnParams &a, const TAB &t)
 {
-    if (!a.table) hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kStrided, TAB>), grid, dim3(64 * waves(D)), 0, st, a, t);
-    else if (a.bt % kTile == 0) hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedTiles, TAB>), grid, dim3(64 * waves(D)), 0, st, a, t);
-    else hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedRows, TAB>), grid, dim3(64 * waves(D)), 0, st, a, t);
+    const unsigned heads = pack16(c.H, c.G), shares = pack16(c.gt, c.subs) | (std::is_same<TAB, ItemTable>::value ? (unsigned)c.heads_first << 7 | (unsigned)c.B << 8 : 0u);
+    typename std::conditional<std::is_same<TAB, ItemTable>::value, const int *, unsigned long long>::type lens;
+    if constexpr (std::is_same<TAB, ItemTable>::value) lens = a.seq_lens;
+    else lens = (unsigned)c.split_tokens | (unsigned long long)(unsigned)c.len_uniform << 32;
+    const dim3 block(64 * waves(D));
+    if (!c.table) {
+        const PackedStrides ps = pack_strides(c.strides);
+        hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kStrided, TAB>), grid, block, 0, st, c.K, c.V, c.q, lens, heads, shares,
+                           ps.ss_sh, ps.sb, ps.high, a, t);
+    } else if (c.bt % kTile == 0) {
+        hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedTiles, TAB>), grid, block, 0, st, c.K, c.V, c.q, lens, heads, shares,
+                           c.table, c.max_blocks, c.bt, a, t);
+    } else {
+        hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedRows, TAB>), grid, block, 0, st, c.K, c.V, c.q, lens, heads, shares,
+                           c.table, c.max_blocks, c.bt, a, t);
+    }
 }
 
 template <int D, int NH, typename TAB>
-void launch_partial_type(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const TAB &t)
+void launch_partial_type(bool bf16, dim3 grid, hipStream_t st, const AttnHead &c, const AttnParams &a, const TAB &t)
 {
-    if (bf16) launch_partial<D, NH, true>(grid, st, a, t);
-    else launch_partial<D, NH, false>(grid, st, a, t);
+    if (bf16) launch_partial<D, NH, true>(grid, st, c, a, t);
+    else launch_partial<D, NH, false>(grid, st, c, a, t);
 }
 
 template <int D, typename TAB>
-void launch_partial_nh(bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const TAB &t)
+void launch_partial_nh(bool bf16, dim3 grid, hipStream_t st, const AttnHead &c, const AttnParams &a, const TAB &t)
 {
     if constexpr (D >= 128) {
-        if (a.gt == 1) return launch_partial_type<D, 1>(bf16, grid, st, a, t);
+        if (c.gt == 1) return launch_partial_type<D, 1>(bf16, grid, st, c, a, t);
     }
-    if (a.gt <= 4) launch_partial_type<D, 4>(bf16, grid, st, a, t);   // from here on NH only sizes the merge's LDS
-    else if (a.gt <= 8) launch_partial_type<D, 8>(bf16, grid, st, a, t);
-    else launch_partial_type<D, kMaxHeads>(bf16, grid, st, a, t);
+    if (c.gt <= 4) launch_partial_type<D, 4>(bf16, grid, st, c, a, t);   // from here on NH only sizes the merge's LDS
+    else if (c.gt <= 8) launch_partial_type<D, 8>(bf16, grid, st, c, a, t);
+    else launch_partial_type<D, kMaxHeads>(bf16, grid, st, c, a, t);
 }
 
 template <typename TAB>
-void launch_partial_d(int D, bool bf16, dim3 grid, hipStream_t st, const AttnParams &a, const TAB &t)
+void launch_partial_d(int D, bool bf16, dim3 grid, hipStream_t st, const AttnHead &c, const AttnParams &a, const TAB &t)
 {
-    if (D == 64) launch_partial_nh<64>(bf16, grid, st, a, t);
-    else if (D == 128) launch_partial_nh<128>(bf16, grid, st, a, t);
-    else launch_partial_nh<256>(bf16, grid, st, a, t);
+    if (D == 64) launch_partial_nh<64>(bf16, grid, st, c, a, t);
+    else if (D == 128) launch_partial_nh<128>(bf16, grid, st, c, a, t);
+    else launch_partial_nh<256>(bf16, grid, st, c, a, t);
 }
 
 template <typename TAB>
-void launch_combine(int D, dim3 grid, hipStream_t st, const AttnParams &a, int out_mode, const TAB &t)
+void launch_combine(int D, dim3 grid, hipStream_t st, const AttnHead &c, const AttnParams &a, int out_mode, const TAB &t)
 {
 #define KV_COMBINE(DD)                                                                                                     \
     hipLaunchKernelGGL((kv_attn_combine_kernel<DD, TAB>), grid, dim3(kCombineThreads), 0, st, a.part_acc, a.part_ml, a.out, \
-                       a.Hq, a.n_splits, out_mode, a.seq_lens, a.len_uniform, a.max_len, a.split_tokens, t)
+                       a.seq_lens, c.Hq, a.n_splits, out_mode, c.len_uniform, a.max_len, c.split_tokens, t)
     if (D == 64) KV_COMBINE(64);
     else if (D == 128) KV_COMBINE(128);
     else KV_COMBINE(256);
@@ -881,6 +951,7 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
         if (len < 0) return KV_EINVAL;
         max_len = std::max(max_len, len);
     }
+    AttnHead c{};
     AttnParams a{};
     const bool paged = kv->layout == KV_LAYOUT_PAGED;
     if (kv->layout == KV_LAYOUT_BHSD) {
@@ -896,7 +967,7 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
             const uint64_t max_elem = base + (uint64_t)(p->H - 1) * kv->stride_h + (uint64_t)(len - 1) * kv->stride_s + p->D;
             if (max_elem * 2 > kv->layer_bytes) return KV_ERANGE;
         }
-        a.sb = kv->stride_b / 8; a.sh = kv->stride_h / 8; a.ss = kv->stride_s / 8;
+        c.strides = Strides{(unsigned long long)kv->stride_s / 8, (unsigned long long)kv->stride_h / 8, (unsigned long long)kv->stride_b / 8};
         a.seq_off = (const long long *)kv->seq_off_dev;
     } else if (paged) {
         if (!kv->block_table || kv->block_tokens < 1 || kv->n_pool_blocks < 0) return KV_EINVAL;
@@ -904,18 +975,17 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
         if (kvb::ceil_div((uint64_t)max_len, (uint64_t)kv->block_tokens) > (uint64_t)kv->max_blocks_per_seq)
             return KV_ERANGE;
         if (max_len > 0 && kv->n_pool_blocks < 1) return KV_ERANGE;
-        a.table = kv->block_table;
-        a.max_blocks = kv->max_blocks_per_seq;
-        a.bt = kv->block_tokens;
-        a.bt_shift = (a.bt & (a.bt - 1)) == 0 ? __builtin_ctz((unsigned)a.bt) : -1;
+        c.table = kv->block_table;
+        c.max_blocks = kv->max_blocks_per_seq;
+        c.bt = kv->block_tokens;
         a.n_pool = kv->n_pool_blocks;
     } else {
         return KV_EINVAL;
     }
 
-    a.len_uniform = max_len;
+    c.len_uniform = max_len;
     for (int b = 0; b < p->B; ++b)
-        if (kv->seq_lens_host[b] != max_len) a.len_uniform = -1;
+        if (kv->seq_lens_host[b] != max_len) c.len_uniform = -1;
 
     // Splits.  A uniform batch takes one split length for all sequences and the grid (split, query-head group, sequence).  A ragged batch of up
     // to kMaxTableSeqs sequences launches workgroups only for splits that hold tokens: its grid walks a table of per-sequence
@@ -925,14 +995,14 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     const SplitTable &tab = cut.tab;
     const bool use_table = cut.use_table;
     const int ns = cut.ns, G = p->Hq / p->H;
-    a.split_tokens = cut.split_tokens;
-    a.subs = cut.subs;
-    a.gt = (G + a.subs - 1) / a.subs;
-    a.K = (const u32x4 *)K; a.V = (const u32x4 *)V; a.q = (const u32x4 *)q;
+    c.split_tokens = cut.split_tokens;
+    c.subs = cut.subs;
+    c.gt = (G + c.subs - 1) / c.subs;
+    c.K = (const u32x4 *)K; c.V = (const u32x4 *)V; c.q = (const u32x4 *)q;
     a.seq_lens = kv->seq_lens_dev;
     a.part_acc = (float *)workspace;
     a.part_ml = a.part_acc + (size_t)p->B * p->Hq * ns * p->D;
-    a.H = p->H; a.Hq = p->Hq; a.G = G; a.B = p->B;
+    c.H = p->H; c.Hq = p->Hq; c.G = G; c.B = p->B;
     a.n_splits = ns;
     a.max_len = max_len;
     a.scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)p->D));
@@ -947,7 +1017,7 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     a.direct_mode = direct ? out_mode : -1;
     a.out = out;
     const long long n_items = use_table ? tab.first[p->B] : (max_len > 0 ? (long long)ns * p->B : 0);
-    const unsigned groups = (unsigned)(p->H * a.subs);
+    const unsigned groups = (unsigned)(p->H * c.subs);
     if (n_items > 0) {
         if (use_table) {
             ItemTable items;
@@ -958,11 +1028,11 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
                 items.seq[r] = (unsigned char)b;
                 first += tab.first[b + 1] - tab.first[b];
             }
-            items.heads_first = cut.longest_first;
+            c.heads_first = cut.longest_first;
             const dim3 grid = cut.longest_first ? dim3(groups, (unsigned)n_items, 1u) : dim3((unsigned)n_items, groups, 1u);
-            launch_partial_d(p->D, bf16, grid, st, a, items);
+            launch_partial_d(p->D, bf16, grid, st, c, a, items);
         } else {
-            launch_partial_d(p->D, bf16, dim3((unsigned)ns, groups, (unsigned)p->B), st, a, NoTable{});
+            launch_partial_d(p->D, bf16, dim3((unsigned)ns, groups, (unsigned)p->B), st, c, a, NoTable{});
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { kvb::set_hip_error((int)e); return KV_EHIP; }
@@ -973,9 +1043,9 @@ int decode_attn(const kv_plan_t *p, const kv_view_t *kv, int layer, const void *
     if (use_table) {
         CountTable counts{};
         for (int b = 0; b < p->B; ++b) counts.splits[b] = (unsigned short)(tab.first[b + 1] - tab.first[b]);
-        launch_combine(p->D, cgrid, st, a, out_mode, counts);
+        launch_combine(p->D, cgrid, st, c, a, out_mode, counts);
     } else {
-        launch_combine(p->D, cgrid, st, a, out_mode, NoTable{});
+        launch_combine(p->D, cgrid, st, c, a, out_mode, NoTable{});
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { kvb::set_hip_error((int)e); return KV_EHIP; }
