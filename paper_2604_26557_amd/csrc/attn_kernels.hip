@@ -180,6 +180,20 @@ __device__ __forceinline__ float wave_sum(float x)
     return (rdlane(x, 0) + rdlane(x, 16)) + (rdlane(x, 32) + rdlane(x, 48));
 }
 
+// The same over the lanes of each half row.
+__device__ __forceinline__ float half_row_max(float x)
+{
+    x = fmaxf(x, dpp_mov<0xB1>(x));
+    x = fmaxf(x, dpp_mov<0x4E>(x));
+    return fmaxf(x, dpp_mov<0x141>(x));
+}
+__device__ __forceinline__ float half_row_sum(float x)
+{
+    x += dpp_mov<0xB1>(x);
+    x += dpp_mov<0x4E>(x);
+    return x + dpp_mov<0x141>(x);
+}
+
 template <bool BF16>
 __device__ __forceinline__ f32x4 mfma_16x16x32(u32x4 a, u32x4 b, f32x4 c)
 {
@@ -203,19 +217,25 @@ __device__ __forceinline__ void store_out(void *out, long long i, int mode, floa
     else if (mode == 1) ((_Float16 *)out)[i] = (_Float16)r;
     else ((unsigned short *)out)[i] = f32_to_bf16_rne(r);
 }
-// Four in a row (i is a multiple of 4); the buffer itself need only be aligned to its elements.
-__device__ __forceinline__ void store_out4(void *out, long long i, int mode, f32x4 r)
+// C in a row (i is a multiple of C); the buffer itself need only be aligned to its elements.
+template <int C>
+__device__ __forceinline__ void store_outs(void *out, long long i, int mode, const float r[C])
 {
-    if (mode == 0 && !((uintptr_t)out & 15)) {
-        *(f32x4 *)((float *)out + i) = r;
-    } else if (mode != 0 && !((uintptr_t)out & 7)) {
-        unsigned short v[4];
+    typedef float fv __attribute__((ext_vector_type(C)));
+    typedef unsigned short hv __attribute__((ext_vector_type(C)));
+    if (mode == 0 && !((uintptr_t)out & (4 * C - 1))) {
+        fv v;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = mode == 1 ? __builtin_bit_cast(unsigned short, (_Float16)r[k]) : f32_to_bf16_rne(r[k]);
-        *(u32x2 *)((unsigned short *)out + i) = u32x2{(unsigned)v[0] | (unsigned)v[1] << 16, (unsigned)v[2] | (unsigned)v[3] << 16};
+        for (int k = 0; k < C; ++k) v[k] = r[k];
+        *(fv *)((float *)out + i) = v;
+    } else if (mode != 0 && !((uintptr_t)out & (2 * C - 1))) {
+        hv v;
+#pragma unroll
+        for (int k = 0; k < C; ++k) v[k] = mode == 1 ? __builtin_bit_cast(unsigned short, (_Float16)r[k]) : f32_to_bf16_rne(r[k]);
+        *(hv *)((unsigned short *)out + i) = v;
     } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) store_out(out, i + k, mode, r[k]);
+        for (int k = 0; k < C; ++k) store_out(out, i + k, mode, r[k]);
     }
 }
 
@@ -301,6 +321,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     constexpr int NT = kTerms<BF16>;
     constexpr bool VALU = NH == 1;
     constexpr int RG = VALU ? 4 : 1;         // states of a wavefront that meet in LDS: one per row group, or one
+    constexpr int kCopies = VALU ? 1 : 16 / NH;   // matrix columns that carry the same query head
     constexpr bool PAGED = LAYOUT != kStrided, TILE_ID = LAYOUT == kPagedTiles;
     typedef unsigned vload_t __attribute__((ext_vector_type(E / 2)));
 
@@ -342,7 +363,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     const int h = subs == 1 ? gy : gy / subs, g0 = (gy - h * subs) * gt;
     const int hq0 = h * G + g0;
     const int ng = min(gt, G - g0);   // query heads of this workgroup
-    int n = lane & 15;          // MFMA column (query head n; columns past the last head repeat it); also the K row this lane loads
+    int n = lane & 15;          // MFMA column (query head n / kCopies; columns past the last head repeat it); also the K row this lane loads
     int tg = lane >> 4;         // row group: owns tokens 4tg..4tg+3 of a tile; also the D sub-slice of the operands
 
     const int t_begin = min(len, split * split_tokens);
@@ -351,10 +372,10 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     // B operand: column n carries query head n; this lane holds elements 32j + 8tg .. +7 of it.
     u32x4 qv[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) qv[j] = q[((long long)b * Hq + hq0 + (VALU ? 0 : min(n, ng - 1))) * DV + 4 * j + tg];
+    for (int j = 0; j < NJ; ++j) qv[j] = q[((long long)b * Hq + hq0 + (VALU ? 0 : min(n / kCopies, ng - 1))) * DV + 4 * j + tg];
 
     float m = kEmptyMax, l = 0.f;     // reference (the same in the four row groups) and this row group's sum
-    f32x4 acc[NV][E];                 // element (w, e)[i]: column d = w * 16E + (4tg + i) * E + e of query head n
+    f32x4 acc[NV][E];                 // element (w, e)[i]: column d = w * 16E + (4tg + i) * E + e of this lane's query head
     float vacc[NV][E];                // VALU: column d = (w * 16 + n) * E + e, this row group's share
 #pragma unroll
     for (int w = 0; w < NV; ++w)
@@ -567,22 +588,26 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     // Steps are handed out in order, on demand.  A wavefront always knows its current and its next step; the
     // one after that is claimed (one LDS atomic by lane 0) right after the current step's loads are issued,
     // so neither the atomic nor, for the paged layout, the block-table lookup sits on the load chain.
-    __shared__ int sh_next, sh_bad;
+    __shared__ int sh_next;
     const int n_steps = (t_end - t_begin + kStepTok - 1) / kStepTok;
-    if (threadIdx.x == 0) {
-        sh_next = 2 * kWaves;   // steps 0 .. 2*kWaves-1 are preassigned: w and w + kWaves to wavefront w
-        sh_bad = 0;
+    // steps 0 .. 2*kWaves-1 are preassigned: w and w + kWaves to wavefront w; a split that has no more needs no counter and
+    // no barrier in front of its first loads
+    const bool claims = n_steps > 2 * kWaves;
+    if (claims) {
+        if (threadIdx.x == 0) sh_next = 2 * kWaves;
+        __syncthreads();
     }
-    __syncthreads();
     int s_cur = wave, s_nxt = wave + kWaves;
     Ids ids{};
     if (PAGED && s_cur < n_steps) fetch_ids(t_begin + s_cur * kStepTok, ids);
     while (s_cur < n_steps) {
         Step x;
         load_step(s_cur, ids, x);
-        int s_new = 0;
-        if (lane == 0) s_new = atomicAdd(&sh_next, 1);
-        s_new = __builtin_amdgcn_readfirstlane(s_new);
+        int s_new = n_steps;
+        if (claims) {
+            if (lane == 0) s_new = atomicAdd(&sh_next, 1);
+            s_new = __builtin_amdgcn_readfirstlane(s_new);
+        }
         if (PAGED && s_nxt < n_steps) fetch_ids(t_begin + s_nxt * kStepTok, ids);
         attend(x);
         s_cur = s_nxt;
@@ -596,7 +621,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     tg = lane >> 4;
 
     // ---- merge: a wavefront is one softmax state (m, l, acc[D]) per head; the states meet in LDS
-    constexpr int DP = D + 4;   // 4 floats of padding: the 16-byte stores of 8 neighbouring heads fall into different banks
+    constexpr int DP = D + 4 * kCopies;   // padding: the 16-byte stores of 8 neighbouring lanes fall into different banks
     __shared__ __attribute__((aligned(16))) float sh_acc[kWaves][RG][NH][DP];
     __shared__ f32x2 sh_ml[kWaves][RG * NH];
     auto far = [](float ref) { return fabsf(ref) > kFusedRef && ref != kEmptyMax; };
@@ -621,24 +646,36 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         if (lane < RG * kWaves) state = (&sh_ml[0][0])[lane];
         again = __any(far(state[0]));
     } else {
+        // A head's columns of the matrix hold the same sums: each of them writes its share.  (Written by one of four, with three of four
+        // lanes idle, the stores took four times as many LDS cycles, in front of the barrier.)
         l = rows_sum(l);
+        const int g = n / kCopies, copy = n % kCopies;
+        constexpr int kParts = NV * E / kCopies;   // 16-byte stores of a lane
         float nf = far(m) ? 1.f : 0.f;   // not 0 (or NaN): again
-        if (n < ng) {
 #pragma unroll
-            for (int w = 0; w < NV; ++w)
+        for (int s = 0; s < kParts; ++s) {
+            f32x4 v;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int e4 = 0; e4 < E; e4 += 4) {
-                        const f32x4 v{acc[w][e4][i], acc[w][e4 + 1][i], acc[w][e4 + 2][i], acc[w][e4 + 3][i]};
-                        nf += ((v[0] + v[1]) + (v[2] + v[3])) * 0.f;
-                        *(f32x4 *)&sh_acc[wave][0][n][w * 16 * E + (4 * tg + i) * E + e4] = v;
-                    }
-            if (tg == 0) sh_ml[wave][n] = f32x2{m, l};
-            if (nf != 0.f) sh_bad = 1;
+            for (int c = 0; c < kCopies; ++c) {
+                const int j = s * kCopies + c, w = j / E, i = j % E / (E / 4), e4 = j % (E / 4) * 4;
+                const f32x4 u{acc[w][e4][i], acc[w][e4 + 1][i], acc[w][e4 + 2][i], acc[w][e4 + 3][i]};
+                if (c == 0) v = u;
+                else v = copy == c ? u : v;
+            }
+            const int j = s * kCopies + copy;
+            nf += ((v[0] + v[1]) + (v[2] + v[3])) * 0.f;
+            if (g < ng) *(f32x4 *)&sh_acc[wave][0][g][(j / E) * 16 * E + tg * 4 * E + (j % E) * 4] = v;
         }
+        const bool bad = __any(!(nf == 0.f));
+        if (tg == 0 && copy == 0 && g < ng) sh_ml[wave][g] = f32x2{bad ? INFINITY : m, l};
         __syncthreads();
-        again = sh_bad != 0;
+        bool some = false;
+#pragma unroll
+        for (int j0 = 0; j0 < kWaves * NH; j0 += 64) {
+            const int j = j0 + lane;
+            if (j < kWaves * NH && j % NH < ng) some = some || far((&sh_ml[0][0])[j][0]);
+        }
+        again = __any(some);
     }
 
     auto head_out = [&](int g) { return ((long long)b * Hq + hq0 + g) * D; };
@@ -653,7 +690,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         constexpr int C = D / 64, kRun = 8, kHeads = NH < 4 ? NH : 4;
         typedef typename std::conditional<BF16, __bf16, _Float16>::type elem_t;
         for (int h0 = 0; h0 < ng; h0 += kHeads) {
-            if (VALU) __syncthreads();   // the states' references have been read
+            if (h0 == 0) __syncthreads();   // the states' references have been read
             float qs[kHeads][C], a[kHeads][C], ms[kHeads], ls[kHeads];
 #pragma unroll
             for (int g = 0; g < kHeads; ++g) {
@@ -747,23 +784,38 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         }
         return;
     }
-    for (int idx = threadIdx.x; idx < ng * (D / 4); idx += kThreads) {   // four consecutive columns of one head
-        const int g = idx / (D / 4), d = (idx - g * (D / 4)) * 4;
-        f32x2 ml[kWaves];
-        float M = kEmptyMax, L = 0.f;
+    // A wavefront forms 64 * C columns of one head at a time: lane = state for the weights, which it then takes from the lanes
+    // by readlane, one weight's exponential per lane in place of every state's in every lane.  us per layer from a graph, together with the stores above:
+    // 8 KV heads x 4 x 128, 1K tokens 7.1 / 6.7, 4K 8.75 / 8.3; 2 x 2 x 64, 256 tokens 4.4 / 3.95; 4 x 2 x 256, 2 sequences of 3000
+    // 11.3 / 10.7; paged, 2 x 7, 4K 8.0 / 7.7; 32K and larger batches within 1 %.
+    constexpr int C = D == 64 ? 1 : D == 256 ? 4 : (NH <= 4 ? 1 : 2), kUnits = D / (64 * C);
+    typedef float cols_t __attribute__((ext_vector_type(C)));
+    static_assert(kWaves <= 8, "half a row of lanes");
+    for (int u = wave; u < ng * kUnits; u += kWaves) {
+        const int g = u / kUnits, d = (u % kUnits) * 64 * C + lane * C;
+        const f32x2 ml = lane < kWaves ? sh_ml[lane][g] : f32x2{kEmptyMax, 0.f};
+        cols_t part[kWaves];
 #pragma unroll
-        for (int k = 0; k < kWaves; ++k) { ml[k] = sh_ml[k][g]; M = fmaxf(M, ml[k][0]); }
-        f32x4 A = {0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < kWaves; ++k) part[k] = *(const cols_t *)&sh_acc[k][0][g][d];
+        const float Ml = half_row_max(ml[0]);
+        const float wgt = exp2f(ml[0] - Ml);
+        const float M = rdlane(Ml, 0), L = rdlane(half_row_sum(ml[1] * wgt), 0);
+        float A[C] = {};
 #pragma unroll
         for (int k = 0; k < kWaves; ++k) {
-            const float wgt = exp2f(ml[k][0] - M);
-            L = fmaf(ml[k][1], wgt, L);
-            A += *(const f32x4 *)&sh_acc[k][0][g][d] * (wgt * (1.f / kLift<BF16>));
+            const float f = rdlane(wgt, k) * (1.f / kLift<BF16>);
+#pragma unroll
+            for (int c = 0; c < C; ++c) A[c] = fmaf(part[k][c], f, A[c]);
         }
         if (p.direct_mode >= 0) {   // the only split of its sequence: the result itself
-            store_out4(p.out, head_out(g) + d, p.direct_mode, L == 0.f ? f32x4{0.f, 0.f, 0.f, 0.f} : A / L);
+#pragma unroll
+            for (int c = 0; c < C; ++c) A[c] = L == 0.f ? 0.f : A[c] / L;
+            store_outs<C>(p.out, head_out(g) + d, p.direct_mode, A);
         } else {
-            *(f32x4 *)&p.part_acc[head_part(g) * D + d] = A;
+            cols_t v;
+#pragma unroll
+            for (int c = 0; c < C; ++c) v[c] = A[c];
+            *(cols_t *)&p.part_acc[head_part(g) * D + d] = v;
             if (d == 0) *(f32x2 *)&p.part_ml[head_part(g) * 2] = f32x2{M, L};
         }
     }

@@ -378,6 +378,31 @@ def test_decode_attention_more_workgroups_than_compute_units(H, G, D, B, lo, hi,
     _attn_check(out, _reference_attention(case, case.k[0], case.v[0], q).float().numpy())
 
 
+# tokens: as many as one workgroup's wavefronts have preassigned (two steps each; above that they claim steps from a counter), and one more
+@pytest.mark.parametrize("D,tokens", [(64, 512), (128, 256), (256, 192)])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("odd", [0, 1])
+def test_decode_attention_merge(D, tokens, G, odd):
+    """The merge of a workgroup's states for every number of copies a query head has among the matrix columns (16, 4, 2, 1), to an aligned
+    output and to one that is aligned to its elements only.  Bars: the file's; 16-bit results are the 32-bit ones rounded, up to the
+    last place where a repetition of the same sums (in another order) falls to the other side of a rounding boundary."""
+    cfg = W.KVConfig("merge", 2300 + D + G, 1, 2, 2 * G, D, 1, W.BF16 if odd else W.F16, 512, 8, 2, W.PER_SEQ, W.BHSD, 0)
+    case = Case(cfg, "cuda", gen_device="cpu", lens=[tokens + odd])
+    q = W.query(cfg, 0, "cpu")
+    n = 2 * G * D
+    ws = torch.empty(kv.kv_decode_attn_workspace(case.plan, 1, tokens + odd), dtype=torch.uint8, device="cuda")
+    buf = torch.full((n + 1,), float("nan"), dtype=torch.float32, device="cuda")
+    half = torch.full((n + 1,), float("nan"), dtype=cfg.torch_dtype, device="cuda")
+    out, out16 = buf[odd:n + odd].view(1, 2 * G, D), half[odd:n + odd].view(1, 2 * G, D)
+    kv.kv_decode_attn(case.plan, case.view, 0, q.cuda(), out, kv.KV_OUT_F32, 1, ws)
+    kv.kv_decode_attn(case.plan, case.view, 0, q.cuda(), out16, kv.KV_OUT_SAME, 1, ws)
+    torch.cuda.synchronize()
+    _attn_check(out, _reference_attention(case, case.k[0], case.v[0], q).float().numpy())
+    eps = 2.0 ** -7 if odd else 2.0 ** -10   # one unit in the last place is at most this much of the value
+    assert ((out16.float() - out).abs() <= eps * out.abs() + 1e-6).all()
+    assert torch.isnan(buf[-1 if not odd else 0]) and torch.isnan(half[-1 if not odd else 0])   # nothing past the output
+
+
 # ------------------------------------------------------------------------------------------ pipeline
 # (span_chunks, depth, copy_streams, d2h_mode, h2d_mode)
 @pytest.mark.parametrize("D,G", [(64, 1), (64, 4), (128, 2), (128, 8), (256, 1), (256, 4)])
