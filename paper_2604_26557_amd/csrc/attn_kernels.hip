@@ -264,6 +264,13 @@ __device__ __forceinline__ float rows_sum(float x)
     return __uint_as_float(t[0]) + __uint_as_float(t[1]);
 }
 
+// Sum over the two halves of the wavefront, in both of them.
+__device__ __forceinline__ float halves_sum(float x)
+{
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+}
+
 // A probability in fp32 is the exact sum of three bf16 numbers (the upper half of its bits, twice of what is left), or
 // of two fp16 numbers up to 2^-24 of itself; P V is one product per term.
 template <bool BF16> constexpr int kTerms = BF16 ? 3 : 2;
@@ -821,81 +828,108 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     }
 }
 
-// out_mode: 0 fp32, 1 fp16, 2 bf16.  One workgroup of 256 threads per (hq, b): threads are (column, split group);
-// a wavefront covers 64 columns of one split group, so the split index is uniform over the wavefront.  Every
+// out_mode: 0 fp32, 1 fp16, 2 bf16.  One workgroup of W wavefronts per (hq, b).  A lane loads 16 bytes of a partial row, so a load of a
+// wavefront is one, two or four rows (head_dim 256, 128, 64), and a round of a wavefront 8, 8 or 16 rows.  Every
 // wavefront forms the split weights exp2(m_s - M) itself (lane = split, 64 at a time, the maximum carried along)
-// and takes them from the lanes by readlane.  The loads of the (m, l) pairs and of a thread's first 16 partial rows do
-// not depend on each other and are issued together, and every further 16 rows while the ones before are added: up to
-// 64 / 32 / 16 splits (head_dim 64 / 128 / 256) the kernel is one memory latency long.  The split groups are added through LDS.
-constexpr int kCombineThreads = 256;
+// and takes them from the lanes by readlane.  The loads of the (m, l) pairs and of the first round do not depend on each other
+// and are issued together, and every further round while the one before is added: up to a round of splits the kernel is one memory latency
+// long.  The wavefronts' sums are added through LDS; up to 8 (16) splits are one wavefront's work, without LDS or barrier, and up to
+// twice as many two wavefronts'.  us per layer from a graph, four wavefronts that load 4 bytes per lane / this: 8 KV heads x 4 x 128, 4K tokens (32 splits)
+// 8.3 / 8.1; 1 x 8 x 128, 16K (64) 10.35 / 10.0; 4 x 2 x 256, 2 of 3000 (32) 10.7 / 10.3; paged, 48 sequences, 4 x 7 x 128 (up to 7) 43.7 / 42.9,
+// 24 sequences, 8 x 8 x 64 24.8 / 24.0.  With four wavefronts for few splits as well, the last two are 44.5 and 25.7.
+constexpr int combine_loads(int D) { return D == 256 ? 8 : 4; }                      // loads of a wavefront per round
+constexpr int combine_rows(int D) { return combine_loads(D) * (D >= 256 ? 1 : 256 / D); }   // partial rows of a wavefront per round
 
-template <int D, typename TAB>
-__global__ void __launch_bounds__(kCombineThreads)
+template <int D, int W, typename TAB>
+__global__ void __launch_bounds__(64 * W)
 kv_attn_combine_kernel(const float *__restrict__ part_acc, const float *__restrict__ part_ml,
                        void *__restrict__ out, const int *__restrict__ seq_lens, int Hq, int n_splits_alloc, int out_mode,
-                       int len_uniform, int max_len, int split_tokens, TAB tab)
+                       int n_uniform, int max_len, int split_tokens, TAB tab)
 {
-    constexpr int CW = D / 64;                       // wavefronts that cover the columns once
-    constexpr int NG = (kCombineThreads / 64) / CW;  // split groups (D = 256: 1, 128: 2, 64: 4)
-    constexpr int kRows = 16;                        // partial rows a thread loads per round
+    constexpr int kRowLanes = D / 4, RPL = 64 / kRowLanes;    // lanes of a row, rows of a load
+    constexpr int kLoads = combine_loads(D), kRound = W * kLoads * RPL;
+    static_assert(kLoads * RPL == combine_rows(D), "rows of a round");
+    constexpr bool kSkips = W == 1 || std::is_same<TAB, CountTable>::value;   // a round is often not full: loads past its last row are left out
     const int hq = blockIdx.x, b = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int grp = __builtin_amdgcn_readfirstlane(wave / CW), d = (wave % CW) * 64 + lane;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int sub = lane / kRowLanes, d = (lane % kRowLanes) * 4;
     const long long o = ((long long)b * Hq + hq) * n_splits_alloc;
     // only the splits that hold tokens of this sequence were written (and matter)
     int n_splits;
     if constexpr (std::is_same<TAB, CountTable>::value) {
         n_splits = tab.splits[b];
     } else {
-        const int len = len_uniform >= 0 ? len_uniform : min(seq_lens[b], max_len);
-        n_splits = min(n_splits_alloc, (len + split_tokens - 1) / split_tokens);
+        n_splits = n_uniform;   // every sequence has as many; a division here would be on the way to the first load
+        if (n_splits < 0) n_splits = min(n_splits_alloc, (min(seq_lens[b], max_len) + split_tokens - 1) / split_tokens);
     }
 
-    auto load_ml = [&](int s0) { return s0 + lane < n_splits ? *(const f32x2 *)&part_ml[(o + s0 + lane) * 2] : f32x2{kEmptyMax, 0.f}; };
-    auto load_rows = [&](int s0, float rows[kRows]) {
+    const float *const pa = part_acc + o * D;
+    const f32x2 *const pm = (const f32x2 *)part_ml + o;
+    // Loads are not masked (each would be a branch): what lies past the last split re-reads the first one and is dropped when it is used.
+    auto load_ml = [&](int s0) { return pm[(unsigned)(s0 + lane < n_splits ? s0 + lane : 0)]; };
+    auto load_rows = [&](int s0, f32x4 rows[kLoads]) {
 #pragma unroll
-        for (int i = 0; i < kRows; ++i) {
-            const int s = s0 + grp + i * NG;             // uniform over the wavefront
-            rows[i] = s < n_splits ? part_acc[(o + s) * D + d] : 0.f;
+        for (int i = 0; i < kLoads; ++i) {
+            const int s_first = s0 + (i * W + wave) * RPL, s = s_first + sub;
+            if (kSkips && s_first >= n_splits) break;
+            rows[i] = *(const f32x4 *)&pa[(unsigned)((s < n_splits ? s : 0) * D + d)];
         }
     };
     f32x2 ml = load_ml(0);
-    float rows[kRows];
+    f32x4 rows[kLoads];
     load_rows(0, rows);                                  // independent of the weights
-    float M = kEmptyMax, A = 0.f, L = 0.f;
+    f32x4 A = {0.f, 0.f, 0.f, 0.f};
+    float M = kEmptyMax, L = 0.f;
     for (int s0 = 0; s0 < n_splits; s0 += 64) {          // 64 splits at a time: lane = split
-        const f32x2 ml_next = load_ml(s0 + 64);
+        f32x2 ml_next;
+        if (s0 + 64 < n_splits) ml_next = load_ml(s0 + 64);
+        if (s0 + lane >= n_splits) ml = f32x2{kEmptyMax, 0.f};
         const float Mn = fmaxf(M, wave_max(ml[0])), rescale = exp2f(M - Mn), wgt = exp2f(ml[0] - Mn);
         M = Mn;
         A *= rescale;
         L = fmaf(ml[1], wgt, L * rescale);
 #pragma unroll
-        for (int r0 = 0; r0 < 64; r0 += kRows * NG) {    // the next rows are on their way while these are added
+        for (int r0 = 0; r0 < 64; r0 += kRound) {        // the next rows are on their way while these are added
             if (s0 + r0 >= n_splits) break;
-            float next[kRows];
-            load_rows(s0 + r0 + kRows * NG, next);
+            f32x4 next[kLoads];
+            if (s0 + r0 + kRound < n_splits) load_rows(s0 + r0 + kRound, next);
 #pragma unroll
-            for (int i = 0; i < kRows; ++i) A = fmaf(rows[i], rdlane(wgt, r0 + grp + i * NG), A);
+            for (int i = 0; i < kLoads; ++i) {
+                const int j = r0 + (i * W + wave) * RPL;
+                if (kSkips && s0 + j >= n_splits) break;
+                float w = rdlane(wgt, j);
 #pragma unroll
-            for (int i = 0; i < kRows; ++i) rows[i] = next[i];
+                for (int k = 1; k < RPL; ++k) {
+                    const float wk = rdlane(wgt, j + k);
+                    w = sub == k ? wk : w;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) A[k] = fmaf(s0 + j + sub < n_splits ? rows[i][k] : 0.f, w, A[k]);
+            }
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) rows[i] = next[i];
         }
         ml = ml_next;
     }
-    L = wave_sum(L);
-
-    __shared__ float colsum[NG][D];
-    if (NG > 1) {
-        colsum[grp][d] = A;
-        __syncthreads();
-        if (grp == 0) {
 #pragma unroll
-            for (int k = 1; k < NG; ++k) A += colsum[k][d];
-        }
+    for (int k = 0; k < 4; ++k) {
+        if (RPL == 4) A[k] = rows_sum(A[k]);
+        if (RPL == 2) A[k] = halves_sum(A[k]);
     }
-    if (grp == 0) {
-        const float r = L == 0.f ? 0.f : A / L;   // nothing attended: zeros; a NaN score: NaN
-        const long long oi = ((long long)b * Hq + hq) * D + d;
-        store_out(out, oi, out_mode, r);
+    L = wave_sum(L);
+    if constexpr (W > 1) {
+        __shared__ __attribute__((aligned(16))) float sums[W][D];
+        if (sub == 0) *(f32x4 *)&sums[wave][d] = A;
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int k = 1; k < W; ++k) A += *(const f32x4 *)&sums[k][d];
+    }
+    if (sub == 0) {
+        float r[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] = L == 0.f ? 0.f : A[k] / L;   // nothing attended: zeros; a NaN score: NaN
+        store_outs<4>(out, ((long long)b * Hq + hq) * D + d, out_mode, r);
     }
 }
 
@@ -962,13 +996,16 @@ void launch_partial_d(int D, bool bf16, dim3 grid, hipStream_t st, const AttnHea
 template <typename TAB>
 void launch_combine(int D, dim3 grid, hipStream_t st, const AttnHead &c, const AttnParams &a, int out_mode, const TAB &t)
 {
-#define KV_COMBINE(DD)                                                                                                     \
-    hipLaunchKernelGGL((kv_attn_combine_kernel<DD, TAB>), grid, dim3(kCombineThreads), 0, st, a.part_acc, a.part_ml, a.out, \
-                       a.seq_lens, c.Hq, a.n_splits, out_mode, c.len_uniform, a.max_len, c.split_tokens, t)
-    if (D == 64) KV_COMBINE(64);
-    else if (D == 128) KV_COMBINE(128);
-    else KV_COMBINE(256);
+    const int n_uniform = c.len_uniform < 0 ? -1 : std::min(a.n_splits, (c.len_uniform + c.split_tokens - 1) / c.split_tokens);
+#define KV_COMBINE_W(DD, W)                                                                                      \
+    hipLaunchKernelGGL((kv_attn_combine_kernel<DD, W, TAB>), grid, dim3(64 * W), 0, st, a.part_acc, a.part_ml, a.out, \
+                       a.seq_lens, c.Hq, a.n_splits, out_mode, n_uniform, a.max_len, c.split_tokens, t)
+#define KV_COMBINE(DD) { if (a.n_splits <= combine_rows(DD)) KV_COMBINE_W(DD, 1); else if (a.n_splits <= 2 * combine_rows(DD)) KV_COMBINE_W(DD, 2); else KV_COMBINE_W(DD, 4); }
+    if (D == 64) KV_COMBINE(64)
+    else if (D == 128) KV_COMBINE(128)
+    else KV_COMBINE(256)
 #undef KV_COMBINE
+#undef KV_COMBINE_W
 }
 
 }  // namespace

@@ -403,6 +403,25 @@ def test_decode_attention_merge(D, tokens, G, odd):
     assert torch.isnan(buf[-1 if not odd else 0]) and torch.isnan(half[-1 if not odd else 0])   # nothing past the output
 
 
+# a round of one wavefront, of two and of four, one split more than each, the weights' window of 64 and what needs several
+@pytest.mark.parametrize("n_splits", [2, 8, 9, 16, 17, 32, 33, 64, 65, 130])
+@pytest.mark.parametrize("D,G", [(64, 2), (128, 1), (256, 2)])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_decode_attention_combine_rounds(D, G, n_splits, ragged):
+    """Every number of wavefronts and rounds of the combine kernel, with NaNs in the part of the workspace that no split writes (the second
+    sequence of the ragged batch has a third of the splits).  Bar: the file's."""
+    q_tok = 64 if D >= 128 else 128   # the shortest split
+    lens = [n_splits * q_tok - 5, n_splits * q_tok // 3 + 1] if ragged else [n_splits * q_tok - 5]
+    cfg = W.KVConfig("combine", 2700 + D + n_splits, 1, 1, G, D, len(lens), W.F16, 512, 8, 2, W.PER_SEQ, W.BHSD, 0)
+    case = Case(cfg, "cuda", gen_device="cpu", lens=lens)
+    q = W.query(cfg, 0, "cpu")
+    out = torch.full((len(lens), G, D), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.full((kv.kv_decode_attn_workspace(case.plan, n_splits, max(lens)),), 0xff, dtype=torch.uint8, device="cuda")
+    kv.kv_decode_attn(case.plan, case.view, 0, q.cuda(), out, kv.KV_OUT_F32, n_splits, ws)
+    torch.cuda.synchronize()
+    _attn_check(out, _reference_attention(case, case.k[0], case.v[0], q).float().numpy())
+
+
 # ------------------------------------------------------------------------------------------ pipeline
 # (span_chunks, depth, copy_streams, d2h_mode, h2d_mode)
 @pytest.mark.parametrize("D,G", [(64, 1), (64, 4), (128, 2), (128, 8), (256, 1), (256, 4)])
