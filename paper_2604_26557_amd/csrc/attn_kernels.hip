@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "attn_splits.hpp"
+#include "launch.hpp"
 #include "plan.hpp"
 
 namespace {
@@ -956,13 +957,13 @@ void launch_partial(dim3 grid, hipStream_t st, const AttnHead &c, const AttnPara
     const dim3 block(64 * waves(D));
     if (!c.table) {
         const PackedStrides ps = pack_strides(c.strides);
-        hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kStrided, TAB>), grid, block, 0, st, c.K, c.V, c.q, lens, heads, shares,
+        (void)kvb::launch_kernel(kv_attn_partial_kernel<D, NH, BF16, kStrided, TAB>, grid, block, st, c.K, c.V, c.q, lens, heads, shares,
                            ps.ss_sh, ps.sb, ps.high, a, t);
     } else if (c.bt % kTile == 0) {
-        hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedTiles, TAB>), grid, block, 0, st, c.K, c.V, c.q, lens, heads, shares,
+        (void)kvb::launch_kernel(kv_attn_partial_kernel<D, NH, BF16, kPagedTiles, TAB>, grid, block, st, c.K, c.V, c.q, lens, heads, shares,
                            c.table, c.max_blocks, c.bt, a, t);
     } else {
-        hipLaunchKernelGGL((kv_attn_partial_kernel<D, NH, BF16, kPagedRows, TAB>), grid, block, 0, st, c.K, c.V, c.q, lens, heads, shares,
+        (void)kvb::launch_kernel(kv_attn_partial_kernel<D, NH, BF16, kPagedRows, TAB>, grid, block, st, c.K, c.V, c.q, lens, heads, shares,
                            c.table, c.max_blocks, c.bt, a, t);
     }
 }
@@ -998,7 +999,7 @@ void launch_combine(int D, dim3 grid, hipStream_t st, const AttnHead &c, const A
 {
     const int n_uniform = c.len_uniform < 0 ? -1 : std::min(a.n_splits, (c.len_uniform + c.split_tokens - 1) / c.split_tokens);
 #define KV_COMBINE_W(DD, W)                                                                                      \
-    hipLaunchKernelGGL((kv_attn_combine_kernel<DD, W, TAB>), grid, dim3(64 * W), 0, st, a.part_acc, a.part_ml, a.out, \
+    (void)kvb::launch_kernel(kv_attn_combine_kernel<DD, W, TAB>, grid, dim3(64 * W), st, a.part_acc, a.part_ml, a.out, \
                        a.seq_lens, c.Hq, a.n_splits, out_mode, n_uniform, a.max_len, c.split_tokens, t)
 #define KV_COMBINE(DD) { if (a.n_splits <= combine_rows(DD)) KV_COMBINE_W(DD, 1); else if (a.n_splits <= 2 * combine_rows(DD)) KV_COMBINE_W(DD, 2); else KV_COMBINE_W(DD, 4); }
     if (D == 64) KV_COMBINE(64)

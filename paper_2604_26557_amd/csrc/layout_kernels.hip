@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <climits>
 
+#include "launch.hpp"
 #include "plan.hpp"
 
 namespace {
@@ -313,8 +314,8 @@ template <bool PACK, bool PAGED, typename TAB>
 void launch_u(int U, dim3 grid, hipStream_t stream, const SrcDesc &s, void *img, const TAB &tab, int rowv, int rx_log2,
               int tpb, int rchunk)
 {
-    if (U == 1) hipLaunchKernelGGL((kv_layout_kernel<PACK, PAGED, 1, TAB>), grid, dim3(kThreads), 0, stream, s, (u32x4 *)img, tab, rowv, rx_log2, tpb, rchunk);
-    else hipLaunchKernelGGL((kv_layout_kernel<PACK, PAGED, 2, TAB>), grid, dim3(kThreads), 0, stream, s, (u32x4 *)img, tab, rowv, rx_log2, tpb, rchunk);
+    if (U == 1) (void)kvb::launch_kernel(kv_layout_kernel<PACK, PAGED, 1, TAB>, grid, dim3(kThreads), stream, s, (u32x4 *)img, tab, rowv, rx_log2, tpb, rchunk);
+    else (void)kvb::launch_kernel(kv_layout_kernel<PACK, PAGED, 2, TAB>, grid, dim3(kThreads), stream, s, (u32x4 *)img, tab, rowv, rx_log2, tpb, rchunk);
 }
 
 template <bool PACK>
@@ -540,9 +541,9 @@ int pack_last_rows(const kv_plan *p, const kv_view_t *v, int layer_begin, int la
             const dim3 grid((unsigned)nb, (unsigned)(2 * nl), gz);
             const int b_first = p->mode == KV_TOKEN_MAJOR ? -1 : b0;
             if (v->layout == KV_LAYOUT_PAGED)
-                hipLaunchKernelGGL((kv_rows_kernel<true>), grid, dim3(threads), 0, stream, s, out, t, rowv, nseq, b_first);
+                (void)kvb::launch_kernel(kv_rows_kernel<true>, grid, dim3(threads), stream, s, out, t, rowv, nseq, b_first);
             else
-                hipLaunchKernelGGL((kv_rows_kernel<false>), grid, dim3(threads), 0, stream, s, out, t, rowv, nseq, b_first);
+                (void)kvb::launch_kernel(kv_rows_kernel<false>, grid, dim3(threads), stream, s, out, t, rowv, nseq, b_first);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) { kvb::set_hip_error((int)e); return KV_EHIP; }
         }
