@@ -98,11 +98,13 @@ kv_layout_kernel(SrcDesc s, u32x4 *__restrict__ img, TAB segs, int rowv, int rx_
     const int hd = s.H * s.dvec;
 
     // Paged source, one sequence per segment: the few block-table entries this tile touches are staged in
-    // LDS once, so the per-token lookup is not a second dependent trip to memory.
+    // LDS once, so the per-token lookup is not a second dependent trip to memory.  Where a thread has one token the lookup is one trip
+    // anyway, and staging only adds the way through LDS and a barrier to the short life of a workgroup (16 heads x 256, batch 4: 361 / 357 us for
+    // 6 layers staged, 303 / 314 not; pack / unpack).
     __shared__ int sh_tbl[kTblStage];
     int j_first = 0;
     bool tbl_in_lds = false;
-    if (PAGED && sg.b >= 0) {
+    if (PAGED && sg.b >= 0 && tpb > TY) {
         j_first = (sg.tok0 + t_begin) / s.bt;
         const int nj = (sg.tok0 + t_end - 1) / s.bt - j_first + 1;
         if (nj <= kTblStage) {  // uniform over the workgroup
@@ -289,13 +291,16 @@ struct Shape {
 //  * paged, rows of up to 4 KiB: whole rows, since a pool block holds all heads of its tokens.  Ragged batch of 8 438 / 480 -> 413 / 449;
 //    8 heads x 256, batch 6 404 / 515 -> 376 / 391; one sequence of 8000 243 / 250 -> 219 / 226; 5 heads, where the lanes do not divide the
 //    row, 38.6 / 41.4 -> 36.4 / 38.2 per layer.
-//  * paged, wider rows (several sequences, whose blocks have nothing to do with each other): two head rows by one block's
-//    tokens (8 KiB).  Batch 32 of 600 tokens 439 / 461 -> 250 / 256; 64-wide heads, batch 16 of 500 1046 / 1344 -> 153 / 155.  256-wide heads
-//    take 4 KiB of one token's row instead: per layer 16 heads, batch 2 34.7 / 35.6 (by four tokens 37.4 / 37.5; two head rows by
-//    a block's tokens 40.9 / 40.3).
+//  * paged, wider rows: 4 KiB of one token's row, or 8 KiB where 4 do not divide the row (the last workgroup of a row would have little
+//    to do: 9 heads x 256, batch 4, unpack 218 against 200). Such a workgroup needs one block id and does not stage the table (see the
+//    kernel); with that, tiles of two head rows by one block's tokens (8 KiB), which 64- and 128-wide heads had, are no longer better.
+//    us for 6 layers, as it was -> now, pack / unpack: 32 heads x 128, batch 4 of 1K-3K 293 / 274 -> 243 / 247, 20 heads, batch 3 149 / 151 ->
+//    144 / 142; 16 heads x 256, batch 4 of 2K-3K 361 / 358 -> 305 / 317, 9 heads 272 / 265 -> 204 / 200; 64 heads x 64 (2 layers) 98 / 92 ->
+//    82 / 83.  Rows of up to 4 KiB gain nothing from 4 KiB tiles: 8 heads x 128, ragged batch of 8 (8 layers) 407 / 451, with them 418 / 443; 5 heads
+//    121 / 123, with them 138 / 137.
 Shape pick_shape(bool paged, int rowv, int dvec)
 {
-    if (paged && rowv > 256) return dvec >= 32 ? Shape{8, 1, 4 * 1024, 0} : Shape{5, 2, 8 * 1024, 4 * 1024};
+    if (paged && rowv > 256) return Shape{8, 1, rowv % 256 == 0 ? 4 * 1024 : 8 * 1024, 0};
     if (paged) return Shape{8, 2, 8 * 1024, 4 * 1024};
     if (rowv > 256) return Shape{8, 1, 4 * 1024, dvec == 16 ? 0 : 1024};
     int lanes = 4;   // one head row, at least 16 lanes

@@ -1022,6 +1022,14 @@ def test_pack_unpack_at_the_edges_of_tiles(D, H, B, layout, mode):
     _check_restored(case, k_new, v_new, range(2))
 
 
+# rows of one, two and three 4 KiB pieces, and rows that end inside their second or fourth
+@pytest.mark.parametrize("D,H,B", [(128, 16, 3), (128, 32, 3), (64, 96, 2), (256, 24, 1), (64, 33, 4), (256, 25, 2), (128, 47, 1)])
+@pytest.mark.parametrize("mode", [W.TOKEN_MAJOR, W.PER_SEQ])
+def test_pack_unpack_of_wide_paged_rows(D, H, B, mode):
+    """Byte for byte, like the test above: one token's row in pieces, a block id per piece, and whole rows where the pieces do not divide them."""
+    test_pack_unpack_at_the_edges_of_tiles(D, H, B, W.PAGED, mode)
+
+
 @pytest.mark.parametrize("D,H", [(64, 1), (128, 8), (128, 20), (256, 2), (256, 9)])
 @pytest.mark.parametrize("layout", [W.BHSD, W.PAGED])
 @pytest.mark.parametrize("n_long", [1, 6, 20])
