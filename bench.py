@@ -25,11 +25,11 @@ HBM_PEAK_GBPS = 8000.0  # MI355X published HBM3E bandwidth
 # workload (profiles/pmc_traffic_<workload>.md), each counter scaled by what it reads for a plain device-to-device
 # copy of known size in the same run.  Valid only for the kernel sources they were taken with: the hash below
 # covers the two kernel files, and a mismatch reports traffic as null.
-PMC_TRAFFIC = {"sha": "a7f5c9c619120042",
-               "llama8b_32k": {"kv_layout_kernel<pack>": 268460273, "kv_layout_kernel<unpack>": 268457994, "kv_attn_partial_kernel+kv_attn_combine_kernel": 135577127},
-               "llama8b_4k": {"kv_layout_kernel<pack>": 268475091, "kv_layout_kernel<unpack>": 268466140, "kv_attn_partial_kernel+kv_attn_combine_kernel": 18149699},
-               "llama8b_ragged_paged": {"kv_layout_kernel<pack>": 282080728, "kv_layout_kernel<unpack>": 282054778, "kv_attn_partial_kernel+kv_attn_combine_kernel": 142711608},
-               "gemma7b_mha_8k": {"kv_layout_kernel<pack>": 536895587, "kv_layout_kernel<unpack>": 536884918, "kv_attn_partial_kernel+kv_attn_combine_kernel": 538453877}}
+PMC_TRAFFIC = {"sha": "5a30c3a7151c7f67",
+               "llama8b_32k": {"kv_layout_kernel<pack>": 268481248, "kv_layout_kernel<unpack>": 268481122, "kv_attn_partial_kernel+kv_attn_combine_kernel": 135567173},
+               "llama8b_4k": {"kv_layout_kernel<pack>": 268465507, "kv_layout_kernel<unpack>": 268601115, "kv_attn_partial_kernel+kv_attn_combine_kernel": 18131144},
+               "llama8b_ragged_paged": {"kv_layout_kernel<pack>": 282079834, "kv_layout_kernel<unpack>": 282056944, "kv_attn_partial_kernel+kv_attn_combine_kernel": 142708951},
+               "gemma7b_mha_8k": {"kv_layout_kernel<pack>": 536897641, "kv_layout_kernel<unpack>": 536884046, "kv_attn_partial_kernel+kv_attn_combine_kernel": 538131536}}
 
 
 def kernel_sources_hash() -> str:

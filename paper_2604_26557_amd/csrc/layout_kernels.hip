@@ -9,7 +9,7 @@
 // the inner loop is adds, U independent 16-byte loads, then U stores.  HBM-bound: 2 bytes of traffic per
 // payload byte, no reuse, no LDS.  Where a plain copy reaches 6.3 TB/s, launches of 128 MiB and more run at
 // 5.5-6.3 (strided, rows to 4 KiB), 5.0-5.9 (strided, wider rows of 128- and 256-wide heads; 64-wide 4.6-4.9)
-// and 4.5-5.4 (paged).  32 layers of 8 heads x 4K tokens x 128 out of one launch pair: 169 us for 1 GiB of traffic.
+// and 4.5-6.0 (paged; 32 heads x 128, batch 4 of 2000: 5.6).  32 layers of 8 heads x 4K tokens x 128 out of one launch pair: 169 us for 1 GiB of traffic.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
