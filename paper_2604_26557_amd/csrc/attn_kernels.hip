@@ -861,7 +861,7 @@ kv_attn_combine_kernel(const float *__restrict__ part_acc, const float *__restri
         n_splits = tab.splits[b];
     } else {
         n_splits = n_uniform;   // every sequence has as many; a division here would be on the way to the first load
-        if (n_splits < 0) n_splits = min(n_splits_alloc, (min(seq_lens[b], max_len) + split_tokens - 1) / split_tokens);
+        if (n_splits < 0) n_splits = min(n_splits_alloc, splits_of(max(0, min(seq_lens[b], max_len)), split_tokens));
     }
 
     const float *const pa = part_acc + o * D;
@@ -997,7 +997,7 @@ void launch_partial_d(int D, bool bf16, dim3 grid, hipStream_t st, const AttnHea
 template <typename TAB>
 void launch_combine(int D, dim3 grid, hipStream_t st, const AttnHead &c, const AttnParams &a, int out_mode, const TAB &t)
 {
-    const int n_uniform = c.len_uniform < 0 ? -1 : std::min(a.n_splits, (c.len_uniform + c.split_tokens - 1) / c.split_tokens);
+    const int n_uniform = c.len_uniform < 0 ? -1 : std::min(a.n_splits, splits_of(c.len_uniform, c.split_tokens));
 #define KV_COMBINE_W(DD, W)                                                                                      \
     (void)kvb::launch_kernel(kv_attn_combine_kernel<DD, W, TAB>, grid, dim3(64 * W), st, a.part_acc, a.part_ml, a.out, \
                        a.seq_lens, c.Hq, a.n_splits, out_mode, n_uniform, a.max_len, c.split_tokens, t)
@@ -1168,7 +1168,7 @@ extern "C" int kv_decode_attn_splits(const kv_plan_t *p, const int32_t *seq_lens
     for (int b = 0; b < p->B; ++b) {
         if (first) first[b] = acc;
         if (tokens) tokens[b] = use_table ? tab.tokens[b] : st;
-        acc += use_table ? tab.first[b + 1] - tab.first[b] : std::min(*n_splits_out, (seq_lens_host[b] + st - 1) / st);
+        acc += use_table ? tab.first[b + 1] - tab.first[b] : std::min(*n_splits_out, splits_of(seq_lens_host[b], st));
     }
     if (first) first[p->B] = acc;
     return KV_OK;

@@ -37,6 +37,9 @@ inline int planned_parts(int G) { return G % 4 == 0 ? G / 4 : (G % 2 == 0 ? G / 
 // Tokens per split are a multiple of this: four steps.
 inline int split_quantum(int D) { return 4 * kTile * tiles_per_step(D); }
 
+// Splits of `st` tokens that hold a sequence of `len` (both up to 2^31 - 1: their sum only fits unsigned).
+constexpr int splits_of(int len, int st) { return (int)(((unsigned)len + (unsigned)st - 1u) / (unsigned)st); }
+
 // Most splits the automatic choice can make for sequences of up to max_len tokens (sizes the workspace).
 inline int max_auto_splits(const AttnShape &s, int max_len)
 {
@@ -99,7 +102,7 @@ inline int apportion_splits(const AttnShape &s, int parts, const int32_t *lens, 
         int st = q;
         if (nb[b] > 0) {
             st = std::max(q, (int)((((long long)lens[b] + nb[b] - 1) / nb[b] + step - 1) / step * step));
-            nb[b] = (lens[b] + st - 1) / st;   // rounding the split length up may leave fewer splits
+            nb[b] = splits_of(lens[b], st);   // rounding the split length up may leave fewer splits
         }
         t->tokens[b] = st;
         first += nb[b];
@@ -134,7 +137,7 @@ inline int plan_splits(const AttnShape &s, int parts, const int32_t *lens, int n
         for (int b = 0; b < s.B; ++b) {
             tab->first[b] = first;
             tab->tokens[b] = *split_tokens;
-            first += (lens[b] + *split_tokens - 1) / *split_tokens;
+            first += splits_of(lens[b], *split_tokens);
         }
         for (int b = s.B; b <= kMaxTableSeqs; ++b) tab->first[b] = first;
     }
@@ -197,8 +200,8 @@ inline int even_splits(const AttnShape &s, int parts, int len, int plan, int cap
         int ns = k == 0 ? plan : (int)std::min<long long>(cap, k * (long long)s.cus / units);
         if (ns < 1) continue;
         const int st = split_tokens_for(s, ns, len);
-        if (k > 0) ns = (len + st - 1) / st;
-        const double per_cu = (double)((len + st - 1) / st) * units / s.cus, rounds = (double)(long long)(per_cu + 0.999999);
+        if (k > 0) ns = splits_of(len, st);
+        const double per_cu = (double)splits_of(len, st) * units / s.cus, rounds = (double)(long long)(per_cu + 0.999999);
         const double cost = cut_cost(s, (double)len * s.B * parts, per_cu, rounds * std::min(st, len), ns > 1);
         if (best == 0 || cost < 0.99 * best_cost) { best = ns; best_cost = cost; }
     }
@@ -245,19 +248,19 @@ inline int finer_splits(const AttnShape &s, int parts, const int32_t *lens, int 
     for (int b = 0; b < s.B; ++b) { total += lens[b]; used += lens[b] > 0; max_len = std::max(max_len, (int)lens[b]); }
     const double m = (double)s.cus / (s.H * parts);
     const int target = std::max((int)(3 * m), used + (int)m);
-    long long lo = std::max<long long>(q, std::max<long long>(total / target, (max_len + cap - 1) / cap)), hi = std::max<long long>(lo, max_len);
+    long long lo = std::max<long long>(q, std::max<long long>(total / target, splits_of(max_len, cap))), hi = std::max<long long>(lo, max_len);
     for (int i = 0; i < 7 && lo < hi; ++i) {   // hi holds the target; lo may not
-        const unsigned st = (unsigned)((lo + hi) / 2);
+        const int st = (int)((lo + hi) / 2);
         int n = 0;
-        for (int b = 0; b < s.B; ++b) n += (int)(((unsigned)lens[b] + st - 1) / st);
+        for (int b = 0; b < s.B; ++b) n += splits_of(lens[b], st);
         if (n <= target) hi = st; else lo = st + 1;
     }
     int first = 0, most = 1;
     for (int b = 0; b < s.B; ++b) {
-        int nb = (int)((lens[b] + hi - 1) / hi), st = q;
+        int nb = splits_of(lens[b], (int)hi), st = q;
         if (nb > 0) {
             st = std::max(q, (int)((((long long)lens[b] + nb - 1) / nb + step - 1) / step * step));
-            nb = (int)(((long long)lens[b] + st - 1) / st);
+            nb = splits_of(lens[b], st);
         }
         t->first[b] = first;
         t->tokens[b] = st;
@@ -318,7 +321,7 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
                     c->tab.first[b] = first;
                     if (b >= s.B) continue;
                     c->tab.tokens[b] = c->split_tokens;
-                    first += (int)(((long long)lens[b] + c->split_tokens - 1) / c->split_tokens);
+                    first += splits_of(lens[b], c->split_tokens);
                 }
             }
             order_splits(s, lens, c->tab, c->order);

@@ -152,3 +152,39 @@ int main()
     exe = str(tmp_path / "order")
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=address,undefined", "-I", os.path.join(ROOT, "paper_2604_26557_amd", "csrc"), str(src), "-o", exe])
     subprocess.check_call([exe])
+
+
+def test_cuts_of_very_long_sequences(tmp_path):
+    """Lengths whose sum with a split length does not fit 32 signed bits: every cut holds its tokens, within the workspace, and no
+    arithmetic overflows."""
+    src = tmp_path / "long.cpp"
+    src.write_text(r"""
+#include <cstdlib>
+#include "attn_splits.hpp"
+int main()
+{
+    std::srand(17);
+    for (int it = 0; it < 4000; ++it) {
+        const int G = 1 + std::rand() % 20, H = 1 + std::rand() % 32, D = 64 << (std::rand() % 3), B = 1 + std::rand() % 140;
+        const int32_t top = (1 << 29) + std::rand() % (3 << 29);
+        int32_t lens[140];
+        for (int b = 0; b < B; ++b) lens[b] = it % 2 ? top : std::rand() % 3 ? top - std::rand() % (1 << 29) : std::rand() % 1000;
+        const kvb::AttnShape s{B, H, H * G, D, 256};
+        const size_t per_split = (size_t)B * H * G * (D + 2) * 4;
+        const int max_ws = it % 5 ? 1024 : 1 + std::rand() % 64;
+        kvb::AttnCut c{};
+        if (!kvb::cut_tokens(s, lens, it % 7 ? 0 : 1 + std::rand() % 40, per_split * max_ws, &c)) continue;
+        if (c.ns < 1 || c.ns > max_ws) return 1;
+        for (int b = 0; b < B; ++b) {
+            const long long st = c.use_table ? c.tab.tokens[b] : c.split_tokens, n = c.use_table ? c.tab.first[b + 1] - c.tab.first[b] : c.ns;
+            if (st < 1 || n < 0 || n > c.ns || n * st < lens[b]) return 2;
+            if (kvb::splits_of(lens[b], (int)st) != (lens[b] + st - 1) / st) return 3;
+        }
+    }
+    return 0;
+}
+""")
+    exe = str(tmp_path / "long")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+                           "-I", os.path.join(ROOT, "paper_2604_26557_amd", "csrc"), str(src), "-o", exe])
+    subprocess.check_call([exe])
