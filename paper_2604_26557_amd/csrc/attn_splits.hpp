@@ -40,6 +40,21 @@ inline int split_quantum(int D) { return 4 * kTile * tiles_per_step(D); }
 // Splits of `st` tokens that hold a sequence of `len` (both up to 2^31 - 1: their sum only fits unsigned).
 constexpr int splits_of(int len, int st) { return (int)(((unsigned)len + (unsigned)st - 1u) / (unsigned)st); }
 
+// The same for a batch, and their sum.  A product with the reciprocal in double takes a fraction of an integer division, and is exact: the
+// numerator, below 2^32 and with a half, puts the quotient at least 0.5 / st from a whole number, which is far more than it is off.
+inline void splits_of_all(const int32_t *lens, int B, int st, int *n)
+{
+    const double up = st - 0.5, per = 1.0 / st;
+    for (int b = 0; b < B; ++b) n[b] = (int)((lens[b] + up) * per);
+}
+inline int splits_in_all(const int32_t *lens, int B, int st)
+{
+    const double up = st - 0.5, per = 1.0 / st;
+    int n = 0;
+    for (int b = 0; b < B; ++b) n += (int)((lens[b] + up) * per);
+    return n;
+}
+
 // Most splits the automatic choice can make for sequences of up to max_len tokens (sizes the workspace).
 inline int max_auto_splits(const AttnShape &s, int max_len)
 {
@@ -112,6 +127,20 @@ inline int apportion_splits(const AttnShape &s, int parts, const int32_t *lens, 
     return most;
 }
 
+// One split length for all sequences.
+inline void common_table(const AttnShape &s, const int32_t *lens, int split_tokens, SplitTable *t)
+{
+    const int B = s.B;
+    int nb[kMaxTableSeqs], first = 0;
+    splits_of_all(lens, B, split_tokens, nb);
+    for (int b = 0; b < B; ++b) {
+        t->first[b] = first;
+        t->tokens[b] = split_tokens;
+        first += nb[b];
+    }
+    for (int b = B; b <= kMaxTableSeqs; ++b) t->first[b] = first;
+}
+
 // Split choice for the given lengths: fills the table (ragged batches of up to kPlanTableSeqs sequences) or the
 // common split length; returns the split count the partials are laid out for, at most `cap` unless the caller gave it.
 inline int plan_splits(const AttnShape &s, int parts, const int32_t *lens, int n_splits, int cap, bool *use_table, SplitTable *tab,
@@ -132,15 +161,7 @@ inline int plan_splits(const AttnShape &s, int parts, const int32_t *lens, int n
     }
     const int ns = n_splits > 0 ? n_splits : std::min(cap, choose_splits(s, parts, total_len, max_len));
     *split_tokens = split_tokens_for(s, ns, max_len);
-    if (*use_table) {
-        int first = 0;
-        for (int b = 0; b < s.B; ++b) {
-            tab->first[b] = first;
-            tab->tokens[b] = *split_tokens;
-            first += splits_of(lens[b], *split_tokens);
-        }
-        for (int b = s.B; b <= kMaxTableSeqs; ++b) tab->first[b] = first;
-    }
+    if (*use_table) common_table(s, lens, *split_tokens, tab);
     return ns;
 }
 
@@ -208,41 +229,79 @@ inline int even_splits(const AttnShape &s, int parts, int len, int plan, int cap
     return best;
 }
 
-// Sequences by descending split length.
+// Sequences by descending split length, equal ones in the order of the batch: a counting sort of up to 7 bits per pass (128 sequences of 200-4000 tokens:
+// 0.43 us of host time; a comparison sort whose branches are predicted 0.75).
 inline void order_splits(const AttnShape &s, const int32_t *lens, const SplitTable &t, unsigned char *order)
 {
-    static_assert(kMaxTableSeqs <= 256, "a sequence is a byte");
-    uint64_t key[kMaxTableSeqs];
-    for (int b = 0; b < s.B; ++b) key[b] = (uint64_t)std::min(t.tokens[b], (int)lens[b]) << 8 | (uint64_t)(255 - b);
-    std::sort(key, key + s.B, [](uint64_t x, uint64_t y) { return x > y; });
-    for (int r = 0; r < s.B; ++r) order[r] = (unsigned char)(255 - (key[r] & 255));
+    static_assert(kMaxTableSeqs < 256, "a sequence, and a number of them, is a byte");
+    const int B = s.B;
+    int size[kMaxTableSeqs], top = 0;
+    unsigned char from[kMaxTableSeqs], to[kMaxTableSeqs];
+    for (int b = 0; b < B; ++b) {
+        size[b] = std::min(t.tokens[b], (int)lens[b]);
+        top = std::max(top, size[b]);
+        to[b] = (unsigned char)b;
+    }
+    const int bits = top > 0 ? 32 - __builtin_clz((unsigned)top) : 0, passes = (bits + 6) / 7;
+    const int width = passes > 0 ? (bits + passes - 1) / passes : 0, mask = (1 << width) - 1;
+    for (int pass = 0, shift = 0; pass < passes; ++pass, shift += width) {
+        unsigned char at[128] = {};
+        for (int b = 0; b < B; ++b) ++at[(top - size[b]) >> shift & mask];
+        for (int i = 0, n = 0; n < B; ++i) {
+            const unsigned char k = at[i];
+            at[i] = (unsigned char)n;
+            n += k;
+        }
+        std::copy(to, to + B, from);
+        for (int r = 0; r < B; ++r) to[at[(top - size[from[r]]) >> shift & mask]++] = from[r];
+    }
+    std::copy(to, to + B, order);
 }
 
-inline double table_cost(const AttnShape &s, int parts, const int32_t *lens, const SplitTable &t, const unsigned char *order, int most)
+// *ordered: whether `order` is the table's; it is made where the cost depends on it.
+inline double table_cost(const AttnShape &s, int parts, const int32_t *lens, const SplitTable &t, int most, unsigned char *order, bool *ordered)
 {
     const double m = (double)s.cus / (s.H * parts);   // compute units for each of the heads
-    const int n = t.first[s.B], at[3] = {0, (int)m, n - (int)m};
-    double size[3] = {0, 0, 0}, total = 0;
-    for (int r = 0, f = 0; r < s.B; ++r) {
-        const int b = order[r], e = f + t.first[b + 1] - t.first[b];
-        for (int i = 0; i < 3; ++i)
-            if (at[i] >= f && at[i] < e) size[i] = std::min(t.tokens[b], (int)lens[b]);
-        total += lens[b];
-        f = e;
+    const int n = t.first[s.B];
+    long long sum = 0;
+    int size0 = 0;
+    for (int b = 0; b < s.B; ++b) {
+        sum += lens[b];
+        size0 = std::max(size0, std::min(t.tokens[b], (int)lens[b]));
     }
     // The grid deals the longest out first, then the next to the same compute units; the third round goes to whichever is free, and where it
     // is not a whole one (whole sequences) part of a split is left at the end.
-    double longest = size[0] + (n > m ? size[1] : 0);
-    if (n > 2 * m) longest = std::max(longest, (total / m + (most > 1 ? 0 : size[2] / 4)) / kAlone);
+    const double total = (double)sum;
+    double longest = size0;
+    if (n > 2 * m && most > 1 && 2.0 * size0 <= total / m / kAlone) {
+        longest = total / m / kAlone;   // whatever the second one is
+    } else if (n > m) {
+        int full = 0;   // items as long as the longest
+        for (int b = 0; b < s.B; ++b) full += std::min(t.tokens[b], (int)lens[b]) == size0 ? t.first[b + 1] - t.first[b] : 0;
+        auto size_at = [&](int item) {
+            if (item < full) return size0;
+            if (!*ordered) order_splits(s, lens, t, order);
+            *ordered = true;
+            for (int r = 0, f = 0; r < s.B; ++r) {
+                const int b = order[r];
+                f += t.first[b + 1] - t.first[b];
+                if (f > item) return std::min(t.tokens[b], (int)lens[b]);
+            }
+            return 0;
+        };
+        longest += size_at((int)m);
+        if (n > 2 * m) longest = std::max(longest, (total / m + (most > 1 ? 0 : size_at(n - (int)m) / 4.0)) / kAlone);
+    }
     return cut_cost(s, total * parts, n / m, longest, most > 1);
 }
 
 // Cuts every sequence into splits of at most as many tokens as make three workgroups for a compute unit, or one more for each than there are
-// sequences.  Returns the largest split count.  (48 sequences of 200-4000 tokens, 4 x 7 x 128: 1.9 workgroups for a compute unit 45.5 us, 2.5 47.2, 2.9
-// 44.7, 3.0 43.8, 3.5 47.2, 3.8 45.9.)
-inline int finer_splits(const AttnShape &s, int parts, const int32_t *lens, int cap, SplitTable *t)
+// sequences.  Returns the largest split count, or 0 (and no table) where the cut cannot cost less than `worth`.  (48 sequences of 200-4000 tokens,
+// 4 x 7 x 128: 1.9 workgroups for a compute unit 45.5 us, 2.5 47.2, 2.9 44.7, 3.0 43.8, 3.5 47.2, 3.8 45.9.)
+inline int finer_splits(const AttnShape &s, int parts, const int32_t *lens, int cap, double worth, SplitTable *t)
 {
-    const int step = kTile * tiles_per_step(s.D), q = split_quantum(s.D);
+    const unsigned step = kTile * tiles_per_step(s.D);
+    const int q = split_quantum(s.D);
     long long total = 0;
     int used = 0, max_len = 0;
     for (int b = 0; b < s.B; ++b) { total += lens[b]; used += lens[b] > 0; max_len = std::max(max_len, (int)lens[b]); }
@@ -251,23 +310,28 @@ inline int finer_splits(const AttnShape &s, int parts, const int32_t *lens, int 
     long long lo = std::max<long long>(q, std::max<long long>(total / target, splits_of(max_len, cap))), hi = std::max<long long>(lo, max_len);
     for (int i = 0; i < 7 && lo < hi; ++i) {   // hi holds the target; lo may not
         const int st = (int)((lo + hi) / 2);
-        int n = 0;
-        for (int b = 0; b < s.B; ++b) n += splits_of(lens[b], st);
-        if (n <= target) hi = st; else lo = st + 1;
+        if (used + (double)total / st <= target || splits_in_all(lens, s.B, st) <= target) hi = st; else lo = st + 1;
+    }
+    // a workgroup for each sequence at least, an even share for every compute unit at best
+    if (cut_cost(s, (double)total * parts, used / m, 0, hi < max_len) >= worth) return 0;
+    const int B = s.B;
+    int nb[kMaxTableSeqs], tokens[kMaxTableSeqs];   // apart from the table, which the compiler must take for the lengths' memory
+    splits_of_all(lens, B, (int)hi, nb);
+    for (int b = 0; b < B; ++b) {
+        const double len = lens[b];
+        const int even = (int)((len + nb[b] - 0.5) / std::max(nb[b], 1));   // no tokens: 0 of 0
+        const int st = std::max(q, (int)(((unsigned)even + step - 1) & ~(step - 1)));   // whole steps, a power of two
+        tokens[b] = st;
+        nb[b] = (int)((len + (st - 0.5)) / st);
     }
     int first = 0, most = 1;
-    for (int b = 0; b < s.B; ++b) {
-        int nb = splits_of(lens[b], (int)hi), st = q;
-        if (nb > 0) {
-            st = std::max(q, (int)((((long long)lens[b] + nb - 1) / nb + step - 1) / step * step));
-            nb = splits_of(lens[b], st);
-        }
+    for (int b = 0; b < B; ++b) {
         t->first[b] = first;
-        t->tokens[b] = st;
-        first += nb;
-        most = std::max(most, nb);
+        t->tokens[b] = tokens[b];
+        first += nb[b];
+        most = std::max(most, nb[b]);
     }
-    for (int b = s.B; b <= kMaxTableSeqs; ++b) t->first[b] = first;
+    for (int b = B; b <= kMaxTableSeqs; ++b) t->first[b] = first;
     return most;
 }
 
@@ -309,6 +373,7 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
         limited = cap < replan_cap(max_len);
     }
     // The plan, or a finer cut where that is the cheaper one.
+    bool ordered = false;   // c->order is the table's
     const int cap = (int)std::min<size_t>(replan_cap(max_len), ws_bytes / per_split);
     if (n_splits == 0 && !whole && max_len > 0 && cap > 0) {
         if (uniform) {
@@ -317,21 +382,18 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
         } else if (s.B <= kMaxTableSeqs) {
             if (!c->use_table) {   // more sequences than the plan tables: as it is launched without a table
                 c->use_table = true;
-                for (int b = 0, first = 0; b <= kMaxTableSeqs; ++b) {
-                    c->tab.first[b] = first;
-                    if (b >= s.B) continue;
-                    c->tab.tokens[b] = c->split_tokens;
-                    first += splits_of(lens[b], c->split_tokens);
-                }
+                common_table(s, lens, c->split_tokens, &c->tab);
             }
-            order_splits(s, lens, c->tab, c->order);
+            const double worth = 0.97 * table_cost(s, c->subs, lens, c->tab, c->ns, c->order, &ordered);
             SplitTable fine;
             unsigned char order[kMaxTableSeqs];
-            const int most = finer_splits(s, c->subs, lens, cap, &fine);
-            order_splits(s, lens, fine, order);
-            if (table_cost(s, c->subs, lens, fine, order, most) < 0.97 * table_cost(s, c->subs, lens, c->tab, c->order, c->ns)) {
+            bool fine_ordered = false;
+            const int most = finer_splits(s, c->subs, lens, cap, worth, &fine);
+            if (most > 0 && table_cost(s, c->subs, lens, fine, most, order, &fine_ordered) < worth) {
                 c->tab = fine;
                 c->ns = most;
+                ordered = fine_ordered;
+                if (ordered) std::copy(order, order + s.B, c->order);
             }
         }
     }
@@ -350,8 +412,8 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
         // More workgroups than compute units: those with most to do start first, whichever KV head they belong to.  us per layer from a graph, in the order
         // of the batch / longest first: 32 sequences of 200-1000 tokens, 32 KV heads x 1 x 128 66.0 / 53.9, 60 of 100-600, 8 x 4 x 128 23.2 / 20.6.
         c->longest_first = c->subs == 1 && (long long)c->tab.first[s.B] * s.H > s.cus && c->tab.first[s.B] <= 65535;   // a grid's y dimension
-        if (c->longest_first) order_splits(s, lens, c->tab, c->order);
-        else for (int b = 0; b < s.B; ++b) c->order[b] = (unsigned char)b;
+        if (!c->longest_first) for (int b = 0; b < s.B; ++b) c->order[b] = (unsigned char)b;
+        else if (!ordered) order_splits(s, lens, c->tab, c->order);
     }
     return true;
 }

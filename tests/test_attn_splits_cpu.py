@@ -188,3 +188,24 @@ int main()
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
                            "-I", os.path.join(ROOT, "paper_2604_26557_amd", "csrc"), str(src), "-o", exe])
     subprocess.check_call([exe])
+
+
+def _cut_harness(tmp_path, *flags):
+    exe = str(tmp_path / "attn_cut")
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", *flags, "-I", os.path.join(ROOT, "paper_2604_26557_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "attn_cut_harness.cpp"), "-o", exe])
+    return exe
+
+
+def test_the_cut_of_a_ragged_batch_is_the_plainly_written_one(tmp_path):
+    """Tables, costs and orders of 20000 batches, every number equal; a cut that is left out unseen is not the cheaper one."""
+    subprocess.check_call([_cut_harness(tmp_path, "-O1", "-fsanitize=address,undefined")])
+
+
+def test_the_cut_of_a_ragged_batch_costs_the_host_little(tmp_path):
+    """Every layer's call makes the cut, so it must not weigh beside a launch.  The yardstick is a comparison sort of 128 keys in the same process
+    (0.8 us where the cuts of batches of more than 64 sequences take 1.0-1.8); a cut that sorts its tables each time takes six to eight of those."""
+    out = subprocess.run([_cut_harness(tmp_path, "-O3"), "time"], capture_output=True, text=True, check=True).stdout.splitlines()
+    ratios = {line.rsplit(" ", 1)[0]: float(line.rsplit(" ", 1)[1]) for line in out}
+    assert len(ratios) == 9
+    assert all(r < 4 for k, r in ratios.items() if int(k.split()[0]) > 64), ratios
