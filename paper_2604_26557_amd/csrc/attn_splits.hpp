@@ -226,10 +226,12 @@ struct AttnCut {
 //  * A compute unit reads no more than 1 / kAlone of its share of HBM when others are idle.
 //  * item_bytes for every workgroup after the first (1.2 us at 25 GB/s and compute unit; 4.4 us where a compute unit holds one workgroup at a time:
 //    5 sequences of 4000 tokens, 8 x 8 x 256, one / two / three workgroups for each 34.4 / 39.4 / 43.8), kCombineBytes for the second launch (3.4 us).
+//  * kFinerBytes (1 us) is what a finer cut has to save: about its own host time, and what the model is off by for batches of 10 us.  128 sequences of
+//    260-400 tokens, 2 x 4 x 128, called one by one: without it 16.4 us a layer, with it 15.6.
 // us per layer from a graph, one workgroup per compute unit (or sequence) / this cut: paged batch of 48 sequences of 200-4000 tokens, 4 KV heads
 // x 7 x 128 51.7 / 42.9, 8 x 4 x 128 113 / 76.6; 20 of 1K-8K, 8 x 4 x 128 74.9 / 65.1; 30 of 200-8000, 5 x 4 x 64 39.7 / 33.2.  Where the plan is
 // even it stays: 8 of 1K-8K 31.0 / 31.8, 3 of 2.5K-20K 26.3 / 29.5.
-constexpr double kAlone = 0.85, kCombineBytes = 84e3;
+constexpr double kAlone = 0.85, kCombineBytes = 84e3, kFinerBytes = 25e3;
 inline double item_bytes(const AttnShape &s) { return s.D >= 256 && s.Hq > s.H ? 110e3 : 30e3; }
 
 // per_cu: workgroups per compute unit; longest: token rows of the compute unit that has most.
@@ -338,12 +340,14 @@ inline int finer_splits(const AttnShape &s, int parts, const int32_t *lens, int 
     const double m = (double)s.cus / (s.H * parts);
     const int target = std::max((int)(3 * m), used + (int)m);
     long long lo = std::max<long long>(q, std::max<long long>(total / target, splits_of(max_len, cap))), hi = std::max<long long>(lo, max_len);
+    // a workgroup for each sequence at least, an even share for every compute unit at best; that it splits is often known beforehand
+    const double mean = (double)total * parts;
+    if (lo < hi && used + (double)total / ((lo + hi) / 2) <= target && cut_cost(s, mean, used / m, 0, true) >= worth) return 0;
     for (int i = 0; i < 7 && lo < hi; ++i) {   // hi holds the target; lo may not
         const int st = (int)((lo + hi) / 2);
         if (used + (double)total / st <= target || splits_in_all(lens, s.B, st) <= target) hi = st; else lo = st + 1;
     }
-    // a workgroup for each sequence at least, an even share for every compute unit at best
-    if (cut_cost(s, (double)total * parts, used / m, 0, hi < max_len) >= worth) return 0;
+    if (cut_cost(s, mean, used / m, 0, hi < max_len) >= worth) return 0;
     int nb[kMaxTableSeqs];
     splits_of_all(lens, s.B, (int)hi, nb);
     return even_table(s, lens, nb, t);
@@ -398,7 +402,7 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
                 c->use_table = true;
                 common_table(s, lens, c->split_tokens, &c->tab);
             }
-            const double worth = 0.97 * table_cost(s, c->subs, lens, c->tab, c->ns, c->order, &ordered);
+            const double cost = table_cost(s, c->subs, lens, c->tab, c->ns, c->order, &ordered), worth = std::min(0.97 * cost, cost - kFinerBytes);
             SplitTable fine;
             unsigned char order[kMaxTableSeqs];
             bool fine_ordered = false;

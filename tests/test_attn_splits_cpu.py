@@ -109,6 +109,13 @@ def test_batches_that_fill_the_compute_units_unevenly_are_cut_more_finely(harnes
     assert r[7]["ok"] and r[7]["ns"] <= 2                           # within the workspace
 
 
+def test_a_finer_cut_has_to_save_more_than_it_costs(harness):
+    """Two workgroups for each compute unit as planned, of at most 256 tokens: three would save less than 1 us by the model, and take more."""
+    rnd = random.Random(5)
+    r = _cut(harness, [(2, 4, 128, [rnd.randint(260, 400) for _ in range(128)], 0, -1)])[0]
+    assert r["ns"] == 2 and set(r["splits"]) <= {1, 2}
+
+
 def test_the_order_of_the_grid_holds_every_sequence(tmp_path):
     """Every sequence is in the order once; where the longest come first, the splits' sizes fall along it."""
     src = tmp_path / "order.cpp"
