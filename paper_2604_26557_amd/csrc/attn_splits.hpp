@@ -328,9 +328,12 @@ inline double table_cost(const AttnShape &s, int parts, const int32_t *lens, con
     return cut_cost(s, total * parts, n / m, longest, most > 1);
 }
 
-// Cuts every sequence into splits of at most as many tokens as make three workgroups for a compute unit, or one more for each than there are
-// sequences.  Returns the largest split count, or 0 (and no table) where the cut cannot cost less than `worth`.  (48 sequences of 200-4000 tokens,
-// 4 x 7 x 128: 1.9 workgroups for a compute unit 45.5 us, 2.5 47.2, 2.9 44.7, 3.0 43.8, 3.5 47.2, 3.8 45.9.)
+// Cuts every sequence into equal splits, of at most as many tokens as make three workgroups for a compute unit, or one more for each than there are
+// sequences; but no more splits than the sequence has eights of steps, a step for each of eight wavefronts.  Returns the largest split count, or 0
+// (and no table) where the cut cannot cost less than `worth`.
+// us per layer from a graph: 48 sequences of 200-4000 tokens, 4 x 7 x 128: 1.9 workgroups for a compute unit 45.5, 2.5 47.2, 2.9 44.7, 3.0 43.8, 3.5 47.2, 3.8
+// 45.9.  The plan / a split per four steps / per eight: 96 sequences of 260-600, 1 x 4 x 128 11.8 / 13.1 / 10.6; 80 of 600-900, 2 x 2 x 64 14.0 / 13.1 / 12.7;
+// 66 of 130-500, 2 x 4 x 256 17.95 / 17.9 / 17.2.
 inline int finer_splits(const AttnShape &s, int parts, const int32_t *lens, int cap, double worth, SplitTable *t)
 {
     const int q = split_quantum(s.D);
@@ -339,7 +342,7 @@ inline int finer_splits(const AttnShape &s, int parts, const int32_t *lens, int 
     for (int b = 0; b < s.B; ++b) { total += lens[b]; used += lens[b] > 0; max_len = std::max(max_len, (int)lens[b]); }
     const double m = (double)s.cus / (s.H * parts);
     const int target = std::max((int)(3 * m), used + (int)m);
-    long long lo = std::max<long long>(q, std::max<long long>(total / target, splits_of(max_len, cap))), hi = std::max<long long>(lo, max_len);
+    long long lo = std::max<long long>(2 * q, std::max<long long>(total / target, splits_of(max_len, cap))), hi = std::max<long long>(lo, max_len);
     // a workgroup for each sequence at least, an even share for every compute unit at best; that it splits is often known beforehand
     const double mean = (double)total * parts;
     if (lo < hi && used + (double)total / ((lo + hi) / 2) <= target && cut_cost(s, mean, used / m, 0, true) >= worth) return 0;

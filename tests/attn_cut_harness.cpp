@@ -56,7 +56,7 @@ int finer(const AttnShape &s, int parts, const int32_t *lens, int cap, SplitTabl
     for (int b = 0; b < s.B; ++b) { total += lens[b]; used += lens[b] > 0; max_len = std::max(max_len, (int)lens[b]); }
     const double m = (double)s.cus / (s.H * parts);
     const int target = std::max((int)(3 * m), used + (int)m);
-    long long lo = std::max<long long>({split_quantum(s.D), total / target, ceil_div(max_len, cap)}), hi = std::max<long long>(lo, max_len);
+    long long lo = std::max<long long>({2 * split_quantum(s.D), total / target, ceil_div(max_len, cap)}), hi = std::max<long long>(lo, max_len);
     for (int i = 0; i < 7 && lo < hi; ++i) {
         const long long st = (lo + hi) / 2;
         long long n = 0;

@@ -116,6 +116,16 @@ def test_a_finer_cut_has_to_save_more_than_it_costs(harness):
     assert r["ns"] == 2 and set(r["splits"]) <= {1, 2}
 
 
+def test_a_finer_cut_has_a_step_for_every_wavefront(harness):
+    """One split for every eight steps of a sequence at most: 128 tokens, 256 at head_dim 64."""
+    rnd = random.Random(9)
+    cases = [(1, 4, 128, [rnd.randint(260, 600) for _ in range(96)], 0, -1), (2, 2, 64, [rnd.randint(600, 900) for _ in range(80)], 0, -1),
+             (2, 4, 256, [rnd.randint(130, 500) for _ in range(66)], 0, -1)]
+    for (H, G, D, lens, _, _), c in zip(cases, _cut(harness, cases)):
+        assert c["table"] and max(c["splits"]) > 1
+        assert all(nb <= -(-n // (256 if D == 64 else 128)) for n, nb in zip(lens, c["splits"]))
+
+
 def test_the_order_of_the_grid_holds_every_sequence(tmp_path):
     """Every sequence is in the order once; where the longest come first, the splits' sizes fall along it."""
     src = tmp_path / "order.cpp"
