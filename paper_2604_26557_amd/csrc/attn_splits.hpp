@@ -328,6 +328,24 @@ inline double table_cost(const AttnShape &s, int parts, const int32_t *lens, con
     return cut_cost(s, total * parts, n / m, longest, most > 1);
 }
 
+// Whether the sequences, not split, are worth a table.  Its order, the longest first, saves up to what those take beyond the mean, but each workgroup of
+// a compute unit in turn waits for the lookup, `lookup` in bytes that it would read meanwhile: more beyond 64 sequences, which take a second round of
+// loads, and at head_dim 256, where a compute unit holds one workgroup at a time.  us per layer of eager calls, table / none: up to 128 KiB, 40 of 20-250 tokens,
+// 32 x 1 x 128 17.4 / 19.5, of 10-60 9.3 / 8.9; 128 of 20-180, 8 x 4 x 128 15.0 / 15.7, of 20-96 12.1 / 11.4; 128 of 20-250, 32 x 4 x 128 61.3 / 58.0, 64 of those
+// 30.1 / 31.0.  Longer, 80 of 300-2000, 8 x 4 x 128 65.8 / 77.3; 128 of 400-700, 32 x 1 x 64 99.2 / 91.1; 66 of 130-300, 16 x 4 x 256 53.5 / 50.1.
+inline bool table_pays(const AttnShape &s, int parts, const int32_t *lens, const SplitTable &t, double lookup)
+{
+    long long sum = 0;
+    int longest = 0, used = 0;
+    for (int b = 0; b < s.B; ++b) {
+        const int size = std::min(t.tokens[b], (int)lens[b]);
+        sum += size;
+        used += size > 0;
+        longest = std::max(longest, size);
+    }
+    return kAlone * (longest - (double)sum / used) * 4.0 * s.D > lookup * t.first[s.B] * s.H * parts / s.cus;
+}
+
 // Cuts every sequence into equal splits, of at most as many tokens as make three workgroups for a compute unit, or one more for each than there are
 // sequences; but no more splits than the sequence has eights of steps, a step for each of eight wavefronts.  Returns the largest split count, or 0
 // (and no table) where the cut cannot cost less than `worth`.
@@ -383,11 +401,13 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
         c->ns = 1;
         c->split_tokens = split_tokens_for(s, 1, max_len);
         c->use_table = !uniform && !empty && s.B <= kMaxTableSeqs && (long long)s.B * s.H * c->subs > s.cus;
-        if (c->use_table)
+        if (c->use_table) {
             for (int b = 0; b <= kMaxTableSeqs; ++b) {
                 c->tab.first[b] = std::min(b, s.B);
                 if (b < s.B) c->tab.tokens[b] = c->split_tokens;
             }
+            c->use_table = table_pays(s, c->subs, lens, c->tab, s.B > 64 ? 7e3 : 3.5e3);
+        }
     } else if (replan) {
         const int cap = (int)std::min<size_t>(replan_cap(max_len), ws_bytes / per_split);
         c->ns = plan_splits(s, group_parts(G), lens, 0, cap, &c->use_table, &c->tab, &c->split_tokens);
@@ -415,6 +435,12 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
                 c->ns = most;
                 ordered = fine_ordered;
                 if (ordered) std::copy(order, order + s.B, c->order);
+            } else if (s.B > kPlanTableSeqs) {
+                // Without a table where few workgroups of the whole grid would have no tokens, and either its order does not pay or there is none.  With several
+                // splits each, the remainders of all sequences would fall to the same XCDs (70 of 300-700 tokens, 4 x 4 x 128: table 20.4, none 24.3).
+                const long long n = c->tab.first[s.B];
+                if (4LL * c->ns * s.B <= 5 * n)
+                    c->use_table = c->ns == 1 ? table_pays(s, c->subs, lens, c->tab, s.D >= 256 ? 20e3 : 8e3) : n * s.H * c->subs > s.cus;
             }
         }
     }

@@ -126,6 +126,23 @@ def test_a_finer_cut_has_a_step_for_every_wavefront(harness):
         assert all(nb <= -(-n // (256 if D == 64 else 128)) for n, nb in zip(lens, c["splits"]))
 
 
+def test_a_table_is_made_where_its_order_saves_more_than_its_lookups(harness):
+    """The cuts that need none (whole sequences, and one split length for more than 64) have one where lengths differ by much, or where there are several splits
+    each and more than compute units; none where a compute unit has many workgroups for that or all are about as long, nor where sequences are fewer
+    than compute units, equal, or empty ones are to be written."""
+    rnd = random.Random(3)
+    ragged = lambda B, lo, hi: [rnd.randint(lo, hi) for _ in range(B)]
+    whole = _cut(harness, [(32, 1, 128, ragged(40, 20, 250), 0, -1), (8, 4, 128, ragged(128, 20, 250), 0, -1), (32, 1, 128, ragged(64, 20, 250), 0, -1),
+                           (32, 1, 128, ragged(40, 10, 60), 0, -1), (3, 4, 64, ragged(128, 20, 100), 0, -1), (32, 4, 128, ragged(128, 20, 250), 0, -1),
+                           (32, 1, 128, ragged(7, 20, 250), 0, -1), (32, 1, 128, [200] * 40, 0, -1), (32, 1, 128, ragged(40, 20, 250) + [0], 0, -1)])
+    assert all(c["ns"] == 1 for c in whole)
+    assert [c["table"] for c in whole] == [1, 1, 1, 0, 0, 0, 0, 0, 0]
+    cut = _cut(harness, [(8, 4, 128, ragged(80, 300, 2000), 0, -1), (16, 2, 128, ragged(80, 130, 400), 0, -1), (1, 4, 128, [200] * 99 + [30000], 0, -1),
+                         (4, 4, 128, ragged(70, 300, 700), 0, -1), (32, 1, 64, ragged(128, 400, 700), 0, -1), (1, 4, 64, ragged(65, 513, 600), 0, -1),
+                         (16, 4, 256, ragged(66, 130, 300), 0, -1)])
+    assert [c["table"] for c in cut] == [1, 1, 1, 1, 0, 0, 0]
+
+
 def test_the_order_of_the_grid_holds_every_sequence(tmp_path):
     """Every sequence is in the order once; where the longest come first, the splits' sizes fall along it."""
     src = tmp_path / "order.cpp"
