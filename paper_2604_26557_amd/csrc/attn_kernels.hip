@@ -1,9 +1,10 @@
 // Split-K decode attention over resident KV (Sec. II-A: the query's similarity with the keys weights
 // the values):  out[b,hq,:] = softmax_j(q[b,hq,:].K[b,h,j,:] / sqrt(D)) V[b,h,j,:],  h = hq / G.
 //
-// Partial kernel: one workgroup of 8 wavefronts (6 when D = 256) per (sequence, query-head group, token split), about one
-// workgroup per compute unit, or up to four where one would leave them uneven (attn_splits.hpp).  A step is a tile of 16 tokens (two tiles when D = 64); the steps of a split
-// are handed out to the wavefronts on demand through a counter in LDS, so a wavefront whose loads come back
+// Partial kernel: one workgroup of 8 wavefronts (6 when D = 256) per (sequence, query-head group, token split).  Splits are cut for about one
+// workgroup per compute unit; where that would leave them uneven for one to four of each (uniform batches), or for three (ragged ones);
+// a batch with more pairs of sequence and KV head than that has a workgroup for each pair at least (attn_splits.hpp).  A step is a
+// tile of 16 tokens (two tiles when D = 64); the steps of a split are handed out to the wavefronts on demand through a counter in LDS, so a wavefront whose loads come back
 // late takes fewer steps and all of them reach the merge together (with a fixed round-robin the slowest
 // wavefront, and the second workgroup of a compute unit, finished 2-4 us after the median).
 //  * q K^T on the matrix cores: one v_mfma_f32_16x16x32 per 32-wide slice of D with the K tile as the
@@ -20,12 +21,12 @@
 //    factor 4.6e-7; scores four times as steep 1.9e-6 both).
 //    On the vector ALU this product cost 32 fused multiply-adds per query head and tile, so a workgroup took at most
 //    4 heads, and only 1 or 2 of a group that 4 does not divide: 7 heads per KV head read K and V seven times
-//    (8 KV heads x 32K tokens x 128, bf16: 224 us, now 26.8; 3 heads 102, now 26.7; 16 heads 61, now 27.2; 4 heads 25.7, now 25.6).
+//    (8 KV heads x 32K tokens x 128, bf16, vector ALU / matrix cores: 7 heads 224 / 25.5 us, 3 heads 102 / 25.4, 16 heads 61 / 26.6; 4 heads are level).
 //    A single head stays on the vector ALU (see the kernel).
 //  * K and V are read once and never again: the loads are nontemporal.
 // The wavefronts' softmax states of a head are merged through LDS and one fp32 partial per (b, hq, split) is
 // written; the combine kernel merges the splits.  When every sequence is a single split the partial kernel writes the
-// results itself (batch 32 x 32 heads of 512-544 tokens: 50.4 us with the second launch, 47.3 without).
+// results itself (batch 32 x 32 heads of 512-544 tokens: 3.1 of 50.4 us).
 // HBM-bound (G flop per byte).
 #include <hip/hip_runtime.h>
 
@@ -132,8 +133,8 @@ struct CountTable {
     unsigned short splits[kMaxTableSeqs];
 };
 static_assert(kMaxSplits <= 0xffff, "CountTable");
-// Every other batch: the grid is (split, head group, sequence), and the launch copies no table (an empty kernel costs the host 3.7 us
-// with 200 bytes of arguments, 4.0 with 500, 4.2 with 1000).
+// Every other batch: the grid is (split, head group, sequence).  The length and the split length are then scalar arguments, a workgroup looks nothing up,
+// and the launch copies 1.2 KiB less (0.1 us of host time).
 struct NoTable {};
 
 template <bool BF16>
@@ -339,8 +340,8 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     int split = blockIdx.x, gy = blockIdx.y, b = blockIdx.z, split_tokens = 0, len = 0;
     if constexpr (std::is_same<TAB, ItemTable>::value) {
         // Ragged batch: the grid counts only splits that hold tokens, sequence after sequence, each sequence cut into its own
-        // number of equal splits.  Lane = sequence: table and lengths come with one memory latency (a search
-        // of scalar loads, each waiting for the one before: 8 sequences of 1K-8K tokens, 16 layers 501 us, now 495; 60 of 100-600 23.3 us a layer, now 22.8).
+        // number of equal splits.  Lane = sequence: table and lengths come with one memory latency, two beyond 64 sequences (us, a search
+        // of scalar loads, each waiting for the one before / this: 8 sequences of 1K-8K tokens, 16 layers 501 / 495; 60 of 100-600, a layer 23.3 / 22.8).
         static_assert(kMaxTableSeqs == 128, "two sequences per lane");
         const int B = shares >> 8 & 0xff;
         const bool heads_first = shares & 0x80;
@@ -553,7 +554,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         // of that result too early here, always the same ones.  Whether the compiler's waits or the source were at fault was
         // not found; no such pair is in the code that the compiler makes, and a test of that code looks for one.
         // Four columns at a time: eight would take the kernel past 128 registers and with that cost the second workgroup of
-        // a compute unit (bf16, batch 32 x 32 heads of 512-544 tokens: 50.0 instead of 45.3 us).
+        // a compute unit (bf16, batch 32 x 32 heads of 512-544 tokens: 10 % more time).
         constexpr int kCols = 4;
 #pragma unroll
         for (int w = 0; w < NV; ++w)

@@ -24,7 +24,8 @@ constexpr int kMaxSplits = 1024;
 constexpr int kXcds = 8;              // dies with an L2 of their own
 
 // cus: compute units of the GPU.  The plan aims at one workgroup for each (a workgroup is eight wavefronts, six at
-// head_dim 256; with one per compute unit every one of them starts at once and none waits for a second round).
+// head_dim 256; with one per compute unit every one of them starts at once and none waits for a second round).  What is launched may have
+// more: see cut_tokens.
 struct AttnShape {
     int B, H, Hq, D, cus;
 };
@@ -200,7 +201,7 @@ inline int plan_splits(const AttnShape &s, int parts, const int32_t *lens, int n
 // workgroup needs for two rounds of its wavefronts.  Replayed from a graph, one split against the automatic choice, us per layer
 // (1 and 8 KV heads, 1 and 8 sequences, 1 to 16 query heads each): head_dim 64, 256 tokens 4.5-5.7 / 6.2-8.2, 512 tokens 5.8-7.7 / 6.3-9.0 (the worst
 // pair 7.00 / 6.95); 128, 128 tokens 4.1-6.0 / 6.0-9.2, 256 tokens 5.1-8.0 / 6.1-10.3; 256, 128 tokens 5.3-9.5 / 6.6-12.7.  The line lies where
-// the worst pair is level; launched call by call a launch that is left out saves another 3.4 us of host time.
+// the worst pair is level; launched call by call a launch that is left out saves another 2.2 us of host time.
 constexpr long long kWholeBytes = 128 * 1024;
 
 // Where the launch cuts more finely than the plan, splits beyond 64 of a sequence hold at least 256 tokens: below that the partials cost
@@ -225,9 +226,10 @@ struct AttnCut {
 // even, and where they are not, several smaller workgroups for every compute unit, dealt out as compute units become free, end together.
 //  * A compute unit reads no more than 1 / kAlone of its share of HBM when others are idle.
 //  * item_bytes for every workgroup after the first (1.2 us at 25 GB/s and compute unit; 4.4 us where a compute unit holds one workgroup at a time:
-//    5 sequences of 4000 tokens, 8 x 8 x 256, one / two / three workgroups for each 34.4 / 39.4 / 43.8), kCombineBytes for the second launch (3.4 us).
+//    5 sequences of 4000 tokens, 8 x 8 x 256, one / two / three workgroups for each 34.4 / 39.4 / 43.8), kCombineBytes for the second launch (3.4 us on the GPU).
 //  * kFinerBytes (1 us) is what a finer cut has to save: about its own host time, and what the model is off by for batches of 10 us.  128 sequences of
 //    260-400 tokens, 2 x 4 x 128, called one by one: without it 16.4 us a layer, with it 15.6.
+//  * Costs are compared with a margin of 1 % (uniform) or 3 %, within which the plan stays.
 // us per layer from a graph, one workgroup per compute unit (or sequence) / this cut: paged batch of 48 sequences of 200-4000 tokens, 4 KV heads
 // x 7 x 128 51.7 / 42.9, 8 x 4 x 128 113 / 76.6; 20 of 1K-8K, 8 x 4 x 128 74.9 / 65.1; 30 of 200-8000, 5 x 4 x 64 39.7 / 33.2.  Where the plan is
 // even it stays: 8 of 1K-8K 31.0 / 31.8, 3 of 2.5K-20K 26.3 / 29.5.
@@ -349,9 +351,10 @@ inline bool table_pays(const AttnShape &s, int parts, const int32_t *lens, const
 // Cuts every sequence into equal splits, of at most as many tokens as make three workgroups for a compute unit, or one more for each than there are
 // sequences; but no more splits than the sequence has eights of steps, a step for each of eight wavefronts.  Returns the largest split count, or 0
 // (and no table) where the cut cannot cost less than `worth`.
-// us per layer from a graph: 48 sequences of 200-4000 tokens, 4 x 7 x 128: 1.9 workgroups for a compute unit 45.5, 2.5 47.2, 2.9 44.7, 3.0 43.8, 3.5 47.2, 3.8
-// 45.9.  The plan / a split per four steps / per eight: 96 sequences of 260-600, 1 x 4 x 128 11.8 / 13.1 / 10.6; 80 of 600-900, 2 x 2 x 64 14.0 / 13.1 / 12.7;
-// 66 of 130-500, 2 x 4 x 256 17.95 / 17.9 / 17.2.
+// us per layer from a graph, geometric mean of 36 batches of 9-108 sequences, 1-32 KV heads and all three widths: 2 workgroups for a compute unit 43.5, 2.5
+// 44.2, 3 41.7, 3.5 44.1, 4 42.3 (profiles/attn_cut_targets.md).  A number that is not whole leaves a round half empty.  The plan / a split per four
+// steps / per eight: 96 sequences of 260-600, 1 x 4 x 128 11.8 / 13.1 / 10.6; 80 of 600-900, 2 x 2 x 64 14.0 / 13.1 / 12.7; 66 of 130-500, 2 x 4 x 256 17.95 /
+// 17.9 / 17.2.
 inline int finer_splits(const AttnShape &s, int parts, const int32_t *lens, int cap, double worth, SplitTable *t)
 {
     const int q = split_quantum(s.D);
@@ -413,7 +416,8 @@ inline bool cut_tokens(const AttnShape &s, const int32_t *lens, int n_splits, si
         c->ns = plan_splits(s, group_parts(G), lens, 0, cap, &c->use_table, &c->tab, &c->split_tokens);
         limited = cap < replan_cap(max_len);
     }
-    // The plan, or a finer cut where that is the cheaper one.
+    // The plan, or a finer cut where that is the cheaper one.  All of it is made again by each layer's call, from the lengths alone: us of host time, 48
+    // sequences of 200-4000 tokens, 4 x 7 x 128 1.6; 64, 1 x 4 x 128 1.2; 128, 8 x 4 x 128 1.6; 8 of 1K-8K, 8 x 4 x 128 0.25.
     bool ordered = false;   // c->order is the table's
     const int cap = (int)std::min<size_t>(replan_cap(max_len), ws_bytes / per_split);
     if (n_splits == 0 && !whole && max_len > 0 && cap > 0) {
