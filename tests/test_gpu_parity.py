@@ -329,9 +329,10 @@ def test_decode_attention_16bit_output_and_short_lengths(case):
 @pytest.mark.parametrize("B", [64, 65, 130])
 @pytest.mark.parametrize("n_splits", [0, 5])
 def test_decode_attention_many_ragged_sequences(B, n_splits):
-    """Ragged batches at and beyond 64 sequences: up to 64 the grid holds only the splits with tokens (the owner
-    search uses one lane per sequence), beyond that the full (split, head group, sequence) grid runs and the
-    combine pass reads each sequence's own split count.  Some sequences are empty."""
+    """Ragged batches at and beyond 64 sequences: up to 64 the grid holds only the splits with tokens (a lane of the
+    lookup for each sequence).  Beyond that it does so where a table pays, with two sequences for each lane; otherwise, with a given
+    split count and beyond 128, the full (split, head group, sequence) grid runs and the combine pass forms each
+    sequence's own split count.  Some sequences are empty."""
     cfg = W.KVConfig(f"many{B}", 500 + B, 1, 2, 4, 64, B, W.F16, 512, 4, 2, W.PER_SEQ, W.BHSD, 0, len_range=(1, 900))
     lens = W.seq_lens(cfg)
     lens[3] = 0
@@ -353,12 +354,16 @@ def test_decode_attention_many_ragged_sequences(B, n_splits):
 # 32 KV heads: 8 sequences are one workgroup for each compute unit of 256
 @pytest.mark.parametrize("H,G,D,B,lo,hi,empty,layout", [
     (32, 1, 128, 9, 1, 1500, 0, W.BHSD),      # just over one workgroup per compute unit, longest first, cut more finely
-    (32, 2, 64, 128, 1, 40, 0, W.PAGED),      # whole sequences, the table's last entry, written without a second launch
+    (32, 2, 64, 128, 1, 40, 0, W.PAGED),      # whole sequences, written without a second launch; too short for a table to pay
     (32, 2, 64, 129, 1, 40, 0, W.BHSD),       # one sequence more than the table holds
     (16, 3, 128, 100, 20, 700, 3, W.PAGED),   # beyond 64 sequences, some without tokens
     (32, 4, 256, 8, 1, 1200, 1, W.PAGED),
     (32, 1, 64, 31, 300, 1300, 0, W.BHSD),
     (5, 17, 128, 70, 5, 900, 2, W.BHSD),      # two parts of a KV head's query heads: the grid stays in the batch's order
+    (8, 4, 128, 128, 20, 250, 0, W.PAGED),    # whole sequences in a table, its last entry, written without a second launch
+    (32, 1, 64, 100, 400, 700, 0, W.BHSD),    # beyond 64, one split each, nearly equal: no table, lengths from the device
+    (16, 4, 256, 66, 130, 300, 0, W.PAGED),   # the same at head_dim 256
+    (1, 4, 64, 65, 513, 600, 0, W.BHSD),      # beyond 64, several splits each without a table, fewer workgroups than compute units
 ])
 @pytest.mark.parametrize("n_splits", [0, 2])
 def test_decode_attention_more_workgroups_than_compute_units(H, G, D, B, lo, hi, empty, layout, n_splits):
@@ -376,6 +381,39 @@ def test_decode_attention_more_workgroups_than_compute_units(H, G, D, B, lo, hi,
     kv.kv_decode_attn(case.plan, case.view, 0, q.cuda(), out, kv.KV_OUT_F32, n_splits, ws)
     torch.cuda.synchronize()
     _attn_check(out, _reference_attention(case, case.k[0], case.v[0], q).float().numpy())
+
+
+@pytest.mark.parametrize("wide", ["sequence", "head", "token"])
+def test_decode_attention_strides_beyond_32_bits(wide):
+    """One stride of 2^32 + 3 16-byte vectors, which reaches the kernel in more than 32 bits, the others small: K and V are two places of one
+    allocation of 64 GiB.  With the upper bits lost the rows would be read from elsewhere in it, where other values lie."""
+    B, H, G, D, S = 2, 2, 4, 128, 2
+    far, apart = (1 << 35) + 24, 1 << 20   # elements
+    sb, sh, ss = {"sequence": (far, 4 * D, 2 * D), "head": (4 * D, far, 2 * D), "token": (8 * D, 2 * D, far)}[wide]
+    cfg = W.KVConfig("far", 77, 1, H, H * G, D, B, W.F16, 512, 4, 2, W.PER_SEQ, W.BHSD, 0, len_range=(S, S))
+    plan = kv.kv_layout_plan(1, H, H * G, D, [S] * B, kv.KV_F16, 512, 4, kv.KV_PER_SEQ, 0, kv.KV_UNBOUNDED, 0, kv.KV_UNBOUNDED)
+    buf = torch.empty(far + 2 * apart, dtype=torch.float16, device="cuda")
+    buf[:2 * apart] = 7.0   # where rows whose stride lost its upper bits would come from
+    k, v = (buf[i * apart:i * apart + far + apart].as_strided((B, H, S, D), (sb, sh, ss, 1)) for i in (0, 1))
+    cpu = [W.normal_tensor((B, H, S, D), torch.float16, 900 + i) for i in (0, 1)]
+    for dst, src in zip((k, v), cpu):
+        for b in range(B):
+            for h in range(H):
+                for t in range(S):
+                    dst[b, h, t].copy_(src[b, h, t])
+    q = W.query(cfg, 0, "cpu")
+    for lens, n_splits in (([S] * B, 0), ([S, 1], 0), ([S, 1], 2)):   # one length for all, lengths from the device, the table's grid
+        view = kv.bhsd_view([k], [v], lens, torch.tensor(lens, dtype=torch.int32, device="cuda"))
+        out = torch.full((B, H * G, D), float("nan"), dtype=torch.float32, device="cuda")
+        ws = torch.empty(kv.kv_decode_attn_workspace(plan, n_splits, S), dtype=torch.uint8, device="cuda")
+        kv.kv_decode_attn(plan, view, 0, q.cuda(), out, kv.KV_OUT_F32, n_splits, ws)
+        torch.cuda.synchronize()
+        for b in range(B):
+            kd, vd = (x[b, :, :lens[b]].double().repeat_interleave(G, 0) for x in cpu)   # [Hq, S, D]
+            p = torch.softmax((q[b].double()[:, None] * kd).sum(-1) / D ** 0.5, -1)
+            _attn_check(out[b], (p[:, :, None] * vd).sum(1).numpy())
+    del buf, k, v, dst
+    torch.cuda.empty_cache()
 
 
 # tokens: as many as one workgroup's wavefronts have preassigned (two steps each; above that they claim steps from a counter), and one more
