@@ -23,21 +23,23 @@ HBM_PEAK_GBPS = 8000.0  # MI355X published HBM3E bandwidth
 
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of `bench.py --leg kernels` on each
 # workload (profiles/pmc_traffic_<workload>.md), each counter scaled by what it reads for a plain device-to-device
-# copy of known size in the same run.  Valid only for the kernel sources they were taken with: the hash below
-# covers the two kernel files, and a mismatch reports traffic as null.
-PMC_TRAFFIC = {"sha": "5a30c3a7151c7f67",
-               "llama8b_32k": {"kv_layout_kernel<pack>": 268481248, "kv_layout_kernel<unpack>": 268481122, "kv_attn_partial_kernel+kv_attn_combine_kernel": 135567173},
-               "llama8b_4k": {"kv_layout_kernel<pack>": 268465507, "kv_layout_kernel<unpack>": 268601115, "kv_attn_partial_kernel+kv_attn_combine_kernel": 18131144},
-               "llama8b_ragged_paged": {"kv_layout_kernel<pack>": 282079834, "kv_layout_kernel<unpack>": 282056944, "kv_attn_partial_kernel+kv_attn_combine_kernel": 142708951},
-               "gemma7b_mha_8k": {"kv_layout_kernel<pack>": 536897641, "kv_layout_kernel<unpack>": 536884046, "kv_attn_partial_kernel+kv_attn_combine_kernel": 538131536}}
+# copy of known size in the same run.  Valid only for the sources they were taken with: the hash below covers the
+# two kernel files, what cuts and launches their work, and the compiler's flags; a mismatch reports traffic as null.
+PMC_TRAFFIC = {"sha": "d5719eab8b9a0057",
+               "llama8b_32k": {"kv_layout_kernel<pack>": 268458522, "kv_layout_kernel<unpack>": 268453175, "kv_attn_partial_kernel+kv_attn_combine_kernel": 135570378},
+               "llama8b_4k": {"kv_layout_kernel<pack>": 268468543, "kv_layout_kernel<unpack>": 268470696, "kv_attn_partial_kernel+kv_attn_combine_kernel": 18130210},
+               "llama8b_ragged_paged": {"kv_layout_kernel<pack>": 282074233, "kv_layout_kernel<unpack>": 282054877, "kv_attn_partial_kernel+kv_attn_combine_kernel": 142711564},
+               "gemma7b_mha_8k": {"kv_layout_kernel<pack>": 536895013, "kv_layout_kernel<unpack>": 536883851, "kv_attn_partial_kernel+kv_attn_combine_kernel": 538127460}}
 
 
 def kernel_sources_hash() -> str:
     import hashlib
+    from paper_2604_26557_amd.build import FLAGS
     h = hashlib.sha256()
-    for fn in ("layout_kernels.hip", "attn_kernels.hip"):
+    for fn in ("layout_kernels.hip", "attn_kernels.hip", "attn_splits.hpp", "launch.hpp"):
         with open(os.path.join(ROOT, "paper_2604_26557_amd", "csrc", fn), "rb") as f:
             h.update(f.read())
+    h.update(" ".join(f for f in FLAGS if not os.path.isabs(f)).encode())   # without this tree's own folders
     return h.hexdigest()[:16]
 
 
