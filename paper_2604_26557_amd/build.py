@@ -16,7 +16,8 @@ FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     # packed fp32 VALU forms stay off for all device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # leading scalar arguments of a kernel arrive in registers
+    # leading scalar arguments of a kernel arrive in registers (an internal option of LLVM's AMDGPU back end: a compiler without it
+    # stops with "Unknown command line argument"; without it the kernels load them from memory)
     "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
