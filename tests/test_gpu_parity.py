@@ -367,7 +367,7 @@ def test_decode_attention_many_ragged_sequences(B, n_splits):
 ])
 @pytest.mark.parametrize("n_splits", [0, 2])
 def test_decode_attention_more_workgroups_than_compute_units(H, G, D, B, lo, hi, empty, layout, n_splits):
-    """Ragged batches whose workgroups outnumber the compute units.  Every sequence and head is checked, so that a split given to the
+    """Ragged batches whose workgroups outnumber the compute units, or of more than 64 sequences.  Every sequence and head is checked, so that a split given to the
     wrong sequence, or to none, shows.  Bar: the file's."""
     cfg = W.KVConfig(f"crowd{B}", 1700 + B + D, 1, H, H * G, D, B, W.BF16 if G % 2 else W.F16, 512, 8, 2, W.PER_SEQ, layout, 0, len_range=(lo, hi))
     lens = W.seq_lens(cfg)
