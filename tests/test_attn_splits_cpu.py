@@ -238,7 +238,7 @@ def test_the_cut_of_a_ragged_batch_is_the_plainly_written_one(tmp_path):
 
 def test_the_cut_of_a_ragged_batch_costs_the_host_little(tmp_path):
     """Every layer's call makes the cut, so it must not weigh beside a launch.  The yardstick is a comparison sort of 128 keys in the same process
-    (0.8 us where these cuts take 0.6-2.3); a cut that sorts its tables each time takes six to eight of those, one that gives out
+    (0.8 us where these cuts take 0.5-2.8); a cut that sorts its tables each time takes six to eight of those, one that gives out
     256 workgroups one by one over 64 sequences more than twenty."""
     out = subprocess.run([_cut_harness(tmp_path, "-O3"), "time"], capture_output=True, text=True, check=True).stdout.splitlines()
     ratios = {line.rsplit(" ", 1)[0]: float(line.rsplit(" ", 1)[1]) for line in out}
