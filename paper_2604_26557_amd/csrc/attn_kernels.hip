@@ -7,12 +7,18 @@
 // tile of 16 tokens (two tiles when D = 64); the steps of a split are handed out to the wavefronts on demand through a counter in LDS, so a wavefront whose loads come back
 // late takes fewer steps and all of them reach the merge together (with a fixed round-robin the slowest
 // wavefront, and the second workgroup of a compute unit, finished 2-4 us after the median).
-//  * q K^T on the matrix cores: one v_mfma_f32_16x16x32 per 32-wide slice of D with the K tile as the
-//    16 x 32 A operand (lane = token row, 16 contiguous bytes of it) and the query heads of the group
-//    as the columns of B.  A 16-byte global load is exactly one operand register set, so K never passes
-//    through LDS, and no cross-lane reduction over D is needed.
-//  * The 16 x 16 fp32 result leaves lane (column n, row group tg) with the scores of tokens 4tg..4tg+3 for query
-//    head n, which is the layout of the B operand of V^T P: probabilities never leave their lane.
+//  * q K^T on the matrix cores: v_mfma_f32_16x16x32 with K as the 16 x 32 A operand (a lane holds 16 contiguous bytes of a
+//    row) and the query heads of the group as the columns of B.  A 16-byte global load is exactly one operand register set, so K
+//    never passes through LDS.
+//    A load of K takes whole 128-byte lines, of 8 rows: two neighbouring rows of the operand hold the two halves of a line of one
+//    token, and the columns of a head the two halves of its query in turn (beyond 8 heads: a product for each half), so a score is two
+//    elements of the result.  With a row of the operand for each token a load took 64 bytes of 16 rows, and the other half of each line was a request of
+//    its own to L2: reading alone 6.12 against 6.53 TB/s at head_dim 64 and 6.47 / 6.57 at 128, with two workgroups per compute unit 6.16 / 6.40
+//    (200 MB per launch).  us per layer from a graph, 16 rows / 8 rows: 16 KV heads x 4 x 64, 7 sequences of 9000 49.6 / 45.2, paged of
+//    6283-11718 57.6 / 52.6; 8 x 4 x 128, 8 of 1K-8K paged 31.5 / 30.0, 32K 26.7 / 26.0, 32 x 1, batch 32 of 528 46.4 / 45.0; 8 x 16 x 128, 12 of 2000
+//    26.2 / 24.2; 5 x 5 x 256, 43 of 2354 97.4 / 87.9, 16 x 4, 4 of 8192 86.9 / 86.5 (paged fp16 85.7 / 86.6); 4K and shorter single sequences the same.
+//  * The result leaves lane (column n, row group tg) with the scores of four tokens (tg, 4 + tg, 8 + tg, 12 + tg) for the column's query
+//    head, which is the layout of the B operand of V^T P: probabilities never leave their lane.
 //  * V^T P on the matrix cores as well: the 16 lanes of a row group load the V rows of their own 4 tokens, 16 bytes
 //    per lane; byte permutes gather the 4 tokens of each of the lane's 8 columns, and that is the A operand.
 //    A probability enters in parts, one product each: three bf16 terms, whose sum is the 32-bit value exactly, or two fp16
@@ -331,6 +337,8 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     constexpr bool VALU = NH == 1;
     constexpr int RG = VALU ? 4 : 1;         // states of a wavefront that meet in LDS: one per row group, or one
     constexpr int kCopies = VALU ? 1 : 16 / NH;   // matrix columns that carry the same query head
+    constexpr bool HALVES = NH <= 8;         // a column holds one half of every 128-byte line of its query head
+    constexpr int NQ = HALVES ? NJ / 2 : NJ;
     constexpr bool PAGED = LAYOUT != kStrided, TILE_ID = LAYOUT == kPagedTiles;
     typedef unsigned vload_t __attribute__((ext_vector_type(E / 2)));
 
@@ -372,16 +380,17 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     const int h = subs == 1 ? gy : gy / subs, g0 = (gy - h * subs) * gt;
     const int hq0 = h * G + g0;
     const int ng = min(gt, G - g0);   // query heads of this workgroup
-    int n = lane & 15;          // MFMA column (query head n / kCopies; columns past the last head repeat it); also the K row this lane loads
-    int tg = lane >> 4;         // row group: owns tokens 4tg..4tg+3 of a tile; also the D sub-slice of the operands
+    int n = lane & 15;          // MFMA column (query head n / kCopies; columns past the last head repeat it); also the pair of K rows this lane loads from
+    int tg = lane >> 4;         // row group: owns tokens tg, 4 + tg, 8 + tg and 12 + tg of a tile; also the D sub-slice of the operands
 
     const int t_begin = min(len, split * split_tokens);
     const int t_end = min(len, t_begin + split_tokens);
 
-    // B operand: column n carries query head n; this lane holds elements 32j + 8tg .. +7 of it.
-    u32x4 qv[NJ];
+    // B operand: column n carries query head n / kCopies; this lane holds elements 32j + 8tg .. +7 of it, or (HALVES) those of its half of line j.
+    u32x4 qv[NQ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) qv[j] = q[((long long)b * Hq + hq0 + (VALU ? 0 : min(n / kCopies, ng - 1))) * DV + 4 * j + tg];
+    for (int j = 0; j < NQ; ++j)
+        qv[j] = q[((long long)b * Hq + hq0 + (VALU ? 0 : min(n / kCopies, ng - 1))) * DV + (HALVES ? 8 * j + 4 * (n & 1) : 4 * j) + tg];
 
     float m = kEmptyMax, l = 0.f;     // reference (the same in the four row groups) and this row group's sum
     f32x4 acc[NV][E];                 // element (w, e)[i]: column d = w * 16E + (4tg + i) * E + e of this lane's query head
@@ -416,23 +425,32 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         }
         return head_off + (long long)row * ss;
     };
+    // Which of a tile's tokens are whose: row group tg has tokens tg, 4 + tg, 8 + tg and 12 + tg, so that a load of V takes four rows that lie side by side.
+    // K registers j = 2c and 2c + 1 hold line c (128 bytes) of one of the first and of one of the last eight tokens, the even lane of a pair the
+    // first half of it and the odd lane the second.
+    auto k_row = [&](int j) -> int { return 8 * (j & 1) + 4 * ((n >> 1) & 1) + (n >> 2); };
+    auto k_vec = [&](int j) -> int { return 8 * (j >> 1) + 4 * (n & 1) + tg; };
     // Paged layout: the block ids of one step's rows are fetched ahead, so that the table lookup is off the load chain.
     // When the block size is a multiple of the tile a tile lies inside one block (kPagedTiles): one lookup per tile, the
-    // same for the whole wavefront and so a scalar load.  Otherwise a lane looks up its K row and the 4 tokens of
+    // same for the whole wavefront and so a scalar load.  Otherwise a lane looks up its two K rows and the 4 tokens of
     // its row group.
-    struct Ids { int k[TI], t[TI][TILE_ID ? 1 : 4]; };
+    struct Ids { int k[TI][TILE_ID ? 1 : 2], t[TI][TILE_ID ? 1 : 4]; };
     auto fetch_ids = [&](int Tw, Ids &ids) {
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) {
             const int T0 = Tw + kTile * ti;
             const int fb = T0 < t_end ? T0 : Tw;   // a valid row of this tile's block (of the step's first tile when the tile is empty)
             if (TILE_ID) {
-                ids.k[ti] = ids.t[ti][0] = tbl[block_of(fb)];
+                ids.k[ti][0] = ids.t[ti][0] = tbl[block_of(fb)];
             } else {
-                ids.k[ti] = tbl[block_of((T0 + n < t_end) ? T0 + n : fb)];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int tok = T0 + k_row(i);
+                    ids.k[ti][i] = tbl[block_of(tok < t_end ? tok : fb)];
+                }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int tok = T0 + 4 * tg + i;
+                    const int tok = T0 + 4 * i + tg;
                     ids.t[ti][i] = tbl[block_of(tok < t_end ? tok : fb)];
                 }
             }
@@ -445,8 +463,19 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         vload_t v[TI][4][NV];
         bool ok[TI][4];
     };
+    // Strided layout: head h starts with step h % 8 of a long split, or of one of just 8 steps.  All workgroups begin together and read at one pace, and where the strides are powers
+    // of two the same step of every head lies at the same place modulo them.  us per layer, 8 x 4 x 128, all heads from step 0 / from step h: 32K tokens 25.4 / 25.0,
+    // 16K 16.0 / 15.7, 2 sequences of 16K 25.9 / 25.6, 16 query heads each 32K 27.2 / 26.9, 4K 8.34 / 8.27, 30001 tokens 24.4 / 24.4.  (Other splits of up to two steps for each
+    // wavefront lose by it: 4 sequences of 4096 15.9 / 16.6, 32 heads, 2 of 4096 25.7 / 27.0; any step of the split, by a hash: 16 x 1 x 256, 4 of 8192 84.8 / 92.2.)
+    const int n_steps = (t_end - t_begin + kStepTok - 1) / kStepTok;
+    constexpr int kTurn = 8;
+    const int first_step = !PAGED && (n_steps > 2 * kWaves || n_steps == kTurn) ? (h + b) % kTurn : 0;
+    auto step_row = [&](int st) -> int {
+        const int s = st + first_step;
+        return t_begin + (PAGED || s < n_steps ? s : s - n_steps) * kStepTok;
+    };
     auto load_step = [&](int st, const Ids &ids, Step &x) {
-        const int Tw = t_begin + st * kStepTok;
+        const int Tw = step_row(st);
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) {
             const int T0 = Tw + kTile * ti;
@@ -454,27 +483,31 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
             const int rem = t_end - T0;               // rows past the end re-read row R0; masked below
             if constexpr (LAYOUT != kPagedRows) {
                 // one base per tile, the same for the wavefront; the lane's part is a row number times the row length
-                const long long tb = row_base(R0, PAGED ? ids.k[ti] : 0);
+                const long long tb = row_base(R0, PAGED ? ids.k[ti][0] : 0);
                 const unsigned long long row_vecs = PAGED ? DV : ss;
-                const bool in_pool = !PAGED || (unsigned)ids.k[ti] < (unsigned)p.n_pool;
-                const u32x4 *kp = K + tb + (unsigned)(n < rem ? n : 0) * row_vecs;
+                const bool in_pool = !PAGED || (unsigned)ids.k[ti][0] < (unsigned)p.n_pool;
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) x.k[ti][j] = __builtin_nontemporal_load(kp + 4 * j + tg);
+                for (int j = 0; j < NJ; ++j) {
+                    const int r = k_row(j);
+                    x.k[ti][j] = __builtin_nontemporal_load(K + tb + (unsigned)(r < rem ? r : 0) * row_vecs + k_vec(j));
+                }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int r = 4 * tg + i;
+                    const int r = 4 * i + tg;
                     x.ok[ti][i] = in_pool && r < rem;
                     const vload_t *vp = (const vload_t *)(V + tb + (unsigned)(r < rem ? r : 0) * row_vecs) + n;
 #pragma unroll
                     for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load(vp + w * 16);
                 }
             } else {
-                const u32x4 *kp = K + row_base(n < rem ? T0 + n : R0, ids.k[ti]);
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) x.k[ti][j] = __builtin_nontemporal_load(kp + 4 * j + tg);
+                for (int j = 0; j < NJ; ++j) {
+                    const int r = k_row(j);
+                    x.k[ti][j] = __builtin_nontemporal_load(K + row_base(r < rem ? T0 + r : R0, ids.k[ti][j & 1]) + k_vec(j));
+                }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int r = 4 * tg + i, blk = ids.t[ti][i];
+                    const int r = 4 * i + tg, blk = ids.t[ti][i];
                     x.ok[ti][i] = r < rem && (unsigned)blk < (unsigned)p.n_pool;
                     const vload_t *vp = (const vload_t *)(V + row_base(r < rem ? T0 + r : R0, blk)) + n;
 #pragma unroll
@@ -483,6 +516,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
             }
         }
     };
+    const unsigned odd = -(unsigned)(n & 1);   // a mask and not a condition, of which the compiler makes three selects by the element's number
     auto attend = [&](const Step &x) {
         // ---- scores of 16 tokens x 16 columns per tile on the matrix cores
         f32x4 sc[TI];
@@ -490,8 +524,25 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) {
             f32x4 c = {0.f, 0.f, 0.f, 0.f};
+            // Rows 4tg + 2i and 4tg + 2i + 1 of u[k] are the first and the second half of token 8k + 4i + tg, each against the columns' halves of the query.
+            if constexpr (HALVES) {
+                f32x4 u[2] = {c, c};
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) c = mfma_16x16x32<BF16>(x.k[ti][j], qv[j], c);
+                for (int j = 0; j < NJ; ++j) u[j & 1] = mfma_16x16x32<BF16>(x.k[ti][j], qv[j >> 1], u[j & 1]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float half = __uint_as_float((__float_as_uint(u[i >> 1][2 * (i & 1) + 1]) & odd) | (__float_as_uint(u[i >> 1][2 * (i & 1)]) & ~odd));
+                    c[i] = half + dpp_mov<0xB1>(half);   // quad_perm [1,0,3,2]: the other half, from the neighbouring column
+                }
+            } else {
+                f32x4 u[2][2] = {{c, c}, {c, c}};
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) u[j & 1][f] = mfma_16x16x32<BF16>(x.k[ti][j], qv[(j & ~1) + f], u[j & 1][f]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[i] = u[i >> 1][0][2 * (i & 1)] + u[i >> 1][1][2 * (i & 1) + 1];
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 sc[ti][i] = x.ok[ti][i] ? c[i] : -INFINITY;
@@ -598,7 +649,6 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     // one after that is claimed (one LDS atomic by lane 0) right after the current step's loads are issued,
     // so neither the atomic nor, for the paged layout, the block-table lookup sits on the load chain.
     __shared__ int sh_next;
-    const int n_steps = (t_end - t_begin + kStepTok - 1) / kStepTok;
     // steps 0 .. 2*kWaves-1 are preassigned: w and w + kWaves to wavefront w; a split that has no more needs no counter and
     // no barrier in front of its first loads
     const bool claims = n_steps > 2 * kWaves;
@@ -608,7 +658,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     }
     int s_cur = wave, s_nxt = wave + kWaves;
     Ids ids{};
-    if (PAGED && s_cur < n_steps) fetch_ids(t_begin + s_cur * kStepTok, ids);
+    if (PAGED && s_cur < n_steps) fetch_ids(step_row(s_cur), ids);
     while (s_cur < n_steps) {
         Step x;
         load_step(s_cur, ids, x);
@@ -617,7 +667,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
             if (lane == 0) s_new = atomicAdd(&sh_next, 1);
             s_new = __builtin_amdgcn_readfirstlane(s_new);
         }
-        if (PAGED && s_nxt < n_steps) fetch_ids(t_begin + s_nxt * kStepTok, ids);
+        if (PAGED && s_nxt < n_steps) fetch_ids(step_row(s_nxt), ids);
         attend(x);
         s_cur = s_nxt;
         s_nxt = s_new;
