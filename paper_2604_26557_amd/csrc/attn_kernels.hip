@@ -90,6 +90,8 @@ struct PackedStrides {
     unsigned long long ss_sh;
     int sb, high;
 };
+// Further bits of `high`: sequences start at seq_off; a token row's address needs more than 32 bits within a tile.
+constexpr int kSeqOff = 1 << 24, kWideRows = 1 << 25;
 constexpr PackedStrides pack_strides(Strides s)
 {
     return {(s.ss & 0xffffffffull) | s.sh << 32, (int)(unsigned)s.sb,
@@ -377,7 +379,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         len = (int)(lens_arg >> 32);
         if (len < 0) len = min(p.seq_lens[b], p.max_len);
     }
-    const int h = subs == 1 ? gy : gy / subs, g0 = (gy - h * subs) * gt;
+    const int h = __builtin_expect(subs == 1, 1) ? gy : gy / subs, g0 = (gy - h * subs) * gt;
     const int hq0 = h * G + g0;
     const int ng = min(gt, G - g0);   // query heads of this workgroup
     int n = lane & 15;          // MFMA column (query head n / kCopies; columns past the last head repeat it); also the pair of K rows this lane loads from
@@ -411,7 +413,13 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     } else {
         const Strides st = unpack_strides({addr_arg, addr2, addr3});
         ss = st.ss;
-        head_off = (p.seq_off ? p.seq_off[b] / 8 : (long long)(b * st.sb)) + (long long)(h * st.sh);
+        long long seq_start = (long long)(b * st.sb);
+        if (__builtin_expect(addr3 & kSeqOff, 0)) {
+            int here = 0;
+            asm volatile("" : "+s"(here));   // or the pointer is loaded, and waited for, ahead of the first addresses of every launch
+            seq_start = (&p.seq_off)[here][b] / 8;
+        }
+        head_off = seq_start + (long long)(h * st.sh);
     }
     const int bt = addr3, bt_shift = (bt & (bt - 1)) == 0 ? __builtin_ctz((unsigned)bt) : -1;   // paged
     auto block_of = [&](int row) -> int { return bt_shift >= 0 ? (row >> bt_shift) : (row / bt); };
@@ -463,41 +471,52 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         vload_t v[TI][4][NV];
         bool ok[TI][4];
     };
+    const bool wide = !PAGED && (addr3 & kWideRows);   // the loop's 32-bit offsets do not reach: all of the split is left to the second pass
     // Strided layout: head h starts with step h % 8 of a long split, or of one of just 8 steps.  All workgroups begin together and read at one pace, and where the strides are powers
     // of two the same step of every head lies at the same place modulo them.  us per layer, 8 x 4 x 128, all heads from step 0 / from step h: 32K tokens 25.4 / 25.0,
     // 16K 16.0 / 15.7, 2 sequences of 16K 25.9 / 25.6, 16 query heads each 32K 27.2 / 26.9, 4K 8.34 / 8.27, 30001 tokens 24.4 / 24.4.  (Other splits of up to two steps for each
     // wavefront lose by it: 4 sequences of 4096 15.9 / 16.6, 32 heads, 2 of 4096 25.7 / 27.0; any step of the split, by a hash: 16 x 1 x 256, 4 of 8192 84.8 / 92.2.)
-    const int n_steps = (t_end - t_begin + kStepTok - 1) / kStepTok;
+    const int n_steps = wide ? 0 : (t_end - t_begin + kStepTok - 1) / kStepTok;
     constexpr int kTurn = 8;
     const int first_step = !PAGED && (n_steps > 2 * kWaves || n_steps == kTurn) ? (h + b) % kTurn : 0;
     auto step_row = [&](int st) -> int {
         const int s = st + first_step;
         return t_begin + (PAGED || s < n_steps ? s : s - n_steps) * kStepTok;
     };
+    // A lane's part of an address, a row number times the row length, is the same in every step and has 32 bits (rows of up to 256 MiB); what changes from tile to
+    // tile is the wavefront's part, in scalar registers.  Rows past the end re-read the tile's first one, and are masked.  us per layer from a graph, 64-bit
+    // addresses in every lane and the pointer to the sequences' starts waited for / this: 2 x 2 x 64, 256 tokens 4.18 / 3.77; 2 x 6 x 64, 2 of 1K-1.6K 6.65 / 6.48; paged
+    // 8 x 4 x 128, 8 of 1K-8K 29.7 / 29.1; the others within 1 %.  (Both kinds of address in the loop: 8 x 4 x 128, 4K 8.50, with this one alone 8.29.)
+    const unsigned row_bytes = PAGED ? 16u * DV : (unsigned)ss * 16u;
+    const unsigned k_first = 16u * k_vec(0), v_first = 2u * E * n;
+    unsigned k_off[2], v_off[4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) k_off[i] = k_first + k_row(i) * row_bytes;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v_off[i] = v_first + (4 * i + tg) * row_bytes;
     auto load_step = [&](int st, const Ids &ids, Step &x) {
         const int Tw = step_row(st);
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) {
             const int T0 = Tw + kTile * ti;
             const int R0 = T0 < t_end ? T0 : Tw;      // the tile's first row (an empty tile: the step's)
-            const int rem = t_end - T0;               // rows past the end re-read row R0; masked below
+            const int rem = t_end - T0;
             if constexpr (LAYOUT != kPagedRows) {
-                // one base per tile, the same for the wavefront; the lane's part is a row number times the row length
                 const long long tb = row_base(R0, PAGED ? ids.k[ti][0] : 0);
-                const unsigned long long row_vecs = PAGED ? DV : ss;
                 const bool in_pool = !PAGED || (unsigned)ids.k[ti][0] < (unsigned)p.n_pool;
+                const char *const kt = (const char *)(K + tb), *const vt = (const char *)(V + tb);
+                unsigned ko[2];
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const int r = k_row(j);
-                    x.k[ti][j] = __builtin_nontemporal_load(K + tb + (unsigned)(r < rem ? r : 0) * row_vecs + k_vec(j));
-                }
+                for (int i = 0; i < 2; ++i) ko[i] = k_row(0) < rem - 8 * i ? k_off[i] : k_first;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) x.k[ti][j] = __builtin_nontemporal_load((const u32x4 *)(kt + 128 * (j >> 1) + ko[j & 1]));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int r = 4 * i + tg;
-                    x.ok[ti][i] = in_pool && r < rem;
-                    const vload_t *vp = (const vload_t *)(V + tb + (unsigned)(r < rem ? r : 0) * row_vecs) + n;
+                    const bool in = tg < rem - 4 * i;
+                    x.ok[ti][i] = in_pool && in;
+                    const unsigned vo = in ? v_off[i] : v_first;
 #pragma unroll
-                    for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load(vp + w * 16);
+                    for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load((const vload_t *)(vt + 32 * E * w + vo));
                 }
             } else {
 #pragma unroll
@@ -684,7 +703,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     __shared__ __attribute__((aligned(16))) float sh_acc[kWaves][RG][NH][DP];
     __shared__ f32x2 sh_ml[kWaves][RG * NH];
     auto far = [](float ref) { return fabsf(ref) > kFusedRef && ref != kEmptyMax; };
-    bool again;   // some accumulated value is not finite, or some reference beyond kFusedRef: the split is done again
+    bool again;   // some accumulated value is not finite, some reference beyond kFusedRef, or `wide`: the split is done again
     f32x2 state = {kEmptyMax, 0.f};   // VALU: lane = state
     if constexpr (VALU) {
         // position ((2w + e4) * 16 + n) * 4 + k of a state holds column (w * 16 + n) * 8 + 4 * e4 + k: contiguous 16-byte stores
@@ -703,7 +722,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         if (n == 0) sh_ml[wave][tg] = f32x2{bad ? INFINITY : m, l};
         __syncthreads();
         if (lane < RG * kWaves) state = (&sh_ml[0][0])[lane];
-        again = __any(far(state[0]));
+        again = __any((int)wide | (int)far(state[0]));
     } else {
         // A head's columns of the matrix hold the same sums: each of them writes its share.  (Written by one of four, with three of four
         // lanes idle, the stores took four times as many LDS cycles, in front of the barrier.)
@@ -734,13 +753,13 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
             const int j = j0 + lane;
             if (j < kWaves * NH && j % NH < ng) some = some || far((&sh_ml[0][0])[j][0]);
         }
-        again = __any(some);
+        again = __any((int)wide | (int)some);
     }
 
     auto head_out = [&](int g) { return ((long long)b * Hq + hq0 + g) * D; };
     auto head_part = [&](int g) { return ((long long)b * Hq + hq0 + g) * p.n_splits + split; };
-    if (again) {
-        // V (or K, or q) holds infinities or NaNs, or scores are beyond kFusedRef.  The terms of a probability meet an infinite
+    if (__builtin_expect(again, 0)) {   // out of the way of what every launch runs through
+        // V (or K, or q) holds infinities or NaNs, or scores are beyond kFusedRef (or rows are too far apart for the loop).  The terms of a probability meet an infinite
         // V one by one, and one that is zero or negative turns it into a NaN, so the split is done again with the
         // probability as one factor, and with exponents from score differences: a wavefront takes every kWaves-th run of 8
         // tokens, whose loads are in flight together, for 4 heads at a time, and leaves its states in their places in LDS.
@@ -1009,7 +1028,7 @@ void launch_partial(dim3 grid, hipStream_t st, const AttnHead &c, const AttnPara
     if (!c.table) {
         const PackedStrides ps = pack_strides(c.strides);
         (void)kvb::launch_kernel(kv_attn_partial_kernel<D, NH, BF16, kStrided, TAB>, grid, block, st, c.K, c.V, c.q, lens, heads, shares,
-                           ps.ss_sh, ps.sb, ps.high, a, t);
+                           ps.ss_sh, ps.sb, ps.high | (a.seq_off ? kSeqOff : 0) | (c.strides.ss >= 1u << 24 ? kWideRows : 0), a, t);
     } else if (c.bt % kTile == 0) {
         (void)kvb::launch_kernel(kv_attn_partial_kernel<D, NH, BF16, kPagedTiles, TAB>, grid, block, st, c.K, c.V, c.q, lens, heads, shares,
                            c.table, c.max_blocks, c.bt, a, t);

@@ -416,6 +416,34 @@ def test_decode_attention_strides_beyond_32_bits(wide):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("row_vecs", [(1 << 24) - 1, 1 << 24])
+@pytest.mark.parametrize("D,G", [(64, 2), (128, 1), (128, 16), (256, 4)])
+def test_decode_attention_rows_as_far_apart_as_32_bit_offsets_reach(D, G, row_vecs):
+    """Token rows of 2^24 - 1 and of 2^24 16-byte vectors: the offsets of a tile's last rows fill 32 bits, and the first stride for which the kernel's loop
+    has no offsets.  A whole tile and a tile of one row, the same tokens as in a dense cache.  Bar: the file's."""
+    S = 17
+    cfg = W.KVConfig("rows", 78, 1, 1, G, D, 1, W.BF16, 512, 8, 2, W.PER_SEQ, W.BHSD, 0, len_range=(S, S))
+    plan = kv.kv_layout_plan(1, 1, G, D, [S], kv.KV_BF16, 512, 8, kv.KV_PER_SEQ, 0, kv.KV_UNBOUNDED, 0, kv.KV_UNBOUNDED)
+    ss = 8 * row_vecs
+    buf = torch.empty((S - 1) * ss + 2 * D, dtype=torch.bfloat16, device="cuda")
+    k, v = (buf[i * D:i * D + (S - 1) * ss + D].as_strided((1, 1, S, D), (S * ss, S * ss, ss, 1)) for i in (0, 1))
+    cpu = [W.normal_tensor((1, 1, S, D), torch.bfloat16, 950 + i) for i in (0, 1)]
+    for dst, src in zip((k, v), cpu):
+        for t in range(S):
+            dst[0, 0, t].copy_(src[0, 0, t])
+    q = W.query(cfg, 0, "cpu")
+    view = kv.bhsd_view([k], [v], [S], torch.tensor([S], dtype=torch.int32, device="cuda"))
+    out = torch.full((1, G, D), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(kv.kv_decode_attn_workspace(plan, 0, S), dtype=torch.uint8, device="cuda")
+    kv.kv_decode_attn(plan, view, 0, q.cuda(), out, kv.KV_OUT_F32, 0, ws)
+    torch.cuda.synchronize()
+    kd, vd = (x[0].double().repeat_interleave(G, 0) for x in cpu)   # [G, S, D]
+    p = torch.softmax((q[0].double()[:, None] * kd).sum(-1) / D ** 0.5, -1)
+    _attn_check(out[0], (p[:, :, None] * vd).sum(1).numpy())
+    del buf, k, v, dst
+    torch.cuda.empty_cache()
+
+
 # tokens: as many as one workgroup's wavefronts have preassigned (two steps each; above that they claim steps from a counter), and one more
 @pytest.mark.parametrize("D,tokens", [(64, 512), (128, 256), (256, 192)])
 @pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8, 9, 16])
