@@ -1,5 +1,6 @@
 // Host threads of the page-cache path's memcpy hop (Sec. IV-B "Data Flow": pinned memory <-> page cache is a
-// CPU memcpy): a pool that copies pieces handed to it and counts each piece down on the command's own counter.
+// CPU memcpy): a pool that copies pieces handed to it and counts each piece down on the command's own counter.  The decode append
+// has it merge rows into their sectors.
 // No GPU calls in here: the pool is exercised on its own, under ThreadSanitizer, by tests/test_workers_cpu.py.
 #pragma once
 
@@ -19,6 +20,7 @@ struct CopyTask {
     const void *src;
     size_t bytes;
     std::atomic<int> *pending;
+    void (*run)(void *) = nullptr;   // called with dst in place of the copy
 };
 
 class Workers {
@@ -29,6 +31,12 @@ public:
         stop();
         quit_ = false;
         for (int i = 0; i < n; ++i) threads_.emplace_back([this] { loop(); });
+    }
+    // One thread more, beside those there are.
+    void add()
+    {
+        if (threads_.empty()) quit_ = false;   // nobody reads it
+        threads_.emplace_back([this] { loop(); });
     }
     void stop()
     {
@@ -53,6 +61,15 @@ public:
         }
         if (wake >= (int)threads_.size()) cv_.notify_all();
         else for (int i = 0; i < wake; ++i) cv_.notify_one();
+    }
+    // Takes back the pieces of a command that no thread has begun, and counts them down: whoever pushed them goes on alone.
+    void take_back(std::atomic<int> *pending)
+    {
+        std::lock_guard<std::mutex> g(mu_);
+        const auto keep = std::remove_if(q_.begin(), q_.end(), [pending](const CopyTask &t) { return t.pending == pending; });
+        pending->fetch_sub((int)(q_.end() - keep), std::memory_order_release);
+        q_.erase(keep, q_.end());
+        queued_.store((int)q_.size(), std::memory_order_release);
     }
     int size() const { return (int)threads_.size(); }
     ~Workers() { stop(); }
@@ -80,7 +97,8 @@ private:
                 q_.pop_front();
                 queued_.store((int)q_.size(), std::memory_order_release);
             }
-            std::memcpy(t.dst, t.src, t.bytes);
+            if (t.run) t.run(t.dst);
+            else std::memcpy(t.dst, t.src, t.bytes);
             t.pending->fetch_sub(1, std::memory_order_release);
         }
     }

@@ -1165,6 +1165,33 @@ def test_decode_append(cfg):
     assert e.value.code == kv.KV_ERANGE
 
 
+@pytest.mark.parametrize("layers", [7, 8])
+@pytest.mark.parametrize("behind_work", [False, True])
+def test_append_merged_by_several_threads(layers, behind_work):
+    """Rows of 252 KiB, which the calling thread merges alone, and of 288, which up to four threads merge (each call makes one more): odd lengths and even ones on both
+    paths, the sector images of one append read by the next.  behind_work: the rows land after the threads that stood by have given up."""
+    cfg = W.KVConfig("append_threads", 2100 + layers, layers, 8, 8, 128, 9, W.F16, 4096, 8, 2, W.PER_SEQ, W.PAGED, 0, len_range=(20, 31),
+                     pc_budget_bytes=4 * 2 * 9 * 18 * 4096)
+    case = Case(cfg, "cuda", gen_device="cpu", cap_extra=5)
+    r = case.ref
+    region = pinned_bytes(r.region_bytes, 0x77)
+    arena = np.full(max(r.pageable_bytes, 1), 0x77, dtype=np.uint8)
+    assert 0 < case.plan.info.n_pagecache_layers < layers
+    want_region, want_arena = case.expected_host(fill=0x77)
+    region.numpy()[:r.region_bytes] = want_region[:r.region_bytes]
+    arena[:r.pageable_bytes] = want_arena[:r.pageable_bytes]
+    lens = list(case.lens)
+    for step in range(5):
+        lens = [n + 1 for n in lens]
+        if behind_work:
+            torch.cuda._sleep(2_000_000)   # about a millisecond
+        st = kv.kv_append_tokens(case.plan, 0, layers, case.make_view(case.k, case.v, lens), region, arena)
+        want_region, want_arena = case.expected_host(fill=0x77, lens=lens)
+        assert np.array_equal(region.numpy()[:r.region_bytes], want_region[:r.region_bytes]), step
+        assert np.array_equal(arena[:r.pageable_bytes], want_arena[:r.pageable_bytes]), step
+        assert st.n_cmds == 2 * layers * 9 and st.n_rmw_reads == (2 * layers * sum(n % 2 == 0 for n in lens) if step == 0 else 0)
+
+
 @pytest.mark.parametrize("layout,mode,B", [(W.PAGED, W.PER_SEQ, 130), (W.BHSD, W.PER_SEQ, 128), (W.BHSD, W.TOKEN_MAJOR, 40)])
 def test_append_more_rows_than_one_launch_holds(layout, mode, B):
     """The rows of 33 layers and up to 130 sequences (a launch holds 32 layers and 128 sequences), and rows of all

@@ -40,6 +40,39 @@ static int run_round(kvb::Workers &w, int n_cmds, size_t cmd_bytes, int ring, bo
     return std::memcmp(src.data(), dst.data(), src.size()) == 0 ? 0 : 1;
 }
 
+// Functions in place of copies, as the decode append pushes them: they wait for a flag and take shares of a counter, the pushing thread takes shares
+// itself, and what no thread has begun by the end is taken back.
+static int run_shares(kvb::Workers &w, int n_tasks, bool nap)
+{
+    struct Job {
+        std::atomic<int> go{0}, next{0};
+        std::vector<int> done;
+        void work() { for (int i; (i = next.fetch_add(1)) < (int)done.size();) ++done[(size_t)i]; }
+        static void run(void *self)
+        {
+            Job &j = *(Job *)self;
+            while (j.go.load(std::memory_order_acquire) == 0) std::this_thread::yield();
+            j.work();
+        }
+    };
+    int bad = 0;
+    for (int round = 0; round < 50; ++round) {
+        if (nap && round % 9 == 0) std::this_thread::sleep_for(std::chrono::milliseconds(2));
+        Job j;
+        j.done.assign(300, 0);
+        std::atomic<int> pending{n_tasks};
+        kvb::CopyTask tasks[16];
+        for (int i = 0; i < n_tasks; ++i) tasks[i] = kvb::CopyTask{&j, nullptr, 0, &pending, &Job::run};
+        w.push(tasks, n_tasks);
+        j.go.store(1, std::memory_order_release);
+        j.work();
+        w.take_back(&pending);
+        while (pending.load(std::memory_order_acquire) != 0) std::this_thread::yield();
+        for (int d : j.done) bad += d != 1;
+    }
+    return bad ? 1 : 0;
+}
+
 int main()
 {
     int bad = 0;
@@ -53,6 +86,10 @@ int main()
         bad += run_round(w, 200, 300 * 1024, 4, false);
         w.start(1);
         bad += run_round(w, 50, 4096, 3, true);
+        w.stop();
+        for (int n = 0; n < 3; ++n) { w.add(); bad += run_shares(w, n + 1, false); }
+        bad += run_shares(w, 16, true);                   // more tasks than threads: some are taken back
+        bad += run_round(w, 40, 64 * 1024, 6, false);     // copies again
         w.stop();
         w.stop();                                         // idempotent
         w.start(2);
