@@ -703,6 +703,19 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     __shared__ __attribute__((aligned(16))) float sh_acc[kWaves][RG][NH][DP];
     __shared__ f32x2 sh_ml[kWaves][RG * NH];
     auto far = [](float ref) { return fabsf(ref) > kFusedRef && ref != kEmptyMax; };
+    constexpr int C = D == 64 ? 1 : D == 256 ? 4 : (NH <= 4 ? 1 : 2), kUnits = D / (64 * C);   // columns of a lane in the merge
+    typedef float cols_t __attribute__((ext_vector_type(C)));
+    // A wavefront's first states are on their way while the references are looked at.  us per layer from a graph, after / before that: 8 x 4 x 128, 4K tokens 8.21 / 8.15,
+    // 1K 6.46 / 6.42; 2 x 2 x 64, 256 3.62 / 3.57; 2 x 6 x 64, 2 of 1K-1.6K 6.54 / 6.43; paged 16 x 8 x 64, 4 of 700 7.73 / 7.62; 8 x 16 x 128, 4K 9.70 / 9.81.
+    constexpr bool kEarly = !VALU && NH <= 8;
+    f32x2 ml;
+    cols_t part[kWaves];
+    auto load_unit = [&](int u) {   // the states of 64 * C columns of one head
+        const int g = u / kUnits, d = (u % kUnits) * 64 * C + lane * C;
+        ml = lane < kWaves ? sh_ml[lane][g] : f32x2{kEmptyMax, 0.f};
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) part[k] = *(const cols_t *)&sh_acc[k][0][g][d];
+    };
     bool again;   // some accumulated value is not finite, some reference beyond kFusedRef, or `wide`: the split is done again
     f32x2 state = {kEmptyMax, 0.f};   // VALU: lane = state
     if constexpr (VALU) {
@@ -747,6 +760,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         const bool bad = __any(!(nf == 0.f));
         if (tg == 0 && copy == 0 && g < ng) sh_ml[wave][g] = f32x2{bad ? INFINITY : m, l};
         __syncthreads();
+        if constexpr (kEarly) load_unit(min(wave, ng * kUnits - 1));
         bool some = false;
 #pragma unroll
         for (int j0 = 0; j0 < kWaves * NH; j0 += 64) {
@@ -841,6 +855,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         }
         __syncthreads();
         if (VALU && lane < RG * kWaves) state = (&sh_ml[0][0])[lane];
+        if constexpr (kEarly) load_unit(min(wave, ng * kUnits - 1));
     }
     if constexpr (VALU) {
         // 64 positions per wavefront, which forms the states' weights itself (lane = state) and takes them from the lanes by readlane
@@ -866,15 +881,10 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     // by readlane, one weight's exponential per lane in place of every state's in every lane.  us per layer from a graph, together with the stores above:
     // 8 KV heads x 4 x 128, 1K tokens 7.1 / 6.7, 4K 8.75 / 8.3; 2 x 2 x 64, 256 tokens 4.4 / 3.95; 4 x 2 x 256, 2 sequences of 3000
     // 11.3 / 10.7; paged, 2 x 7, 4K 8.0 / 7.7; 32K and larger batches within 1 %.
-    constexpr int C = D == 64 ? 1 : D == 256 ? 4 : (NH <= 4 ? 1 : 2), kUnits = D / (64 * C);
-    typedef float cols_t __attribute__((ext_vector_type(C)));
     static_assert(kWaves <= 8, "half a row of lanes");
     for (int u = wave; u < ng * kUnits; u += kWaves) {
         const int g = u / kUnits, d = (u % kUnits) * 64 * C + lane * C;
-        const f32x2 ml = lane < kWaves ? sh_ml[lane][g] : f32x2{kEmptyMax, 0.f};
-        cols_t part[kWaves];
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) part[k] = *(const cols_t *)&sh_acc[k][0][g][d];
+        if (!kEarly || u != wave) load_unit(u);
         const float Ml = half_row_max(ml[0]);
         const float wgt = exp2f(ml[0] - Ml);
         const float M = rdlane(Ml, 0), L = rdlane(half_row_sum(ml[1] * wgt), 0);
