@@ -25,11 +25,11 @@ HBM_PEAK_GBPS = 8000.0  # MI355X published HBM3E bandwidth
 # workload (profiles/pmc_traffic_<workload>.md), each counter scaled by what it reads for a plain device-to-device
 # copy of known size in the same run.  Valid only for the sources they were taken with: the hash below covers the
 # two kernel files, what cuts and launches their work, and the compiler's flags; a mismatch reports traffic as null.
-PMC_TRAFFIC = {"sha": "d5719eab8b9a0057",
-               "llama8b_32k": {"kv_layout_kernel<pack>": 268458522, "kv_layout_kernel<unpack>": 268453175, "kv_attn_partial_kernel+kv_attn_combine_kernel": 135570378},
-               "llama8b_4k": {"kv_layout_kernel<pack>": 268468543, "kv_layout_kernel<unpack>": 268470696, "kv_attn_partial_kernel+kv_attn_combine_kernel": 18130210},
-               "llama8b_ragged_paged": {"kv_layout_kernel<pack>": 282074233, "kv_layout_kernel<unpack>": 282054877, "kv_attn_partial_kernel+kv_attn_combine_kernel": 142711564},
-               "gemma7b_mha_8k": {"kv_layout_kernel<pack>": 536895013, "kv_layout_kernel<unpack>": 536883851, "kv_attn_partial_kernel+kv_attn_combine_kernel": 538127460}}
+PMC_TRAFFIC = {"sha": "2ea30c53aac53eee",
+               "llama8b_32k": {"kv_layout_kernel<pack>": 268470222, "kv_layout_kernel<unpack>": 268458344, "kv_attn_partial_kernel+kv_attn_combine_kernel": 135533890},
+               "llama8b_4k": {"kv_layout_kernel<pack>": 268467739, "kv_layout_kernel<unpack>": 268472260, "kv_attn_partial_kernel+kv_attn_combine_kernel": 18124989},
+               "llama8b_ragged_paged": {"kv_layout_kernel<pack>": 282073657, "kv_layout_kernel<unpack>": 282055318, "kv_attn_partial_kernel+kv_attn_combine_kernel": 142689736},
+               "gemma7b_mha_8k": {"kv_layout_kernel<pack>": 536894703, "kv_layout_kernel<unpack>": 536883871, "kv_attn_partial_kernel+kv_attn_combine_kernel": 537745183}}
 
 
 def kernel_sources_hash() -> str:
