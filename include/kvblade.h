@@ -426,6 +426,8 @@ int kv_pipeline_run(kv_plan_t *plan, int dir, int layer_begin, int layer_end, co
  * starts inside a sector is merged with the sector's earlier bytes: the first append after an offload
  * reads that sector back (counted in n_rmw_reads), later appends use the image the library keeps;
  * bytes after the row up to the sector end are written as zeros (no later row exists yet).
+ * A call is meant for the token after the last one appended: rows of a kept sector that no append has written,
+ * because a length moved by more, are written as zeros too.
  * Blocking.  lba_region / pageable as in kv_pipeline_run (pinned-ness is not required here).
  * The kept sector images are forgotten by kv_pipeline_run(KV_DIR_OFFLOAD), by kv_plan_trim, and whenever a call
  * names another lba_region or pageable base address than the one the images were taken from; they assume that

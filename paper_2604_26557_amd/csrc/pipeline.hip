@@ -161,6 +161,7 @@ struct kv_pipeline {
     size_t append_host_bytes = 0;
     std::vector<char> tail_img;
     std::vector<int64_t> tail_sector;
+    std::vector<uint32_t> tail_valid;  // bytes of the image that are the sector's; behind them it holds zeros, which the image itself need not
     const void *tail_region = nullptr, *tail_pageable = nullptr;  // host buffers the images were taken from
     kvb::LinkRate link[2];       // issue pacing: the host link's rate per direction (0 offload, 1 reload)
     Schedule sched;              // the last call's spans and chunk commands: a decode loop repeats the same call
@@ -1046,11 +1047,16 @@ struct AppendMerge {
         const Place w = place(idx);
         const uint64_t sec = (uint64_t)p->sector, rb = p->row_bytes, pad = w.nsec * sec - w.end;
         kv_pipeline *const q = p->pipe;
+        const uint64_t valid = q->tail_valid[w.entry];
         char *const host = (char *)(w.direct ? lba_region : pageable) + w.off, *const img = q->tail_img.data() + w.entry * sec;
         const char *const row = (const char *)rows + idx * rb;
         const bool kept = q->tail_sector[w.entry] == (int64_t)w.sec0;
-        // write command (nlb = nsec - 1): the head from the kept image, or as the read has found it; the row; zeros
-        if (w.head > 0 && kept) std::memcpy(host, img, w.head);
+        // write command (nlb = nsec - 1): the head from the kept image, or as the read has found it; the row; zeros.  Rows of the sector that
+        // no append has written, because the length moved by more than one, are zeros.
+        if (w.head > 0 && kept) {
+            if (w.head > valid) std::memset(img + valid, 0, w.head - valid);
+            std::memcpy(host, img, w.head);
+        }
         std::memcpy(host + w.head, row, rb);
         if (pad > 0) {  // the row ends inside a sector: keep that sector's bytes so far for the next append
             std::memset(host + w.end, 0, pad);
@@ -1062,6 +1068,7 @@ struct AppendMerge {
                 std::memcpy(img, row + (rb - tail), tail);
             }
             q->tail_sector[w.entry] = (int64_t)(w.sec0 + w.nsec - 1);
+            q->tail_valid[w.entry] = (uint32_t)tail;
         } else {
             q->tail_sector[w.entry] = -1;
         }
@@ -1136,6 +1143,7 @@ extern "C" int kv_append_tokens(kv_plan_t *p, int layer_begin, int layer_end, co
     const size_t n_entries = (size_t)p->L * 2 * (size_t)nseq;
     if (q->tail_sector.size() != n_entries) {
         q->tail_sector.assign(n_entries, -1);
+        q->tail_valid.assign(n_entries, 0);
         q->tail_img.assign(n_entries * sec, 0);
     }
     // images taken from other host buffers say nothing about these

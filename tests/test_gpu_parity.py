@@ -1192,6 +1192,42 @@ def test_append_merged_by_several_threads(layers, behind_work):
         assert st.n_cmds == 2 * layers * 9 and st.n_rmw_reads == (2 * layers * sum(n % 2 == 0 for n in lens) if step == 0 else 0)
 
 
+@pytest.mark.parametrize("H,D,layers", [(2, 128, 4), (3, 128, 4), (3, 64, 80)])
+def test_append_of_a_length_that_moves_by_more_than_one(H, D, layers):
+    """Rows of 512, 768 and 384 bytes in sectors of 4 KiB (one thread; 270 KiB of rows: several).  A length that skips rows of a sector, skips into the next one or goes
+    back: rows of a kept sector that no append has written are zeros, whatever an earlier sector or a longer length had in their place; the rest is as for any append."""
+    cfg = W.KVConfig("append_skips", 2200 + H + D, layers, H, H, D, 9, W.F16, 4096, 32, 2, W.PER_SEQ, W.PAGED, 0, len_range=(14, 30),
+                     pc_budget_bytes=layers // 2 * 2 * 9 * 12 * 4096)
+    case = Case(cfg, "cuda", gen_device="cpu", cap_extra=48)
+    r, nseq, sec, rb = case.ref, 9, 4096, 2 * H * D
+    region = pinned_bytes(r.region_bytes, 0x77)
+    arena = np.full(max(r.pageable_bytes, 1), 0x77, dtype=np.uint8)
+    host = [region.numpy().copy(), arena.copy()]   # direct path, page-cache path
+    rows = [case.expected_extent(n // 2, n % 2, lens=case.caps) for n in range(2 * layers)]
+    kept = {}
+    lens = list(case.lens)
+    for step, move in enumerate([1] * 9 + [2, 1, 3, 1, 1, 2, -1, 2, 1, -2, 1, 5, 9, 1, 2, 1]):
+        lens = [n + move + (b % 3 == 1 and move > 1) for b, n in enumerate(lens)]
+        st = kv.kv_append_tokens(case.plan, 0, layers, case.make_view(case.k, case.v, lens), region, arena)
+        reads = 0
+        for n in range(2 * layers):
+            buf, base = host[int(r.path[n] != 0)], r.ext_byte_off(n)
+            for b, ln in enumerate(lens):
+                a = (ln - 1) * rb
+                first, end = a // sec * sec, -(-(a + rb) // sec) * sec
+                off, head = base + int(r.seq_base[b]) * sec, a % sec
+                sector, img = kept.get((n, b), (-1, None))
+                if head and sector == first:
+                    buf[off + first:off + a] = img[:head]
+                reads += bool(head and sector != first)
+                buf[off + a:off + a + rb] = rows[n][int(r.seq_base[b]) * sec + a:][:rb]
+                buf[off + a + rb:off + end] = 0
+                kept[n, b] = (end - sec, buf[off + end - sec:off + end].copy()) if (a + rb) % sec else (-1, None)
+        assert np.array_equal(region.numpy()[:r.region_bytes], host[0][:r.region_bytes]), (step, lens)
+        assert np.array_equal(arena[:r.pageable_bytes], host[1][:r.pageable_bytes]), (step, lens)
+        assert st.n_rmw_reads == reads, step
+
+
 @pytest.mark.parametrize("layout,mode,B", [(W.PAGED, W.PER_SEQ, 130), (W.BHSD, W.PER_SEQ, 128), (W.BHSD, W.TOKEN_MAJOR, 40)])
 def test_append_more_rows_than_one_launch_holds(layout, mode, B):
     """The rows of 33 layers and up to 130 sequences (a launch holds 32 layers and 128 sequences), and rows of all
