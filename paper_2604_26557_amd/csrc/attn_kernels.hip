@@ -67,8 +67,12 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr int waves(int D) { return D >= 256 ? 6 : 8; }
 constexpr float kEmptyMax = -1.0e30f; // running maximum of a row group that has seen no token
 // How K and V are addressed: a strided view; a block pool whose blocks hold whole tiles (split starts are multiples of
-// the tile); any other block pool.
-constexpr int kStrided = 0, kPagedTiles = 1, kPagedRows = 2;
+// the tile); any other block pool; a strided view whose token rows lie kFarRows 16-byte vectors (256 MiB) or more apart, so that the offsets within a tile
+// (15 rows and a row's own bytes) do not fit 32 bits.  An instance of its own: both kinds of
+// address in one loop cost near rows 2 %, and the second pass, which has 64-bit addresses anyway, is 2 to 9 times slower.  us per layer, 129 rows 256 MiB apart,
+// second pass / this: 1 KV head x 4 x 64 11.5 / 3.5, 4 x 128 12.3 / 3.8, 16 x 128 43.6 / 5.0, 4 x 256 14.5 / 5.9.
+constexpr int kStrided = 0, kPagedTiles = 1, kPagedRows = 2, kStridedFar = 3;
+constexpr unsigned long long kFarRows = 1ull << 24;
 struct AttnParams {
     const int *seq_lens;   // device [B]
     float *part_acc;       // [B, Hq, n_splits, D]
@@ -90,8 +94,8 @@ struct PackedStrides {
     unsigned long long ss_sh;
     int sb, high;
 };
-// Further bits of `high`: sequences start at seq_off; a token row's address needs more than 32 bits within a tile.
-constexpr int kSeqOff = 1 << 24, kWideRows = 1 << 25;
+// A further bit of `high`: sequences start at seq_off.
+constexpr int kSeqOff = 1 << 24;
 constexpr PackedStrides pack_strides(Strides s)
 {
     return {(s.ss & 0xffffffffull) | s.sh << 32, (int)(unsigned)s.sb,
@@ -325,7 +329,7 @@ __global__ void __launch_bounds__(64 * waves(D), D <= 128 ? 4 : 2)
 kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
                        typename std::conditional<std::is_same<TAB, ItemTable>::value, const int *, unsigned long long>::type lens_arg,
                        unsigned heads, unsigned shares,
-                       typename std::conditional<LAYOUT != kStrided, const int *, unsigned long long>::type addr_arg, int addr2, int addr3,
+                       typename std::conditional<LAYOUT == kPagedTiles || LAYOUT == kPagedRows, const int *, unsigned long long>::type addr_arg, int addr2, int addr3,
                        AttnParams p, TAB tab)
 {
     constexpr int kWaves = waves(D), kThreads = 64 * kWaves;
@@ -341,7 +345,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     constexpr int kCopies = VALU ? 1 : 16 / NH;   // matrix columns that carry the same query head
     constexpr bool HALVES = NH <= 8;         // a column holds one half of every 128-byte line of its query head
     constexpr int NQ = HALVES ? NJ / 2 : NJ;
-    constexpr bool PAGED = LAYOUT != kStrided, TILE_ID = LAYOUT == kPagedTiles;
+    constexpr bool PAGED = LAYOUT == kPagedTiles || LAYOUT == kPagedRows, TILE_ID = LAYOUT == kPagedTiles;
     typedef unsigned vload_t __attribute__((ext_vector_type(E / 2)));
 
     int lane = threadIdx.x & 63;
@@ -471,12 +475,11 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         vload_t v[TI][4][NV];
         bool ok[TI][4];
     };
-    const bool wide = !PAGED && (addr3 & kWideRows);   // the loop's 32-bit offsets do not reach: all of the split is left to the second pass
     // Strided layout: head h starts with step h % 8 of a long split, or of one of just 8 steps.  All workgroups begin together and read at one pace, and where the strides are powers
     // of two the same step of every head lies at the same place modulo them.  us per layer, 8 x 4 x 128, all heads from step 0 / from step h: 32K tokens 25.4 / 25.0,
     // 16K 16.0 / 15.7, 2 sequences of 16K 25.9 / 25.6, 16 query heads each 32K 27.2 / 26.9, 4K 8.34 / 8.27, 30001 tokens 24.4 / 24.4.  (Other splits of up to two steps for each
     // wavefront lose by it: 4 sequences of 4096 15.9 / 16.6, 32 heads, 2 of 4096 25.7 / 27.0; any step of the split, by a hash: 16 x 1 x 256, 4 of 8192 84.8 / 92.2.)
-    const int n_steps = wide ? 0 : (t_end - t_begin + kStepTok - 1) / kStepTok;
+    const int n_steps = (t_end - t_begin + kStepTok - 1) / kStepTok;
     constexpr int kTurn = 8;
     const int first_step = !PAGED && (n_steps > 2 * kWaves || n_steps == kTurn) ? (h + b) % kTurn : 0;
     auto step_row = [&](int st) -> int {
@@ -501,7 +504,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
             const int T0 = Tw + kTile * ti;
             const int R0 = T0 < t_end ? T0 : Tw;      // the tile's first row (an empty tile: the step's)
             const int rem = t_end - T0;
-            if constexpr (LAYOUT != kPagedRows) {
+            if constexpr (LAYOUT == kStrided || TILE_ID) {
                 const long long tb = row_base(R0, PAGED ? ids.k[ti][0] : 0);
                 const bool in_pool = !PAGED || (unsigned)ids.k[ti][0] < (unsigned)p.n_pool;
                 const char *const kt = (const char *)(K + tb), *const vt = (const char *)(V + tb);
@@ -527,7 +530,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = 4 * i + tg, blk = ids.t[ti][i];
-                    x.ok[ti][i] = r < rem && (unsigned)blk < (unsigned)p.n_pool;
+                    x.ok[ti][i] = r < rem && (!PAGED || (unsigned)blk < (unsigned)p.n_pool);
                     const vload_t *vp = (const vload_t *)(V + row_base(r < rem ? T0 + r : R0, blk)) + n;
 #pragma unroll
                     for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load(vp + w * 16);
@@ -716,7 +719,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
 #pragma unroll
         for (int k = 0; k < kWaves; ++k) part[k] = *(const cols_t *)&sh_acc[k][0][g][d];
     };
-    bool again;   // some accumulated value is not finite, some reference beyond kFusedRef, or `wide`: the split is done again
+    bool again;   // some accumulated value is not finite, or some reference beyond kFusedRef: the split is done again
     f32x2 state = {kEmptyMax, 0.f};   // VALU: lane = state
     if constexpr (VALU) {
         // position ((2w + e4) * 16 + n) * 4 + k of a state holds column (w * 16 + n) * 8 + 4 * e4 + k: contiguous 16-byte stores
@@ -735,7 +738,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         if (n == 0) sh_ml[wave][tg] = f32x2{bad ? INFINITY : m, l};
         __syncthreads();
         if (lane < RG * kWaves) state = (&sh_ml[0][0])[lane];
-        again = __any((int)wide | (int)far(state[0]));
+        again = __any(far(state[0]));
     } else {
         // A head's columns of the matrix hold the same sums: each of them writes its share.  (Written by one of four, with three of four
         // lanes idle, the stores took four times as many LDS cycles, in front of the barrier.)
@@ -767,13 +770,13 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
             const int j = j0 + lane;
             if (j < kWaves * NH && j % NH < ng) some = some || far((&sh_ml[0][0])[j][0]);
         }
-        again = __any((int)wide | (int)some);
+        again = __any(some);
     }
 
     auto head_out = [&](int g) { return ((long long)b * Hq + hq0 + g) * D; };
     auto head_part = [&](int g) { return ((long long)b * Hq + hq0 + g) * p.n_splits + split; };
     if (__builtin_expect(again, 0)) {   // out of the way of what every launch runs through
-        // V (or K, or q) holds infinities or NaNs, or scores are beyond kFusedRef (or rows are too far apart for the loop).  The terms of a probability meet an infinite
+        // V (or K, or q) holds infinities or NaNs, or scores are beyond kFusedRef.  The terms of a probability meet an infinite
         // V one by one, and one that is zero or negative turns it into a NaN, so the split is done again with the
         // probability as one factor, and with exponents from score differences: a wavefront takes every kWaves-th run of 8
         // tokens, whose loads are in flight together, for 4 heads at a time, and leaves its states in their places in LDS.
@@ -1037,8 +1040,13 @@ void launch_partial(dim3 grid, hipStream_t st, const AttnHead &c, const AttnPara
     const dim3 block(64 * waves(D));
     if (!c.table) {
         const PackedStrides ps = pack_strides(c.strides);
-        (void)kvb::launch_kernel(kv_attn_partial_kernel<D, NH, BF16, kStrided, TAB>, grid, block, st, c.K, c.V, c.q, lens, heads, shares,
-                           ps.ss_sh, ps.sb, ps.high | (a.seq_off ? kSeqOff : 0) | (c.strides.ss >= 1u << 24 ? kWideRows : 0), a, t);
+        const int high = ps.high | (a.seq_off ? kSeqOff : 0);
+        if (c.strides.ss < kFarRows)
+            (void)kvb::launch_kernel(kv_attn_partial_kernel<D, NH, BF16, kStrided, TAB>, grid, block, st, c.K, c.V, c.q, lens, heads, shares,
+                               ps.ss_sh, ps.sb, high, a, t);
+        else
+            (void)kvb::launch_kernel(kv_attn_partial_kernel<D, NH, BF16, kStridedFar, TAB>, grid, block, st, c.K, c.V, c.q, lens, heads, shares,
+                               ps.ss_sh, ps.sb, high, a, t);
     } else if (c.bt % kTile == 0) {
         (void)kvb::launch_kernel(kv_attn_partial_kernel<D, NH, BF16, kPagedTiles, TAB>, grid, block, st, c.K, c.V, c.q, lens, heads, shares,
                            c.table, c.max_blocks, c.bt, a, t);

@@ -444,6 +444,40 @@ def test_decode_attention_rows_as_far_apart_as_32_bit_offsets_reach(D, G, row_ve
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("row_vecs", [(1 << 24) - 1, 1 << 24, (1 << 24) + 2])
+@pytest.mark.parametrize("D,G,dtype", [(64, 4, torch.float16), (128, 1, torch.bfloat16), (128, 16, torch.float16), (256, 3, torch.bfloat16)])
+def test_decode_attention_of_far_rows_is_that_of_a_dense_cache(D, G, dtype, row_vecs):
+    """The same tokens in the same steps: the last bits too are those of a dense cache, on both sides of the first stride that takes 64-bit row addresses, for
+    one split and two, of whole tiles and of one that is a row short."""
+    S, L2 = 95, 79
+    plan = kv.kv_layout_plan(1, 1, G, D, [S, L2], kv.KV_F16 if dtype == torch.float16 else kv.KV_BF16, 512, 16, kv.KV_PER_SEQ, 0, kv.KV_UNBOUNDED, 0, kv.KV_UNBOUNDED)
+    k, v = (W.normal_tensor((2, 1, S, D), dtype, 970 + i) for i in (0, 1))
+    q = W.normal_tensor((2, G, D), dtype, 972).cuda()
+    outs = []
+    for far in (True, False):
+        ss = 8 * row_vecs if far else 4 * D
+        buf = torch.empty((S - 1) * ss + 4 * D, dtype=dtype, device="cuda")   # K and V of both sequences side by side in a row
+        at = [[buf[(2 * b + i) * D:(2 * b + i) * D + (S - 1) * ss + D].as_strided((S, D), (ss, 1)) for b in (0, 1)] for i in (0, 1)]
+        for i, src in enumerate((k, v)):
+            for b in (0, 1):
+                for t in range(S):
+                    at[i][b][t].copy_(src[b, 0, t])
+        kk, vv = (buf[i * D:i * D + (S - 1) * ss + 3 * D].as_strided((2, 1, S, D), (2 * D, S * ss, ss, 1)) for i in (0, 1))
+        view = kv.bhsd_view([kk], [vv], [S, L2], torch.tensor([S, L2], dtype=torch.int32, device="cuda"))
+        for n_splits in (1, 2):
+            out = torch.full((2, G, D), float("nan"), dtype=torch.float32, device="cuda")
+            ws = torch.empty(kv.kv_decode_attn_workspace(plan, n_splits, S), dtype=torch.uint8, device="cuda")
+            kv.kv_decode_attn(plan, view, 0, q, out, kv.KV_OUT_F32, n_splits, ws)
+            torch.cuda.synchronize()
+            outs.append(out.cpu())
+        del buf, at, kk, vv, view
+        torch.cuda.empty_cache()
+    assert torch.equal(outs[0], outs[2]) and torch.equal(outs[1], outs[3])
+    for b, n in enumerate((S, L2)):
+        p = torch.softmax((q[b].cpu().double() @ k[b, 0, :n].double().T) / D ** 0.5, -1)
+        _attn_check(outs[0][b], (p @ v[b, 0, :n].double()).numpy())
+
+
 # tokens: as many as one workgroup's wavefronts have preassigned (two steps each; above that they claim steps from a counter), and one more
 @pytest.mark.parametrize("D,tokens", [(64, 512), (128, 256), (256, 192)])
 @pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8, 9, 16])
