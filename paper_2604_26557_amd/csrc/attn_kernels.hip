@@ -446,7 +446,37 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     // When the block size is a multiple of the tile a tile lies inside one block (kPagedTiles): one lookup per tile, the
     // same for the whole wavefront and so a scalar load.  Otherwise a lane looks up its two K rows and the 4 tokens of
     // its row group.
-    struct Ids { int k[TI][TILE_ID ? 1 : 2], t[TI][TILE_ID ? 1 : 4]; };
+    struct Ids { int k[TI][TILE_ID ? 1 : 2], t[TI][TILE_ID ? 1 : 4], slot0[TI]; };   // slot0: the first row's place in its block
+    // kPagedRows: the rows of a tile that a lane loads, two of K and four of V, as places from the start of the block in which the tile's first row has place
+    // slot0 (past the end: that row's own), and those cut into blocks on from there and a place in the block.  One division for the tile and not one for each
+    // row: above 16 tokens a block a place is at most one block on, below it the quotient of a number up to 29 comes from a product.  The branch
+    // is one for all six rows: as a choice for each row it took 1-14 % more.  us per layer from a graph, a division for each row with a row of K per lane / with whole
+    // lines of K / this: 16 x 4 x 64, 7 of 6283-11718, blocks of 24 75.4 / 79.9 / 59.5, of 10 77.4 / 81.8 / 61.3, of 8 66.6 / 65.1 / 60.3; 2 x 2 x 64, 256 tokens in 24 5.86 / 6.10
+    // / 4.82; 8 x 4 x 128, 8 of 1K-8K in 24 35.1 / 35.6 / 30.4, 4K 8.93 / 8.84 / 8.64; 4 x 7 x 128, 48 of 200-4000 in 20 46.4 / 43.3 / 42.4; 8 x 4 x 256, 9 of 1K-5K in 24 48.1 / 44.3 / 43.4.
+    constexpr int kLaneRows = 6;
+    auto lane_places = [&](int slot0, int rem, int place[kLaneRows]) {
+#pragma unroll
+        for (int i = 0; i < kLaneRows; ++i) {
+            const int r = i < 2 ? k_row(i) : 4 * (i - 2) + tg;
+            place[i] = slot0 + (r < rem ? r : 0);
+        }
+    };
+    const int bt_recip = 65536 / max(bt, 1) + 1;
+    auto cut_places = [&](int place[kLaneRows], int on[kLaneRows]) {
+        if (bt >= kTile) {
+#pragma unroll
+            for (int i = 0; i < kLaneRows; ++i) {
+                on[i] = place[i] >= bt;
+                place[i] -= on[i] ? bt : 0;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kLaneRows; ++i) {
+                on[i] = (int)(__umul24(place[i], bt_recip) >> 16);
+                place[i] -= (int)__umul24(on[i], bt);
+            }
+        }
+    };
     auto fetch_ids = [&](int Tw, Ids &ids) {
 #pragma unroll
         for (int ti = 0; ti < TI; ++ti) {
@@ -455,16 +485,15 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
             if (TILE_ID) {
                 ids.k[ti][0] = ids.t[ti][0] = tbl[block_of(fb)];
             } else {
+                const int b0 = block_of(fb);
+                int place[kLaneRows], on[kLaneRows];
+                ids.slot0[ti] = fb - b0 * bt;
+                lane_places(ids.slot0[ti], t_end - T0, place);
+                cut_places(place, on);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int tok = T0 + k_row(i);
-                    ids.k[ti][i] = tbl[block_of(tok < t_end ? tok : fb)];
-                }
+                for (int i = 0; i < 2; ++i) ids.k[ti][i] = tbl[b0 + on[i]];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int tok = T0 + 4 * i + tg;
-                    ids.t[ti][i] = tbl[block_of(tok < t_end ? tok : fb)];
-                }
+                for (int i = 0; i < 4; ++i) ids.t[ti][i] = tbl[b0 + on[2 + i]];
             }
         }
     };
@@ -522,16 +551,23 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
                     for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load((const vload_t *)(vt + 32 * E * w + vo));
                 }
             } else {
+                int place[kLaneRows], on[kLaneRows];
+                long long at[kLaneRows];   // the lane's rows, as vector indices
+                lane_places(PAGED ? ids.slot0[ti] : 0, rem, place);
+                if (PAGED) cut_places(place, on);
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const int r = k_row(j);
-                    x.k[ti][j] = __builtin_nontemporal_load(K + row_base(r < rem ? T0 + r : R0, ids.k[ti][j & 1]) + k_vec(j));
+                for (int i = 0; i < kLaneRows; ++i) {
+                    int blk = PAGED ? (i < 2 ? ids.k[ti][i] : ids.t[ti][i - 2]) : 0;
+                    if ((unsigned)blk >= (unsigned)p.n_pool) blk = 0;
+                    at[i] = PAGED ? (((long long)blk * H + h) * bt + place[i]) * DV : row_base(R0 + place[i], 0);
                 }
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) x.k[ti][j] = __builtin_nontemporal_load(K + at[j & 1] + k_vec(j));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = 4 * i + tg, blk = ids.t[ti][i];
                     x.ok[ti][i] = r < rem && (!PAGED || (unsigned)blk < (unsigned)p.n_pool);
-                    const vload_t *vp = (const vload_t *)(V + row_base(r < rem ? T0 + r : R0, blk)) + n;
+                    const vload_t *vp = (const vload_t *)(V + at[2 + i]) + n;
 #pragma unroll
                     for (int w = 0; w < NV; ++w) x.v[ti][i][w] = __builtin_nontemporal_load(vp + w * 16);
                 }

@@ -743,6 +743,44 @@ def test_decode_attention_scores_beyond_the_exact_range(D, dtype):
                 assert torch.equal(out[b, g].cpu(), case.v[0][b, 0, best[b, g]].float().cpu()), (n_splits, b, g)
 
 
+@pytest.mark.parametrize("bt", [1, 2, 3, 5, 7, 8, 9, 10, 12, 13, 14, 15, 17, 20, 24, 31, 33, 100, 700])
+@pytest.mark.parametrize("D,G,dtype", [(64, 4, torch.float16), (128, 1, torch.bfloat16), (128, 9, torch.float16), (256, 2, torch.bfloat16)])
+def test_decode_attention_of_blocks_that_tiles_cross(D, G, dtype, bt):
+    """Every place of a row in its block, blocks shorter and longer than a tile: the bits of the same tokens in blocks of whole tiles (up to 12 steps a split, which no
+    wavefront takes out of turn)."""
+    H, lens = 2, [190, 33, 161, 1, 16]
+    plan = kv.kv_layout_plan(1, H, H * G, D, lens, kv.KV_F16 if dtype == torch.float16 else kv.KV_BF16, 512, 8, kv.KV_PER_SEQ, 0, kv.KV_UNBOUNDED, 0, kv.KV_UNBOUNDED)
+    k, v = (W.normal_tensor((len(lens), H, max(lens), D), dtype, 980 + i) for i in (0, 1))
+    q = W.normal_tensor((len(lens), H * G, D), dtype, 982).cuda()
+    lens_dev = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    outs = []
+    for block in (bt, 16):
+        per = [-(-n // block) for n in lens]
+        ids = np.random.default_rng(5).permutation(sum(per))
+        table = np.full((len(lens), max(per)), -1, dtype=np.int32)
+        pools = [torch.zeros((sum(per), H, block, D), dtype=dtype) for _ in (0, 1)]
+        at = 0
+        for b, n in enumerate(lens):
+            table[b, :per[b]] = ids[at:at + per[b]]
+            at += per[b]
+            for pool, src in zip(pools, (k, v)):
+                for j in range(per[b]):
+                    rows = src[b, :, j * block:min(n, (j + 1) * block)]
+                    pool[table[b, j], :, :rows.shape[1]] = rows
+        view = kv.paged_view([pools[0].cuda()], [pools[1].cuda()], torch.from_numpy(table).cuda(), lens, lens_dev)
+        for n_splits in (1, 0):
+            out = torch.full((len(lens), H * G, D), float("nan"), dtype=torch.float32, device="cuda")
+            ws = torch.empty(kv.kv_decode_attn_workspace(plan, n_splits, max(lens)), dtype=torch.uint8, device="cuda")
+            kv.kv_decode_attn(plan, view, 0, q, out, kv.KV_OUT_F32, n_splits, ws)
+            torch.cuda.synchronize()
+            outs.append(out.cpu())
+    assert torch.equal(outs[0], outs[2]) and torch.equal(outs[1], outs[3])
+    for b, n in enumerate(lens):
+        kd, vd = (x[b, :, :n].double().repeat_interleave(G, 0) for x in (k, v))
+        p = torch.softmax((q[b].cpu().double()[:, None] * kd).sum(-1) / D ** 0.5, -1)
+        _attn_check(outs[0][b], (p[:, :, None] * vd).sum(1).numpy())
+
+
 @pytest.mark.parametrize("bt", [1, 8, 12, 32, 48])
 def test_paged_source_other_block_sizes(bt):
     """Paged pools whose blocks hold other than 16 token rows (a power of two below and above the 16-row tile, sizes
