@@ -193,7 +193,8 @@ typedef struct kv_pipe_opts {
     int32_t span_chunks;  /* chunks of one tensor per kernel launch and staging slot; 0 = whole extents: K and V
                              of a layer in one launch, and consecutive layers of one path together while their
                              images stay within 128 MiB (a launch must be tens of MiB to run at HBM speed) */
-    int32_t host_workers; /* threads for the page-cache path's memcpy hop; 0 = default (8) */
+    int32_t host_workers; /* threads for the page-cache path's memcpy hop; 0 = default (8).  Given, it also bounds the
+                             threads that help later kv_append_tokens calls of the plan (until a call without it) */
     uint32_t flags;       /* KV_PIPE_* */
     int32_t copy_streams; /* streams the chunk commands rotate over, 1..4; 0 = default (3 for the copy kernel,
                              4 for hipMemcpyAsync); never more than depth */
@@ -429,6 +430,9 @@ int kv_pipeline_run(kv_plan_t *plan, int dir, int layer_begin, int layer_end, co
  * A call is meant for the token after the last one appended: rows of a kept sector that no append has written,
  * because a length moved by more, are written as zeros too.
  * Blocking.  lba_region / pageable as in kv_pipeline_run (pinned-ness is not required here).
+ * Threads: rows of 256 KiB and more are merged by the caller and up to three threads that the plan keeps for that; each
+ * call makes one of them until there are as many as host_workers of the plan's last kv_pipeline_run (if given) and the
+ * CPUs that the calling thread may run on, less one, allow.  They poll for up to about 100 us after a call, then sleep.
  * The kept sector images are forgotten by kv_pipeline_run(KV_DIR_OFFLOAD), by kv_plan_trim, and whenever a call
  * names another lba_region or pageable base address than the one the images were taken from; they assume that
  * only this library writes the extents in between.

@@ -21,13 +21,15 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <sched.h>
+
 #include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cstring>
+#include <exception>
 #include <functional>
 #include <mutex>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -152,7 +154,9 @@ struct kv_pipeline {
     std::vector<hipEvent_t> ev_done;            // per staging slot and copy stream
     std::vector<Entry> ring;                    // per in-flight command
     std::vector<hipEvent_t> timing;             // pairs
-    kvb::Workers workers;
+    kvb::Workers workers;         // the memcpy hop: as many threads as the last call with page-cache layers asked for
+    kvb::Workers append_workers;  // the append's own, which must not change that number: another one joins all threads and starts anew
+    int host_workers = 0;         // the last pipeline call's option; 0: not given
     // decode append: pinned landing buffer for the packed rows, and per (tensor, sequence) the image of
     // the last partly filled sector (so that only the first append after an offload has to read it back)
     void *seq_off_dev = nullptr;  // per-sequence element offsets inside an extent image (attention from extents)
@@ -172,6 +176,7 @@ struct kv_pipeline {
     ~kv_pipeline()
     {
         workers.stop();
+        append_workers.stop();
         (void)hipSetDevice(device);
         for (auto st : s_copy) if (st) (void)hipStreamSynchronize(st);
         for (auto e : ev_ready) (void)hipEventDestroy(e);
@@ -617,6 +622,7 @@ extern "C" int kv_pipeline_run(kv_plan_t *p, int dir, int layer_begin, int layer
     int rc = ensure_pipeline(p, n_slots, slot_bytes, (int)NB, bounce_slot, any_pc, n_workers, ws_bytes, n_timing);
     if (rc != KV_OK) return rc;
     kv_pipeline *q = p->pipe;
+    q->host_workers = opts && opts->host_workers > 0 ? opts->host_workers : 0;
     rc = order_after_caller(q, opts ? opts->caller_stream : nullptr);
     if (rc != KV_OK) return rc;
     if (attn_from_extent && p->mode == KV_PER_SEQ && !q->seq_off_dev) {
@@ -1015,6 +1021,14 @@ inline double clock_s() { return std::chrono::duration<double>(std::chrono::stea
 
 constexpr int kAppendHelpers = 3;
 
+// CPUs that the calling thread, and so a thread that it makes, may run on.
+int cpus_allowed()
+{
+    cpu_set_t set;
+    if (sched_getaffinity(0, sizeof(set), &set) == 0) return CPU_COUNT(&set);
+    return std::max(1, (int)std::thread::hardware_concurrency());
+}
+
 // Host side of an append: Alg. 2 with i0 = len - 1 gives a row's byte range; the write command carries whole sectors, so a row that starts inside
 // a sector is merged with that sector's earlier bytes (read-modify-write; the sector image is kept for the next append) and the rest is zeros.
 // Every row has sectors and an image of its own, so that several threads can merge rows at a time.
@@ -1168,15 +1182,16 @@ extern "C" int kv_append_tokens(kv_plan_t *p, int layer_begin, int layer_end, co
             tasks[i] = kvb::CopyTask{&helpers[i], nullptr, 0, &helping, &AppendHelper::run};
         }
         helping.store(m.parts - 1, std::memory_order_release);
-        q->workers.push(tasks, m.parts - 1);
+        try { q->append_workers.push(tasks, m.parts - 1); } catch (const std::exception &) { helping.store(0, std::memory_order_release); }   // none was pushed
     };
     if (total >= kHelpBytes) {
         // One call makes one thread, in the time that the rows take over the link (three made by the first call put 100 us on it).
-        if (q->workers.size() < kAppendHelpers) {
-            try { q->workers.add(); } catch (const std::system_error &) {}   // no more to be had: with those there are
+        const int most = q->host_workers > 0 ? std::min(kAppendHelpers, q->host_workers) : kAppendHelpers;
+        if (q->append_workers.size() < most && q->append_workers.size() + 1 < cpus_allowed()) {
+            try { q->append_workers.add(); } catch (const std::exception &) {}   // no more to be had: with those there are
         }
-        m.parts = 1 + std::min(kAppendHelpers, q->workers.size());
-        call_helpers();
+        m.parts = 1 + std::min(most, q->append_workers.size());
+        if (m.parts > 1) call_helpers();
     }
     for (size_t idx = 0; idx < n_rows && rc == KV_OK; ++idx) {
         const AppendMerge::Place w = m.place(idx);
@@ -1195,7 +1210,7 @@ extern "C" int kv_append_tokens(kv_plan_t *p, int layer_begin, int layer_end, co
         m.merge(0);
     }
     if (m.parts > 1) {
-        q->workers.take_back(&helping);
+        q->append_workers.take_back(&helping);
         spin_until_zero(helping);
     }
     if (landed != hipSuccess) { kvb::set_hip_error((int)landed); return KV_EHIP; }

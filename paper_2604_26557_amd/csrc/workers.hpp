@@ -48,14 +48,14 @@ public:
         for (auto &t : threads_) t.join();
         threads_.clear();
     }
-    // All pieces of one command under one lock; sleeping threads are woken only if there are any, and no
+    // All pieces of one command under one lock, or none (std::bad_alloc); sleeping threads are woken only if there are any, and no
     // more of them than there are pieces (the issuing thread pays for every wake-up call).
     void push(const CopyTask *t, int n)
     {
         int wake = 0;
         {
             std::lock_guard<std::mutex> g(mu_);
-            for (int i = 0; i < n; ++i) q_.push_back(t[i]);
+            q_.insert(q_.end(), t, t + n);   // at the end: all or nothing
             queued_.store((int)q_.size(), std::memory_order_release);
             wake = std::min(n, sleeping_);
         }

@@ -2,6 +2,8 @@
 reduced shapes of the five evaluation configs that still span several tiles and a ragged tail.
 Pack / unpack / host-region bytes must be bit-exact; attention within 2e-3 max abs error of the fp64
 reference (and 1e-2 of the reference's own max magnitude, so the check is not vacuous)."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -1262,6 +1264,53 @@ def test_append_merged_by_several_threads(layers, behind_work):
         assert np.array_equal(region.numpy()[:r.region_bytes], want_region[:r.region_bytes]), step
         assert np.array_equal(arena[:r.pageable_bytes], want_arena[:r.pageable_bytes]), step
         assert st.n_cmds == 2 * layers * 9 and st.n_rmw_reads == (2 * layers * sum(n % 2 == 0 for n in lens) if step == 0 else 0)
+
+
+@pytest.mark.parametrize("host_workers", [1, 2, 8])
+def test_append_and_pipeline_keep_their_threads(host_workers):
+    """Calls in turn, as in a decode loop: after the first ones neither makes a thread or ends one, and the append has at most three, and no more than host_workers."""
+    layers = 8
+    cfg = W.KVConfig("threads", 2150, layers, 8, 8, 128, 9, W.F16, 4096, 8, 2, W.PER_SEQ, W.PAGED, 0, len_range=(20, 31), pc_budget_bytes=4 * 2 * 9 * 18 * 4096)
+    case = Case(cfg, "cuda", gen_device="cpu", cap_extra=7)
+    r = case.ref
+    region, arena = pinned_bytes(r.region_bytes, 0x77), np.zeros(max(r.pageable_bytes, 1), dtype=np.uint8)
+    assert 0 < case.plan.info.n_pagecache_layers < layers
+    q, outs = [W.query(cfg, l, "cuda") for l in range(layers)], [torch.zeros((9, 8, 128), dtype=torch.float32, device="cuda") for _ in range(layers)]
+    kv.kv_pipeline_run(case.plan, kv.KV_DIR_OFFLOAD, 0, layers, case.view, region, arena, depth=2, host_workers=host_workers)
+    threads, lens = [], list(case.lens)
+    for step in range(7):
+        lens = [n + 1 for n in lens]
+        view = case.make_view(case.k, case.v, lens)
+        threads.append(set(os.listdir("/proc/self/task")))
+        kv.kv_append_tokens(case.plan, 0, layers, view, region, arena)
+        threads.append(set(os.listdir("/proc/self/task")))
+        kv.kv_pipeline_run(case.plan, kv.KV_DIR_RELOAD_ATTN, 0, layers, view, region, arena, depth=2, q_layers=q, out_layers=outs, host_workers=host_workers)
+    want_region, want_arena = case.expected_host(fill=0x77, lens=lens)
+    assert np.array_equal(region.numpy()[:r.region_bytes], want_region[:r.region_bytes])
+    made = [b - a for a, b in zip(threads[::2], threads[1::2])]   # by each append
+    assert sum(map(len, made)) <= min(3, host_workers) and not any(made[3:])
+    assert all(t == threads[7] for t in threads[7:])
+
+
+def test_append_of_a_thread_that_has_one_cpu():
+    """No thread helps one that shares its only CPU with them."""
+    cfg = W.KVConfig("one_cpu", 2160, 8, 8, 8, 128, 9, W.F16, 4096, 8, 2, W.PER_SEQ, W.PAGED, 0, len_range=(20, 31))
+    case = Case(cfg, "cuda", gen_device="cpu", cap_extra=3)
+    r = case.ref
+    region, arena = pinned_bytes(r.region_bytes, 0x77), np.zeros(1, dtype=np.uint8)
+    kv.kv_pipeline_run(case.plan, kv.KV_DIR_OFFLOAD, 0, 8, case.view, region, arena, depth=2)
+    lens, cpus = list(case.lens), os.sched_getaffinity(0)
+    os.sched_setaffinity(0, {min(cpus)})
+    try:
+        for step in range(3):
+            lens = [n + 1 for n in lens]
+            view = case.make_view(case.k, case.v, lens)
+            before = os.listdir("/proc/self/task")
+            kv.kv_append_tokens(case.plan, 0, 8, view, region, arena)
+            assert os.listdir("/proc/self/task") == before
+    finally:
+        os.sched_setaffinity(0, cpus)
+    assert np.array_equal(region.numpy()[:r.region_bytes], case.expected_host(fill=0x77, lens=lens)[0][:r.region_bytes])
 
 
 @pytest.mark.parametrize("H,D,layers", [(2, 128, 4), (3, 128, 4), (3, 64, 80)])
