@@ -430,7 +430,7 @@ int kv_pipeline_run(kv_plan_t *plan, int dir, int layer_begin, int layer_end, co
  * A call is meant for the token after the last one appended: rows of a kept sector that no append has written,
  * because a length moved by more, are written as zeros too.
  * Blocking.  lba_region / pageable as in kv_pipeline_run (pinned-ness is not required here).
- * Threads: rows of 256 KiB and more are merged by the caller and up to three threads that the plan keeps for that; each
+ * Threads: rows of 256 KiB and more (few and wide ones: of 512) are merged by the caller and up to three threads that the plan keeps for that; each
  * call makes one of them until there are as many as host_workers of the plan's last kv_pipeline_run (if given) and the
  * CPUs that the calling thread may run on, less one, allow.  They poll for up to about 100 us after a call, then sleep.
  * The kept sector images are forgotten by kv_pipeline_run(KV_DIR_OFFLOAD), by kv_plan_trim, and whenever a call

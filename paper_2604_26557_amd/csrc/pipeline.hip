@@ -1116,10 +1116,14 @@ struct AppendHelper {
     }
 };
 
-// Rows of 256 KiB and more are merged by four threads.  The copies wait for memory, and one thread took longer for them than the rows take over the link:
-// us per call, one thread / four: 512 rows of 2 KiB 125 / 60, 2048 420 / 201, 512 of 1 KiB 80 / 48, 256 of 8 KiB 111 / 84; 128 of 2 KiB 37 / 30; with eight
-// threads 61, 200, 47, 83, 29, but 20 us more where 200 us lie between two calls.  (Rows dealt out eight at a time, with no part of one's own: 72, 266, 60, 98, 31.)
-constexpr size_t kHelpBytes = 256 * 1024;
+// Rows of 256 KiB and more are merged by four threads.  The copies wait for memory, and one thread took longer for them than the rows take over the link.
+// us per call, one thread / four, calls back to back, 200 us apart and 5 ms apart (the threads then sleep): 128 rows of 2 KiB 39 / 30, 44 / 36, 55 / 48; 512 of 2 KiB 125 / 65,
+// 125 / 70, 135 / 85; 2048 440 / 210, 445 / 210, 470 / 240; 256 of 1 KiB 51 / 30, 54 / 34, 68 / 50; 512 of 1 KiB 84 / 52, 87 / 58, 100 / 70; 256 of 8 KiB 109 / 86, 113 / 86, 123 / 102.
+// With eight threads 61 for 512 rows of 2 KiB and 200 for 2048, but 20 us more where 200 us lie between two calls.  (Rows dealt out eight at a time, with no part of one's own:
+// 72, 266.)  A wide row takes one thread less time for its bytes: about as if a row were 4 KiB longer at one rate.  By that measure 512 KiB is the line:
+// 64 of 4 KiB 31 / 28, 36 / 31, 46 / 44; 8 of 64 KiB 36 / 32, 42 / 38, 51 / 47; below it 16 of 20 KiB 28.5 / 27.7, 33.7 / 32.4, 44.1 / 46.7; 4 of 64 KiB 25.6 / 25.1, 30.5 / 29.1,
+// 37 / 42; 32 of 8 KiB 26.9 / 26.1, 31.9 / 30.9, 41.8 / 40.8, and the call that makes a thread takes some 40 us longer.
+inline bool rows_need_help(size_t n_rows, size_t bytes) { return bytes >= 256 * 1024 && bytes + n_rows * 4096 >= 512 * 1024; }
 
 }  // namespace
 
@@ -1184,7 +1188,7 @@ extern "C" int kv_append_tokens(kv_plan_t *p, int layer_begin, int layer_end, co
         helping.store(m.parts - 1, std::memory_order_release);
         try { q->append_workers.push(tasks, m.parts - 1); } catch (const std::exception &) { helping.store(0, std::memory_order_release); }   // none was pushed
     };
-    if (total >= kHelpBytes) {
+    if (rows_need_help(n_rows, total)) {
         // One call makes one thread, in the time that the rows take over the link (three made by the first call put 100 us on it).
         const int most = q->host_workers > 0 ? std::min(kAppendHelpers, q->host_workers) : kAppendHelpers;
         if (q->append_workers.size() < most && q->append_workers.size() + 1 < cpus_allowed()) {

@@ -1313,6 +1313,25 @@ def test_append_of_a_thread_that_has_one_cpu():
     assert np.array_equal(region.numpy()[:r.region_bytes], case.expected_host(fill=0x77, lens=lens)[0][:r.region_bytes])
 
 
+@pytest.mark.parametrize("layers,helped", [(8, False), (16, True)])
+def test_append_of_few_wide_rows(layers, helped):
+    """16 rows of 20 KiB, which one thread merges before another is awake, and 32."""
+    cfg = W.KVConfig("wide_rows", 2170, layers, 8, 8, 64, 20, W.F16, 4096, 8, 2, W.TOKEN_MAJOR, W.PAGED, 30, pc_budget_bytes=0)
+    case = Case(cfg, "cuda", gen_device="cpu", cap_extra=3)
+    r = case.ref
+    assert r.row_bytes == 20480
+    region, arena = pinned_bytes(r.region_bytes, 0x77), np.zeros(1, dtype=np.uint8)
+    kv.kv_pipeline_run(case.plan, kv.KV_DIR_OFFLOAD, 0, layers, case.view, region, arena, depth=2)
+    lens = list(case.lens)
+    for step in range(3):
+        lens = [n + 1 for n in lens]
+        view = case.make_view(case.k, case.v, lens)
+        before = set(os.listdir("/proc/self/task"))
+        kv.kv_append_tokens(case.plan, 0, layers, view, region, arena)
+        assert len(set(os.listdir("/proc/self/task")) - before) == int(helped)
+    assert np.array_equal(region.numpy()[:r.region_bytes], case.expected_host(fill=0x77, lens=lens)[0][:r.region_bytes])
+
+
 @pytest.mark.parametrize("H,D,layers", [(2, 128, 4), (3, 128, 4), (3, 64, 80)])
 def test_append_of_a_length_that_moves_by_more_than_one(H, D, layers):
     """Rows of 512, 768 and 384 bytes in sectors of 4 KiB (one thread; 270 KiB of rows: several).  A length that skips rows of a sector, skips into the next one or goes
