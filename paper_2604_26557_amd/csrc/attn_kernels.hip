@@ -15,7 +15,7 @@
 //    elements of the result.  With a row of the operand for each token a load took 64 bytes of 16 rows, and the other half of each line was a request of
 //    its own to L2: reading alone 6.12 against 6.53 TB/s at head_dim 64 and 6.47 / 6.57 at 128, with two workgroups per compute unit 6.16 / 6.40
 //    (200 MB per launch).  us per layer from a graph, 16 rows / 8 rows: 16 KV heads x 4 x 64, 7 sequences of 9000 49.6 / 45.2, paged of
-//    6283-11718 57.6 / 52.6; 8 x 4 x 128, 8 of 1K-8K paged 31.5 / 30.0, 32K 26.7 / 26.0, 32 x 1, batch 32 of 528 46.4 / 45.0; 8 x 16 x 128, 12 of 2000
+//    6283-11718 57.6 / 52.6; 8 x 4 x 128, 8 of 1K-8K paged 31.5 / 30.0, 32K fp16 26.4 / 26.0, bf16 25.0 / 25.3 (the turn below takes 0.3 of both), 16K 16.8 / 16.0, 32 x 1, batch 32 of 528 46.4 / 45.0; 8 x 16 x 128, 12 of 2000
 //    26.2 / 24.2; 5 x 5 x 256, 43 of 2354 97.4 / 87.9, 16 x 4, 4 of 8192 86.9 / 86.5 (paged fp16 85.7 / 86.6); 4K and shorter single sequences the same.
 //  * The result leaves lane (column n, row group tg) with the scores of four tokens (tg, 4 + tg, 8 + tg, 12 + tg) for the column's query
 //    head, which is the layout of the B operand of V^T P: probabilities never leave their lane.
@@ -504,13 +504,15 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         vload_t v[TI][4][NV];
         bool ok[TI][4];
     };
-    // Strided layout: head h starts with step h % 8 of a long split, or of one of just 8 steps.  All workgroups begin together and read at one pace, and where the strides are powers
-    // of two the same step of every head lies at the same place modulo them.  us per layer, 8 x 4 x 128, all heads from step 0 / from step h: 32K tokens 25.4 / 25.0,
-    // 16K 16.0 / 15.7, 2 sequences of 16K 25.9 / 25.6, 16 query heads each 32K 27.2 / 26.9, 4K 8.34 / 8.27, 30001 tokens 24.4 / 24.4.  (Other splits of up to two steps for each
-    // wavefront lose by it: 4 sequences of 4096 15.9 / 16.6, 32 heads, 2 of 4096 25.7 / 27.0; any step of the split, by a hash: 16 x 1 x 256, 4 of 8192 84.8 / 92.2.)
+    // Strided layout: head h starts a split whose steps are a power of two, 32 and more (128 at head_dim 256), with step h % 8.  All workgroups begin together and read at one pace,
+    // and where the strides are powers of two the same step of every head lies at the same place modulo them.  us per layer, all heads from step 0 / from step h, otherwise the same
+    // code: 8 x 4 x 128, 32 steps (16K tokens) 15.94 / 15.80, 64 (32K) 26.29 / 26.02, 8 x 16 x 128, 64 27.52 / 27.29, 8 x 4 x 64, 32 16.05 / 15.86; over 22 shapes of 32 and 64 steps
+    // 0.5 % less (the worst, 32 KV heads of 32 steps, 15.63 / 16.11); 16 x 1 x 256, 128 steps 82.5 / 80.6.  Other splits gain nothing by it, or lose: 8 and 16 steps level or 1 % slower
+    // (one sequence of 8 steps up to 0.8 % faster, two and four 0.5 % slower), 24, 40 and 56 up to 1 % slower; head_dim 256, 32 steps 26.79 / 27.21, 64 46.71 / 46.95
+    // (profiles/attn_turn.md); any step of the split, by a hash: 16 x 1 x 256, 4 of 8192 84.8 / 92.2.
     const int n_steps = (t_end - t_begin + kStepTok - 1) / kStepTok;
     constexpr int kTurn = 8;
-    const int first_step = !PAGED && (n_steps > 2 * kWaves || n_steps == kTurn) ? (h + b) % kTurn : 0;
+    const int first_step = (h + b) & (!PAGED && n_steps >= (D < 256 ? 4 : 16) * kTurn && !(n_steps & (n_steps - 1)) ? kTurn - 1 : 0);
     auto step_row = [&](int st) -> int {
         const int s = st + first_step;
         return t_begin + (PAGED || s < n_steps ? s : s - n_steps) * kStepTok;
