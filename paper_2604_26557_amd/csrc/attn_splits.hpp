@@ -225,8 +225,10 @@ struct AttnCut {
 // it is an even one: every further workgroup costs its start and its merge.  But whole sequences, or few splits of each, are rarely
 // even, and where they are not, several smaller workgroups for every compute unit, dealt out as compute units become free, end together.
 //  * A compute unit reads no more than 1 / kAlone of its share of HBM when others are idle.
-//  * item_bytes for every workgroup after the first (1.2 us at 25 GB/s and compute unit; 4.4 us where a compute unit holds one workgroup at a time:
-//    5 sequences of 4000 tokens, 8 x 8 x 256, one / two / three workgroups for each 34.4 / 39.4 / 43.8), kCombineBytes for the second launch (3.4 us on the GPU).
+//  * item_bytes for every workgroup after the first (1.2 us at 25 GB/s and compute unit; 4.4 us at head_dim 256 with several query heads per KV head:
+//    5 sequences of 4000 tokens, 8 x 8 x 256, one / two / three workgroups for each 30.6 / 33.4 / 36.8, where 8 x 1 x 256, 4 of 4000 takes 24.9 / 25.1 / 26.7.  The geometric mean over
+//    22 shapes in two types and layouts whose cut depends on it is 32.2 us with 110e3, 32.4 with 60e3, 33.9 with 30e3, over ten 34.4, with 85e3 34.8, with 160e3 34.9:
+//    profiles/attn_cut_width256.md), kCombineBytes for the second launch (3.4 us on the GPU).
 //  * kFinerBytes (1 us) is what a finer cut has to save: about its own host time, and what the model is off by for batches of 10 us.  128 sequences of
 //    260-400 tokens, 2 x 4 x 128, called one by one: without it 16.4 us a layer, with it 15.6.
 //  * Costs are compared with a margin of 1 % (uniform) or 3 %, within which the plan stays.
@@ -332,9 +334,9 @@ inline double table_cost(const AttnShape &s, int parts, const int32_t *lens, con
 
 // Whether the sequences, not split, are worth a table.  Its order, the longest first, saves up to what those take beyond the mean, but each workgroup of
 // a compute unit in turn waits for the lookup, `lookup` in bytes that it would read meanwhile: more beyond 64 sequences, which take a second round of
-// loads, and at head_dim 256, where a compute unit holds one workgroup at a time.  us per layer of eager calls, table / none: up to 128 KiB, 40 of 20-250 tokens,
+// loads, and at head_dim 256, of whose larger instances a compute unit holds one workgroup or two.  us per layer of eager calls, table / none: up to 128 KiB, 40 of 20-250 tokens,
 // 32 x 1 x 128 17.4 / 19.5, of 10-60 9.3 / 8.9; 128 of 20-180, 8 x 4 x 128 15.0 / 15.7, of 20-96 12.1 / 11.4; 128 of 20-250, 32 x 4 x 128 61.3 / 58.0, 64 of those
-// 30.1 / 31.0.  Longer, 80 of 300-2000, 8 x 4 x 128 65.8 / 77.3; 128 of 400-700, 32 x 1 x 64 99.2 / 91.1; 66 of 130-300, 16 x 4 x 256 53.5 / 50.1.
+// 30.1 / 31.0.  Longer, 80 of 300-2000, 8 x 4 x 128 65.8 / 77.3; 128 of 400-700, 32 x 1 x 64 99.2 / 91.1; 66 of 130-300, 16 x 4 x 256 49.7 / 45.2.
 inline bool table_pays(const AttnShape &s, int parts, const int32_t *lens, const SplitTable &t, double lookup)
 {
     long long sum = 0;
