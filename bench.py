@@ -25,11 +25,11 @@ HBM_PEAK_GBPS = 8000.0  # MI355X published HBM3E bandwidth
 # workload (profiles/pmc_traffic_<workload>.md), each counter scaled by what it reads for a plain device-to-device
 # copy of known size in the same run.  Valid only for the sources they were taken with: the hash below covers the
 # two kernel files, what cuts and launches their work, and the compiler's flags; a mismatch reports traffic as null.
-PMC_TRAFFIC = {"sha": "2ea30c53aac53eee",
-               "llama8b_32k": {"kv_layout_kernel<pack>": 268470222, "kv_layout_kernel<unpack>": 268458344, "kv_attn_partial_kernel+kv_attn_combine_kernel": 135533890},
-               "llama8b_4k": {"kv_layout_kernel<pack>": 268467739, "kv_layout_kernel<unpack>": 268472260, "kv_attn_partial_kernel+kv_attn_combine_kernel": 18124989},
-               "llama8b_ragged_paged": {"kv_layout_kernel<pack>": 282073657, "kv_layout_kernel<unpack>": 282055318, "kv_attn_partial_kernel+kv_attn_combine_kernel": 142689736},
-               "gemma7b_mha_8k": {"kv_layout_kernel<pack>": 536894703, "kv_layout_kernel<unpack>": 536883871, "kv_attn_partial_kernel+kv_attn_combine_kernel": 537745183}}
+PMC_TRAFFIC = {"sha": "90a2c03dd0da1a3a",
+               "llama8b_32k": {"kv_layout_kernel<pack>": 268458307, "kv_layout_kernel<unpack>": 268454775, "kv_attn_partial_kernel+kv_attn_combine_kernel": 135563990},
+               "llama8b_4k": {"kv_layout_kernel<pack>": 268468511, "kv_layout_kernel<unpack>": 268463344, "kv_attn_partial_kernel+kv_attn_combine_kernel": 18137246},
+               "llama8b_ragged_paged": {"kv_layout_kernel<pack>": 282080321, "kv_layout_kernel<unpack>": 282054250, "kv_attn_partial_kernel+kv_attn_combine_kernel": 142712142},
+               "gemma7b_mha_8k": {"kv_layout_kernel<pack>": 536894812, "kv_layout_kernel<unpack>": 536883735, "kv_attn_partial_kernel+kv_attn_combine_kernel": 537767573}}
 
 
 def kernel_sources_hash() -> str:

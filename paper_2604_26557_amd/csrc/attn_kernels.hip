@@ -16,7 +16,8 @@
 //    its own to L2: reading alone 6.12 against 6.53 TB/s at head_dim 64 and 6.47 / 6.57 at 128, with two workgroups per compute unit 6.16 / 6.40
 //    (200 MB per launch).  us per layer from a graph, 16 rows / 8 rows: 16 KV heads x 4 x 64, 7 sequences of 9000 49.6 / 45.2, paged of
 //    6283-11718 57.6 / 52.6; 8 x 4 x 128, 8 of 1K-8K paged 31.5 / 30.0, 32K fp16 26.4 / 26.0, bf16 25.0 / 25.3 (the turn below takes 0.3 of both), 16K 16.8 / 16.0, 32 x 1, batch 32 of 528 46.4 / 45.0; 8 x 16 x 128, 12 of 2000
-//    26.2 / 24.2; 5 x 5 x 256, 43 of 2354 97.4 / 87.9, 16 x 4, 4 of 8192 86.9 / 86.5 (paged fp16 85.7 / 86.6); 4K and shorter single sequences the same.
+//    26.2 / 24.2; 5 x 5 x 256, 43 of 2354 97.4 / 87.9, 16 x 4, 4 of 8192 86.9 / 86.5 (paged fp16 85.7 / 86.6); shorter single sequences the same (32 layers of 4K 259.6 / 261.6, with
+//    the 32-bit offsets below 260.5).
 //  * The result leaves lane (column n, row group tg) with the scores of four tokens (tg, 4 + tg, 8 + tg, 12 + tg) for the column's query
 //    head, which is the layout of the B operand of V^T P: probabilities never leave their lane.
 //  * V^T P on the matrix cores as well: the 16 lanes of a row group load the V rows of their own 4 tokens, 16 bytes
@@ -420,7 +421,7 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
         long long seq_start = (long long)(b * st.sb);
         if (__builtin_expect(addr3 & kSeqOff, 0)) {
             int here = 0;
-            asm volatile("" : "+s"(here));   // or the pointer is loaded, and waited for, ahead of the first addresses of every launch
+            asm volatile("" : "+s"(here));   // or the pointer is loaded, and waited for, ahead of the first addresses of every launch (only where the load stands rests on it)
             seq_start = (&p.seq_off)[here][b] / 8;
         }
         head_off = seq_start + (long long)(h * st.sh);
@@ -521,6 +522,8 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     // tile is the wavefront's part, in scalar registers.  Rows past the end re-read the tile's first one, and are masked.  us per layer from a graph, 64-bit
     // addresses in every lane and the pointer to the sequences' starts waited for / this: 2 x 2 x 64, 256 tokens 4.18 / 3.77; 2 x 6 x 64, 2 of 1K-1.6K 6.65 / 6.48; paged
     // 8 x 4 x 128, 8 of 1K-8K 29.7 / 29.1; the others within 1 %.  (Both kinds of address in the loop: 8 x 4 x 128, 4K 8.50, with this one alone 8.29.)
+    // At head_dim 64, fp16, strided, it takes 91 registers where 74 did, and with them the third workgroup of a compute unit: no slower on any shape tried (16 x 4 x 64, 7 of 9000 43.8 /
+    // 43.1, 32 x 4, 64 of 500-700 51.6 / 51.8, 8 x 8, 96 of 300-2000 42.6 / 40.5).
     const unsigned row_bytes = PAGED ? 16u * DV : (unsigned)ss * 16u;
     const unsigned k_first = 16u * k_vec(0), v_first = 2u * E * n;
     unsigned k_off[2], v_off[4];
@@ -747,7 +750,8 @@ kv_attn_partial_kernel(const u32x4 *K, const u32x4 *V, const u32x4 *q,
     constexpr int C = D == 64 ? 1 : D == 256 ? 4 : (NH <= 4 ? 1 : 2), kUnits = D / (64 * C);   // columns of a lane in the merge
     typedef float cols_t __attribute__((ext_vector_type(C)));
     // A wavefront's first states are on their way while the references are looked at.  us per layer from a graph, after / before that: 8 x 4 x 128, 4K tokens 8.21 / 8.15,
-    // 1K 6.46 / 6.42; 2 x 2 x 64, 256 3.62 / 3.57; 2 x 6 x 64, 2 of 1K-1.6K 6.54 / 6.43; paged 16 x 8 x 64, 4 of 700 7.73 / 7.62; 8 x 16 x 128, 4K 9.70 / 9.81.
+    // 1K 6.46 / 6.42; 2 x 2 x 64, 256 3.62 / 3.57; 2 x 6 x 64, 2 of 1K-1.6K 6.54 / 6.43; paged 16 x 8 x 64, 4 of 700 7.73 / 7.62; 8 x 16 x 128, 4K 9.70 / 9.81.  (Over 32 layers of 4K each,
+    // 260.8 us / 260.5: level.)
     constexpr bool kEarly = !VALU && NH <= 8;
     f32x2 ml;
     cols_t part[kWaves];

@@ -1,6 +1,6 @@
 // Host threads of the page-cache path's memcpy hop (Sec. IV-B "Data Flow": pinned memory <-> page cache is a
 // CPU memcpy): a pool that copies pieces handed to it and counts each piece down on the command's own counter.  The decode append
-// has it merge rows into their sectors.
+// has one of its own, whose threads merge rows into their sectors.
 // No GPU calls in here: the pool is exercised on its own, under ThreadSanitizer, by tests/test_workers_cpu.py.
 #pragma once
 
